@@ -56,39 +56,202 @@ __device__ __forceinline__ void for_each_ell(const SegView& sv, int is_k, int sl
   }
 }
 
-// grid (ceil(n/64), B*H), block 256.
-__global__ __launch_bounds__(256) void decompress_kernel(Dims dm, SegView sv, int is_k, uint16_t* __restrict__ out,
-                                                         int n_total) {
-  __shared__ float sp[TILE][D];
-  __shared__ float Bs[D][8];
-  const int slab = blockIdx.y, tile = blockIdx.x;
-  const int b = slab / dm.H;
-  const int tid = threadIdx.x;
-  for (int i = tid; i < TILE * D; i += 256) sp[i / D][i % D] = 0.0f;
-  for (int i = tid; i < D * 8; i += 256) {
-    const int c = i >> 3, r = i & 7;
-    Bs[c][r] = r < sv.rank ? h2f(sv.Bf[((size_t)slab * D + c) * sv.rank + r]) : 0.0f;
-  }
-  block_lds_sync();
-  if (dm.ppm > 0) {
-    const uint2 oc = sv.sp_table[(size_t)slab * sv.ntile_cap + tile];
-    const uint32_t* lst = sv.sp_pool + (size_t)(is_k ? slab : b) * sv.pool_cap + oc.x;
-    for (uint32_t e = tid; e < oc.y; e += 256) {
-      const uint32_t en = lst[e];
-      sp[(en & 0xFFFFu) >> 7][en & 127u] = h2f(en >> 16);
+// ---- decompress: X-hat = D + A B^T + S of one 64-token tile ----
+// The floor is HBM (2 bytes written per entry, about 0.45 read).  A thread owns eight neighbouring channels, i.e. one
+// 16-byte piece of each of its four rows; the 16 lanes of a row write its 256 bytes together.  Which rows it takes
+// follows the code layout:
+//   Keys    rows r0 + 16 k of the tile (token-major code rows: 2 or 4 bytes hold the thread's eight codes)
+//   Values  four consecutive tokens of one code word per channel: eight words give four row pieces (and serve the
+//           other threads of the same tokens from the cache), and no exchange between lanes is needed
+// S goes through an fp16 tile in LDS (entries off its support are 0) because its slots and lists belong to rows (Keys)
+// or channels (Values) and not to the piece's owner.  To keep the arithmetic under the write stream, codes become
+// floats a byte at a time (no bit-field extract per entry) and the rank sum runs on the fp16 factors as they are
+// stored, two ranks per instruction.  Every load that does not depend on the list table is requested before the first
+// wait.  LLaMA-2-7B layer, batch 16, 4096 tokens, 2 bits (0.66 GB moved per tensor): 1296 us with one entry per thread
+// and step and a fp32 S tile, 284 us in this layout with the loads after the S tile and unpacked factors, 190 us now.
+// R: the rank rounded up to 0, 2, 4 or 8; NW = R / 2 words of two factors.
+template <int R>
+struct FactorRow {
+  uint32_t w[R > 0 ? R / 2 : 1];
+};
+// Row `row` of a rank-`rank` factor through a view of its rows (zeros past the view); entries r >= rank are 0.
+template <int R>
+__device__ __forceinline__ FactorRow<R> load_factor(GEAR_BUF_T view, int row, int rank) {
+  FactorRow<R> f;
+  if constexpr (R == 0) {
+    f.w[0] = 0u;
+  } else if (rank == R) {   // (the same in every thread of the launch) one 4-, 8- or 16-byte read
+    if constexpr (R == 2) {
+      f.w[0] = GEAR_BUF_LOAD4(view, row * 4);
+    } else if constexpr (R == 4) {
+      const uint2 t = GEAR_BUF_LOAD8(view, row * 8);
+      f.w[0] = t.x; f.w[1] = t.y;
+    } else {
+      const uint4 t = GEAR_BUF_LOAD16(view, row * 16);
+      f.w[0] = t.x; f.w[1] = t.y; f.w[2] = t.z; f.w[3] = t.w;
     }
-    for_each_ell(sv, is_k, slab, tile, tid, [&](int tl, int c, uint32_t hb) { sp[tl][c] = h2f(hb); });
+  } else {
+    uint32_t h[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) h[r] = GEAR_BUF_LOAD2(view, (row * rank + r) * 2);
+#pragma unroll
+    for (int r = 0; r < R; r += 2) f.w[r / 2] = (r < rank ? h[r] : 0u) | ((r + 1 < rank ? h[r + 1] : 0u) << 16);
   }
-  block_lds_sync();
-  for (int i = tid; i < TILE * D; i += 256) {
-    const int tl = i / D, c = i % D, t = tile * TILE + tl;
-    if (t >= sv.n) break;
-    const uint32_t sb = load_sz(sv, dm, is_k, slab, t, c);
-    float v = (float)load_code(sv, dm, is_k, slab, t, c) * h2f(sb & 0xFFFFu) + h2f(sb >> 16);
-    float lr = 0.0f;
-    for (int r = 0; r < sv.rank; ++r) lr += h2f(sv.A[((size_t)slab * sv.n_cap + t) * sv.rank + r]) * Bs[c][r];
-    v = v + lr + sp[tl][c];
-    out[((size_t)slab * n_total + sv.t0 + t) * D + c] = (uint16_t)f2h(v);
+  return f;
+}
+// Eight entries of one row: code * scale + zero, + A B^T, + S, in fp32 in this order, then fp16.
+// c0, c1: the codes of entries 0..3 and 4..7, one per byte.
+template <int R>
+__device__ __forceinline__ uint4 decompress_piece(uint32_t c0, uint32_t c1, const float (&dl)[8], const float (&mn)[8],
+                                                  const FactorRow<R>& a, const FactorRow<R> (&bf)[8], const uint4& sp) {
+  const uint32_t sw[4] = {sp.x, sp.y, sp.z, sp.w};
+  uint32_t o[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    float v[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int e = 2 * j + h;
+      float x = (float)(((e < 4 ? c0 : c1) >> (8 * (e & 3))) & 0xFFu) * dl[e] + mn[e];
+      if constexpr (R > 0) {
+#pragma unroll
+        for (int i = 0; i < R / 2; ++i) x = GEAR_FDOT2(a.w[i], bf[e].w[i], x);
+      }
+      v[h] = x + h2f(h ? (sw[j] >> 16) : (sw[j] & 0xFFFFu));
+    }
+    const h2_t p = {(_Float16)v[0], (_Float16)v[1]};
+    o[j] = __builtin_bit_cast(uint32_t, p);
+  }
+  return make_uint4(o[0], o[1], o[2], o[3]);
+}
+constexpr int SP_PITCH = D + 8;   // fp16 entries per row of the S tile (16-byte pieces of neighbouring rows in different banks)
+
+// grid (ceil(n/64), B*H), block 256.
+template <bool IS_K, int BITS, int R>
+__global__ __launch_bounds__(256) void decompress_kernel(Dims dm, SegView sv, uint16_t* __restrict__ out, int n_total) {
+  constexpr int TPW = 32 / BITS;
+  constexpr int NWG = TILE / TPW;   // Values: code words of a channel in the tile
+  constexpr uint32_t CMASK = BITS == 2 ? 0x03030303u : 0x0F0F0F0Fu;
+  __shared__ __align__(16) uint16_t sp[TILE * SP_PITCH];
+  const int slab = blockIdx.y, tile = blockIdx.x, t0 = tile * TILE;
+  const int tid = threadIdx.x, oc = tid & 15, q16 = tid >> 4;
+  const int lg = 31 - __clz(dm.g), lng = 7 - lg;   // log2 of the group size, of a Value row's groups
+  const bool sparse = dm.ppm > 0;
+  // the thread's rows of the tile: row0 + step * k
+  const int wg = q16 & (NWG - 1), part = q16 / NWG;   // Values
+  const int row0 = IS_K ? q16 : wg * TPW + 4 * part;
+  constexpr int step = IS_K ? 16 : 1;
+  // views of the slab's rows: what lies past the last row reads as 0 and is not written
+  const GEAR_BUF_T ob = GEAR_BUF_MAKE(out + ((size_t)slab * n_total + sv.t0) * D, (uint32_t)sv.n * (D * 2));
+  const GEAR_BUF_T ab = GEAR_BUF_MAKE(sv.A + (size_t)slab * sv.n_cap * sv.rank, (uint32_t)sv.n * sv.rank * 2);
+  const GEAR_BUF_T bb = GEAR_BUF_MAKE(sv.Bf + (size_t)slab * D * sv.rank, (uint32_t)(D * 2) * sv.rank);
+  uint2 tab = make_uint2(0u, 0u);
+  uint32_t slot = 0u;   // the thread's one fixed slot of the tile (256 of them)
+  if (sparse) {
+    tab = sv.sp_table[(size_t)slab * sv.ntile_cap + tile];
+    if constexpr (IS_K)
+      slot = GEAR_BUF_LOAD4(GEAR_BUF_MAKE(sv.ell + (size_t)slab * sv.n_cap * ELL_K, (uint32_t)sv.n * (ELL_K * 4)), (t0 * ELL_K + tid) * 4);
+    else
+      slot = sv.ell[((size_t)slab * sv.ntile_cap + tile) * (D * ELL_V) + tid];
+  }
+  uint32_t cw[8];       // Keys: cw[k] the 8 codes of row k; Values: cw[e] the word of channel 8 oc + e
+  uint32_t zv[4];       // Values: (scale, zero) of the rows
+  uint4 zk[2][2];       // Keys: (scale, zero) of the channels in the tile's groups (two when g = 32)
+  FactorRow<R> a[4], bf[8];
+  const bool two = IS_K && !dm.kcvt && lg == 5;
+  if constexpr (IS_K) {
+    const GEAR_BUF_T cb = GEAR_BUF_MAKE(sv.codes + (size_t)slab * sv.n_cap * (4 * BITS), (uint32_t)sv.n * (16 * BITS));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int t = t0 + row0 + 16 * k;
+      cw[k] = BITS == 4 ? GEAR_BUF_LOAD4(cb, t * 64 + oc * 4) : GEAR_BUF_LOAD2(cb, t * 32 + oc * 2);
+    }
+    const int g0 = dm.kcvt ? 0 : t0 >> lg;
+    const GEAR_BUF_T zb = GEAR_BUF_MAKE(sv.sz + (size_t)slab * sv.ng_cap * D, (uint32_t)sv.ng_cap * (D * 4));
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      zk[0][h] = GEAR_BUF_LOAD16(zb, (g0 * D + oc * 8) * 4 + 16 * h);
+      zk[1][h] = zk[0][h];
+    }
+    if (two) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) zk[1][h] = GEAR_BUF_LOAD16(zb, ((g0 + 1) * D + oc * 8) * 4 + 16 * h);
+    }
+  } else {
+    // (a tile's last code block may lie past the segment: nothing of it is used then)
+    const int blk = (t0 / TPW + wg) >> 2;
+    const GEAR_BUF_T cb = GEAR_BUF_MAKE(sv.codes + (size_t)slab * sv.nblk_cap * 512, (uint32_t)sv.nblk_cap * 2048);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) cw[e] = GEAR_BUF_LOAD4(cb, (blk * 512 + (wg & 3) * 128 + ((oc & 1) * 8 + e) * 8 + (oc >> 1)) * 4);
+    const GEAR_BUF_T zb = GEAR_BUF_MAKE(sv.sz + (((size_t)slab * sv.n_cap) << lng), ((uint32_t)sv.n << lng) * 4);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) zv[k] = GEAR_BUF_LOAD4(zb, (((t0 + row0 + k) << lng) + ((oc * 8) >> lg)) * 4);
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) a[k] = load_factor<R>(ab, t0 + row0 + step * k, sv.rank);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) bf[e] = load_factor<R>(bb, oc * 8 + e, sv.rank);
+
+  if (sparse) {
+    for (int i = tid; i < TILE * SP_PITCH / 8; i += 256) reinterpret_cast<uint4*>(sp)[i] = make_uint4(0, 0, 0, 0);
+    block_lds_sync();
+    const uint32_t* lst = sv.sp_pool + (size_t)(IS_K ? slab : slab / dm.H) * sv.pool_cap + tab.x;
+    for (uint32_t e = tid; e < tab.y; e += 256) {
+      const uint32_t en = lst[e];
+      sp[((en & 0xFFFFu) >> 7) * SP_PITCH + (en & 127u)] = (uint16_t)(en >> 16);
+    }
+    if (slot & ELL_VALID) {
+      const int tl = IS_K ? tid / ELL_K : (int)(slot & 63u), c = IS_K ? (int)(slot & 127u) : tid / ELL_V;
+      sp[tl * SP_PITCH + c] = (uint16_t)(slot >> 16);
+    }
+    block_lds_sync();
+  }
+  float dl[8], mn[8];
+  if constexpr (!IS_K && BITS == 2) {
+    // byte `part` of a word holds the codes of the thread's four tokens: four channels' bytes in one word
+    const uint32_t s2 = 0x0c0c0400u + 0x0101u * part;   // bytes (lo[part], hi[part])
+    const uint32_t x0 = GEAR_BYTE_PERM(GEAR_BYTE_PERM(cw[3], cw[2], s2), GEAR_BYTE_PERM(cw[1], cw[0], s2), 0x05040100u);
+    const uint32_t x1 = GEAR_BYTE_PERM(GEAR_BYTE_PERM(cw[7], cw[6], s2), GEAR_BYTE_PERM(cw[5], cw[4], s2), 0x05040100u);
+    cw[0] = x0;
+    cw[1] = x1;
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int tl = row0 + step * k;
+    uint32_t c0, c1;
+    if constexpr (IS_K) {
+      if (k == 0 || (k == 2 && two)) {
+        const uint4 z0 = zk[k >> 1][0], z1 = zk[k >> 1][1];
+        const uint32_t w[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { dl[e] = h2f(w[e] & 0xFFFFu); mn[e] = h2f(w[e] >> 16); }
+      }
+      if constexpr (BITS == 2) {
+        // codes e = 0..3 in byte 0, 4..7 in byte 1: spread two bits per byte
+        const uint32_t lo = cw[k] & 0xFFu, hi = cw[k] >> 8;
+        c0 = (lo | (lo << 6) | (lo << 12) | (lo << 18)) & CMASK;
+        c1 = (hi | (hi << 6) | (hi << 12) | (hi << 18)) & CMASK;
+      } else {
+        const uint32_t ev = cw[k] & CMASK, od = (cw[k] >> 4) & CMASK;   // codes 0 2 4 6 and 1 3 5 7
+        c0 = GEAR_BYTE_PERM(od, ev, 0x05010400u);
+        c1 = GEAR_BYTE_PERM(od, ev, 0x07030602u);
+      }
+    } else {
+      const float d = h2f(zv[k] & 0xFFFFu), m = h2f(zv[k] >> 16);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) { dl[e] = d; mn[e] = m; }
+      if constexpr (BITS == 2) {
+        c0 = (cw[0] >> (2 * k)) & CMASK;
+        c1 = (cw[1] >> (2 * k)) & CMASK;
+      } else {
+        // token 4 part + k: nibble k of half word `part`
+        const uint32_t sh = 16 * part + 4 * k;
+        c0 = GEAR_UBFE(cw[0], sh, 4) | (GEAR_UBFE(cw[1], sh, 4) << 8) | (GEAR_UBFE(cw[2], sh, 4) << 16) | (GEAR_UBFE(cw[3], sh, 4) << 24);
+        c1 = GEAR_UBFE(cw[4], sh, 4) | (GEAR_UBFE(cw[5], sh, 4) << 8) | (GEAR_UBFE(cw[6], sh, 4) << 16) | (GEAR_UBFE(cw[7], sh, 4) << 24);
+      }
+    }
+    const uint4 s4 = sparse ? *reinterpret_cast<const uint4*>(sp + tl * SP_PITCH + oc * 8) : make_uint4(0, 0, 0, 0);
+    GEAR_BUF_STORE16_NT(ob, (uint32_t)(t0 + tl) * (D * 2) + oc * 16, decompress_piece<R>(c0, c1, dl, mn, a[k], bf, s4));
   }
 }
 
@@ -253,11 +416,24 @@ __global__ void export_lowrank_kernel(SegView sv, uint16_t* __restrict__ A, uint
   }
 }
 
+template <bool IS_K, int BITS>
+static void launch_decompress_t(const Dims& dm, const SegView& sv, uint16_t* out, int n_total, hipStream_t st) {
+  const dim3 grid((sv.n + TILE - 1) / TILE, dm.B * dm.H);
+  if (sv.rank == 0) hipLaunchKernelGGL((decompress_kernel<IS_K, BITS, 0>), grid, dim3(256), 0, st, dm, sv, out, n_total);
+  else if (sv.rank <= 2) hipLaunchKernelGGL((decompress_kernel<IS_K, BITS, 2>), grid, dim3(256), 0, st, dm, sv, out, n_total);
+  else if (sv.rank <= 4) hipLaunchKernelGGL((decompress_kernel<IS_K, BITS, 4>), grid, dim3(256), 0, st, dm, sv, out, n_total);
+  else hipLaunchKernelGGL((decompress_kernel<IS_K, BITS, 8>), grid, dim3(256), 0, st, dm, sv, out, n_total);
+}
+
 hipError_t launch_decompress(const Dims& dm, const SegView& ks, const SegView& vs, uint16_t* Kout,
                              uint16_t* Vout, int n_total, hipStream_t st) {
-  dim3 grid((ks.n + TILE - 1) / TILE, dm.B * dm.H);
-  if (Kout) hipLaunchKernelGGL(decompress_kernel, grid, dim3(256), 0, st, dm, ks, 1, Kout, n_total);
-  if (Vout) hipLaunchKernelGGL(decompress_kernel, grid, dim3(256), 0, st, dm, vs, 0, Vout, n_total);
+  if (dm.bits == 2) {
+    if (Kout) launch_decompress_t<true, 2>(dm, ks, Kout, n_total, st);
+    if (Vout) launch_decompress_t<false, 2>(dm, vs, Vout, n_total, st);
+  } else {
+    if (Kout) launch_decompress_t<true, 4>(dm, ks, Kout, n_total, st);
+    if (Vout) launch_decompress_t<false, 4>(dm, vs, Vout, n_total, st);
+  }
   return hipGetLastError();
 }
 

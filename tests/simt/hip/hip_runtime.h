@@ -52,6 +52,7 @@ inline hipError_t hipGetSymbolAddress(void** p, const void* sym) { *p = const_ca
 #define GEAR_WAVE_UNIFORM(x) (x)
 #define GEAR_BYTE_PERM(hi, lo, sel) simt_byte_perm((hi), (lo), (sel))
 #define GEAR_FMED3(x, lo, hi) fminf(fmaxf((x), (lo)), (hi))
+#define GEAR_FDOT2(a, b, c) simt_fdot2((a), (b), (c))
 #define GEAR_UBFE(x, off, width) (((uint32_t)(x) >> (off)) & ((1u << (width)) - 1u))
 struct simt_buf { const unsigned char* p; uint32_t n; };
 #define GEAR_BUF_T simt_buf
@@ -74,6 +75,12 @@ template <typename T> static inline T simt_buf_load(const simt_buf& b, uint32_t 
   memset(&r, 0, sizeof(T));
   if ((uint64_t)off + sizeof(T) <= b.n) memcpy(&r, b.p + off, sizeof(T));
   return r;
+}
+static inline float simt_fdot2(uint32_t a, uint32_t b, float c) {   // two fp16 products and a sum
+  _Float16 x[2], y[2];
+  memcpy(x, &a, 4);
+  memcpy(y, &b, 4);
+  return (float)((double)x[0] * (double)y[0] + (double)x[1] * (double)y[1] + (double)c);
 }
 static inline uint32_t simt_byte_perm(uint32_t hi, uint32_t lo, uint32_t sel) {
   const uint64_t src = ((uint64_t)hi << 32) | lo;
