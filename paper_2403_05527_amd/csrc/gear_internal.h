@@ -432,24 +432,41 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
-// inclusive prefix sum over lanes
+// Lane exchange with zero fill: a lane without a source (row_shl / row_shr past the row's end) reads 0.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u_zero(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint32_t dpp_rows_u(uint32_t old, uint32_t v) {   // rows outside ROW_MASK keep `old`
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROW_MASK, 0xF, false);
+}
+__device__ __forceinline__ uint32_t row16_incl_prefix(uint32_t v) {   // sum over lanes 0 .. i of a row of 16
+  v += dpp_u_zero<0x111>(v);
+  v += dpp_u_zero<0x112>(v);
+  v += dpp_u_zero<0x114>(v);
+  v += dpp_u_zero<0x118>(v);
+  return v;
+}
+__device__ __forceinline__ uint32_t row16_incl_suffix(uint32_t v) {   // sum over lanes i .. 15 of the row
+  v += dpp_u_zero<0x101>(v);
+  v += dpp_u_zero<0x102>(v);
+  v += dpp_u_zero<0x104>(v);
+  v += dpp_u_zero<0x108>(v);
+  return v;
+}
+__device__ __forceinline__ uint32_t lane_bcast_u(uint32_t v, int lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, lane); }
+// Inclusive prefix / suffix sums over the 64 lanes: prefixes inside the rows of 16, then the rows' totals handed on
+// (row_bcast:15, row_bcast:31).  Register moves only: a shuffle through the LDS unit would cost its latency six times.
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
-  const int lane = lane_id();
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    uint32_t t = __shfl_up(v, o, 64);
-    if (lane >= o) v += t;
-  }
+  v = row16_incl_prefix(v);
+  v += dpp_rows_u<DPP_ROW_BCAST15, 0xA>(0u, v);
+  v += dpp_rows_u<DPP_ROW_BCAST31, 0xC>(0u, v);
   return v;
 }
 __device__ __forceinline__ uint32_t wave_incl_suffix(uint32_t v) {
-  const int lane = lane_id();
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    uint32_t t = __shfl_down(v, o, 64);
-    if (lane + o < 64) v += t;
-  }
-  return v;
+  const uint32_t pre = wave_incl_scan(v);
+  return lane_bcast_u(pre, 63) - pre + v;
 }
 
 }  // namespace gear

@@ -70,8 +70,8 @@ __device__ __forceinline__ void scan_from_top(const uint32_t* h, uint32_t k, int
       }
     }
   }
-  bin = __shfl(bsel, L, 64);
-  above = __shfl(ab, L, 64);
+  bin = (int)lane_bcast_u((uint32_t)bsel, GEAR_WAVE_UNIFORM(L));
+  above = lane_bcast_u(ab, GEAR_WAVE_UNIFORM(L));
 }
 __device__ __forceinline__ void scan_from_bottom(const uint32_t* h, uint32_t k, int& bin, uint32_t& below) {
   const int lane = lane_id();
@@ -98,8 +98,8 @@ __device__ __forceinline__ void scan_from_bottom(const uint32_t* h, uint32_t k, 
       }
     }
   }
-  bin = __shfl(bsel, L, 64);
-  below = __shfl(be, L, 64);
+  bin = (int)lane_bcast_u((uint32_t)bsel, GEAR_WAVE_UNIFORM(L));
+  below = lane_bcast_u(be, GEAR_WAVE_UNIFORM(L));
 }
 
 // Index of the m-th (1-based) entry whose key equals tau, in index order.
@@ -118,7 +118,7 @@ __device__ __forceinline__ int find_kth_equal(const Src& src, int N, int nch, ui
     for (int e = 0; e < 8; ++e)
       if (base + e < N && slot16(v, e) == tau) ++c;
     const uint32_t inc = wave_incl_scan(c);
-    const uint32_t total = __shfl(inc, 63, 64);
+    const uint32_t total = lane_bcast_u(inc, 63);
     if (base_cnt + total >= m) {
       const uint32_t exc = base_cnt + inc - c;
       const bool mine = (exc < m) && (m <= base_cnt + inc);
@@ -134,7 +134,7 @@ __device__ __forceinline__ int find_kth_equal(const Src& src, int N, int nch, ui
       }
       const unsigned long long bm = __ballot(mine);
       const int L = bm ? (int)__ffsll((long long)bm) - 1 : 0;
-      found = __shfl(idx, L, 64);
+      found = (int)lane_bcast_u((uint32_t)idx, GEAR_WAVE_UNIFORM(L));
       have = true;
     }
     base_cnt += total;
@@ -188,18 +188,18 @@ __device__ __forceinline__ void find_kth_equal_pair(const Src& src, int N, int n
   uint32_t rank_a = 0, rank_b = 0;
   const uint32_t cmax = ca > cb ? ca : cb;
   for (uint32_t j = 0; j < cmax; ++j) {   // wave-uniform trip count
-    rank_a += (uint32_t)__shfl(mine_a, (int)j, 64) < mine_a ? 1u : 0u;
-    rank_b += (uint32_t)__shfl(mine_b, (int)j, 64) < mine_b ? 1u : 0u;
+    rank_a += lane_bcast_u(mine_a, GEAR_WAVE_UNIFORM((int)j)) < mine_a ? 1u : 0u;
+    rank_b += lane_bcast_u(mine_b, GEAR_WAVE_UNIFORM((int)j)) < mine_b ? 1u : 0u;
   }
   idx_a = INT_MAX;
   idx_b = INT_MAX;
   if (m_a) {
     const unsigned long long bm = __ballot(lane < (int)ca && rank_a + 1u == m_a);
-    if (bm) idx_a = (int)__shfl(mine_a, (int)__ffsll((long long)bm) - 1, 64);
+    if (bm) idx_a = (int)lane_bcast_u(mine_a, GEAR_WAVE_UNIFORM((int)__ffsll((long long)bm) - 1));
   }
   if (m_b) {
     const unsigned long long bm = __ballot(lane < (int)cb && rank_b + 1u == m_b);
-    if (bm) idx_b = (int)__shfl(mine_b, (int)__ffsll((long long)bm) - 1, 64);
+    if (bm) idx_b = (int)lane_bcast_u(mine_b, GEAR_WAVE_UNIFORM((int)__ffsll((long long)bm) - 1));
   }
   wave_lds_sync();
 }

@@ -17,26 +17,6 @@ namespace gear {
 
 constexpr int SELECT_ROW_LDS_WORDS = 512;   // LDS words per vector (row of 16 lanes)
 
-// Lane exchanges inside a row of 16 with zero fill: lane i reads lane i + N (row_shl) or i - N (row_shr);
-// a lane without a source reads 0.
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_u_zero(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
-}
-__device__ __forceinline__ uint32_t row16_incl_suffix(uint32_t v) {   // sum over lanes i .. 15 of the row
-  v += dpp_u_zero<0x101>(v);
-  v += dpp_u_zero<0x102>(v);
-  v += dpp_u_zero<0x104>(v);
-  v += dpp_u_zero<0x108>(v);
-  return v;
-}
-__device__ __forceinline__ uint32_t row16_incl_prefix(uint32_t v) {   // sum over lanes 0 .. i of the row
-  v += dpp_u_zero<0x111>(v);
-  v += dpp_u_zero<0x112>(v);
-  v += dpp_u_zero<0x114>(v);
-  v += dpp_u_zero<0x118>(v);
-  return v;
-}
 // bit j: the predicate of lane j of my row
 __device__ __forceinline__ uint32_t row16_ballot(bool p) {
   const unsigned long long m = __ballot(p);
