@@ -89,7 +89,7 @@ ArenaLayout arena_layout(const gear_config& c) {
 }
 
 struct WorkLayout {
-  size_t thrK, thrV, vsz, pool_ctr, Bcur, partial, Atmp, cmat, dec, gram, resid, bytes;
+  size_t maskK, maskV, vsz, pool_ctr, Bcur, partial, Atmp, cmat, dec, gram, resid, bytes;
   int gram_strips;
 };
 
@@ -100,8 +100,8 @@ WorkLayout work_layout(const gear_config& c) {
   const int npart = (n_max + 255) / 256;
   const int R = 8;
   size_t o = 0;
-  w.thrK = o; o += up(slabs * D * sizeof(ThreshPair));
-  w.thrV = o; o += up((size_t)c.B * n_max * sizeof(ThreshPair));
+  w.maskK = o; o += up(c.outlier_ppm > 0 ? slabs * (size_t)n_max * 16 : 0);   // which entries belong to S, 16 bytes per token row
+  w.maskV = o; o += up(c.outlier_ppm > 0 ? slabs * (size_t)n_max * 16 : 0);
   w.vsz = o; o += up(c.group == 0 ? (size_t)c.B * n_max * 4 : 0);   // per-vector grouping: a Value token's (scale, zero)
   w.pool_ctr = o; o += up((slabs + (size_t)c.B) * 4);   // Key counters per slab, then Value counters per batch
   w.Bcur = o; o += up(slabs * D * R * 4);
@@ -115,8 +115,8 @@ WorkLayout work_layout(const gear_config& c) {
   w.dec = o; o += up((size_t)c.B * c.H_q * (nsplit + ncb + 1) * DECODE_REC * 4);
   w.gram_strips = c.rank_max > 0 && n_max > 256 ? pi_gram_strips_max(n_max, (int)slabs) : 0;
   w.gram = o; o += up(slabs * (size_t)w.gram_strips * 36 * 256 * 4);
-  // the filtered tensor for the low-rank passes; before it is written, the channel-major copy of the
-  // keys of a long Key segment (see launch_k_select) lives in the same place
+  // the filtered tensor Y for the low-rank solvers that walk over it; the channel-major copy of the keys of a long Key
+  // segment (see launch_k_select) lives in the same place
   w.resid = o;
   {
     const size_t resid = c.rank_max > 0 ? slabs * (size_t)n_max * D * 2 : 0;
@@ -356,8 +356,8 @@ int gear_compress_recent(gear_cache* cache, const void* K, const void* V, int32_
   seg_views(cache, a, seg, n, rank, &ks, &vs);
   const uint16_t* Kp = static_cast<const uint16_t*>(K);
   const uint16_t* Vp = static_cast<const uint16_t*>(V);
-  ThreshPair* thrK = reinterpret_cast<ThreshPair*>(ws + w.thrK);
-  ThreshPair* thrV = reinterpret_cast<ThreshPair*>(ws + w.thrV);
+  uint4* maskK = reinterpret_cast<uint4*>(ws + w.maskK);
+  uint4* maskV = reinterpret_cast<uint4*>(ws + w.maskV);
   uint32_t* pool_ctr = reinterpret_cast<uint32_t*>(ws + w.pool_ctr);
 
   const int kv_k = outlier_count(n, c.outlier_ppm);
@@ -365,23 +365,28 @@ int gear_compress_recent(gear_cache* cache, const void* K, const void* V, int32_
   const int kv_v = outlier_count(vhead ? D : (long long)c.H_kv * D, c.outlier_ppm);   // per Value vector
   // the Key selection kernel also finds a channel's (scale, zero) under the per-vector grouping
   if (c.outlier_ppm > 0 || dm.kcvt) {
-    GEAR_HIP(launch_k_select(Kp, dm, n, (kv_k + 1) / 2, kv_k / 2, thrK, pool_ctr, c.B * c.H_kv + c.B, ks,
+    GEAR_HIP(launch_k_select(Kp, dm, n, (kv_k + 1) / 2, kv_k / 2, maskK, pool_ctr, c.B * c.H_kv + c.B, ks,
                              n > 8192 ? reinterpret_cast<uint16_t*>(ws + w.resid) : nullptr, st));
   }
-  // Keys: quantize (leaving Y = X - S in the workspace), then their power iteration;
-  // Values reuse the same buffer afterwards.
-  uint16_t* resid = rank > 0 ? reinterpret_cast<uint16_t*>(ws + w.resid) : nullptr;
   float* Bcur = reinterpret_cast<float*>(ws + w.Bcur);
   float* partial = reinterpret_cast<float*>(ws + w.partial);
   float* Atmp = reinterpret_cast<float*>(ws + w.Atmp);
   float* cmat = reinterpret_cast<float*>(ws + w.cmat);
-  float* gram = reinterpret_cast<float*>(ws + w.gram);
   uint32_t* vsz = reinterpret_cast<uint32_t*>(ws + w.vsz);
-  GEAR_HIP(launch_k_quant(Kp, ks, dm, n, thrK, pool_ctr, resid, st));
-  if (rank > 0) GEAR_HIP(launch_power_iteration(true, resid, ks, dm, n, t_lr, iters, init_B, seed, Bcur, partial, Atmp, cmat, gram, w.gram_strips, st));
-  GEAR_HIP(launch_v_filter_quant(Vp, vs, dm, n, (kv_v + 1) / 2, kv_v / 2, thrV, vsz, pool_ctr + (size_t)c.B * c.H_kv, resid, st));
+  // Keys: quantize (with the Gram matrix of the residual, or leaving Y = X - S in the workspace), then their power
+  // iteration; Values reuse the same buffers afterwards.
+  const bool on_gram = pi_on_gram(n, rank, iters);
+  const int strip = on_gram ? pi_gram_strip(n, c.B * c.H_kv) : 128, nstrips = (n + strip - 1) / strip;
+  if (on_gram && nstrips > w.gram_strips) return GEAR_ECAPACITY;   // (the workspace is sized for every n the cache takes)
+  float* gram = on_gram ? reinterpret_cast<float*>(ws + w.gram) : nullptr;
+  uint16_t* resid = rank > 0 && !on_gram ? reinterpret_cast<uint16_t*>(ws + w.resid) : nullptr;
+  GEAR_HIP(launch_k_quant(Kp, ks, dm, n, t_lr, maskK, pool_ctr, resid, gram, strip, st));
   if (rank > 0)
-    GEAR_HIP(launch_power_iteration(false, resid, vs, dm, n, t_lr, iters, init_B, seed, Bcur, partial, Atmp, cmat, gram, w.gram_strips, st));
+    GEAR_HIP(launch_power_iteration(true, Kp, maskK, resid, ks, dm, n, t_lr, iters, init_B, seed, Bcur, partial, Atmp, cmat, gram, nstrips, st));
+  GEAR_HIP(launch_v_select(Vp, dm, n, (kv_v + 1) / 2, kv_v / 2, maskV, vsz, st));
+  GEAR_HIP(launch_v_quant(Vp, vs, dm, n, t_lr, (kv_v + 1) / 2, kv_v / 2, maskV, vsz, pool_ctr + (size_t)c.B * c.H_kv, resid, gram, strip, st));
+  if (rank > 0)
+    GEAR_HIP(launch_power_iteration(false, Vp, maskV, resid, vs, dm, n, t_lr, iters, init_B, seed, Bcur, partial, Atmp, cmat, gram, nstrips, st));
 
   if (first) {
     cache->n_prefill = n;

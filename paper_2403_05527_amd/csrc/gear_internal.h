@@ -25,6 +25,16 @@
 #define GEAR_PIN_VGPR(x) asm volatile("" : "+v"(x))
 #endif
 
+// The same for a value kept in a scalar register.
+#ifndef GEAR_PIN_SGPR
+#define GEAR_PIN_SGPR(x) asm volatile("" : "+s"(x))
+#endif
+
+// The scheduler moves no instruction across this point.
+#ifndef GEAR_SCHED_FENCE
+#define GEAR_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
+#endif
+
 // Block barrier that orders LDS traffic only.  __syncthreads() also drains every
 // outstanding global load and store of the wave (loads and stores share one
 // counter on this chip), which would serialise prefetched loads with the barrier;
@@ -77,6 +87,7 @@
 #define GEAR_BUF_LOAD16_NT(b, off) __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128((b), (int)(off), 0, 2))
 #define GEAR_BUF_LOAD4(b, off) ((uint32_t)__builtin_amdgcn_raw_buffer_load_b32((b), (int)(off), 0, 0))
 #define GEAR_BUF_LOAD2(b, off) ((uint32_t)__builtin_amdgcn_raw_buffer_load_b16((b), (int)(off), 0, 0))
+#define GEAR_BUF_LOAD1(b, off) ((uint32_t)__builtin_amdgcn_raw_buffer_load_b8((b), (int)(off), 0, 0))
 // a store that does not lie wholly inside the view is dropped; non-temporal (data written once, read by a later kernel)
 #define GEAR_BUF_STORE16_NT(b, off, v) \
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(gear::u32x4_t, (v)), (b), (int)(off), 0, 2)
@@ -220,6 +231,29 @@ __device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b) {
 __device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {
   return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b)));
 }
+// min / max of two pairs of fp16 values (-0 < +0; two of them in a row are one three-operand instruction)
+#ifndef GEAR_PK_MIN_F16
+#define GEAR_PK_MIN_F16(a, b) \
+  __builtin_bit_cast(uint32_t, __builtin_elementwise_minimum(__builtin_bit_cast(gear::h2_t, (a)), __builtin_bit_cast(gear::h2_t, (b))))
+#define GEAR_PK_MAX_F16(a, b) \
+  __builtin_bit_cast(uint32_t, __builtin_elementwise_maximum(__builtin_bit_cast(gear::h2_t, (a)), __builtin_bit_cast(gear::h2_t, (b))))
+#endif
+__device__ __forceinline__ uint32_t pk_min_f16(uint32_t a, uint32_t b) { return GEAR_PK_MIN_F16(a, b); }
+__device__ __forceinline__ uint32_t pk_max_f16(uint32_t a, uint32_t b) { return GEAR_PK_MAX_F16(a, b); }
+// two floats rounded to nearest even fp16 values, one instruction
+__device__ __forceinline__ uint32_t pack_h2(float a, float b) {
+  h2_t h = {(_Float16)a, (_Float16)b};
+  return __builtin_bit_cast(uint32_t, h);
+}
+// A row piece of eight fp16 values with the entries whose bit is set in f (bit e: entry e) replaced by 0.
+__device__ __forceinline__ uint4 drop_entries(uint4 v, uint32_t f) {
+  const uint32_t g = f | (f << 15);   // bit 2w and bit 2w + 16: the entries of word w
+  auto word = [&](uint32_t x, int w) {
+    const uint32_t m = __builtin_bit_cast(uint32_t, u16x2_t{0, 0} - __builtin_bit_cast(u16x2_t, (g >> (2 * w)) & 0x00010001u));
+    return x & ~m;
+  };
+  return make_uint4(word(v.x, 0), word(v.y, 1), word(v.z, 2), word(v.w, 3));
+}
 // fp16 entry e (0..7) of a row piece of four words
 // (the words are passed by value: selecting between elements of an array in place is
 // compiled into an indexed load, which moves the array to scratch memory)
@@ -237,6 +271,12 @@ __device__ __forceinline__ uint32_t half_of(uint32_t w0, uint32_t w1, uint32_t w
 struct ThreshPair {
   uint32_t top, bot;
 };
+__device__ __forceinline__ bool outlier(uint32_t key, uint32_t idx, const ThreshPair& p) {
+  return ((key << 16) | (0xFFFFu - idx)) >= p.top || ((key << 16) | idx) < p.bot;
+}
+__device__ __forceinline__ uint32_t slot_key(const uint32_t (&kw)[4], int e) {   // key e (0..7, a constant) of a row piece
+  return (e & 1) ? kw[e >> 1] >> 16 : kw[e >> 1] & 0xFFFFu;
+}
 __device__ __forceinline__ ThreshPair pack_thresh(const Thresh& th) {
   ThreshPair p;
   if (th.tau_top > 0xFFFFu) {

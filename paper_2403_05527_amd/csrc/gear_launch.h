@@ -16,30 +16,38 @@ struct ChunkSet {
 
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, size_t count, hipStream_t st);
 
-// also clears zero[0 .. zero_count) (the list counters of the call); under the per-vector grouping it also writes
-// every channel's (scale, zero) of the segment sv
-hipError_t launch_k_select(const uint16_t* K, const Dims& dm, int n, int k_top, int k_bot, ThreshPair* thrK,
+// mask: [slab][n], 16 bytes per token row: bit c = entry (row, c) belongs to S (Filter_s, Eq. 4); not written when ppm is 0.
+// The Key kernel also clears zero[0 .. zero_count) (the list counters of the call); under the per-vector grouping it also
+// writes every channel's (scale, zero) of the segment sv
+hipError_t launch_k_select(const uint16_t* K, const Dims& dm, int n, int k_top, int k_bot, uint4* mask,
                            uint32_t* zero, int zero_count, const SegView& sv, uint16_t* kt_scratch, hipStream_t st);
-// Yout (nullable): [slab][n][128] fp16, Y = X - S (the input with its outliers zeroed), from
-// which the power iteration re-derives the residual R = Y - D-hat.
-hipError_t launch_k_quant(const uint16_t* K, const SegView& sv, const Dims& dm, int n, const ThreshPair* thrK,
-                          uint32_t* pool_ctr, uint16_t* Yout, hipStream_t st);
-// k_top / k_bot: per Value vector (the token's row over all heads, or one head's channels of it); vsz: [B][n] words,
-// a token's (scale, zero) under the per-vector grouping
-hipError_t launch_v_filter_quant(const uint16_t* V, const SegView& sv, const Dims& dm, int n, int k_top,
-                                 int k_bot, ThreshPair* thrV, uint32_t* vsz, uint32_t* pool_ctr, uint16_t* Yout,
-                                 hipStream_t st);
+// k_top / k_bot: per Value vector (the token's row over all heads); vsz: [B][n] words, a token's (scale, zero) under the
+// per-vector grouping
+hipError_t launch_v_select(const uint16_t* V, const Dims& dm, int n, int k_top, int k_bot, uint4* mask, uint32_t* vsz,
+                           hipStream_t st);
+// Quantization of one tensor given its mask (compress_quant.h).  gram != nullptr: the same pass leaves the partial Gram
+// matrices of the residual, [slab][strip of `strip` tokens][GRAM_FLOATS].  Yout (nullable): [slab][n][128] fp16,
+// Y = X - S, from which the other low-rank solvers re-derive the residual R = Y - D-hat.  k_top / k_bot (Values with the
+// Filter per head, which this launch finds by itself): per head's vector.
+constexpr int GRAM_TILES = 36;
+constexpr int GRAM_FLOATS = GRAM_TILES * 256;
+hipError_t launch_k_quant(const uint16_t* K, const SegView& sv, const Dims& dm, int n, int t_lr, uint4* mask, uint32_t* pool_ctr,
+                          uint16_t* Yout, float* gram, int strip, hipStream_t st);
+hipError_t launch_v_quant(const uint16_t* V, const SegView& sv, const Dims& dm, int n, int t_lr, int k_top, int k_bot, uint4* mask,
+                          const uint32_t* vsz, uint32_t* pool_ctr, uint16_t* Yout, float* gram, int strip, hipStream_t st);
 
 int pi_padded_rank(int rank);
-// gram: [slab][strip][36 * 256] floats, the partial Gram matrices of the residual (segments of more than 256 tokens
-// with iters > 1); gram_strips_cap: strips per slab it has room for (pi_gram_strips_max of the largest segment)
+// Tokens per strip of the pass that forms the Gram matrices; the most strips per slab any segment of up to n_max tokens gets
+int pi_gram_strip(int n, int slabs);
 int pi_gram_strips_max(int n_max, int slabs);
+// whether a segment of n tokens is solved on its Gram matrix (launch_power_iteration then takes X and its mask instead of Y)
+inline bool pi_on_gram(int n, int rank, int iters) { return rank > 0 && iters > 1 && n > 256; }
 // init_B: the whole start array [2 (K, V), B, H, 128, rank] (the launcher takes this tensor's half), or
 // nullptr: the same array is drawn from `seed` (start_entry in gear_internal.h)
 // t_lr: first token of the segment that takes part in the low-rank term (rows before it get A = 0)
-hipError_t launch_power_iteration(bool is_k, const uint16_t* Yf, const SegView& sv, const Dims& dm, int n, int t_lr, int iters,
-                                  const float* init_B, uint64_t seed, float* Bcur, float* partial, float* Atmp, float* cmat,
-                                  float* gram, int gram_strips_cap, hipStream_t st);
+hipError_t launch_power_iteration(bool is_k, const uint16_t* X, const uint4* mask, const uint16_t* Yf, const SegView& sv,
+                                  const Dims& dm, int n, int t_lr, int iters, const float* init_B, uint64_t seed, float* Bcur,
+                                  float* partial, float* Atmp, float* cmat, float* gram, int nstrips, hipStream_t st);
 
 constexpr int DECODE_TS = 256;           // rows per pass of the chunk / buffer path
 constexpr int DECODE_SPLIT = 512;        // prefill tokens per split block

@@ -1,16 +1,13 @@
 // SVDSolver_r (Eq. 6, Algorithm 2): batched power iteration on the per-head
-// residual R = X - D - S.  The quantization kernels leave Y = X - S (fp16, outliers
-// zeroed) in a workspace buffer; every sweep re-derives R = (Y - zero) - code * scale from it
-// (Keys: with the stored codes; Values: with the code recomputed by the quantizer's own
-// operation sequence).  That is exact (no rounded copy of R) and costs 2 bytes per entry and
-// pass, for three more vector instructions per entry than reading a stored remainder; a
-// 16-bit copy of R itself flips enough fp16 roundings of the stored factors to fail the
-// attention tolerance.
+// residual R = X - D - S.  No copy of R exists: every pass re-derives R = (Y - zero) - code * scale, Y = X - S, from
+// X and the mask of S (or, in the solvers of short segments and of a single round, from a copy of Y in the workspace)
+// and the stored scale (Keys: with the stored codes; Values: with the code recomputed by the quantizer's own operation
+// sequence).  That is exact, and a 16-bit copy of R itself flips enough fp16 roundings of the stored factors to fail
+// the attention tolerance.
 //
-//   pi_gram    : G = R^T R (128 x 128 per slab) in one pass over the residual, on the
-//                matrix cores.  Every round of Algorithm 2 before the last maps
-//                B -> R^T (R B) = G B, so those rounds need no pass over R of their
-//                own: they become 128 x 128 x r products on G.
+//   (the quantization kernel leaves G = R^T R, 128 x 128 per slab, as partial sums: compress_quant.h.  Every round of
+//   Algorithm 2 before the last maps B -> R^T (R B) = G B, so those rounds need no pass over R of their own: they become
+//   128 x 128 x r products on G.)
 //   pi_solve   : B <- G^(L-1) B0 (columns rescaled between the products: the span,
 //                hence A B^T, is unchanged), then the QR of B that opens the last round.
 //                With L > 1 the last round comes out of G as well: for A = R Q (Q = that
@@ -283,7 +280,8 @@ __device__ __forceinline__ void pi_sweep_body(SweepSmem<IS_K, R>& sm, int slab, 
                                               const uint32_t* __restrict__ sv_sz, const uint32_t* __restrict__ sv_codes,
                                               int sv_n_cap, int sv_ng_cap, int g, int bits, int n, int t_lr,
                                               const float* __restrict__ Bcur, float* __restrict__ partial, int npart,
-                                              float* __restrict__ Atmp, uint16_t* __restrict__ A_out = nullptr, int rank = 0) {
+                                              float* __restrict__ Atmp, uint16_t* __restrict__ A_out = nullptr, int rank = 0,
+                                              const uint4* __restrict__ mask = nullptr) {
   float (&red)[4][D * R] = sm.red;
   float (&redg)[4][R * R] = sm.redg;
   float* prm = sm.prm;
@@ -300,12 +298,14 @@ __device__ __forceinline__ void pi_sweep_body(SweepSmem<IS_K, R>& sm, int slab, 
   // (buffer views of the slab's rows: a row past the end reads as 0)
   const GEAR_BUF_T xbuf = GEAR_BUF_MAKE(Xs, n * (D * 2));
   const GEAR_BUF_T cbuf = GEAR_BUF_MAKE(crow, IS_K ? n * (16 * bits) : 0);
+  const GEAR_BUF_T mbuf = GEAR_BUF_MAKE(mask + (size_t)slab * n, PROJECT && mask ? n * 16 : 0);   // without a mask: reads as 0
   const int xoff0 = (pt * PT + r0) * (D * 2) + oc * 16;
   const int coff0 = (pt * PT + r0) * (16 * bits) + oc * (bits == 4 ? 4 : 2);
-  auto request = [&](int k0, uint4 (&xv)[UN], uint32_t (&cw)[UN]) {
+  auto request = [&](int k0, uint4 (&xv)[UN], uint32_t (&cw)[UN], uint32_t (&mk)[UN]) {
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
       xv[u] = GEAR_BUF_LOAD16_NT(xbuf, xoff0 + 16 * (k0 + u) * (D * 2));
+      if (PROJECT) mk[u] = GEAR_BUF_LOAD1(mbuf, (pt * PT + r0 + 16 * (k0 + u)) * 16 + oc);
       cw[u] = 0u;
       if (IS_K) {
         const int co = coff0 + 16 * (k0 + u) * (16 * bits);
@@ -315,7 +315,8 @@ __device__ __forceinline__ void pi_sweep_body(SweepSmem<IS_K, R>& sm, int slab, 
   };
   uint4 xv_first[UN];
   uint32_t cw_first[UN];   // Keys: the row piece's 8 codes
-  request(0, xv_first, cw_first);   // in flight while the parameters are prepared
+  uint32_t mk_first[UN];   // PROJECT: which of its entries belong to S
+  request(0, xv_first, cw_first, mk_first);   // in flight while the parameters are prepared
 
   if (IS_K) {
     const int ngb = (PT >> lg) > 0 ? (PT >> lg) : 1, grp0 = (pt * PT) >> lg, ng = (n + g - 1) >> lg;
@@ -360,12 +361,16 @@ __device__ __forceinline__ void pi_sweep_body(SweepSmem<IS_K, R>& sm, int slab, 
   for (int k0 = 0; k0 < PT / 16; k0 += UN) {
     if (pt * PT + 16 * k0 >= n) break;  // block-uniform
     uint4 xv[UN];
-    uint32_t cw[UN];
+    uint32_t cw[UN], mk[UN];
     if (k0 == 0) {
 #pragma unroll
-      for (int u = 0; u < UN; ++u) { xv[u] = xv_first[u]; cw[u] = cw_first[u]; }
+      for (int u = 0; u < UN; ++u) { xv[u] = xv_first[u]; cw[u] = cw_first[u]; mk[u] = mk_first[u]; }
     } else {
-      request(k0, xv, cw);
+      request(k0, xv, cw, mk);
+    }
+    if (PROJECT) {
+#pragma unroll
+      for (int u = 0; u < UN; ++u) xv[u] = drop_entries(xv[u], mk[u]);
     }
     float pmn[8], pdl[8];   // Keys: parameters of my 8 channels in the current group
     int gi_prev = -1;
@@ -506,13 +511,14 @@ __global__ __launch_bounds__(256, (R <= 2 ? 4 : R <= 4 ? 3 : 2)) void pi_sweep_k
 }
 
 // The pass of the last round when the Gram matrix exists: A = R W with the projection matrix W that
-// pi_solve_kernel left in Bcur, written to the arena as fp16.  grid (ceil(n / 256), B*H), block 256.
+// pi_solve_kernel left in Bcur, written to the arena as fp16; from X itself, whose entries in S are masked out.  grid (ceil(n / 256), B*H), block 256.
 template <bool IS_K, int R>
-__global__ __launch_bounds__(256, (R <= 4 ? 4 : 3)) void pi_project_kernel(const uint16_t* __restrict__ Y, SegView sv, int g, int bits,
+__global__ __launch_bounds__(256, (R <= 4 ? 4 : 3)) void pi_project_kernel(const uint16_t* __restrict__ X, const uint4* __restrict__ mask,
+                                                                         SegView sv, int g, int bits,
                                                                          int n, int t_lr, const float* __restrict__ Bcur) {
   __shared__ SweepSmem<IS_K, R> sm;
-  pi_sweep_body<IS_K, R, false, true>(sm, blockIdx.y, blockIdx.x, Y, sv.sz, sv.codes, sv.n_cap, sv.ng_cap, g, bits, n, t_lr, Bcur,
-                                      nullptr, 0, nullptr, sv.A, sv.rank);
+  pi_sweep_body<IS_K, R, false, true>(sm, blockIdx.y, blockIdx.x, X, sv.sz, sv.codes, sv.n_cap, sv.ng_cap, g, bits, n, t_lr, Bcur,
+                                      nullptr, 0, nullptr, sv.A, sv.rank, mask);
 }
 
 // A = a C for tokens [256 * pt, 256 * pt + 256) of one slab, one token per thread.  Cs: LDS, R * R floats.
@@ -579,199 +585,23 @@ __global__ __launch_bounds__(256, 1) void pi_small_kernel(const uint16_t* __rest
   pi_finish_body<R>(Cs, slab, 0, Atmp, cmat, sv, n);
 }
 
-// ------------------------------------------------------------------ Gram matrix of the residual
-// Rounds 1 .. L-1 of Algorithm 2 compute A = R B, B = R^T A without any orthonormalisation in
-// between, i.e. B <- (R^T R) B.  G = R^T R is formed once, in one pass over the slab, as a dense
-// contraction over the tokens on v_mfma_f32_16x16x32_f16; the rounds themselves then cost
-// 128 x 128 x r multiply-adds per slab (pi_solve_kernel).  A residual entry enters the
-// contraction as two fp16 numbers, its leading part and what that leaves (22 bits together), and
-// a product as three MFMA terms; accumulation is fp32.  (The leading parts alone are not enough:
-// without orthonormalisation between the rounds the weaker directions of G^(L-1) B0 are small
-// differences of large numbers, and a relative error of 2^-11 in G is amplified by the square
-// of the ratio of its leading eigenvalues.)  G only chooses the subspace that the last round
-// projects on: that round (pi_sweep_kernel<.., LAST>) still reads the residual itself, so
-// A = orth(R B) and B = R^T A are computed from R.
-//
-// grid (ceil(n / strip), B*H), block 256.  A block walks its strip of tokens in steps of 128;
-// thread (r0 = tid/16, oc = tid%16) takes channels 8*oc..+7 of rows base + r0 + 16*k, k = 0..7.
-// The 16 lanes that share r0 hold the same 8 tokens: as an MFMA operand, register j of
-// "channel e" holds rows (2j, 2j+1) of channel 8*oc + e, so operand e is the 16 channels
-// {8*oc + e} x 32 tokens of the wave and acc(e, e') += op_e^T op_e' is one 16 x 16 tile of G:
-// lane l, register i <-> G[8*(4*(l/16)+i) + e][8*(l%16) + e'].  Only the 36 tiles e <= e' are
-// computed (G is symmetric).  The four waves' tiles are summed through LDS and written as one
-// partial per strip: [slab][strip][36][4][64] floats.
-constexpr int GRAM_TILES = 36;
-constexpr int GRAM_FLOATS = GRAM_TILES * 256;
-
-typedef _Float16 gram_h2 __attribute__((ext_vector_type(2)));
-typedef _Float16 gram_h8 __attribute__((ext_vector_type(8)));
-__device__ __forceinline__ uint32_t pack_h2(float a, float b) {   // two roundings to nearest even, one instruction
-  gram_h2 h = {(_Float16)a, (_Float16)b};
-  return __builtin_bit_cast(uint32_t, h);
-}
-
-// The loads of one step of the Gram pass (128 tokens, 8 rows per thread), requested together.
-template <bool IS_K, int NGS>
-struct GramLoads {
-  uint4 xv[8];
-  uint32_t cw[8];      // Keys: the row piece's 8 codes
-  uint32_t pv[8];      // Values: (scale, zero) of my row's channel group
-  uint4 pz[NGS][2];    // Keys: (scale, zero) of my 8 channels in the step's groups
-};
-
-template <bool IS_K, int LG>   // LG: log2 of the Key group size (Values take the group size at run time)
-__global__ __launch_bounds__(256, 2) void pi_gram_kernel(const uint16_t* __restrict__ Y, SegView sv, int g, int bits, int n,
-                                                         int t_lr, int strip, float* __restrict__ gram_partial) {
-  __shared__ float red[GRAM_FLOATS];
-  const int slab = blockIdx.y, sidx = blockIdx.x, nstrips = gridDim.x;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int r0 = tid >> 4, oc = tid & 15;
-  const int t_begin = sidx * strip;
-  const int t_end = t_begin + strip < n ? t_begin + strip : n;
-  const float qmax = (float)((1 << bits) - 1);
-  const int lgv = 31 - __clz(g), ngl = 7 - lgv;   // Values: log2 of the group size / of the groups per row
-  const GEAR_BUF_T xbuf = GEAR_BUF_MAKE(Y + (size_t)slab * n * D, n * (D * 2));
-  const GEAR_BUF_T cbuf = GEAR_BUF_MAKE(sv.codes + (size_t)slab * sv.n_cap * (4 * bits), IS_K ? n * (16 * bits) : 0);
-  // (scale, zero) words: Keys [group][128] of this slab, Values [row][groups of a row]
-  const GEAR_BUF_T pbuf = IS_K ? GEAR_BUF_MAKE(sv.sz + (size_t)slab * sv.ng_cap * D, ((n + g - 1) >> LG) * (D * 4))
-                               : GEAR_BUF_MAKE(sv.sz + (((size_t)slab * sv.n_cap) << ngl), (n << ngl) * 4);
-  constexpr int GT = 128;                          // tokens per step (32 per wave)
-  constexpr int NGS = (IS_K && (GT >> LG) > 0) ? (GT >> LG) : 1;   // Key groups per step
-  typedef GramLoads<IS_K, NGS> Loads;
-
-  floatx4 acc[GRAM_TILES];
+// Sums a slab's partial Gram matrices into the first of them where there are many (long segments with few slabs): the
+// solve kernel, one block per slab, would wait for one after another.  grid (GRAM_TILES, B*H), block 256.
+constexpr int GRAM_SUM_MIN = 8;   // fewer than this are summed by the solve kernel: a launch costs as much as four to eight of them
+__global__ __launch_bounds__(256) void gram_sum_kernel(float* __restrict__ gram, int nstrips) {
+  float* g = gram + (size_t)blockIdx.y * nstrips * GRAM_FLOATS + blockIdx.x * 256 + threadIdx.x;
+  float sum = 0.0f;
+  for (int s0 = 0; s0 < nstrips; s0 += 16) {
+    float t[16];
 #pragma unroll
-  for (int i = 0; i < GRAM_TILES; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-#pragma unroll 1
-  for (int base = t_begin; base < t_end; base += GT) {
-    // every load of the step is requested before the first one is used
-    Loads L;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int t = base + r0 + 16 * k;
-      L.xv[k] = GEAR_BUF_LOAD16_NT(xbuf, t * (D * 2) + oc * 16);   // rows past the end read as 0
-      L.cw[k] = 0u;
-      L.pv[k] = 0u;
-      if (IS_K) {
-        const int co = t * (16 * bits) + oc * (bits == 4 ? 4 : 2);
-        L.cw[k] = bits == 4 ? GEAR_BUF_LOAD4(cbuf, co) : GEAR_BUF_LOAD2(cbuf, co);
-      } else {
-        L.pv[k] = GEAR_BUF_LOAD4(pbuf, ((t << ngl) + ((oc * 8) >> lgv)) * 4);
-      }
+    for (int u = 0; u < 16; ++u) {
+      t[u] = 0.0f;
+      if (s0 + u < nstrips) t[u] = __builtin_nontemporal_load(g + (size_t)(s0 + u) * GRAM_FLOATS);   // block-uniform
     }
-    if (IS_K) {
 #pragma unroll
-      for (int j = 0; j < NGS; ++j) {
-        const int off = (((base >> LG) + j) * D + oc * 8) * 4;
-        L.pz[j][0] = GEAR_BUF_LOAD16(pbuf, off);
-        L.pz[j][1] = GEAR_BUF_LOAD16(pbuf, off + 16);
-      }
-    }
-    // residuals of the step as fp16 operands: leading part, and what it leaves (22 bits together)
-    const bool ragged = base + GT > n;   // block-uniform: only such a step has rows past the end
-    uint32_t oph[8][4], opl[8][4];
-    float pmn[8], pdl[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) { pmn[e] = 0.0f; pdl[e] = 0.0f; }
-    float ra[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const uint32_t w[4] = {L.xv[k].x, L.xv[k].y, L.xv[k].z, L.xv[k].w};
-      float res[8];
-      if (IS_K) {
-        if ((16 * k) % (1 << (LG < 8 ? LG : 8)) == 0) {   // first rows of a group: its parameters
-          const int j = (16 * k) >> LG;
-          const uint32_t z[8] = {L.pz[j][0].x, L.pz[j][0].y, L.pz[j][0].z, L.pz[j][0].w,
-                                 L.pz[j][1].x, L.pz[j][1].y, L.pz[j][1].z, L.pz[j][1].w};
-#pragma unroll
-          for (int e = 0; e < 8; ++e) { pdl[e] = h2f(z[e] & 0xFFFFu); pmn[e] = h2f(z[e] >> 16); }
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float y = h2f((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xFFFFu));
-          res[e] = __builtin_fmaf(-(float)GEAR_UBFE(L.cw[k], e * bits, bits), pdl[e], y - pmn[e]);
-        }
-      } else {
-        const GroupQ q = load_group(L.pv[k]);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float y = h2f((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xFFFFu));
-          res[e] = quant_error(y, q.mn, q.inv, q.delta, qmax);
-        }
-      }
-      // Keys: a row past the end has res = -zero-point, not 0 (Values: the parameters of such rows are 0)
-      // (rows before t_lr take no part in the low-rank term)
-      if ((IS_K && ragged && base + r0 + 16 * k >= n) || base + r0 + 16 * k < t_lr) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) res[e] = 0.0f;
-      }
-      if ((k & 1) == 0) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) ra[e] = res[e];
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const uint32_t hi = pack_h2(ra[e], res[e]);
-          oph[e][k >> 1] = hi;
-          opl[e][k >> 1] = pack_h2(ra[e] - h2f(hi & 0xFFFFu), res[e] - h2f(hi >> 16));
-        }
-      }
-    }
-    // the 36 tiles: r r' = hi hi' + hi lo' + lo hi' (the lo lo' term is below fp32 resolution)
-    int ti = 0;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const gram_h8 ah = __builtin_bit_cast(gram_h8, make_uint4(oph[e][0], oph[e][1], oph[e][2], oph[e][3]));
-      const gram_h8 al = __builtin_bit_cast(gram_h8, make_uint4(opl[e][0], opl[e][1], opl[e][2], opl[e][3]));
-#pragma unroll
-      for (int f = e; f < 8; ++f) {
-        const gram_h8 bh = __builtin_bit_cast(gram_h8, make_uint4(oph[f][0], oph[f][1], oph[f][2], oph[f][3]));
-        const gram_h8 bl = __builtin_bit_cast(gram_h8, make_uint4(opl[f][0], opl[f][1], opl[f][2], opl[f][3]));
-        acc[ti] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bh, acc[ti], 0, 0, 0);
-        acc[ti] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bl, acc[ti], 0, 0, 0);
-        acc[ti] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, bh, acc[ti], 0, 0, 0);
-        ++ti;
-      }
-    }
+    for (int u = 0; u < 16; ++u) sum += t[u];
   }
-
-  // the four waves' tiles, added in wave order (a fixed order: results do not vary from run to run);
-  // a few tiles at a time, so that the LDS reads in flight stay few
-  float* out = gram_partial + ((size_t)slab * nstrips + sidx) * GRAM_FLOATS;
-  if (wave == 0) {
-#pragma unroll
-    for (int ti = 0; ti < GRAM_TILES; ++ti)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) red[ti * 256 + i * 64 + lane] = acc[ti][i];
-  }
-  block_lds_sync();
-#pragma unroll 1
-  for (int w = 1; w < 3; ++w) {
-    if (wave == w) {
-#pragma unroll
-      for (int ti = 0; ti < GRAM_TILES; ++ti) {
-        float v[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = red[ti * 256 + i * 64 + lane];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) red[ti * 256 + i * 64 + lane] = v[i] + acc[ti][i];
-        GEAR_PIN_VGPR(v[0]);   // keeps the tiles' reads from being hoisted above each other's writes en bloc
-      }
-    }
-    block_lds_sync();
-  }
-  if (wave == 3) {
-#pragma unroll
-    for (int ti = 0; ti < GRAM_TILES; ++ti) {
-      float v[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) v[i] = red[ti * 256 + i * 64 + lane];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) out[ti * 256 + i * 64 + lane] = v[i] + acc[ti][i];
-      GEAR_PIN_VGPR(v[0]);
-    }
-  }
+  *g = sum;
 }
 
 // B <- G^rounds B0, then the Q factor of its QR (the orthonormalisation of B that opens the last
@@ -864,7 +694,7 @@ __device__ __forceinline__ void qr_columns(double (&q)[R], double (*Bq)[R] /* LD
 // (0, c); the upper half of the block helps with the loads of G and with half of every product.
 template <int R>
 __global__ __launch_bounds__(256) void pi_solve_kernel(StartB sb, int rank,
-                                                       const float* __restrict__ gram_partial, int nstrips, int rounds,
+                                                       const float* __restrict__ gram_partial, int nstrips, int stride, int rounds,
                                                        float* __restrict__ Bcur, int last_round, SegView sv) {
   GEAR_DYN_LDS(smem_raw);
   SolveSmem<R>& sm = *reinterpret_cast<SolveSmem<R>*>(smem_raw);
@@ -872,7 +702,7 @@ __global__ __launch_bounds__(256) void pi_solve_kernel(StartB sb, int rank,
   const bool owner = half == 0;
   if (rounds > 0) {
     // G = sum of the strips' partial tiles (fixed order): element tid + 256 j is register j % 4... of tile j
-    const float* gp = gram_partial + (size_t)slab * nstrips * GRAM_FLOATS + threadIdx.x;
+    const float* gp = gram_partial + (size_t)slab * stride * GRAM_FLOATS + threadIdx.x;   // (stride: strips per slab in memory)
     float s[GRAM_TILES];
 #pragma unroll
     for (int j = 0; j < GRAM_TILES; ++j) s[j] = 0.0f;
@@ -1200,31 +1030,24 @@ __global__ __launch_bounds__(256) void pi_tiny_kernel(const uint16_t* __restrict
 }
 
 // ------------------------------------------------------------------ host side
-// Tokens per strip of the Gram pass: the longest that still gives every resident block slot (two per CU,
-// 512 on the chip) a strip; the solve kernel, one block per slab, then has the fewest partials to add.
+// Tokens per strip of the pass that forms the Gram matrices: the longest that still gives every resident block slot (two
+// per CU, 512 on the chip) a strip; the solve kernel, one block per slab, then has the fewest partials to add.
 int pi_gram_strip(int n, int slabs) {
-  for (int strip = 2048; strip > 512; strip >>= 1)
+  for (int strip = 2048; strip > 128; strip >>= 1)
     if ((long long)slabs * ((n + strip - 1) / strip) >= 512) return strip;
-  return 512;
+  return 128;
 }
 int pi_gram_strips_max(int n_max, int slabs) {
   const int m = (1024 + slabs - 1) / slabs;   // strips per slab that fill the chip
-  const int coarse = (n_max + 2047) / 2048, fine = (n_max + 511) / 512;
+  const int coarse = (n_max + 2047) / 2048, fine = (n_max + 127) / 128;
   const int want = 2 * m > coarse ? 2 * m : coarse;
   return want < fine ? want : fine;
 }
 
-template <bool IS_K, int LG>
-static void launch_gram(const uint16_t* Yf, const SegView& sv, const Dims& dm, int n, int t_lr, int strip, int nstrips, float* gram,
-                        hipStream_t st) {
-  // (per-vector grouping: the one Key group of a segment is addressed as a group of 32768 tokens)
-  hipLaunchKernelGGL((pi_gram_kernel<IS_K, LG>), dim3(nstrips, dm.B * dm.H), dim3(256), 0, st, Yf, sv, IS_K ? 1 << LG : dm.g, dm.bits, n, t_lr, strip, gram);
-}
-
 template <int R>
-static hipError_t run_pi(bool is_k, const uint16_t* Yf, const SegView& sv, const Dims& dm, int n, int t_lr, int iters,
-                         StartB sb, float* Bcur, float* partial, float* Atmp, float* cmat, float* gram,
-                         int gram_strips_cap, hipStream_t st) {
+static hipError_t run_pi(bool is_k, const uint16_t* X, const uint4* mask, const uint16_t* Yf, const SegView& sv, const Dims& dm,
+                         int n, int t_lr, int iters, StartB sb, float* Bcur, float* partial, float* Atmp, float* cmat,
+                         float* gram, int nstrips, hipStream_t st) {
   const int slabs = dm.B * dm.H;
   const int npart = (n + PT - 1) / PT;
   const int g_eff = (is_k && dm.kcvt) ? 32768 : dm.g;   // per-vector grouping: one Key group per segment
@@ -1242,18 +1065,6 @@ static hipError_t run_pi(bool is_k, const uint16_t* Yf, const SegView& sv, const
       hipLaunchKernelGGL((pi_small_kernel<false, R>), dim3(slabs), dim3(256), 0, st, Yf, sv, dm.g, dm.bits, n, t_lr, iters, sb, Bcur, partial, Atmp, cmat);
     return hipGetLastError();
   }
-  // rounds 1 .. L-1: B <- (R^T R)^(L-1) B0 from one pass that forms the Gram matrix; then QR(B)
-  int nstrips = 0;
-  if (iters > 1) {
-    const int strip = pi_gram_strip(n, slabs);
-    nstrips = (n + strip - 1) / strip;
-    if (nstrips > gram_strips_cap) return hipErrorInvalidValue;
-    if (!is_k) launch_gram<false, 0>(Yf, sv, dm, n, t_lr, strip, nstrips, gram, st);
-    else if (dm.kcvt) launch_gram<true, 15>(Yf, sv, dm, n, t_lr, strip, nstrips, gram, st);
-    else if (dm.g == 32) launch_gram<true, 5>(Yf, sv, dm, n, t_lr, strip, nstrips, gram, st);
-    else if (dm.g == 64) launch_gram<true, 6>(Yf, sv, dm, n, t_lr, strip, nstrips, gram, st);
-    else launch_gram<true, 7>(Yf, sv, dm, n, t_lr, strip, nstrips, gram, st);
-  }
   {
     static std::atomic<bool> lds_raised{false};   // per kernel instance (R); two threads may both raise it: harmless
     if (!lds_raised.load(std::memory_order_relaxed)) {
@@ -1263,15 +1074,18 @@ static hipError_t run_pi(bool is_k, const uint16_t* Yf, const SegView& sv, const
       lds_raised.store(true, std::memory_order_relaxed);
     }
   }
+  // rounds 1 .. L-1: B <- (R^T R)^(L-1) B0 on the Gram matrix; then QR(B)
+  const bool summed = iters > 1 && nstrips >= GRAM_SUM_MIN;
+  if (summed) hipLaunchKernelGGL(gram_sum_kernel, dim3(GRAM_TILES, slabs), dim3(256), 0, st, gram, nstrips);
   hipLaunchKernelGGL(pi_solve_kernel<R>, dim3(slabs), dim3(256), sizeof(SolveSmem<R>), st, sb, sv.rank, (const float*)gram,
-                     nstrips, iters - 1, Bcur, iters > 1 ? 1 : 0, sv);
+                     iters > 1 ? (summed ? 1 : nstrips) : 0, nstrips, iters - 1, Bcur, iters > 1 ? 1 : 0, sv);
   if (iters > 1) {
     // the last round's B and the factor of orth(A) came out of the Gram matrix; one light pass writes A
     const dim3 grid(npart, slabs);
     if (is_k)
-      hipLaunchKernelGGL((pi_project_kernel<true, R>), grid, dim3(256), 0, st, Yf, sv, g_eff, dm.bits, n, t_lr, (const float*)Bcur);
+      hipLaunchKernelGGL((pi_project_kernel<true, R>), grid, dim3(256), 0, st, X, mask, sv, g_eff, dm.bits, n, t_lr, (const float*)Bcur);
     else
-      hipLaunchKernelGGL((pi_project_kernel<false, R>), grid, dim3(256), 0, st, Yf, sv, dm.g, dm.bits, n, t_lr, (const float*)Bcur);
+      hipLaunchKernelGGL((pi_project_kernel<false, R>), grid, dim3(256), 0, st, X, mask, sv, dm.g, dm.bits, n, t_lr, (const float*)Bcur);
     return hipGetLastError();
   }
   // a single round (no Gram pass): A = R B, orth(A) through its r x r Gram matrix, B = R^T A
@@ -1291,16 +1105,17 @@ static hipError_t run_pi(bool is_k, const uint16_t* Yf, const SegView& sv, const
 
 int pi_padded_rank(int rank) { return rank <= 2 ? 2 : rank <= 4 ? 4 : 8; }
 
-hipError_t launch_power_iteration(bool is_k, const uint16_t* Yf, const SegView& sv, const Dims& dm, int n, int t_lr, int iters,
-                                  const float* init_B, uint64_t seed, float* Bcur, float* partial, float* Atmp, float* cmat,
-                                  float* gram, int gram_strips_cap, hipStream_t st) {
+hipError_t launch_power_iteration(bool is_k, const uint16_t* X, const uint4* mask, const uint16_t* Yf, const SegView& sv,
+                                  const Dims& dm, int n, int t_lr, int iters, const float* init_B, uint64_t seed, float* Bcur,
+                                  float* partial, float* Atmp, float* cmat, float* gram, int nstrips, hipStream_t st) {
   // this tensor's part of the [2 (K, V), B, H, 128, rank] start array
   const uint64_t tensor_entries = (uint64_t)dm.B * dm.H * D * sv.rank;
   const StartB sb{init_B ? init_B + (is_k ? 0 : tensor_entries) : nullptr, seed, is_k ? 0 : tensor_entries};
+  if (dm.ppm == 0) mask = nullptr;
   switch (pi_padded_rank(sv.rank)) {
-    case 2: return run_pi<2>(is_k, Yf, sv, dm, n, t_lr, iters, sb, Bcur, partial, Atmp, cmat, gram, gram_strips_cap, st);
-    case 4: return run_pi<4>(is_k, Yf, sv, dm, n, t_lr, iters, sb, Bcur, partial, Atmp, cmat, gram, gram_strips_cap, st);
-    default: return run_pi<8>(is_k, Yf, sv, dm, n, t_lr, iters, sb, Bcur, partial, Atmp, cmat, gram, gram_strips_cap, st);
+    case 2: return run_pi<2>(is_k, X, mask, Yf, sv, dm, n, t_lr, iters, sb, Bcur, partial, Atmp, cmat, gram, nstrips, st);
+    case 4: return run_pi<4>(is_k, X, mask, Yf, sv, dm, n, t_lr, iters, sb, Bcur, partial, Atmp, cmat, gram, nstrips, st);
+    default: return run_pi<8>(is_k, X, mask, Yf, sv, dm, n, t_lr, iters, sb, Bcur, partial, Atmp, cmat, gram, nstrips, st);
   }
 }
 

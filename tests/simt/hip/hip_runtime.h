@@ -47,7 +47,13 @@ inline hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 #define HIP_SYMBOL(x) x
 inline hipError_t hipGetSymbolAddress(void** p, const void* sym) { *p = const_cast<void*>(sym); return hipSuccess; }
 #define GEAR_DYN_LDS(name) unsigned char* name = simt::dyn_lds
-#define GEAR_PIN_VGPR(x) asm volatile("" : "+r"(x))
+#define GEAR_PIN_VGPR(x) asm volatile("" : "+m"(x))
+#define GEAR_SCHED_FENCE() ((void)0)
+#define GEAR_PIN_SGPR(x) asm volatile("" : "+x"(x))
+#define GEAR_PK_MIN_F16(a, b) simt_pk_f16((a), (b), true)
+#define GEAR_PK_MAX_F16(a, b) simt_pk_f16((a), (b), false)
+#define GEAR_LANE_SWAP32(a, b) simt::lane_swap((a), (b), 32)
+#define GEAR_LANE_SWAP16(a, b) simt::lane_swap((a), (b), 16)
 #define GEAR_LDS_BARRIER() pthread_barrier_wait(&simt::block_bar)
 #define GEAR_WAVE_UNIFORM(x) (x)
 #define GEAR_BYTE_PERM(hi, lo, sel) simt_byte_perm((hi), (lo), (sel))
@@ -62,6 +68,7 @@ struct simt_buf { const unsigned char* p; uint32_t n; };
 #define GEAR_BUF_LOAD16_NT(b, off) simt_buf_load<uint4>((b), (uint32_t)(off))
 #define GEAR_BUF_LOAD4(b, off) simt_buf_load<uint32_t>((b), (uint32_t)(off))
 #define GEAR_BUF_LOAD2(b, off) ((uint32_t)simt_buf_load<uint16_t>((b), (uint32_t)(off)))
+#define GEAR_BUF_LOAD1(b, off) ((uint32_t)simt_buf_load<uint8_t>((b), (uint32_t)(off)))
 #define GEAR_BUF_STORE16_NT(b, off, v) simt_buf_store((b), (uint32_t)(off), (v))
 #define GEAR_BUF_STORE4(b, off, v) simt_buf_store<uint32_t>((b), (uint32_t)(off), (uint32_t)(v))
 #define GEAR_BUF_STORE2(b, off, v) simt_buf_store<uint16_t>((b), (uint32_t)(off), (uint16_t)(v))
@@ -81,6 +88,16 @@ static inline float simt_fdot2(uint32_t a, uint32_t b, float c) {   // two fp16 
   memcpy(x, &a, 4);
   memcpy(y, &b, 4);
   return (float)((double)x[0] * (double)y[0] + (double)x[1] * (double)y[1] + (double)c);
+}
+static inline uint32_t simt_pk_f16(uint32_t a, uint32_t b, bool lesser) {
+  _Float16 x[2], y[2];
+  memcpy(x, &a, 4);
+  memcpy(y, &b, 4);
+  for (int i = 0; i < 2; ++i)
+    if (lesser ? y[i] < x[i] : y[i] > x[i]) x[i] = y[i];
+  uint32_t r;
+  memcpy(&r, x, 4);
+  return r;
 }
 static inline uint32_t simt_byte_perm(uint32_t hi, uint32_t lo, uint32_t sel) {
   const uint64_t src = ((uint64_t)hi << 32) | lo;
@@ -145,6 +162,14 @@ inline int dpp_rows(int old, int v, int ctrl, int row_mask, bool bound_ctrl = fa
   if (!enabled) return old;
   if (!valid) return bound_ctrl ? 0 : old;
   return got;
+}
+// v_permlane32_swap / v_permlane16_swap: the upper part of a changes places with the lower part of b (halves of the wave /
+// rows of 16 in each half)
+inline void lane_swap(uint32_t& a, uint32_t& b, int n) {
+  const int l = lane();
+  const uint32_t fb = (uint32_t)xchg(b, (l & n) ? l - n : l), fa = (uint32_t)xchg(a, (l & n) ? l : l + n);
+  if (l & n) a = fb;
+  else b = fa;
 }
 inline int readlane(int v, int l) { return (int)(uint32_t)xchg((uint32_t)v, l); }
 template <typename T>
