@@ -27,16 +27,15 @@ __device__ __forceinline__ void store_mask_bytes(const uint32_t* bits, uint4* ma
 }
 // A wave's channel (bit j of the byte): the entries of one chunk (8 consecutive tokens per lane, from `base`) that the
 // predicate takes.
-__device__ __forceinline__ void mark_chunk(const uint4& v, int base, int n, const ThreshPair& tp, uint32_t* bits, int j) {
-  const uint32_t kw[4] = {v.x, v.y, v.z, v.w};
-  uint32_t f = 0;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) f |= (outlier(slot_key(kw, e), (uint32_t)(base + e), tp) ? 1u : 0u) << e;
+// Two keys per instruction find the few entries by key alone, and only those are asked for the index where a
+// threshold's ties are cut (which a fifth of the vectors of normally distributed keys need).
+__device__ __forceinline__ void mark_chunk(const uint4& v, int base, int n, const ThreshPair& tp, const ThreshKeys& tk, uint32_t* bits, int j) {
+  uint32_t f = key_bits(v, tk);
   if (base + 8 > n) f &= base < n ? (1u << (n - base)) - 1u : 0u;
   while (f != 0u) {
-    const int t = base + __ffs((int)f) - 1;
+    const int e = __ffs((int)f) - 1, t = base + e;
     f &= f - 1u;
-    atomicOr(&bits[t >> 2], 1u << (8 * (t & 3) + j));
+    if (!tk.cut || outlier(half_of(v.x, v.y, v.z, v.w, e), (uint32_t)t, tp)) atomicOr(&bits[t >> 2], 1u << (8 * (t & 3) + j));
   }
 }
 
@@ -202,7 +201,8 @@ __global__ __launch_bounds__(512) void k_select_long_kernel(const uint16_t* __re
   }
   if (!mask) return;
   block_lds_sync();
-  for_each_chunk(src, (n + 511) >> 9, [&](int ch, const uint4& v4) { mark_chunk(v4, ch * 512 + lane * 8, n, tp, bits, wave); });
+  const ThreshKeys tk = key_thresh(tp);
+  for_each_chunk(src, (n + 511) >> 9, [&](int ch, const uint4& v4) { mark_chunk(v4, ch * 512 + lane * 8, n, tp, tk, bits, wave); });
   block_lds_sync();
   store_mask_bytes(bits, mask + (size_t)(blockIdx.x / (D / 8)) * n, n, blockIdx.x % (D / 8));
 }
@@ -291,9 +291,10 @@ __global__ __launch_bounds__(512, (NC <= 8 ? 4 : 2)) void k_select_reg_kernel(co
     if (lane == 0) ksz[(size_t)slab * ng_cap * D + ch] = group_bits(make_group(h2f(unkey16(kmn)), h2f(unkey16(kmx)), qmax));
   }
   if (!mask) return;
+  const ThreshKeys tk = key_thresh(tp);
 #pragma unroll
   for (int c = 0; c < NC; ++c)
-    if (c * 512 < n) mark_chunk(x[c], c * 512 + lane * 8, n, tp, bits, wave);
+    if (c * 512 < n) mark_chunk(x[c], c * 512 + lane * 8, n, tp, tk, bits, wave);
   block_lds_sync();
   store_mask_bytes(bits, mask + (size_t)slab * n, n, cb);
 }

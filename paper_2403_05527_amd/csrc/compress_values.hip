@@ -64,10 +64,13 @@ __global__ __launch_bounds__(256, (NC <= 8 ? 5 : NC <= 10 ? 4 : 2)) void v_selec
       const Thresh th = wave_select(src, N, k_top, k_bot, hist + wave * SELECT_LDS_WORDS, tvalid);
       tp = pack_thresh(th);
       if (tvalid && mask) {
+        const ThreshKeys tk = key_thresh(tp);
+        const bool cut = __ballot(tk.cut) != 0ull;   // wave-uniform
 #pragma unroll
         for (int ch = 0; ch < NC; ++ch) {
           if (ch * 4 + hsub < H)
-            reinterpret_cast<uint8_t*>(mask + ((size_t)b * H + ch * 4 + hsub) * n + t)[oc] = (uint8_t)piece_bits(x[ch], (uint32_t)(ch * 512 + lane * 8), tp);
+            reinterpret_cast<uint8_t*>(mask + ((size_t)b * H + ch * 4 + hsub) * n + t)[oc] =
+                (uint8_t)(cut ? piece_bits(x[ch], (uint32_t)(ch * 512 + lane * 8), tp) : key_bits(x[ch], tk));
           GEAR_SCHED_FENCE();
         }
       }
@@ -132,11 +135,14 @@ __global__ __launch_bounds__(256, 4) void v_select_rows_kernel(const uint16_t* _
     ThreshPair tp = pack_thresh(thresh_none());
     if (k_top > 0 || k_bot > 0) {
       tp = pack_thresh(row_select(x, H, k_top, k_bot, hrow));
+      const ThreshKeys tk = key_thresh(tp);
+      const bool cut = __ballot(tk.cut) != 0ull;   // wave-uniform
       if (tvalid && mask) {
 #pragma unroll
         for (int h = 0; h < 8; ++h) {
           if (h < H)
-            reinterpret_cast<uint8_t*>(mask + ((size_t)b * H + h) * n + t)[i] = (uint8_t)piece_bits(x[h], (uint32_t)(128 * h + 8 * i), tp);
+            reinterpret_cast<uint8_t*>(mask + ((size_t)b * H + h) * n + t)[i] =
+                (uint8_t)(cut ? piece_bits(x[h], (uint32_t)(128 * h + 8 * i), tp) : key_bits(x[h], tk));
           GEAR_SCHED_FENCE();
         }
       }

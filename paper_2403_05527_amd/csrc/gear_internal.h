@@ -289,6 +289,51 @@ __device__ __forceinline__ ThreshPair pack_thresh(const Thresh& th) {
   p.bot = (th.tau_bot << 16) + lob;
   return p;
 }
+// The same predicate on two keys per instruction, by key alone: the halves of top / bot are T - 1 and B, an entry is taken
+// iff key >= T or key < B.  `cut`: among the entries that equal a threshold the index decides (or a bound does not fit
+// 16 bits); the packed test then takes all of them, a superset of S.  2.5 instructions per entry against the 6 of the exact
+// test; with the second histogram level built the same way (high_byte_bits) v_select of 4096-entry rows 253 -> 229 us,
+// k_select on 512 x 128 vectors of 8192 keys 680 -> 650, v_select_rows on 64 x 8192 rows of 1024 entries 525 -> 495.
+struct ThreshKeys {
+  uint32_t top, bot;
+  bool cut;
+};
+__device__ __forceinline__ ThreshKeys key_thresh(const ThreshPair& p) {
+  const uint32_t T = p.top >> 16, B = (p.bot >> 16) + ((p.bot & 0xFFFFu) != 0u ? 1u : 0u);
+  ThreshKeys k;
+  k.top = (T == 0u ? 0u : T - 1u) * 0x00010001u;
+  k.bot = (B > 0xFFFFu ? 0xFFFFu : B) * 0x00010001u;
+  k.cut = ((p.top | p.bot) & 0xFFFFu) != 0u || T == 0u || B > 0xFFFFu;
+  return k;
+}
+typedef unsigned short key2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t sub_sat_u16x2(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(key2_t, a), __builtin_bit_cast(key2_t, b)));
+}
+__device__ __forceinline__ uint32_t min_u16x2(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(key2_t, a), __builtin_bit_cast(key2_t, b)));
+}
+// Eight flags (a half of z[j] is 0 or 1: entries 2j, 2j + 1) as the bits of a byte.
+__device__ __forceinline__ uint32_t flag_byte(const uint32_t (&z)[4]) {
+  const uint32_t f = z[0] | z[1] << 2 | z[2] << 4 | z[3] << 6;
+  return (f | f >> 15) & 0xFFu;
+}
+// bit e: entry e of a row piece of eight keys passes the packed test
+__device__ __forceinline__ uint32_t key_bits(const uint4& v, const ThreshKeys& k) {
+  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  uint32_t z[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) z[j] = min_u16x2(sub_sat_u16x2(w[j], k.top) | sub_sat_u16x2(k.bot, w[j]), 0x00010001u);
+  return flag_byte(z);
+}
+// bit e: the high byte of entry e's key is that of a (a2: the byte << 8 in both halves) or that of b
+__device__ __forceinline__ uint32_t high_byte_bits(const uint4& v, uint32_t a2, uint32_t b2) {
+  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  uint32_t z[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) z[j] = min_u16x2(sub_sat_u16x2(0x01000100u, min_u16x2(w[j] ^ a2, w[j] ^ b2)), 0x00010001u);
+  return flag_byte(z);
+}
 __device__ __forceinline__ Thresh thresh_none() {
   Thresh th;
   th.tau_top = 0x10000u;

@@ -274,10 +274,15 @@ __device__ __forceinline__ Thresh wave_select(const Src& src, int N, int k_top, 
   // few bins, and adds of one instruction to one address are applied one after another)
   uint32_t* hmine = hist + ((lane & 1) << 8);
   for_each_chunk(src, nch, [&](int ch, const uint4& v) {
-    const int base = ch * 512 + lane * 8;
+    if (ch * 512 + 512 <= N) {   // wave-uniform: every chunk but the last one
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
-      if (base + e < N) atomicAdd(&hmine[slot16(v, e) >> 8], 1u);
+      for (int e = 0; e < 8; ++e) atomicAdd(&hmine[slot16(v, e) >> 8], 1u);
+    } else {
+      const int base = ch * 512 + lane * 8;
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (base + e < N) atomicAdd(&hmine[slot16(v, e) >> 8], 1u);
+    }
   });
   wave_lds_sync();
   for (int i = lane; i < 256; i += 64) hist[i] += hist[256 + i];
@@ -299,16 +304,20 @@ __device__ __forceinline__ Thresh wave_select(const Src& src, int N, int k_top, 
   // ---- level 2: histograms of the low key byte inside the two boundary bins
   for (int i = lane; i < 512; i += 64) hist[i] = 0u;
   wave_lds_sync();
-  for_each_chunk(src, nch, [&](int ch, const uint4& v) {
-    const int base = ch * 512 + lane * 8;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const uint32_t k = slot16(v, e);
-      const int hi = (base + e < N) ? (int)(k >> 8) : -2;
-      const bool in_t = hi == bin_t, in_b = hi == bin_b;
-      // (only the few lanes with an entry in a boundary bin take part: the LDS serves an add of 64 lanes to
-      // random bins in ~7 cycles, of a handful of lanes in 2)
-      if (in_t || in_b) atomicAdd(&hist[(in_t ? 0u : 256u) + (k & 255u)], 1u);
+  // (a few per cent of the entries lie in these bins: found two keys per instruction and visited by set bit.  The
+  // add is then done by a handful of lanes, 2 cycles of the LDS against ~7 for 64 lanes with random bins)
+  const uint32_t bt2 = (uint32_t)(bin_t >= 0 ? bin_t : bin_b) * 0x01000100u, bb2 = (uint32_t)(bin_b >= 0 ? bin_b : bin_t) * 0x01000100u;
+  const int nch2 = bin_t >= 0 || bin_b >= 0 ? nch : 0;
+  for_each_chunk(src, nch2, [&](int ch, const uint4& v) {
+    uint32_t f = high_byte_bits(v, bt2, bb2);
+    if (ch * 512 + 512 > N) {   // wave-uniform: the ragged end
+      const int left = N - (ch * 512 + lane * 8);
+      f &= left >= 8 ? 0xFFu : left > 0 ? (1u << left) - 1u : 0u;
+    }
+    while (f != 0u) {
+      const uint32_t k = half_of(v.x, v.y, v.z, v.w, __ffs((int)f) - 1);
+      f &= f - 1u;
+      atomicAdd(&hist[((int)(k >> 8) == bin_t ? 0u : 256u) + (k & 255u)], 1u);
     }
   });
   wave_lds_sync();

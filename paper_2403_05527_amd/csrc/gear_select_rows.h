@@ -156,17 +156,19 @@ __device__ __forceinline__ Thresh row_select(const uint4 (&x)[8], int H, int k_t
 #pragma unroll
   for (int j = 0; j < 512; j += 64) *reinterpret_cast<uint4*>(hist + j + 4 * i) = make_uint4(0, 0, 0, 0);
   wave_lds_sync();
+  if (bin_t >= 0 || bin_b >= 0) {
+    const uint32_t bt2 = (uint32_t)(bin_t >= 0 ? bin_t : bin_b) * 0x01000100u, bb2 = (uint32_t)(bin_b >= 0 ? bin_b : bin_t) * 0x01000100u;
 #pragma unroll
-  for (int h = 0; h < 8; ++h)
-    if (h < H) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const uint32_t k = slot16(x[h], e);
-        const int hi = (int)(k >> 8);
-        const bool in_t = hi == bin_t, in_b = hi == bin_b;
-        if (in_t || in_b) atomicAdd(&hist[(in_t ? 0u : 256u) + (k & 255u)], 1u);
+    for (int h = 0; h < 8; ++h)
+      if (h < H) {
+        uint32_t f = high_byte_bits(x[h], bt2, bb2);
+        while (f != 0u) {
+          const uint32_t k = half_of(x[h].x, x[h].y, x[h].z, x[h].w, __ffs((int)f) - 1);
+          f &= f - 1u;
+          atomicAdd(&hist[((int)(k >> 8) == bin_t ? 0u : 256u) + (k & 255u)], 1u);
+        }
       }
-    }
+  }
   wave_lds_sync();
   if (bin_t == bin_b && bin_t >= 0) {   // one bin holds both thresholds: its entries count for both
 #pragma unroll
