@@ -104,7 +104,7 @@ WorkLayout work_layout(const gear_config& c) {
   w.maskV = o; o += up(c.outlier_ppm > 0 ? slabs * (size_t)n_max * 16 : 0);
   w.vsz = o; o += up(c.group == 0 ? (size_t)c.B * n_max * 4 : 0);   // per-vector grouping: a Value token's (scale, zero)
   w.pool_ctr = o; o += up((slabs + (size_t)c.B) * 4);   // Key counters per slab, then Value counters per batch
-  w.Bcur = o; o += up(slabs * D * R * 4);
+  w.Bcur = o; o += up(2 * slabs * D * R * 4);   // (Keys and Values are solved together)
   w.partial = o; o += up(slabs * (size_t)npart * (D * R + R * R) * 4);
   w.Atmp = o; o += up(slabs * (size_t)n_max * R * 4);
   w.cmat = o; o += up(slabs * R * R * 4);
@@ -114,12 +114,14 @@ WorkLayout work_layout(const gear_config& c) {
   const int ncb = (c.n_chunks_max * (c.n_buf_cap > 128 ? 2 : 1) + 3) / 4;
   w.dec = o; o += up((size_t)c.B * c.H_q * (nsplit + ncb + 1) * DECODE_REC * 4);
   w.gram_strips = c.rank_max > 0 && n_max > 256 ? pi_gram_strips_max(n_max, (int)slabs) : 0;
-  w.gram = o; o += up(slabs * (size_t)w.gram_strips * 36 * 256 * 4);
+  w.gram = o; o += up(2 * slabs * (size_t)w.gram_strips * 36 * 256 * 4);
   // the filtered tensor Y for the low-rank solvers that walk over it; the channel-major copy of the keys of a long Key
   // segment (see launch_k_select) lives in the same place
   w.resid = o;
   {
-    const size_t resid = c.rank_max > 0 ? slabs * (size_t)n_max * D * 2 : 0;
+    // one tensor at a time, or both of a flushed buffer
+    const int rows = n_max > 2 * PI_TINY_ROWS ? n_max : 2 * (n_max < PI_TINY_ROWS ? n_max : PI_TINY_ROWS);
+    const size_t resid = c.rank_max > 0 ? slabs * (size_t)(rows > n_max ? rows : n_max) * D * 2 : 0;
     const size_t kt = c.n_prefill_max > 8192 ? slabs * (size_t)((c.n_prefill_max + 7) & ~7) * D * 2 : 0;
     o += up(resid > kt ? resid : kt);
   }
@@ -373,20 +375,26 @@ int gear_compress_recent(gear_cache* cache, const void* K, const void* V, int32_
   float* Atmp = reinterpret_cast<float*>(ws + w.Atmp);
   float* cmat = reinterpret_cast<float*>(ws + w.cmat);
   uint32_t* vsz = reinterpret_cast<uint32_t*>(ws + w.vsz);
-  // Keys: quantize (with the Gram matrix of the residual, or leaving Y = X - S in the workspace), then their power
-  // iteration; Values reuse the same buffers afterwards.
-  const bool on_gram = pi_on_gram(n, rank, iters);
+  // Quantize (with the Gram matrix of the residual, or leaving Y = X - S in the workspace), then the power iteration; where
+  // that goes one tensor at a time, the Values reuse the Keys' buffers afterwards.
+  const bool on_gram = pi_on_gram(n, rank, iters), paired = pi_paired(n, rank, iters);
+  const size_t slabs = (size_t)c.B * c.H_kv;
   const int strip = on_gram ? pi_gram_strip(n, c.B * c.H_kv) : 128, nstrips = (n + strip - 1) / strip;
   if (on_gram && nstrips > w.gram_strips) return GEAR_ECAPACITY;   // (the workspace is sized for every n the cache takes)
   float* gram = on_gram ? reinterpret_cast<float*>(ws + w.gram) : nullptr;
+  float* gramV = on_gram ? gram + slabs * nstrips * GRAM_FLOATS : nullptr;
   uint16_t* resid = rank > 0 && !on_gram ? reinterpret_cast<uint16_t*>(ws + w.resid) : nullptr;
+  uint16_t* residV = resid && paired ? resid + slabs * n * D : resid;
+  // init_B: [2 (K, V), B, H, 128, rank], or nullptr: the same array is drawn from the seed
+  const uint64_t tensor_entries = (uint64_t)slabs * D * rank;
+  const PiTensor pk{Kp, c.outlier_ppm > 0 ? maskK : nullptr, resid, ks, {init_B, seed, 0}};
+  const PiTensor pv{Vp, c.outlier_ppm > 0 ? maskV : nullptr, residV, vs, {init_B ? init_B + tensor_entries : nullptr, seed, tensor_entries}};
   GEAR_HIP(launch_k_quant(Kp, ks, dm, n, t_lr, maskK, pool_ctr, resid, gram, strip, st));
-  if (rank > 0)
-    GEAR_HIP(launch_power_iteration(true, Kp, maskK, resid, ks, dm, n, t_lr, iters, init_B, seed, Bcur, partial, Atmp, cmat, gram, nstrips, st));
+  if (rank > 0 && !paired) GEAR_HIP(launch_power_iteration(true, pk, dm, n, t_lr, iters, Bcur, partial, Atmp, cmat, st));
   GEAR_HIP(launch_v_select(Vp, dm, n, (kv_v + 1) / 2, kv_v / 2, maskV, vsz, st));
-  GEAR_HIP(launch_v_quant(Vp, vs, dm, n, t_lr, (kv_v + 1) / 2, kv_v / 2, maskV, vsz, pool_ctr + (size_t)c.B * c.H_kv, resid, gram, strip, st));
-  if (rank > 0)
-    GEAR_HIP(launch_power_iteration(false, Vp, maskV, resid, vs, dm, n, t_lr, iters, init_B, seed, Bcur, partial, Atmp, cmat, gram, nstrips, st));
+  GEAR_HIP(launch_v_quant(Vp, vs, dm, n, t_lr, (kv_v + 1) / 2, kv_v / 2, maskV, vsz, pool_ctr + slabs, residV, gramV, strip, st));
+  if (rank > 0 && !paired) GEAR_HIP(launch_power_iteration(false, pv, dm, n, t_lr, iters, Bcur, partial, Atmp, cmat, st));
+  if (paired) GEAR_HIP(launch_power_iteration_pair(pk, pv, dm, n, t_lr, iters, Bcur, gram, nstrips, st));
 
   if (first) {
     cache->n_prefill = n;

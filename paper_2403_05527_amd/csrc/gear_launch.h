@@ -40,14 +40,28 @@ int pi_padded_rank(int rank);
 // Tokens per strip of the pass that forms the Gram matrices; the most strips per slab any segment of up to n_max tokens gets
 int pi_gram_strip(int n, int slabs);
 int pi_gram_strips_max(int n_max, int slabs);
-// whether a segment of n tokens is solved on its Gram matrix (launch_power_iteration then takes X and its mask instead of Y)
+// whether a segment of n tokens is solved on its Gram matrix (from X and its mask instead of Y)
 inline bool pi_on_gram(int n, int rank, int iters) { return rank > 0 && iters > 1 && n > 256; }
-// init_B: the whole start array [2 (K, V), B, H, 128, rank] (the launcher takes this tensor's half), or
-// nullptr: the same array is drawn from `seed` (start_entry in gear_internal.h)
+// whether Keys and Values of a segment are solved together, launch by launch: on their Gram matrices, or (a flushed
+// buffer, whose Y tensors are small) with the residual in LDS.  The other solvers work through the same scratch arrays,
+// sized for one tensor, one tensor after the other.
+constexpr int PI_TINY_ROWS = 64;
+inline bool pi_paired(int n, int rank, int iters) { return rank > 0 && (n <= PI_TINY_ROWS || pi_on_gram(n, rank, iters)); }
+// One tensor of a call.  sb: the start matrices of its slabs; X and mask (nullptr: nothing filtered) for the solver on
+// the Gram matrix, Y = X - S for the others.
+struct PiTensor {
+  const uint16_t* X;
+  const uint4* mask;
+  const uint16_t* Y;
+  SegView sv;
+  StartB sb;
+};
 // t_lr: first token of the segment that takes part in the low-rank term (rows before it get A = 0)
-hipError_t launch_power_iteration(bool is_k, const uint16_t* X, const uint4* mask, const uint16_t* Yf, const SegView& sv,
-                                  const Dims& dm, int n, int t_lr, int iters, const float* init_B, uint64_t seed, float* Bcur,
-                                  float* partial, float* Atmp, float* cmat, float* gram, int nstrips, hipStream_t st);
+// Bcur: [2][slab][128][padded rank]; gram: [2][slab][nstrips][GRAM_FLOATS], Keys first
+hipError_t launch_power_iteration_pair(const PiTensor& k, const PiTensor& v, const Dims& dm, int n, int t_lr, int iters, float* Bcur,
+                                       float* gram, int nstrips, hipStream_t st);
+hipError_t launch_power_iteration(bool is_k, const PiTensor& x, const Dims& dm, int n, int t_lr, int iters, float* Bcur, float* partial,
+                                  float* Atmp, float* cmat, hipStream_t st);
 
 constexpr int DECODE_TS = 256;           // rows per pass of the chunk / buffer path
 constexpr int DECODE_SPLIT = 512;        // prefill tokens per split block

@@ -690,19 +690,27 @@ __device__ __forceinline__ void qr_columns(double (&q)[R], double (*Bq)[R] /* LD
 #pragma unroll
   for (int r = 0; r < R; ++r) q[r] = c < 64 ? a[r] : b[r];
 }
-// grid (B*H), block 256: thread (half = tid / 128, c = tid % 128).  Row c of B belongs to thread
+// grid (B*H, tensors), block 256: thread (half = tid / 128, c = tid % 128).  Row c of B belongs to thread
 // (0, c); the upper half of the block helps with the loads of G and with half of every product.
+// A block is a chain of dependent fp64 steps that nothing in it hides, and at most two blocks fit a CU: Keys (y = 0) and
+// Values (y = 1) of one call go in one launch, which up to 256 slabs costs the time of one tensor.  32 slabs of rank 8:
+// 45 + 45 -> 47 us for both tensors, 128 slabs of rank 4: 23 + 23 -> 25; 512 slabs take what they took (37 us each).
 template <int R>
-__global__ __launch_bounds__(256) void pi_solve_kernel(StartB sb, int rank,
+__global__ __launch_bounds__(256) void pi_solve_kernel(StartB sb0, StartB sb1, int rank,
                                                        const float* __restrict__ gram_partial, int nstrips, int stride, int rounds,
-                                                       float* __restrict__ Bcur, int last_round, SegView sv) {
+                                                       float* __restrict__ Bcur_all, int last_round, uint16_t* Bf0, uint16_t* Bf1) {
   GEAR_DYN_LDS(smem_raw);
   SolveSmem<R>& sm = *reinterpret_cast<SolveSmem<R>*>(smem_raw);
   const int slab = blockIdx.x, c = threadIdx.x & (D - 1), half = threadIdx.x >> 7;
+  const bool second = blockIdx.y != 0;
+  const StartB sb = second ? sb1 : sb0;
+  uint16_t* Bf = second ? Bf1 : Bf0;
+  float* Bcur = Bcur_all + (size_t)blockIdx.y * gridDim.x * (D * R);
   const bool owner = half == 0;
   if (rounds > 0) {
     // G = sum of the strips' partial tiles (fixed order): element tid + 256 j is register j % 4... of tile j
-    const float* gp = gram_partial + (size_t)slab * stride * GRAM_FLOATS + threadIdx.x;   // (stride: strips per slab in memory)
+    // (stride: strips per slab in memory)
+    const float* gp = gram_partial + ((size_t)blockIdx.y * gridDim.x + slab) * stride * GRAM_FLOATS + threadIdx.x;
     float s[GRAM_TILES];
 #pragma unroll
     for (int j = 0; j < GRAM_TILES; ++j) s[j] = 0.0f;
@@ -833,7 +841,7 @@ __global__ __launch_bounds__(256) void pi_solve_kernel(StartB sb, int rank,
         bo += pr[r] * sm.C[r][j];
       }
       Bcur[((size_t)slab * D + c) * R + j] = (float)w;
-      if (j < rank) sv.Bf[((size_t)slab * D + c) * sv.rank + j] = (uint16_t)f2h((float)bo);
+      if (j < rank) Bf[((size_t)slab * D + c) * rank + j] = (uint16_t)f2h((float)bo);
     }
   }
 }
@@ -844,10 +852,12 @@ __global__ __launch_bounds__(256) void pi_solve_kernel(StartB sb, int rank,
 // of Algorithm 2 runs out of LDS with a handful of block barriers; nothing goes through the workspace.
 // Same steps and the same precision choices as the kernels above: A = R B and B' = R^T A accumulate in
 // fp32, column scaling, the QR of B and the coefficient-space orth(A) in fp64.
-// grid (B*H), block 256.  Thread (r0 = tid/16, oc = tid%16) derives channels 8*oc..+7 of rows
+// grid (B*H, 2): Keys (y = 0) and Values (y = 1) in one launch, block 256 (a block is one long chain of steps: a
+// flushed buffer of 128 slabs takes 12 us, the two launches one after the other took 13 + 11).
+// Thread (r0 = tid/16, oc = tid%16) derives channels 8*oc..+7 of rows
 // r0 + 16 k and later forms their share of A; thread (half = tid/128, c = tid%128) sums rows
 // [32 half, 32 half + 32) of B'[c][:], thread (0, c) owns row c of B.
-constexpr int TINY_ROWS = 64;
+constexpr int TINY_ROWS = PI_TINY_ROWS;
 constexpr int TINY_PITCH = D + 4;   // floats per residual row in LDS (16-byte aligned pieces)
 template <int R>
 struct TinySmem {
@@ -861,10 +871,16 @@ struct TinySmem {
   double C[R][R];
   double cj[R];
 };
-template <bool IS_K, int R>
-__global__ __launch_bounds__(256) void pi_tiny_kernel(const uint16_t* __restrict__ Y, SegView sv, int g, int bits, int n,
-                                                      int t_lr, int iters, StartB sb) {
+template <int R>
+__global__ __launch_bounds__(256) void pi_tiny_kernel(const uint16_t* __restrict__ YK, const uint16_t* __restrict__ YV, SegView ks,
+                                                      SegView vs, int gk, int gv, int bits, int n, int t_lr, int iters, StartB sbk,
+                                                      StartB sbv) {
   __shared__ TinySmem<R> sm;
+  const bool is_k = blockIdx.y == 0;
+  const SegView sv = is_k ? ks : vs;
+  const StartB sb = is_k ? sbk : sbv;
+  const uint16_t* Y = is_k ? YK : YV;
+  const int g = is_k ? gk : gv;
   const int slab = blockIdx.x, tid = threadIdx.x;
   const int r0 = tid >> 4, oc = tid & 15;
   const int c = tid & (D - 1), half = tid >> 7;
@@ -875,8 +891,8 @@ __global__ __launch_bounds__(256) void pi_tiny_kernel(const uint16_t* __restrict
     const int lg = 31 - __clz(g), ngl = 7 - lg;   // (Keys with per-vector groups pass g = 32768: one group)
     const float qmax = (float)((1 << bits) - 1);
     const GEAR_BUF_T xbuf = GEAR_BUF_MAKE(Y + (size_t)slab * n * D, n * (D * 2));
-    const GEAR_BUF_T cbuf = GEAR_BUF_MAKE(sv.codes + (size_t)slab * sv.n_cap * (4 * bits), IS_K ? n * (16 * bits) : 0);
-    const GEAR_BUF_T pbuf = IS_K ? GEAR_BUF_MAKE(sv.sz + (size_t)slab * sv.ng_cap * D, ((n + g - 1) >> lg) * (D * 4))
+    const GEAR_BUF_T cbuf = GEAR_BUF_MAKE(sv.codes + (size_t)slab * sv.n_cap * (4 * bits), is_k ? n * (16 * bits) : 0);
+    const GEAR_BUF_T pbuf = is_k ? GEAR_BUF_MAKE(sv.sz + (size_t)slab * sv.ng_cap * D, ((n + g - 1) >> lg) * (D * 4))
                                  : GEAR_BUF_MAKE(sv.sz + (((size_t)slab * sv.n_cap) << ngl), (n << ngl) * 4);
     uint4 xv[4], pz[2][2];
     uint32_t cw[4], pv[4];
@@ -884,20 +900,16 @@ __global__ __launch_bounds__(256) void pi_tiny_kernel(const uint16_t* __restrict
     for (int k = 0; k < 4; ++k) {   // every load is requested before the first one is used
       const int t = r0 + 16 * k;
       xv[k] = GEAR_BUF_LOAD16_NT(xbuf, t * (D * 2) + oc * 16);   // rows past the end read as 0
-      cw[k] = 0u;
-      pv[k] = 0u;
-      if (IS_K) {
-        const int co = t * (16 * bits) + oc * (bits == 4 ? 4 : 2);
-        cw[k] = bits == 4 ? GEAR_BUF_LOAD4(cbuf, co) : GEAR_BUF_LOAD2(cbuf, co);
-      } else {
-        pv[k] = GEAR_BUF_LOAD4(pbuf, ((t << ngl) + ((oc * 8) >> lg)) * 4);
-      }
+      // (Values: a view of no codes; Keys: a word that is not used)
+      const int co = t * (16 * bits) + oc * (bits == 4 ? 4 : 2);
+      cw[k] = bits == 4 ? GEAR_BUF_LOAD4(cbuf, co) : GEAR_BUF_LOAD2(cbuf, co);
+      pv[k] = GEAR_BUF_LOAD4(pbuf, is_k ? 0 : ((t << ngl) + ((oc * 8) >> lg)) * 4);
     }
 #pragma unroll
     for (int j = 0; j < 2; ++j) {   // Keys: 64 rows lie in at most two groups (g >= 32)
       pz[j][0] = make_uint4(0, 0, 0, 0);
       pz[j][1] = make_uint4(0, 0, 0, 0);
-      if (IS_K) {
+      if (is_k) {
         pz[j][0] = GEAR_BUF_LOAD16(pbuf, (j * D + oc * 8) * 4);
         pz[j][1] = GEAR_BUF_LOAD16(pbuf, (j * D + oc * 8) * 4 + 16);
       }
@@ -907,7 +919,7 @@ __global__ __launch_bounds__(256) void pi_tiny_kernel(const uint16_t* __restrict
       const int t = r0 + 16 * k;
       const uint32_t w[4] = {xv[k].x, xv[k].y, xv[k].z, xv[k].w};
       float res[8];
-      if (IS_K) {
+      if (is_k) {
         const bool second = (t >> lg) != 0;
         const uint4 z0 = second ? pz[1][0] : pz[0][0], z1 = second ? pz[1][1] : pz[0][1];
         const uint32_t z[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
@@ -1045,77 +1057,90 @@ int pi_gram_strips_max(int n_max, int slabs) {
 }
 
 template <int R>
-static hipError_t run_pi(bool is_k, const uint16_t* X, const uint4* mask, const uint16_t* Yf, const SegView& sv, const Dims& dm,
-                         int n, int t_lr, int iters, StartB sb, float* Bcur, float* partial, float* Atmp, float* cmat,
-                         float* gram, int nstrips, hipStream_t st) {
-  const int slabs = dm.B * dm.H;
-  const int npart = (n + PT - 1) / PT;
-  const int g_eff = (is_k && dm.kcvt) ? 32768 : dm.g;   // per-vector grouping: one Key group per segment
-  if (npart == 1) {   // a short segment: everything in one block per slab
-    if (n <= TINY_ROWS) {   // (a flushed buffer of the paper's sizes) with its residual resident in LDS
-      if (is_k)
-        hipLaunchKernelGGL((pi_tiny_kernel<true, R>), dim3(slabs), dim3(256), 0, st, Yf, sv, g_eff, dm.bits, n, t_lr, iters, sb);
-      else
-        hipLaunchKernelGGL((pi_tiny_kernel<false, R>), dim3(slabs), dim3(256), 0, st, Yf, sv, dm.g, dm.bits, n, t_lr, iters, sb);
-      return hipGetLastError();
-    }
-    if (is_k)
-      hipLaunchKernelGGL((pi_small_kernel<true, R>), dim3(slabs), dim3(256), 0, st, Yf, sv, g_eff, dm.bits, n, t_lr, iters, sb, Bcur, partial, Atmp, cmat);
-    else
-      hipLaunchKernelGGL((pi_small_kernel<false, R>), dim3(slabs), dim3(256), 0, st, Yf, sv, dm.g, dm.bits, n, t_lr, iters, sb, Bcur, partial, Atmp, cmat);
+static hipError_t raise_solve_lds() {
+  static std::atomic<bool> lds_raised{false};   // per kernel instance (R); two threads may both raise it: harmless
+  if (lds_raised.load(std::memory_order_relaxed)) return hipSuccess;
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pi_solve_kernel<R>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(SolveSmem<R>));
+  if (e == hipSuccess) lds_raised.store(true, std::memory_order_relaxed);
+  return e;
+}
+
+// Keys' per-vector grouping: one group per segment
+static int key_group_size(const Dims& dm) { return dm.kcvt ? 32768 : dm.g; }
+
+template <int R>
+static hipError_t run_pi_pair(const PiTensor& k, const PiTensor& v, const Dims& dm, int n, int t_lr, int iters, float* Bcur,
+                              float* gram, int nstrips, hipStream_t st) {
+  const int slabs = dm.B * dm.H, rank = k.sv.rank;
+  if (n <= TINY_ROWS) {   // (a flushed buffer of the paper's sizes) with its residual resident in LDS
+    hipLaunchKernelGGL(pi_tiny_kernel<R>, dim3(slabs, 2), dim3(256), 0, st, k.Y, v.Y, k.sv, v.sv, key_group_size(dm), dm.g, dm.bits, n,
+                       t_lr, iters, k.sb, v.sb);
     return hipGetLastError();
   }
-  {
-    static std::atomic<bool> lds_raised{false};   // per kernel instance (R); two threads may both raise it: harmless
-    if (!lds_raised.load(std::memory_order_relaxed)) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pi_solve_kernel<R>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(SolveSmem<R>));
-      if (e != hipSuccess) return e;
-      lds_raised.store(true, std::memory_order_relaxed);
-    }
-  }
-  // rounds 1 .. L-1: B <- (R^T R)^(L-1) B0 on the Gram matrix; then QR(B)
-  const bool summed = iters > 1 && nstrips >= GRAM_SUM_MIN;
-  if (summed) hipLaunchKernelGGL(gram_sum_kernel, dim3(GRAM_TILES, slabs), dim3(256), 0, st, gram, nstrips);
-  hipLaunchKernelGGL(pi_solve_kernel<R>, dim3(slabs), dim3(256), sizeof(SolveSmem<R>), st, sb, sv.rank, (const float*)gram,
-                     iters > 1 ? (summed ? 1 : nstrips) : 0, nstrips, iters - 1, Bcur, iters > 1 ? 1 : 0, sv);
-  if (iters > 1) {
-    // the last round's B and the factor of orth(A) came out of the Gram matrix; one light pass writes A
-    const dim3 grid(npart, slabs);
+  const hipError_t e = raise_solve_lds<R>();
+  if (e != hipSuccess) return e;
+  // rounds 1 .. L-1: B <- (R^T R)^(L-1) B0 on the Gram matrix; then QR(B), the last round's B and the factor of orth(A)
+  const bool summed = nstrips >= GRAM_SUM_MIN;
+  if (summed) hipLaunchKernelGGL(gram_sum_kernel, dim3(GRAM_TILES, 2 * slabs), dim3(256), 0, st, gram, nstrips);
+  hipLaunchKernelGGL(pi_solve_kernel<R>, dim3(slabs, 2), dim3(256), sizeof(SolveSmem<R>), st, k.sb, v.sb, rank, (const float*)gram,
+                     summed ? 1 : nstrips, nstrips, iters - 1, Bcur, 1, k.sv.Bf, v.sv.Bf);
+  // one light pass writes A
+  const dim3 grid((n + PT - 1) / PT, slabs);
+  hipLaunchKernelGGL((pi_project_kernel<true, R>), grid, dim3(256), 0, st, k.X, k.mask, k.sv, key_group_size(dm), dm.bits, n, t_lr,
+                     (const float*)Bcur);
+  hipLaunchKernelGGL((pi_project_kernel<false, R>), grid, dim3(256), 0, st, v.X, v.mask, v.sv, dm.g, dm.bits, n, t_lr,
+                     (const float*)(Bcur + (size_t)slabs * D * R));
+  return hipGetLastError();
+}
+
+template <int R>
+static hipError_t run_pi(bool is_k, const PiTensor& x, const Dims& dm, int n, int t_lr, int iters, float* Bcur, float* partial,
+                         float* Atmp, float* cmat, hipStream_t st) {
+  const int slabs = dm.B * dm.H;
+  const int npart = (n + PT - 1) / PT;
+  const int g = is_k ? key_group_size(dm) : dm.g;
+  if (npart == 1) {   // a short segment: everything in one block per slab
     if (is_k)
-      hipLaunchKernelGGL((pi_project_kernel<true, R>), grid, dim3(256), 0, st, X, mask, sv, g_eff, dm.bits, n, t_lr, (const float*)Bcur);
+      hipLaunchKernelGGL((pi_small_kernel<true, R>), dim3(slabs), dim3(256), 0, st, x.Y, x.sv, g, dm.bits, n, t_lr, iters, x.sb, Bcur, partial, Atmp, cmat);
     else
-      hipLaunchKernelGGL((pi_project_kernel<false, R>), grid, dim3(256), 0, st, X, mask, sv, dm.g, dm.bits, n, t_lr, (const float*)Bcur);
+      hipLaunchKernelGGL((pi_small_kernel<false, R>), dim3(slabs), dim3(256), 0, st, x.Y, x.sv, g, dm.bits, n, t_lr, iters, x.sb, Bcur, partial, Atmp, cmat);
     return hipGetLastError();
   }
   // a single round (no Gram pass): A = R B, orth(A) through its r x r Gram matrix, B = R^T A
-  {
-    const dim3 grid(npart, slabs);
-    if (is_k)
-      hipLaunchKernelGGL((pi_sweep_kernel<true, R, true>), grid, dim3(256), 0, st, Yf, sv, g_eff, dm.bits, n, t_lr, (const float*)Bcur, partial, npart, Atmp);
-    else
-      hipLaunchKernelGGL((pi_sweep_kernel<false, R, true>), grid, dim3(256), 0, st, Yf, sv, dm.g, dm.bits, n, t_lr, (const float*)Bcur, partial, npart, Atmp);
-    hipLaunchKernelGGL(pi_update_kernel<R>, dim3(slabs), dim3(256), 0, st, 0, sb, sv.rank,
-                       (const float*)partial, npart, 0, 1, Bcur, cmat, sv);
-  }
+  const hipError_t e = raise_solve_lds<R>();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(pi_solve_kernel<R>, dim3(slabs), dim3(256), sizeof(SolveSmem<R>), st, x.sb, x.sb, x.sv.rank, (const float*)nullptr,
+                     0, 0, 0, Bcur, 0, x.sv.Bf, x.sv.Bf);
+  const dim3 grid(npart, slabs);
+  if (is_k)
+    hipLaunchKernelGGL((pi_sweep_kernel<true, R, true>), grid, dim3(256), 0, st, x.Y, x.sv, g, dm.bits, n, t_lr, (const float*)Bcur, partial, npart, Atmp);
+  else
+    hipLaunchKernelGGL((pi_sweep_kernel<false, R, true>), grid, dim3(256), 0, st, x.Y, x.sv, g, dm.bits, n, t_lr, (const float*)Bcur, partial, npart, Atmp);
+  hipLaunchKernelGGL(pi_update_kernel<R>, dim3(slabs), dim3(256), 0, st, 0, x.sb, x.sv.rank,
+                     (const float*)partial, npart, 0, 1, Bcur, cmat, x.sv);
   hipLaunchKernelGGL(pi_finish_kernel<R>, dim3((n + 255) / 256, slabs), dim3(256), 0, st, (const float*)Atmp,
-                     (const float*)cmat, sv, n);
+                     (const float*)cmat, x.sv, n);
   return hipGetLastError();
 }
 
 int pi_padded_rank(int rank) { return rank <= 2 ? 2 : rank <= 4 ? 4 : 8; }
 
-hipError_t launch_power_iteration(bool is_k, const uint16_t* X, const uint4* mask, const uint16_t* Yf, const SegView& sv,
-                                  const Dims& dm, int n, int t_lr, int iters, const float* init_B, uint64_t seed, float* Bcur,
-                                  float* partial, float* Atmp, float* cmat, float* gram, int nstrips, hipStream_t st) {
-  // this tensor's part of the [2 (K, V), B, H, 128, rank] start array
-  const uint64_t tensor_entries = (uint64_t)dm.B * dm.H * D * sv.rank;
-  const StartB sb{init_B ? init_B + (is_k ? 0 : tensor_entries) : nullptr, seed, is_k ? 0 : tensor_entries};
-  if (dm.ppm == 0) mask = nullptr;
-  switch (pi_padded_rank(sv.rank)) {
-    case 2: return run_pi<2>(is_k, X, mask, Yf, sv, dm, n, t_lr, iters, sb, Bcur, partial, Atmp, cmat, gram, nstrips, st);
-    case 4: return run_pi<4>(is_k, X, mask, Yf, sv, dm, n, t_lr, iters, sb, Bcur, partial, Atmp, cmat, gram, nstrips, st);
-    default: return run_pi<8>(is_k, X, mask, Yf, sv, dm, n, t_lr, iters, sb, Bcur, partial, Atmp, cmat, gram, nstrips, st);
+hipError_t launch_power_iteration_pair(const PiTensor& k, const PiTensor& v, const Dims& dm, int n, int t_lr, int iters, float* Bcur,
+                                       float* gram, int nstrips, hipStream_t st) {
+  switch (pi_padded_rank(k.sv.rank)) {
+    case 2: return run_pi_pair<2>(k, v, dm, n, t_lr, iters, Bcur, gram, nstrips, st);
+    case 4: return run_pi_pair<4>(k, v, dm, n, t_lr, iters, Bcur, gram, nstrips, st);
+    default: return run_pi_pair<8>(k, v, dm, n, t_lr, iters, Bcur, gram, nstrips, st);
+  }
+}
+
+hipError_t launch_power_iteration(bool is_k, const PiTensor& x, const Dims& dm, int n, int t_lr, int iters, float* Bcur, float* partial,
+                                  float* Atmp, float* cmat, hipStream_t st) {
+  switch (pi_padded_rank(x.sv.rank)) {
+    case 2: return run_pi<2>(is_k, x, dm, n, t_lr, iters, Bcur, partial, Atmp, cmat, st);
+    case 4: return run_pi<4>(is_k, x, dm, n, t_lr, iters, Bcur, partial, Atmp, cmat, st);
+    default: return run_pi<8>(is_k, x, dm, n, t_lr, iters, Bcur, partial, Atmp, cmat, st);
   }
 }
 

@@ -1,0 +1,38 @@
+"""Filter and quantization at the edges of their tiles (chunks of 512 entries, tiles of 128 tokens, strips), on values with many
+ties: thresholds that many entries equal, both thresholds at one value, signed zeros, constant vectors.  Codes, scales,
+outlier places and values are whole numbers and bits: equal to the oracle's."""
+import pytest
+import torch
+
+import gear_workloads as gw
+from tests import parity_util as pu
+
+pytestmark = pytest.mark.gpu
+
+
+def _values(kind, shape, seed):
+    gen = torch.Generator().manual_seed(seed)
+    x = torch.randn(shape, generator=gen)
+    if kind == "steps":        # a few dozen distinct values: every threshold is tied
+        x = torch.round(x * 4) / 4
+    elif kind == "signs":      # three values, zeros of both signs: the two thresholds meet
+        x = torch.sign(x) * (torch.rand(shape, generator=gen) < 0.01) * torch.sign(torch.randn(shape, generator=gen))
+    elif kind == "constant":
+        x = torch.full(shape, -0.75)
+    return x.to(torch.float16).to("cuda:0")
+
+
+@pytest.mark.parametrize("kind,B,H,n,bits,group,ppm", [
+    ("steps", 1, 2, 65, 2, 64, 20000), ("steps", 1, 3, 257, 4, 32, 50000), ("signs", 1, 2, 511, 2, 128, 20000),
+    ("steps", 2, 4, 512, 4, 64, 10000), ("constant", 1, 5, 513, 2, 0, 20000), ("signs", 1, 2, 1025, 4, 0, 50000),
+    ("normal", 1, 3, 2049, 2, 32, 20000), ("steps", 1, 2, 4097, 2, 64, 20000), ("steps", 2, 2, 8193, 2, 64, 20000),
+    ("signs", 1, 9, 385, 2, 64, 500000), ("steps", 1, 2, 300, 2, 64, 1),
+    ("steps", 1, 33, 130, 4, 64, 20000), ("steps", 1, 2, 8192, 4, 128, 20000),
+])
+def test_filter_and_codes_equal_the_oracle(kind, B, H, n, bits, group, ppm):
+    w = gw.Workload("f", B=B, H_kv=H, H_q=H, n=n, bits=bits, group=group, outlier_ppm=ppm, rank=2, rank_chunk=2, n_b=64, steps=1, seed=n)
+    gc, oc = pu.make_pair(B, H, H, bits, group, ppm, 64, n, 1, 2)
+    for seg, ns in enumerate((n, 64)):   # the second segment: a flushed buffer
+        pu.compress_both(gc, oc, _values(kind, (B, H, ns, 128), n + seg), _values(kind, (B, H, ns, 128), n + seg + 7), 2, w.iters,
+                         gw.make_init_B(w, 2, seg, "cuda:0"))
+    pu.compare_components(gc, oc)
