@@ -340,8 +340,8 @@ static hipError_t launch_k_quant_b(const QuantArgs& a, hipStream_t st) {
   return launch_quant_t<true, BITS, 5>(a, st);
 }
 hipError_t launch_k_quant(const uint16_t* K, const SegView& sv, const Dims& dm, int n, int t_lr, uint4* mask, uint32_t* pool_ctr,
-                          uint16_t* Yout, float* gram, int strip, hipStream_t st) {
-  const QuantArgs a{K, sv, dm, n, t_lr, strip, mask, nullptr, 0, 0, pool_ctr, Yout, gram};
+                          uint16_t* Yout, hipStream_t st) {
+  const QuantArgs a{K, sv, dm, n, t_lr, QT, mask, nullptr, 0, 0, pool_ctr, Yout, nullptr};
   return dm.bits == 2 ? launch_k_quant_b<2>(a, st) : launch_k_quant_b<4>(a, st);
 }
 

@@ -113,16 +113,18 @@ struct QuantSmem<false, BITS, LG> {
   uint32_t list_off[2];
 };
 
-// grid (ceil(n / strip), B*H), block 256.
 template <bool IS_K, int BITS, int LG, bool GRAM>
-__global__ __launch_bounds__(256, (GRAM ? 2 : 3)) void quant_kernel(QuantArgs a) {
+union QuantLds {
+  QuantSmem<IS_K, BITS, LG> s;
+  float red[GRAM ? GRAM_FLOATS : 4];
+};
+
+// One block's strip of slab blockIdx.y, 256 threads.
+template <bool IS_K, int BITS, int LG, bool GRAM>
+__device__ __forceinline__ void quant_body(QuantLds<IS_K, BITS, LG, GRAM>& sm, const QuantArgs& a) {
   typedef QuantSmem<IS_K, BITS, LG> Smem;
   constexpr int NG = Smem::NG;
   constexpr float QMAX = (float)((1 << BITS) - 1);
-  __shared__ union {
-    Smem s;
-    float red[GRAM ? GRAM_FLOATS : 4];
-  } sm;
   Smem& s = sm.s;
   const int slab = blockIdx.y, n = a.n;
   int tid = threadIdx.x;
@@ -615,11 +617,31 @@ __global__ __launch_bounds__(256, (GRAM ? 2 : 3)) void quant_kernel(QuantArgs a)
   }
 }
 
+// One tensor, with Y for the solvers that go one tensor at a time.  grid (ceil(n / 128), B*H), block 256.
+template <bool IS_K, int BITS, int LG>
+__global__ __launch_bounds__(256, 3) void quant_kernel(QuantArgs a) {
+  __shared__ QuantLds<IS_K, BITS, LG, false> sm;
+  quant_body<IS_K, BITS, LG, false>(sm, a);
+}
+
+// Keys and Values of a call whose low-rank terms are solved together: the blocks of z = 0 take the Keys, those of z = 1 the
+// Values.  A short prompt or a flushed buffer has fewer blocks than the chip has slots, and a block's time is the latency of
+// its chain, so the second tensor rides along: 512 tokens of 32 heads took 15 + 15 us one after the other (a whole request of
+// 24 steps 398 us, now 374 with the last round's projection taken together too; 7 x 40 heads x 1777 tokens compressed and read back
+// 565 -> 520).  With the chip full it makes no difference (64 x 8 heads x 8192 tokens: 2640 and 2635 us).  grid (ceil(n / strip), B*H, 2), block 256.
+template <int BITS, int KLG, int VLG, bool GRAM>
+__global__ __launch_bounds__(256, (GRAM ? 2 : 3)) void quant_pair_kernel(QuantArgs k, QuantArgs v) {
+  __shared__ union {
+    QuantLds<true, BITS, KLG, GRAM> k;
+    QuantLds<false, BITS, VLG, GRAM> v;
+  } sm;
+  if (blockIdx.z == 0) quant_body<true, BITS, KLG, GRAM>(sm.k, k);
+  else quant_body<false, BITS, VLG, GRAM>(sm.v, v);
+}
+
 template <bool IS_K, int BITS, int LG>
 static hipError_t launch_quant_t(const QuantArgs& a, hipStream_t st) {
-  const dim3 grid((a.n + a.strip - 1) / a.strip, a.dm.B * a.dm.H);
-  if (a.gram) hipLaunchKernelGGL((quant_kernel<IS_K, BITS, LG, true>), grid, dim3(256), 0, st, a);
-  else hipLaunchKernelGGL((quant_kernel<IS_K, BITS, LG, false>), grid, dim3(256), 0, st, a);
+  hipLaunchKernelGGL((quant_kernel<IS_K, BITS, LG>), dim3((a.n + a.strip - 1) / a.strip, a.dm.B * a.dm.H), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

@@ -208,9 +208,30 @@ static hipError_t launch_v_quant_b(const QuantArgs& a, hipStream_t st) {
   return launch_quant_t<false, BITS, 5>(a, st);
 }
 hipError_t launch_v_quant(const uint16_t* V, const SegView& sv, const Dims& dm, int n, int t_lr, int k_top, int k_bot, uint4* mask,
-                          const uint32_t* vsz, uint32_t* pool_ctr, uint16_t* Yout, float* gram, int strip, hipStream_t st) {
-  const QuantArgs a{V, sv, dm, n, t_lr, strip, mask, vsz, k_top, k_bot, pool_ctr, Yout, gram};
+                          const uint32_t* vsz, uint32_t* pool_ctr, uint16_t* Yout, hipStream_t st) {
+  const QuantArgs a{V, sv, dm, n, t_lr, QT, mask, vsz, k_top, k_bot, pool_ctr, Yout, nullptr};
   return dm.bits == 2 ? launch_v_quant_b<2>(a, st) : launch_v_quant_b<4>(a, st);
+}
+
+template <int BITS, int KLG, int VLG>
+static hipError_t launch_quant_pair_t(const QuantArgs& k, const QuantArgs& v, hipStream_t st) {
+  const dim3 grid((k.n + k.strip - 1) / k.strip, k.dm.B * k.dm.H, 2);
+  if (k.gram) hipLaunchKernelGGL((quant_pair_kernel<BITS, KLG, VLG, true>), grid, dim3(256), 0, st, k, v);
+  else hipLaunchKernelGGL((quant_pair_kernel<BITS, KLG, VLG, false>), grid, dim3(256), 0, st, k, v);
+  return hipGetLastError();
+}
+template <int BITS>
+static hipError_t launch_quant_pair_b(const QuantArgs& k, const QuantArgs& v, hipStream_t st) {
+  if (k.dm.kcvt) return launch_quant_pair_t<BITS, KLG_VEC, 7>(k, v, st);   // (a Value row's one group: all 128 channels of a head)
+  if (k.dm.g == 128) return launch_quant_pair_t<BITS, 7, 7>(k, v, st);
+  if (k.dm.g == 64) return launch_quant_pair_t<BITS, 6, 6>(k, v, st);
+  return launch_quant_pair_t<BITS, 5, 5>(k, v, st);
+}
+hipError_t launch_quant_pair(const QuantTensor& k, const QuantTensor& v, const Dims& dm, int n, int t_lr, int v_top, int v_bot,
+                             const uint32_t* vsz, int strip, hipStream_t st) {
+  const QuantArgs ka{k.X, k.sv, dm, n, t_lr, strip, k.mask, nullptr, 0, 0, k.pool_ctr, k.Yout, k.gram};
+  const QuantArgs va{v.X, v.sv, dm, n, t_lr, strip, v.mask, vsz, v_top, v_bot, v.pool_ctr, v.Yout, v.gram};
+  return dm.bits == 2 ? launch_quant_pair_b<2>(ka, va, st) : launch_quant_pair_b<4>(ka, va, st);
 }
 
 }  // namespace gear

@@ -389,12 +389,18 @@ int gear_compress_recent(gear_cache* cache, const void* K, const void* V, int32_
   const uint64_t tensor_entries = (uint64_t)slabs * D * rank;
   const PiTensor pk{Kp, c.outlier_ppm > 0 ? maskK : nullptr, resid, ks, {init_B, seed, 0}};
   const PiTensor pv{Vp, c.outlier_ppm > 0 ? maskV : nullptr, residV, vs, {init_B ? init_B + tensor_entries : nullptr, seed, tensor_entries}};
-  GEAR_HIP(launch_k_quant(Kp, ks, dm, n, t_lr, maskK, pool_ctr, resid, gram, strip, st));
-  if (rank > 0 && !paired) GEAR_HIP(launch_power_iteration(true, pk, dm, n, t_lr, iters, Bcur, partial, Atmp, cmat, st));
-  GEAR_HIP(launch_v_select(Vp, dm, n, (kv_v + 1) / 2, kv_v / 2, maskV, vsz, st));
-  GEAR_HIP(launch_v_quant(Vp, vs, dm, n, t_lr, (kv_v + 1) / 2, kv_v / 2, maskV, vsz, pool_ctr + slabs, residV, gramV, strip, st));
-  if (rank > 0 && !paired) GEAR_HIP(launch_power_iteration(false, pv, dm, n, t_lr, iters, Bcur, partial, Atmp, cmat, st));
-  if (paired) GEAR_HIP(launch_power_iteration_pair(pk, pv, dm, n, t_lr, iters, Bcur, gram, nstrips, st));
+  const int v_top = (kv_v + 1) / 2, v_bot = kv_v / 2;
+  GEAR_HIP(launch_v_select(Vp, dm, n, v_top, v_bot, maskV, vsz, st));
+  if (paired) {
+    GEAR_HIP(launch_quant_pair({Kp, ks, maskK, pool_ctr, resid, gram}, {Vp, vs, maskV, pool_ctr + slabs, residV, gramV}, dm, n, t_lr,
+                               v_top, v_bot, vsz, strip, st));
+    GEAR_HIP(launch_power_iteration_pair(pk, pv, dm, n, t_lr, iters, Bcur, gram, nstrips, st));
+  } else {
+    GEAR_HIP(launch_k_quant(Kp, ks, dm, n, t_lr, maskK, pool_ctr, resid, st));
+    if (rank > 0) GEAR_HIP(launch_power_iteration(true, pk, dm, n, t_lr, iters, Bcur, partial, Atmp, cmat, st));
+    GEAR_HIP(launch_v_quant(Vp, vs, dm, n, t_lr, v_top, v_bot, maskV, vsz, pool_ctr + slabs, residV, st));
+    if (rank > 0) GEAR_HIP(launch_power_iteration(false, pv, dm, n, t_lr, iters, Bcur, partial, Atmp, cmat, st));
+  }
 
   if (first) {
     cache->n_prefill = n;

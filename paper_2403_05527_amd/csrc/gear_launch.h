@@ -25,16 +25,27 @@ hipError_t launch_k_select(const uint16_t* K, const Dims& dm, int n, int k_top, 
 // per-vector grouping
 hipError_t launch_v_select(const uint16_t* V, const Dims& dm, int n, int k_top, int k_bot, uint4* mask, uint32_t* vsz,
                            hipStream_t st);
-// Quantization of one tensor given its mask (compress_quant.h).  gram != nullptr: the same pass leaves the partial Gram
-// matrices of the residual, [slab][strip of `strip` tokens][GRAM_FLOATS].  Yout (nullable): [slab][n][128] fp16,
-// Y = X - S, from which the other low-rank solvers re-derive the residual R = Y - D-hat.  k_top / k_bot (Values with the
-// Filter per head, which this launch finds by itself): per head's vector.
+// Quantization of one tensor given its mask (compress_quant.h).  Yout (nullable): [slab][n][128] fp16, Y = X - S, from which
+// the low-rank solvers that walk over it re-derive the residual R = Y - D-hat.  k_top / k_bot (Values with the Filter per
+// head, which this launch finds by itself): per head's vector.
 constexpr int GRAM_TILES = 36;
 constexpr int GRAM_FLOATS = GRAM_TILES * 256;
 hipError_t launch_k_quant(const uint16_t* K, const SegView& sv, const Dims& dm, int n, int t_lr, uint4* mask, uint32_t* pool_ctr,
-                          uint16_t* Yout, float* gram, int strip, hipStream_t st);
+                          uint16_t* Yout, hipStream_t st);
 hipError_t launch_v_quant(const uint16_t* V, const SegView& sv, const Dims& dm, int n, int t_lr, int k_top, int k_bot, uint4* mask,
-                          const uint32_t* vsz, uint32_t* pool_ctr, uint16_t* Yout, float* gram, int strip, hipStream_t st);
+                          const uint32_t* vsz, uint32_t* pool_ctr, uint16_t* Yout, hipStream_t st);
+// Both tensors of a call in one launch.  gram != nullptr (in both): the same pass leaves the partial Gram matrices of the
+// residual, [slab][strip of `strip` tokens][GRAM_FLOATS]; otherwise Yout as above.
+struct QuantTensor {
+  const uint16_t* X;
+  SegView sv;
+  uint4* mask;
+  uint32_t* pool_ctr;
+  uint16_t* Yout;
+  float* gram;
+};
+hipError_t launch_quant_pair(const QuantTensor& k, const QuantTensor& v, const Dims& dm, int n, int t_lr, int v_top, int v_bot,
+                             const uint32_t* vsz, int strip, hipStream_t st);
 
 int pi_padded_rank(int rank);
 // Tokens per strip of the pass that forms the Gram matrices; the most strips per slab any segment of up to n_max tokens gets

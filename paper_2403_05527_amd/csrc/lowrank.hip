@@ -510,15 +510,26 @@ __global__ __launch_bounds__(256, (R <= 2 ? 4 : R <= 4 ? 3 : 2)) void pi_sweep_k
                                npart, Atmp);
 }
 
-// The pass of the last round when the Gram matrix exists: A = R W with the projection matrix W that
-// pi_solve_kernel left in Bcur, written to the arena as fp16; from X itself, whose entries in S are masked out.  grid (ceil(n / 256), B*H), block 256.
-template <bool IS_K, int R>
-__global__ __launch_bounds__(256, (R <= 4 ? 4 : 3)) void pi_project_kernel(const uint16_t* __restrict__ X, const uint4* __restrict__ mask,
-                                                                         SegView sv, int g, int bits,
+// The pass of the last round when the Gram matrix exists: A = R W with the projection matrices W ([2][slab][128][R], Keys
+// first) that pi_solve_kernel left in Bcur, written to the arena as fp16; from X itself, whose entries in S are masked out.
+// Both tensors in one launch (z = 0: Keys, 1: Values): on a short prompt each is a few blocks' latency (512 tokens of 32
+// heads: 9.6 + 9.3 us one after the other).
+// grid (ceil(n / 256), B*H, 2), block 256.
+template <int R>
+__global__ __launch_bounds__(256, (R <= 4 ? 4 : 3)) void pi_project_kernel(const uint16_t* __restrict__ XK, const uint16_t* __restrict__ XV,
+                                                                         const uint4* __restrict__ maskK, const uint4* __restrict__ maskV,
+                                                                         SegView ks, SegView vs, int gk, int gv, int bits,
                                                                          int n, int t_lr, const float* __restrict__ Bcur) {
-  __shared__ SweepSmem<IS_K, R> sm;
-  pi_sweep_body<IS_K, R, false, true>(sm, blockIdx.y, blockIdx.x, X, sv.sz, sv.codes, sv.n_cap, sv.ng_cap, g, bits, n, t_lr, Bcur,
-                                      nullptr, 0, nullptr, sv.A, sv.rank, mask);
+  __shared__ union {
+    SweepSmem<true, R> k;
+    SweepSmem<false, R> v;
+  } sm;
+  if (blockIdx.z == 0)
+    pi_sweep_body<true, R, false, true>(sm.k, blockIdx.y, blockIdx.x, XK, ks.sz, ks.codes, ks.n_cap, ks.ng_cap, gk, bits, n, t_lr, Bcur,
+                                        nullptr, 0, nullptr, ks.A, ks.rank, maskK);
+  else
+    pi_sweep_body<false, R, false, true>(sm.v, blockIdx.y, blockIdx.x, XV, vs.sz, vs.codes, vs.n_cap, vs.ng_cap, gv, bits, n, t_lr,
+                                         Bcur + (size_t)gridDim.y * D * R, nullptr, 0, nullptr, vs.A, vs.rank, maskV);
 }
 
 // A = a C for tokens [256 * pt, 256 * pt + 256) of one slab, one token per thread.  Cs: LDS, R * R floats.
@@ -1086,11 +1097,8 @@ static hipError_t run_pi_pair(const PiTensor& k, const PiTensor& v, const Dims& 
   hipLaunchKernelGGL(pi_solve_kernel<R>, dim3(slabs, 2), dim3(256), sizeof(SolveSmem<R>), st, k.sb, v.sb, rank, (const float*)gram,
                      summed ? 1 : nstrips, nstrips, iters - 1, Bcur, 1, k.sv.Bf, v.sv.Bf);
   // one light pass writes A
-  const dim3 grid((n + PT - 1) / PT, slabs);
-  hipLaunchKernelGGL((pi_project_kernel<true, R>), grid, dim3(256), 0, st, k.X, k.mask, k.sv, key_group_size(dm), dm.bits, n, t_lr,
-                     (const float*)Bcur);
-  hipLaunchKernelGGL((pi_project_kernel<false, R>), grid, dim3(256), 0, st, v.X, v.mask, v.sv, dm.g, dm.bits, n, t_lr,
-                     (const float*)(Bcur + (size_t)slabs * D * R));
+  hipLaunchKernelGGL(pi_project_kernel<R>, dim3((n + PT - 1) / PT, slabs, 2), dim3(256), 0, st, k.X, v.X, k.mask, v.mask, k.sv, v.sv,
+                     key_group_size(dm), dm.g, dm.bits, n, t_lr, (const float*)Bcur);
   return hipGetLastError();
 }
 

@@ -28,6 +28,7 @@ def _values(kind, shape, seed):
     ("normal", 1, 3, 2049, 2, 32, 20000), ("steps", 1, 2, 4097, 2, 64, 20000), ("steps", 2, 2, 8193, 2, 64, 20000),
     ("signs", 1, 9, 385, 2, 64, 500000), ("steps", 1, 2, 300, 2, 64, 1),
     ("steps", 1, 33, 130, 4, 64, 20000), ("steps", 1, 2, 8192, 4, 128, 20000),
+    ("steps", 1, 2, 256, 4, 0, 20000), ("normal", 2, 3, 64, 2, 32, 20000),   # the last sizes before the tensors of a call go apart, and together
 ])
 def test_filter_and_codes_equal_the_oracle(kind, B, H, n, bits, group, ppm):
     w = gw.Workload("f", B=B, H_kv=H, H_q=H, n=n, bits=bits, group=group, outlier_ppm=ppm, rank=2, rank_chunk=2, n_b=64, steps=1, seed=n)
