@@ -19,24 +19,42 @@ struct RegSource {  // the vector lives in the wave's registers
   __device__ __forceinline__ uint4 operator()(int ch) const { return x[ch]; }
 };
 
-// The block's eight channels' outlier bits, gathered in LDS as one byte per token (bit j: channel j of the eight), go into
-// the mask rows: byte cb of row t.
-__device__ __forceinline__ void store_mask_bytes(const uint32_t* bits, uint4* mask_slab, int n, int cb) {
+// Decodes a 1-D grid of 16 * nslab blocks, one per slab and block of eight channels.  Consecutive block ids go round-robin to
+// the chip's 8 XCDs (each with its own L2), so the id is decoded with the column block fastest INSIDE one XCD: the blocks
+// that share the 128-byte lines of one slab (of its rows, of its mask) then meet in one L2 instead of eight.  The up to
+// seven slabs past a multiple of eight go to all XCDs.  231 slabs x 3000 tokens, which went to all XCDs as a whole before:
+// 245 -> 106 us.
+__device__ __forceinline__ void slab_and_column_block(int nslab, int& slab, int& cb) {
+  constexpr int ncb = D / 8;
+  const int i = blockIdx.x, even = (nslab & ~7) * ncb;
+  if (i < even) {
+    const int xcd = i & 7, j = i >> 3;
+    cb = j % ncb;
+    slab = (j / ncb) * 8 + xcd;
+  } else {
+    cb = i % ncb;
+    slab = i / ncb;
+  }
+}
+
+// A block's eight channels' outlier bits go through LDS as an 8 x 8 bit matrix per eight consecutive tokens, 8 bytes at
+// 8 (t / 8).  Every wave leaves its channel's byte (bit e: token 8 (t / 8) + e), one byte store per chunk and lane; the block
+// then transposes the matrices in place (byte e: the eight channels of that token) and stores them into the mask rows, byte
+// cb of row t.  Bits past n are not masked out: they end up in rows that are not stored.  Whole bytes, because hardly a chunk of
+// 512 keys holds no outlier: one atomic per set bit ran its divergent loop for every chunk.  Keys of 512 slabs x 8192 tokens
+// 645 -> 620 us, 32 slabs x 32768 (rank-8 call) 201 -> 187, 8 slabs x 32768 109 -> 96.
+__device__ __forceinline__ void mark_chunk(const uint4& v, int ch, uint32_t* bits, const ThreshPair& tp, const ThreshKeys& tk) {
+  const uint32_t first = (uint32_t)(ch * 512 + lane_id() * 8);
+  reinterpret_cast<uint8_t*>(bits)[first + (threadIdx.x >> 6)] = (uint8_t)(tk.cut ? piece_bits(v, first, tp) : key_bits(v, tk));
+}
+__device__ __forceinline__ void store_mask_bytes(uint32_t* bits, uint4* mask_slab, int n, int cb) {
+  for (int q = threadIdx.x; q < (n + 7) / 8; q += blockDim.x) {
+    uint2* m = reinterpret_cast<uint2*>(bits) + q;
+    *m = transpose_bits8(*m);
+  }
+  block_lds_sync();
   for (int t = threadIdx.x; t < n; t += blockDim.x)
     reinterpret_cast<uint8_t*>(mask_slab + t)[cb] = reinterpret_cast<const uint8_t*>(bits)[t];
-}
-// A wave's channel (bit j of the byte): the entries of one chunk (8 consecutive tokens per lane, from `base`) that the
-// predicate takes.
-// Two keys per instruction find the few entries by key alone, and only those are asked for the index where a
-// threshold's ties are cut (which a fifth of the vectors of normally distributed keys need).
-__device__ __forceinline__ void mark_chunk(const uint4& v, int base, int n, const ThreshPair& tp, const ThreshKeys& tk, uint32_t* bits, int j) {
-  uint32_t f = key_bits(v, tk);
-  if (base + 8 > n) f &= base < n ? (1u << (n - base)) - 1u : 0u;
-  while (f != 0u) {
-    const int e = __ffs((int)f) - 1, t = base + e;
-    f &= f - 1u;
-    if (!tk.cut || outlier(half_of(v.x, v.y, v.z, v.w, e), (uint32_t)t, tp)) atomicOr(&bits[t >> 2], 1u << (8 * (t & 3) + j));
-  }
 }
 
 // ------------------------------------------------------------------ K select, segments of at most 64 tokens
@@ -130,7 +148,7 @@ __global__ __launch_bounds__(128) void k_select_tiny_kernel(const uint16_t* __re
 // read one channel at a time from the [token][channel] tensor every 2-byte value costs a whole memory
 // sector.  So the keys are first written channel-major ([slab][channel][stride] u16, stride = n rounded up
 // to 8) into scratch memory, and the selection then reads every vector contiguously, straight from global
-// memory, once per pass: no LDS tile, so the occupancy does not depend on the segment length.
+// memory, once per pass.  LDS holds the histograms and the block's eight channels of outlier bits (32 KB).
 struct GlobalKeySource {   // one vector stored contiguously in global memory as 16-bit keys
   static constexpr int kMaxChunks = -1;
   GEAR_BUF_T buf;          // view of the vector's stride keys; reads past it return 0
@@ -162,17 +180,18 @@ __global__ __launch_bounds__(256) void k_transpose_keys_kernel(const uint16_t* _
   }
 }
 
-// grid (B*H * 128 / 8), block 512: one wave per channel vector.
-__global__ __launch_bounds__(512) void k_select_long_kernel(const uint16_t* __restrict__ KT, int n, int stride, int k_top,
+// 1-D grid of 16 * nslab blocks of 512 threads, decoded like that of k_select_reg_kernel: one wave per channel vector.
+__global__ __launch_bounds__(512) void k_select_long_kernel(const uint16_t* __restrict__ KT, int n, int stride, int nslab, int k_top,
                                                             int k_bot, uint4* __restrict__ mask,
                                                             uint32_t* __restrict__ zero, int zero_count,
                                                             uint32_t* __restrict__ ksz, int ng_cap, float qmax) {
   __shared__ uint32_t hist_all[8 * SELECT_LDS_WORDS];
-  __shared__ uint32_t bits[32768 / 4];
+  __shared__ __align__(16) uint32_t bits[32768 / 4];
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < zero_count; i += gridDim.x * blockDim.x) zero[i] = 0u;
-  for (int i = threadIdx.x; i < (n + 3) / 4; i += blockDim.x) bits[i] = 0u;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int v = blockIdx.x * 8 + wave;   // slab * 128 + channel
+  int slab, cb;
+  slab_and_column_block(nslab, slab, cb);
+  const int v = slab * D + cb * 8 + wave;   // vector: slab, channel
   const GlobalKeySource src{GEAR_BUF_MAKE(KT + (size_t)v * stride, stride * 2)};
   const Thresh th = wave_select(src, n, k_top, k_bot, hist_all + wave * SELECT_LDS_WORDS, true);
   const ThreshPair tp = pack_thresh(th);
@@ -200,11 +219,10 @@ __global__ __launch_bounds__(512) void k_select_long_kernel(const uint16_t* __re
       ksz[(size_t)(v / D) * ng_cap * D + (v % D)] = group_bits(make_group(h2f(unkey16(kmn)), h2f(unkey16(kmx)), qmax));
   }
   if (!mask) return;
-  block_lds_sync();
   const ThreshKeys tk = key_thresh(tp);
-  for_each_chunk(src, (n + 511) >> 9, [&](int ch, const uint4& v4) { mark_chunk(v4, ch * 512 + lane * 8, n, tp, tk, bits, wave); });
+  for_each_chunk(src, (n + 511) >> 9, [&](int ch, const uint4& v4) { mark_chunk(v4, ch, bits, tp, tk); });
   block_lds_sync();
-  store_mask_bytes(bits, mask + (size_t)(blockIdx.x / (D / 8)) * n, n, blockIdx.x % (D / 8));
+  store_mask_bytes(bits, mask + (size_t)slab * n, n, cb);
 }
 
 // ------------------------------------------------------------------ K select, vectors in registers
@@ -215,29 +233,18 @@ __global__ __launch_bounds__(512) void k_select_long_kernel(const uint16_t* __re
 // 16-byte row pieces (8 channels) of rows 2 tid and 2 tid + 1, pairs the two rows' keys of each channel
 // in one word and writes it to stage[channel][tid]; wave w then reads channel w's 1024 keys back as two
 // 16-byte pieces per lane.  All of a thread's loads are requested at the start.
-// 1-D grid of 16 * B*H blocks of 512 threads.  Consecutive block ids go round-robin to the chip's 8 XCDs (each with its
-// own L2), so the id is decoded with the column block fastest INSIDE one XCD: the blocks that share the 128-byte lines of
-// one slab then meet in one L2 instead of eight.
+// 1-D grid of 16 * nslab blocks of 512 threads (slab_and_column_block).
 template <int NC>
 __global__ __launch_bounds__(512, (NC <= 8 ? 4 : 2)) void k_select_reg_kernel(const uint16_t* __restrict__ K, int n, int nslab,
                                                                             int k_top, int k_bot, uint4* __restrict__ mask,
                                                                             uint32_t* __restrict__ zero, int zero_count,
                                                                             uint32_t* __restrict__ ksz, int ng_cap, float qmax) {
   __shared__ uint32_t hist[8 * SELECT_LDS_WORDS];
-  __shared__ uint32_t bits[NC * 512 / 4];
+  __shared__ __align__(16) uint32_t bits[NC * 512 / 4];
   __shared__ __align__(16) uint32_t stage[8][512];
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < zero_count; i += gridDim.x * blockDim.x) zero[i] = 0u;
-  for (int i = threadIdx.x; i < NC * 512 / 4; i += 512) bits[i] = 0u;   // (ordered before their use by the staging barriers)
-  constexpr int ncb = D / 8;
   int slab, cb;
-  if ((nslab & 7) == 0) {
-    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-    cb = j % ncb;
-    slab = (j / ncb) * 8 + xcd;
-  } else {
-    cb = blockIdx.x % ncb;
-    slab = blockIdx.x / ncb;
-  }
+  slab_and_column_block(nslab, slab, cb);
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   // a view of the column block that ends with its last row: rows past n read as 0
   const GEAR_BUF_T xb = GEAR_BUF_MAKE(K + (size_t)slab * n * D + cb * 8, (n - 1) * (D * 2) + 16);
@@ -294,7 +301,7 @@ __global__ __launch_bounds__(512, (NC <= 8 ? 4 : 2)) void k_select_reg_kernel(co
   const ThreshKeys tk = key_thresh(tp);
 #pragma unroll
   for (int c = 0; c < NC; ++c)
-    if (c * 512 < n) mark_chunk(x[c], c * 512 + lane * 8, n, tp, tk, bits, wave);
+    if (c * 512 < n) mark_chunk(x[c], c, bits, tp, tk);
   block_lds_sync();
   store_mask_bytes(bits, mask + (size_t)slab * n, n, cb);
 }
@@ -316,7 +323,7 @@ hipError_t launch_k_select(const uint16_t* K, const Dims& dm, int n, int k_top, 
     const int stride = (n + 7) & ~7;
     hipLaunchKernelGGL(k_transpose_keys_kernel, dim3((n + 127) / 128, dm.B * dm.H), dim3(256), 0, st, K, n, stride, kt_scratch);
     hipLaunchKernelGGL(k_select_long_kernel, dim3(dm.B * dm.H * (D / 8)), dim3(512), 0, st, (const uint16_t*)kt_scratch, n,
-                       stride, k_top, k_bot, mask, zero, zero_count, dm.kcvt ? sv.sz : (uint32_t*)nullptr, sv.ng_cap, dm.qmax);
+                       stride, dm.B * dm.H, k_top, k_bot, mask, zero, zero_count, dm.kcvt ? sv.sz : (uint32_t*)nullptr, sv.ng_cap, dm.qmax);
     return hipGetLastError();
   }
   // a flushed buffer: one thread per channel vector

@@ -18,15 +18,6 @@ struct RegSource {  // the vector lives in the wave's registers
   __device__ __forceinline__ uint4 operator()(int ch) const { return x[ch]; }
 };
 
-// bit e: entry e of a row piece of eight keys (in-vector indices from idx0) belongs to S
-__device__ __forceinline__ uint32_t piece_bits(const uint4& v, uint32_t idx0, const ThreshPair& tp) {
-  const uint32_t kw[4] = {v.x, v.y, v.z, v.w};
-  uint32_t f = 0;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) f |= (outlier(slot_key(kw, e), idx0 + e, tp) ? 1u : 0u) << e;
-  return f;
-}
-
 // grid (ceil(n / (4 * tpw)), B); block 256: tpw tokens per wave, one after another.
 // lane l, chunk ch  <->  head 4*ch + l/16, channels 8*(l%16)..+7, i.e. in-vector index
 // ch*512 + l*8 + e.

@@ -326,6 +326,26 @@ __device__ __forceinline__ uint32_t key_bits(const uint4& v, const ThreshKeys& k
   for (int j = 0; j < 4; ++j) z[j] = min_u16x2(sub_sat_u16x2(w[j], k.top) | sub_sat_u16x2(k.bot, w[j]), 0x00010001u);
   return flag_byte(z);
 }
+// bit e: entry e of a row piece of eight keys (in-vector indices from idx0) belongs to S, by the exact test
+__device__ __forceinline__ uint32_t piece_bits(const uint4& v, uint32_t idx0, const ThreshPair& tp) {
+  const uint32_t kw[4] = {v.x, v.y, v.z, v.w};
+  uint32_t f = 0;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) f |= (outlier(slot_key(kw, e), idx0 + e, tp) ? 1u : 0u) << e;
+  return f;
+}
+// The transposed 8 x 8 bit matrix (row i: byte i, column e: bit e).  Blocks of 2 x 2 and 4 x 4 bits inside the two words, then
+// the halves of the rows between them.
+__device__ __forceinline__ uint2 transpose_bits8(uint2 m) {
+  auto in_word = [](uint32_t x) {
+    uint32_t t = (x ^ (x >> 7)) & 0x00AA00AAu;
+    x ^= t ^ (t << 7);
+    t = (x ^ (x >> 14)) & 0x0000CCCCu;
+    return x ^ t ^ (t << 14);
+  };
+  const uint32_t x = in_word(m.x), y = in_word(m.y), t = ((x >> 4) ^ y) & 0x0F0F0F0Fu;
+  return make_uint2(x ^ (t << 4), y ^ t);
+}
 // bit e: the high byte of entry e's key is that of a (a2: the byte << 8 in both halves) or that of b
 __device__ __forceinline__ uint32_t high_byte_bits(const uint4& v, uint32_t a2, uint32_t b2) {
   const uint32_t w[4] = {v.x, v.y, v.z, v.w};

@@ -27,6 +27,7 @@ def _values(kind, shape, seed):
     ("steps", 2, 4, 512, 4, 64, 10000), ("constant", 1, 5, 513, 2, 0, 20000), ("signs", 1, 2, 1025, 4, 0, 50000),
     ("normal", 1, 3, 2049, 2, 32, 20000), ("steps", 1, 2, 4097, 2, 64, 20000), ("steps", 2, 2, 8193, 2, 64, 20000),
     ("signs", 1, 9, 385, 2, 64, 500000), ("steps", 1, 2, 300, 2, 64, 1),
+    ("steps", 1, 9, 8201, 2, 64, 20000),     # one slab past a multiple of eight: the grids decoded by XCD
     ("steps", 1, 33, 130, 4, 64, 20000), ("steps", 1, 2, 8192, 4, 128, 20000),
     ("steps", 1, 2, 256, 4, 0, 20000), ("normal", 2, 3, 64, 2, 32, 20000),   # the last sizes before the tensors of a call go apart, and together
 ])
