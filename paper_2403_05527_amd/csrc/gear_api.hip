@@ -348,7 +348,12 @@ int gear_compress_recent(gear_cache* cache, const void* K, const void* V, int32_
   }
   const WorkLayout w = work_layout(c);
   if (workspace_bytes < w.bytes) return GEAR_ECAPACITY;
+  const bool on_gram = pi_on_gram(n, rank, iters), paired = pi_paired(n, rank, iters);
+  const size_t slabs = (size_t)c.B * c.H_kv;
+  const int strip = on_gram ? pi_gram_strip(n, c.B * c.H_kv) : 128, nstrips = (n + strip - 1) / strip;
+  if (on_gram && nstrips > w.gram_strips) return GEAR_ECAPACITY;   // (the workspace is sized for every n the cache takes)
 
+  // nothing is refused from here on: the first launch may write into the arena
   const ArenaLayout a = arena_layout(c);
   const Dims dm = make_dims(c);
   hipStream_t st = static_cast<hipStream_t>(stream);
@@ -377,10 +382,6 @@ int gear_compress_recent(gear_cache* cache, const void* K, const void* V, int32_
   uint32_t* vsz = reinterpret_cast<uint32_t*>(ws + w.vsz);
   // Quantize (with the Gram matrix of the residual, or leaving Y = X - S in the workspace), then the power iteration; where
   // that goes one tensor at a time, the Values reuse the Keys' buffers afterwards.
-  const bool on_gram = pi_on_gram(n, rank, iters), paired = pi_paired(n, rank, iters);
-  const size_t slabs = (size_t)c.B * c.H_kv;
-  const int strip = on_gram ? pi_gram_strip(n, c.B * c.H_kv) : 128, nstrips = (n + strip - 1) / strip;
-  if (on_gram && nstrips > w.gram_strips) return GEAR_ECAPACITY;   // (the workspace is sized for every n the cache takes)
   float* gram = on_gram ? reinterpret_cast<float*>(ws + w.gram) : nullptr;
   float* gramV = on_gram ? gram + slabs * nstrips * GRAM_FLOATS : nullptr;
   uint16_t* resid = rank > 0 && !on_gram ? reinterpret_cast<uint16_t*>(ws + w.resid) : nullptr;
