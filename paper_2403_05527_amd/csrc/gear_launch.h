@@ -48,9 +48,38 @@ hipError_t launch_quant_pair(const QuantTensor& k, const QuantTensor& v, const D
                              const uint32_t* vsz, int strip, hipStream_t st);
 
 int pi_padded_rank(int rank);
-// Tokens per strip of the pass that forms the Gram matrices; the most strips per slab any segment of up to n_max tokens gets
-int pi_gram_strip(int n, int slabs);
-int pi_gram_strips_max(int n_max, int slabs);
+// Tokens per strip of the pass that quantizes and forms the Gram matrices.  A strip is one block's work and leaves one partial
+// matrix (36 KB) per tensor, which the solve kernel, one block per slab, adds up: the longest strips whose blocks, those of both
+// tensors, fill the resident slots one and a quarter times (just above once, the few blocks of the second round cost as much as
+// the first: 280 slabs of 1777 tokens in one strip each, 560 blocks, 524 us for a compress and decompress against 516 in two
+// strips).  Counting one tensor only, with strips down to 128 tokens, took 160 us for a call on 5 x 8 slabs of 3001 tokens (now
+// 140), 106 on 4 x 32 of 512 (95), 82 on 32 of 1003 (78), and twice the partials' memory.
+// A grid that stays under an eighth of the slots with 256-token strips is a few blocks' latency: strips of 128 tokens halve the
+// block's chain (8 slabs of 512 tokens 56 against 58 us).  Above that they gain a microsecond at most (32 slabs of 300 tokens 67
+// against 68) or lose (32 of 512: 72 against 70), and their partials would be the largest array of such a cache.
+constexpr int STRIP_BLOCKS = GEAR_BLOCK_SLOTS + GEAR_BLOCK_SLOTS / 4;
+constexpr long long STRIP_ROWS_FEW = 256ll * (GEAR_BLOCK_SLOTS / 8);   // token rows of both tensors
+inline int pi_gram_strip(int n, int slabs) {
+  for (int strip = 2048; strip > 256; strip >>= 1)
+    if (2ll * slabs * ((n + strip - 1) / strip) >= STRIP_BLOCKS) return strip;
+  return 2ll * slabs * n >= STRIP_ROWS_FEW ? 256 : 128;
+}
+// The most strips per slab any segment of up to n_max tokens gets.  The strip length grows with n, and for one length the count
+// does: the maximum lies at n_max or at the last n before a longer strip.
+inline int pi_gram_strips_max(int n_max, int slabs) {
+  const long long per = (STRIP_BLOCKS - 1) / (2ll * slabs);   // strips per slab that are too few
+  int most = 0;
+  auto take = [&](long long n) {
+    if (n < 1) return;
+    if (n > n_max) n = n_max;
+    const int strip = pi_gram_strip((int)n, slabs), count = ((int)n + strip - 1) / strip;
+    most = count > most ? count : most;
+  };
+  take(n_max);
+  for (int strip = 512; strip <= 2048; strip <<= 1) take(strip * per);
+  take((STRIP_ROWS_FEW - 1) / (2ll * slabs));
+  return most;
+}
 // whether a segment of n tokens is solved on its Gram matrix (from X and its mask instead of Y)
 inline bool pi_on_gram(int n, int rank, int iters) { return rank > 0 && iters > 1 && n > 256; }
 // whether Keys and Values of a segment are solved together, launch by launch: on their Gram matrices, or (a flushed

@@ -1053,20 +1053,6 @@ __global__ __launch_bounds__(256) void pi_tiny_kernel(const uint16_t* __restrict
 }
 
 // ------------------------------------------------------------------ host side
-// Tokens per strip of the pass that forms the Gram matrices: the longest that still gives every resident block slot (two
-// per CU, 512 on the chip) a strip; the solve kernel, one block per slab, then has the fewest partials to add.
-int pi_gram_strip(int n, int slabs) {
-  for (int strip = 2048; strip > 128; strip >>= 1)
-    if ((long long)slabs * ((n + strip - 1) / strip) >= 512) return strip;
-  return 128;
-}
-int pi_gram_strips_max(int n_max, int slabs) {
-  const int m = (1024 + slabs - 1) / slabs;   // strips per slab that fill the chip
-  const int coarse = (n_max + 2047) / 2048, fine = (n_max + 127) / 128;
-  const int want = 2 * m > coarse ? 2 * m : coarse;
-  return want < fine ? want : fine;
-}
-
 template <int R>
 static hipError_t raise_solve_lds() {
   static std::atomic<bool> lds_raised{false};   // per kernel instance (R); two threads may both raise it: harmless

@@ -60,6 +60,21 @@ def emulator(tmp_path_factory):
     return exe
 
 
+@pytest.mark.parametrize("slots", [512, 16])
+def test_workspace_holds_exactly_the_most_strips(tmp_path, slots):
+    """The bound by which the workspace of the Gram matrices is sized is reached and never passed, at the device's number of
+    block slots and at the stand-in's."""
+    cxx = find_clang()
+    if cxx is None:
+        pytest.skip("no clang++")
+    exe = str(tmp_path / "check_strips")
+    r = subprocess.run([cxx, "-std=c++17", "-O2", "-pthread", "-DGEAR_BLOCK_SLOTS=%d" % slots, os.path.join(SIMT, "check_strips.cpp"), "-o", exe,
+                        "-I", SIMT, "-I", os.path.join(ROOT, "include"), "-I", CSRC], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
+
+
 @pytest.mark.parametrize("B,H,Hq,n,bits,g,ppm,rank,n_buf,per_head,chunk_n,n_b,n_lowrank", [
     (1, 4, 8, 290, 2, 64, 20000, 4, 5, False, 20, 20, -1),     # the method as stated; n > 256: Gram-matrix power iteration
     (1, 2, 2, 140, 4, 0, 30000, 2, 3, True, 20, 20, -1),       # per-vector groups and the per-head Value Filter
