@@ -169,7 +169,8 @@ int gear_decode_attn(const gear_cache* cache, const void* q, const void* K_buf, 
  * q_len     : a power of two with q_len * (H_q / H_kv) <= 8 (longer blocks: several calls);
  *             causal needs n_buf >= q_len.  Otherwise GEAR_EINVAL.
  * workspace : the workspace of gear_cache_bytes; GEAR_ECAPACITY if the records of q_len rows do
- *             not fit behind those of one (they do whenever rank_max > 0).
+ *             not fit into it (they do whenever rank_max > 0 and n_prefill_max > 256; behind a
+ *             shorter prompt it depends on the number of appended segments).
  */
 int gear_decode_attn_mq(const gear_cache* cache, const void* q, int32_t q_len, int32_t causal,
                         const void* K_buf, const void* V_buf, int32_t n_buf, void* out,
@@ -225,8 +226,8 @@ int gear_export_lowrank(const gear_cache* cache, int which, int seg, void* A_f16
  *                  form are index / d_h and index % d_h).
  *  value_f16     : device fp16 [nnz], the entries (bit copies of the input) in the same order.
  *  workspace     : device scratch, >= 4 * B * H_kv * n_total + 4 * ceil(B * H_kv * n_total / 1024)
- *                  + 512 bytes (the workspace of gear_cache_bytes is large enough whenever
- *                  n_total <= 8 * n_prefill_max); GEAR_ECAPACITY otherwise.
+ *                  + 512 bytes (the workspace of gear_cache_bytes is large enough); GEAR_ECAPACITY
+ *                  otherwise.
  */
 int gear_export_sparse_coo(const gear_cache* cache, int which, int64_t* nnz, void* lin_index_i64,
                            void* value_f16, void* workspace, size_t workspace_bytes, void* stream);

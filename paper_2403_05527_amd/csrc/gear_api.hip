@@ -88,44 +88,79 @@ ArenaLayout arena_layout(const gear_config& c) {
   return a;
 }
 
+// Byte offsets inside the workspace.  What a compress call needs depends on which solver its segment takes, so those arrays
+// share one region, laid out for each of them:
+//   pair   both tensors on their Gram matrices: both masks, the iterates, the partial Gram matrices
+//   tiny   both tensors of a flushed buffer (at most PI_TINY_ROWS tokens): both masks, Y of both
+//   one    one tensor after the other (up to 256 tokens, a single round, no low-rank term): one mask, Y, what the sweeps leave
+// The channel-major copy of the keys of a long segment (launch_k_select) lies behind the Keys' mask; it is dead before the next
+// array is written there.
 struct WorkLayout {
-  size_t maskK, maskV, vsz, pool_ctr, Bcur, partial, Atmp, cmat, dec, gram, resid, bytes;
+  size_t pool_ctr, vsz, dec, mask;
+  struct { size_t mask_v, Bcur, gram; } pair;
+  struct { size_t mask_v, Y; } tiny;
+  struct { size_t Y, partial, Atmp, cmat, Bcur; } one;
+  size_t kt, bytes;
   int gram_strips;
 };
+
+// Records of a decode call of one query row per head: one per 512 prefill tokens, one per four chunk pieces (a chunk is one
+// piece of up to 128 rows, two when n_buf_cap > 128), one for the buffer.
+size_t record_bytes(const gear_config& c, int n_prefill, int n_chunks) {
+  const int nsplit = (n_prefill + DECODE_SPLIT - 1) / DECODE_SPLIT;
+  const int ncb = (n_chunks * (c.n_buf_cap > 128 ? 2 : 1) + 3) / 4;
+  return (size_t)c.B * c.H_q * (nsplit + ncb + 1) * DECODE_REC * 4;
+}
+// Scratch of gear_export_sparse_coo over `rows` token rows: a count each, and partial sums of 1024 of them.
+size_t coo_row_bytes(size_t rows) { return up(rows * 4); }
+size_t coo_bytes(size_t rows) { return coo_row_bytes(rows) + up(((rows + 1023) / 1024) * 4); }
 
 WorkLayout work_layout(const gear_config& c) {
   WorkLayout w;
   const size_t slabs = (size_t)c.B * c.H_kv;
   const int n_max = c.n_prefill_max > c.n_buf_cap ? c.n_prefill_max : c.n_buf_cap;
-  const int npart = (n_max + 255) / 256;
+  const int n_tiny = n_max < PI_TINY_ROWS ? n_max : PI_TINY_ROWS;
   const int R = 8;
+  const auto mask_bytes = [&](int rows) { return up(c.outlier_ppm > 0 ? slabs * (size_t)rows * 16 : 0); };   // a bit per entry
+  const auto y_bytes = [&](int rows) { return slabs * (size_t)rows * D * 2; };
   size_t o = 0;
-  w.maskK = o; o += up(c.outlier_ppm > 0 ? slabs * (size_t)n_max * 16 : 0);   // which entries belong to S, 16 bytes per token row
-  w.maskV = o; o += up(c.outlier_ppm > 0 ? slabs * (size_t)n_max * 16 : 0);
-  w.vsz = o; o += up(c.group == 0 ? (size_t)c.B * n_max * 4 : 0);   // per-vector grouping: a Value token's (scale, zero)
   w.pool_ctr = o; o += up((slabs + (size_t)c.B) * 4);   // Key counters per slab, then Value counters per batch
-  w.Bcur = o; o += up(2 * slabs * D * R * 4);   // (Keys and Values are solved together)
-  w.partial = o; o += up(slabs * (size_t)npart * (D * R + R * R) * 4);
-  w.Atmp = o; o += up(slabs * (size_t)n_max * R * 4);
-  w.cmat = o; o += up(slabs * R * R * 4);
-  // decode records: one per 512 prefill tokens, one per four chunk pieces (a chunk is one
-  // piece of up to 128 rows, two when n_buf_cap > 128), one for the buffer
-  const int nsplit = (c.n_prefill_max + DECODE_SPLIT - 1) / DECODE_SPLIT;
-  const int ncb = (c.n_chunks_max * (c.n_buf_cap > 128 ? 2 : 1) + 3) / 4;
-  w.dec = o; o += up((size_t)c.B * c.H_q * (nsplit + ncb + 1) * DECODE_REC * 4);
+  w.vsz = o; o += up(c.group == 0 ? (size_t)c.B * n_max * 4 : 0);   // per-vector grouping: a Value token's (scale, zero)
+  const size_t dec_bytes = up(record_bytes(c, c.n_prefill_max, c.n_chunks_max));
+  w.dec = o; o += dec_bytes;
+  w.mask = o;
+  size_t end = o;
+  const auto reach = [&](size_t e) { end = e > end ? e : end; };
+  // pair
+  o = w.mask + mask_bytes(n_max);
+  w.pair.mask_v = o; o += mask_bytes(n_max);
+  w.pair.Bcur = o; o += up(2 * slabs * D * R * 4);
+  w.pair.gram = o;
   w.gram_strips = c.rank_max > 0 && n_max > 256 ? pi_gram_strips_max(n_max, (int)slabs) : 0;
-  w.gram = o; o += up(2 * slabs * (size_t)w.gram_strips * 36 * 256 * 4);
-  // the filtered tensor Y for the low-rank solvers that walk over it; the channel-major copy of the keys of a long Key
-  // segment (see launch_k_select) lives in the same place
-  w.resid = o;
-  {
-    // one tensor at a time, or both of a flushed buffer
-    const int rows = n_max > 2 * PI_TINY_ROWS ? n_max : 2 * (n_max < PI_TINY_ROWS ? n_max : PI_TINY_ROWS);
-    const size_t resid = c.rank_max > 0 ? slabs * (size_t)(rows > n_max ? rows : n_max) * D * 2 : 0;
-    const size_t kt = c.n_prefill_max > 8192 ? slabs * (size_t)((c.n_prefill_max + 7) & ~7) * D * 2 : 0;
-    o += up(resid > kt ? resid : kt);
+  if (w.gram_strips > 0) reach(o + up(2 * slabs * (size_t)w.gram_strips * GRAM_FLOATS * 4));
+  // tiny
+  o = w.mask + mask_bytes(n_tiny);
+  w.tiny.mask_v = o; o += mask_bytes(n_tiny);
+  w.tiny.Y = o;
+  if (c.rank_max > 0) reach(o + up(2 * y_bytes(n_tiny)));
+  // one
+  o = w.mask + mask_bytes(n_max);
+  w.kt = o;
+  if (c.n_prefill_max > 8192) reach(o + up(y_bytes((c.n_prefill_max + 7) & ~7)));
+  w.one.Y = o; o += c.rank_max > 0 ? up(y_bytes(n_max)) : 0;
+  if (c.rank_max > 0) {
+    w.one.partial = o; o += up(slabs * (size_t)((n_max + 255) / 256) * (D * R + R * R) * 4);
+    w.one.Atmp = o; o += up(slabs * (size_t)n_max * R * 4);
+    w.one.cmat = o; o += up(slabs * R * R * 4);
+    w.one.Bcur = o; o += up(slabs * D * R * 4);
   }
-  w.bytes = o;
+  reach(o);
+  // gear_decode_attn_mq: the records of as many query rows as one call takes (behind a short prompt they fit unless a hundred
+  // segments or so have been appended)
+  if (c.rank_max > 0 && n_max > 256) reach(w.dec + (size_t)(8 / (c.H_q / c.H_kv)) * dec_bytes);
+  // gear_export_sparse_coo: a full cache
+  if (c.outlier_ppm > 0) reach(coo_bytes(slabs * ((size_t)c.n_prefill_max + (size_t)c.n_chunks_max * c.n_buf_cap)));
+  w.bytes = end;
   return w;
 }
 
@@ -246,15 +281,10 @@ int current_device_scratch(void** out) {
   return GEAR_OK;
 }
 
-// Common body of the two decode entry points.  `partial` holds the split records
-// (at least decode_record_bytes(cache) bytes).
-size_t decode_record_bytes(const gear_cache* cache) {
-  const gear_config& c = cache->cfg;
-  const int nsplit = (cache->n_prefill + DECODE_SPLIT - 1) / DECODE_SPLIT;
-  const int ncb = (cache->n_chunks * (c.n_buf_cap > 128 ? 2 : 1) + 3) / 4;
-  return (size_t)c.B * c.H_q * (nsplit + ncb + 1) * DECODE_REC * 4;
-}
+size_t decode_record_bytes(const gear_cache* cache) { return record_bytes(cache->cfg, cache->n_prefill, cache->n_chunks); }
 
+// Common body of the decode entry points.  `partial` holds the split records
+// (at least decode_record_bytes(cache) bytes per query row).
 int decode_checked(const gear_cache* cache, const void* q, const void* K_buf, const void* V_buf, int32_t n_buf,
                    int q_len, int causal, void* out, float* partial, void* stream) {
   const gear_config& c = cache->cfg;
@@ -363,44 +393,52 @@ int gear_compress_recent(gear_cache* cache, const void* K, const void* V, int32_
   seg_views(cache, a, seg, n, rank, &ks, &vs);
   const uint16_t* Kp = static_cast<const uint16_t*>(K);
   const uint16_t* Vp = static_cast<const uint16_t*>(V);
-  uint4* maskK = reinterpret_cast<uint4*>(ws + w.maskK);
-  uint4* maskV = reinterpret_cast<uint4*>(ws + w.maskV);
   uint32_t* pool_ctr = reinterpret_cast<uint32_t*>(ws + w.pool_ctr);
+  uint32_t* vsz = reinterpret_cast<uint32_t*>(ws + w.vsz);
+  uint4* maskK = reinterpret_cast<uint4*>(ws + w.mask);
 
   const int kv_k = outlier_count(n, c.outlier_ppm);
   const bool vhead = (c.flags & GEAR_FLAG_V_FILTER_PER_HEAD) != 0;
   const int kv_v = outlier_count(vhead ? D : (long long)c.H_kv * D, c.outlier_ppm);   // per Value vector
+  const int v_top = (kv_v + 1) / 2, v_bot = kv_v / 2;
+  // init_B: [2 (K, V), B, H, 128, rank], or nullptr: the same array is drawn from the seed
+  const uint64_t tensor_entries = (uint64_t)slabs * D * rank;
+  const StartB sbk{init_B, seed, 0}, sbv{init_B ? init_B + tensor_entries : nullptr, seed, tensor_entries};
   // the Key selection kernel also finds a channel's (scale, zero) under the per-vector grouping
   if (c.outlier_ppm > 0 || dm.kcvt) {
     GEAR_HIP(launch_k_select(Kp, dm, n, (kv_k + 1) / 2, kv_k / 2, maskK, pool_ctr, c.B * c.H_kv + c.B, ks,
-                             n > 8192 ? reinterpret_cast<uint16_t*>(ws + w.resid) : nullptr, st));
+                             n > 8192 ? reinterpret_cast<uint16_t*>(ws + w.kt) : nullptr, st));
   }
-  float* Bcur = reinterpret_cast<float*>(ws + w.Bcur);
-  float* partial = reinterpret_cast<float*>(ws + w.partial);
-  float* Atmp = reinterpret_cast<float*>(ws + w.Atmp);
-  float* cmat = reinterpret_cast<float*>(ws + w.cmat);
-  uint32_t* vsz = reinterpret_cast<uint32_t*>(ws + w.vsz);
-  // Quantize (with the Gram matrix of the residual, or leaving Y = X - S in the workspace), then the power iteration; where
-  // that goes one tensor at a time, the Values reuse the Keys' buffers afterwards.
-  float* gram = on_gram ? reinterpret_cast<float*>(ws + w.gram) : nullptr;
-  float* gramV = on_gram ? gram + slabs * nstrips * GRAM_FLOATS : nullptr;
-  uint16_t* resid = rank > 0 && !on_gram ? reinterpret_cast<uint16_t*>(ws + w.resid) : nullptr;
-  uint16_t* residV = resid && paired ? resid + slabs * n * D : resid;
-  // init_B: [2 (K, V), B, H, 128, rank], or nullptr: the same array is drawn from the seed
-  const uint64_t tensor_entries = (uint64_t)slabs * D * rank;
-  const PiTensor pk{Kp, c.outlier_ppm > 0 ? maskK : nullptr, resid, ks, {init_B, seed, 0}};
-  const PiTensor pv{Vp, c.outlier_ppm > 0 ? maskV : nullptr, residV, vs, {init_B ? init_B + tensor_entries : nullptr, seed, tensor_entries}};
-  const int v_top = (kv_v + 1) / 2, v_bot = kv_v / 2;
-  GEAR_HIP(launch_v_select(Vp, dm, n, v_top, v_bot, maskV, vsz, st));
+  // Quantize (with the Gram matrix of the residual, or leaving Y = X - S in the workspace), then the power iteration.
   if (paired) {
-    GEAR_HIP(launch_quant_pair({Kp, ks, maskK, pool_ctr, resid, gram}, {Vp, vs, maskV, pool_ctr + slabs, residV, gramV}, dm, n, t_lr,
-                               v_top, v_bot, vsz, strip, st));
+    uint4* maskV = reinterpret_cast<uint4*>(ws + (on_gram ? w.pair.mask_v : w.tiny.mask_v));
+    float* Bcur = on_gram ? reinterpret_cast<float*>(ws + w.pair.Bcur) : nullptr;
+    float* gram = on_gram ? reinterpret_cast<float*>(ws + w.pair.gram) : nullptr;
+    float* gramV = on_gram ? gram + slabs * nstrips * GRAM_FLOATS : nullptr;
+    uint16_t* YK = on_gram ? nullptr : reinterpret_cast<uint16_t*>(ws + w.tiny.Y);
+    uint16_t* YV = on_gram ? nullptr : YK + slabs * n * D;
+    const PiTensor pk{Kp, c.outlier_ppm > 0 ? maskK : nullptr, YK, ks, sbk};
+    const PiTensor pv{Vp, c.outlier_ppm > 0 ? maskV : nullptr, YV, vs, sbv};
+    GEAR_HIP(launch_v_select(Vp, dm, n, v_top, v_bot, maskV, vsz, st));
+    GEAR_HIP(launch_quant_pair({Kp, ks, maskK, pool_ctr, YK, gram}, {Vp, vs, maskV, pool_ctr + slabs, YV, gramV}, dm, n, t_lr, v_top,
+                               v_bot, vsz, strip, st));
     GEAR_HIP(launch_power_iteration_pair(pk, pv, dm, n, t_lr, iters, Bcur, gram, nstrips, st));
   } else {
-    GEAR_HIP(launch_k_quant(Kp, ks, dm, n, t_lr, maskK, pool_ctr, resid, st));
-    if (rank > 0) GEAR_HIP(launch_power_iteration(true, pk, dm, n, t_lr, iters, Bcur, partial, Atmp, cmat, st));
-    GEAR_HIP(launch_v_quant(Vp, vs, dm, n, t_lr, v_top, v_bot, maskV, vsz, pool_ctr + slabs, residV, st));
-    if (rank > 0) GEAR_HIP(launch_power_iteration(false, pv, dm, n, t_lr, iters, Bcur, partial, Atmp, cmat, st));
+    // the Values reuse the Keys' mask and buffers
+    uint4* maskV = maskK;
+    uint16_t* Y = rank > 0 ? reinterpret_cast<uint16_t*>(ws + w.one.Y) : nullptr;
+    const PiTensor pk{Kp, nullptr, Y, ks, sbk}, pv{Vp, nullptr, Y, vs, sbv};
+    const auto power_iteration = [&](bool is_k) -> hipError_t {
+      if (rank == 0) return hipSuccess;
+      return launch_power_iteration(is_k, is_k ? pk : pv, dm, n, t_lr, iters, reinterpret_cast<float*>(ws + w.one.Bcur),
+                                    reinterpret_cast<float*>(ws + w.one.partial), reinterpret_cast<float*>(ws + w.one.Atmp),
+                                    reinterpret_cast<float*>(ws + w.one.cmat), st);
+    };
+    GEAR_HIP(launch_k_quant(Kp, ks, dm, n, t_lr, maskK, pool_ctr, Y, st));
+    GEAR_HIP(power_iteration(true));
+    GEAR_HIP(launch_v_select(Vp, dm, n, v_top, v_bot, maskV, vsz, st));
+    GEAR_HIP(launch_v_quant(Vp, vs, dm, n, t_lr, v_top, v_bot, maskV, vsz, pool_ctr + slabs, Y, st));
+    GEAR_HIP(power_iteration(false));
   }
 
   if (first) {
@@ -461,7 +499,7 @@ int gear_decode_attn_mq(const gear_cache* cache, const void* q, int32_t q_len, i
   if (!workspace) return GEAR_EINVAL;
   if (!aligned16(workspace)) return GEAR_EALIGN;
   const WorkLayout w = work_layout(c);
-  // the records of all q_len rows; what follows them in the workspace is scratch of gear_compress
+  // the records of all q_len rows; what follows those of one in the workspace is scratch of gear_compress
   if (workspace_bytes < w.bytes || w.dec + decode_record_bytes(cache) * (size_t)q_len > w.bytes) return GEAR_ECAPACITY;
   return decode_checked(cache, q, K_buf, V_buf, n_buf, q_len, causal ? 1 : 0, out,
                         reinterpret_cast<float*>(static_cast<char*>(workspace) + w.dec), stream);
@@ -539,10 +577,9 @@ int gear_export_sparse_coo(const gear_cache* cache, int which, int64_t* nnz, voi
   if (total == 0) return GEAR_OK;
   if (total >= (1ll << 32)) return GEAR_ECAPACITY;
   const size_t rows = (size_t)c.B * c.H_kv * cache->n_total;
-  const size_t need = up(rows * 4) + up(((rows + 1023) / 1024) * 4);
-  if (workspace_bytes < need) return GEAR_ECAPACITY;
+  if (workspace_bytes < coo_bytes(rows)) return GEAR_ECAPACITY;
   uint32_t* rowcnt = static_cast<uint32_t*>(workspace);
-  uint32_t* sums = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + up(rows * 4));
+  uint32_t* sums = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + coo_row_bytes(rows));
   const ArenaLayout a = arena_layout(c);
   const Dims dm = make_dims(c);
   hipStream_t st = static_cast<hipStream_t>(stream);

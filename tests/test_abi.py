@@ -66,6 +66,30 @@ def test_arena_accounting_matches_algorithmic_bytes(lib):
     assert algo + slots <= a <= (algo + slots) * 1.03
 
 
+@pytest.mark.parametrize("B,H_kv,H_q,n,chunks", [
+    (1, 32, 32, 512, 4), (1, 8, 32, 32768, 4), (1, 32, 32, 32768, 1), (16, 32, 32, 4096, 13), (64, 8, 32, 8192, 7), (7, 40, 40, 1777, 1), (1, 8, 8, 16384, 0)])
+def test_workspace_holds_one_solver_at_a_time(lib, B, H_kv, H_q, n, chunks):
+    """The solvers share one region, so the workspace is what the largest of them needs.  Per token row of one tensor that is the
+    one that goes tensor by tensor: mask 16, Y 256, A 32 and partial sums 17 bytes; the one on the Gram matrices has both
+    masks (32) and a 36 KB matrix per tensor and strip, which at 256 tokens a strip comes to the same 320 bytes.  Then the
+    iterates (8 KB per slab) and the decode records."""
+    _, w = gb.gear_cache_bytes(gb.make_config(B, H_kv, H_q, 2, 64, 20000, 20, n, chunks, 8))
+    slabs = B * H_kv
+    records = 520 * B * H_q * (-(-n // 512) + -(-chunks // 4) + 1)
+    assert slabs * n * (16 + 256 + 32 + 17) < w <= slabs * (n + 256) * (16 + 256 + 32 + 17) + 8500 * slabs + records + 4096
+
+
+def test_workspace_is_enough_for_every_entry_point(lib):
+    """Where other calls need more than the solvers: many appended segments behind a short prompt."""
+    for B, H_kv, gq, n, n_b, chunks, rank, ppm in ((1, 2, 1, 257, 20, 256, 1, 20000), (2, 4, 4, 300, 255, 256, 4, 1), (1, 1, 2, 512, 1, 256, 8, 0),
+                                                   (3, 8, 8, 5000, 129, 3, 2, 20000), (1, 64, 1, 300, 40, 0, 8, 500000), (1, 8, 1, 20, 255, 256, 0, 20000)):
+        _, w = gb.gear_cache_bytes(gb.make_config(B, H_kv, H_kv * gq, 2, 64, ppm, n_b, n, chunks, rank))
+        records = 520 * B * H_kv * gq * (-(-n // 512) + -(-chunks * (2 if n_b > 128 else 1) // 4) + 1)
+        assert w >= records * (8 // gq if rank > 0 else 1)                       # gear_decode_attn_mq
+        rows = B * H_kv * (n + chunks * n_b)
+        assert ppm == 0 or w >= 4 * rows + 4 * -(-rows // 1024)                   # gear_export_sparse_coo
+
+
 def test_init_and_call_validation_on_host(lib):
     c = good()
     a, w = gb.gear_cache_bytes(c)
