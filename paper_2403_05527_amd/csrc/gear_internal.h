@@ -96,7 +96,6 @@
 // a store that does not lie wholly inside the view is dropped; non-temporal (data written once, read by a later kernel)
 #define GEAR_BUF_STORE16_NT(b, off, v) \
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(gear::u32x4_t, (v)), (b), (int)(off), 0, 2)
-#define GEAR_BUF_STORE4(b, off, v) __builtin_amdgcn_raw_buffer_store_b32((uint32_t)(v), (b), (int)(off), 0, 0)
 #define GEAR_BUF_STORE2(b, off, v) __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(v), (b), (int)(off), 0, 0)
 #endif
 
@@ -213,29 +212,13 @@ __device__ __forceinline__ uint32_t key16x2(uint32_t h2) {
   const uint32_t x = h2 ^ (s | 0x80008000u);                                                // negative: ~h, positive: h + 0x8000
   return __builtin_bit_cast(uint32_t, __builtin_bit_cast(k16x2_t, x) - __builtin_bit_cast(k16x2_t, s));   // negative: ~h + 1
 }
-// Loads and stores of data that is touched once per kernel and is larger than the
-// caches (non-temporal: the lines are not kept).
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint4 load_stream16(const void* p) {
-  const u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
-  return make_uint4(v.x, v.y, v.z, v.w);
-}
-__device__ __forceinline__ void store_stream16(void* p, uint4 v) {
-  u32x4_t x = {v.x, v.y, v.z, v.w};
-  __builtin_nontemporal_store(x, reinterpret_cast<u32x4_t*>(p));
-}
 // fp16 bit pattern of a key (the key of +-0 gives +0)
 __device__ __forceinline__ uint32_t unkey16(uint32_t k) {
   return (k & 0x8000u) ? (k & 0x7FFFu) : ((0u - k) & 0xFFFFu);
 }
 // two unsigned 16-bit lanes per 32-bit word
 typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b) {
-  return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b)));
-}
-__device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {
-  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b)));
-}
 // min / max of two pairs of fp16 values (-0 < +0; two of them in a row are one three-operand instruction)
 #ifndef GEAR_PK_MIN_F16
 #define GEAR_PK_MIN_F16(a, b) \
@@ -297,8 +280,7 @@ __device__ __forceinline__ ThreshPair pack_thresh(const Thresh& th) {
 // The same predicate on two keys per instruction, by key alone: the halves of top / bot are T - 1 and B, an entry is taken
 // iff key >= T or key < B.  `cut`: among the entries that equal a threshold the index decides (or a bound does not fit
 // 16 bits); the packed test then takes all of them, a superset of S.  2.5 instructions per entry against the 6 of the exact
-// test; with the second histogram level built the same way (high_byte_bits) v_select of 4096-entry rows 253 -> 229 us,
-// k_select on 512 x 128 vectors of 8192 keys 680 -> 650, v_select_rows on 64 x 8192 rows of 1024 entries 525 -> 495.
+// test: with the second histogram level built the same way (high_byte_bits) v_select of 4096-entry rows 253 -> 229 us.
 struct ThreshKeys {
   uint32_t top, bot;
   bool cut;
@@ -311,12 +293,11 @@ __device__ __forceinline__ ThreshKeys key_thresh(const ThreshPair& p) {
   k.cut = ((p.top | p.bot) & 0xFFFFu) != 0u || T == 0u || B > 0xFFFFu;
   return k;
 }
-typedef unsigned short key2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t sub_sat_u16x2(uint32_t a, uint32_t b) {
-  return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(key2_t, a), __builtin_bit_cast(key2_t, b)));
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b)));
 }
 __device__ __forceinline__ uint32_t min_u16x2(uint32_t a, uint32_t b) {
-  return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(key2_t, a), __builtin_bit_cast(key2_t, b)));
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b)));
 }
 // Eight flags (a half of z[j] is 0 or 1: entries 2j, 2j + 1) as the bits of a byte.
 __device__ __forceinline__ uint32_t flag_byte(const uint32_t (&z)[4]) {
@@ -410,10 +391,6 @@ __device__ __forceinline__ GroupQ load_group(uint32_t sz_bits) {
 }
 __device__ __forceinline__ uint32_t group_bits(const GroupQ& q) {
   return f2h(q.delta) | (f2h(q.mn) << 16);
-}
-// Byte 0 of four words in one word (codes and the like read off float mantissas).
-__device__ __forceinline__ uint32_t low_bytes4(uint32_t b0, uint32_t b1, uint32_t b2, uint32_t b3) {
-  return GEAR_BYTE_PERM(GEAR_BYTE_PERM(b3, b2, 0x0c0c0400u), GEAR_BYTE_PERM(b1, b0, 0x0c0c0400u), 0x05040100u);
 }
 __device__ __forceinline__ float clamp_f32(float x, float lo, float hi) { return GEAR_FMED3(x, lo, hi); }
 // Quantization error of one entry (Alg. 1: R = Y - D-hat, D-hat = code * scale + zero) with

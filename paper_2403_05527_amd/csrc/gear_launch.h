@@ -103,7 +103,6 @@ hipError_t launch_power_iteration_pair(const PiTensor& k, const PiTensor& v, con
 hipError_t launch_power_iteration(bool is_k, const PiTensor& x, const Dims& dm, int n, int t_lr, int iters, float* Bcur, float* partial,
                                   float* Atmp, float* cmat, hipStream_t st);
 
-constexpr int DECODE_TS = 256;           // rows per pass of the chunk / buffer path
 constexpr int DECODE_SPLIT = 512;        // prefill tokens per split block
 constexpr int DECODE_REC = 2 + D;        // floats per partial record: m, l, o[128]
 // q: [B, H_q, q_len, 128]; q_len a power of two with (H_q / H) * q_len <= 8; causal: query row j sees the buffer

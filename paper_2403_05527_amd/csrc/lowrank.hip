@@ -241,14 +241,12 @@ __device__ __forceinline__ void pi_update_body(UpdateSmem<R>& sm, int slab, bool
   }
 }
 
+// The last round of a single-round call.
 template <int R>
-__global__ __launch_bounds__(256) void pi_update_kernel(int from_start, StartB sb, int rank,
-                                                        const float* __restrict__ partial, int npart,
-                                                        int do_orth, int final_round,
-                                                        float* __restrict__ Bcur, float* __restrict__ cmat,
-                                                        SegView sv) {
+__global__ __launch_bounds__(256) void pi_update_kernel(const float* __restrict__ partial, int npart, float* __restrict__ Bcur,
+                                                        float* __restrict__ cmat, SegView sv) {
   __shared__ UpdateSmem<R> sm;
-  pi_update_body<R>(sm, blockIdx.x, from_start != 0, sb, rank, partial, npart, do_orth, final_round, Bcur, cmat, sv);
+  pi_update_body<R>(sm, blockIdx.x, false, StartB{nullptr, 0, 0}, sv.rank, partial, npart, 0, 1, Bcur, cmat, sv);
 }
 
 // grid (ceil(n/PT), B*H), block 256; thread (r0 = tid/16, oc = tid%16) owns
@@ -500,13 +498,13 @@ __device__ __forceinline__ void pi_sweep_body(SweepSmem<IS_K, R>& sm, int slab, 
   if (tid < R * R) out[D * R + tid] = LAST ? (redg[0][tid] + redg[1][tid] + redg[2][tid] + redg[3][tid]) : 0.0f;
 }
 
-template <bool IS_K, int R, bool LAST>
+template <bool IS_K, int R>
 __global__ __launch_bounds__(256, (R <= 2 ? 4 : R <= 4 ? 3 : 2)) void pi_sweep_kernel(const uint16_t* __restrict__ Y, SegView sv, int g,
                                                        int bits, int n, int t_lr, const float* __restrict__ Bcur,
                                                        float* __restrict__ partial, int npart,
                                                        float* __restrict__ Atmp) {
   __shared__ SweepSmem<IS_K, R> sm;
-  pi_sweep_body<IS_K, R, LAST>(sm, blockIdx.y, blockIdx.x, Y, sv.sz, sv.codes, sv.n_cap, sv.ng_cap, g, bits, n, t_lr, Bcur, partial,
+  pi_sweep_body<IS_K, R, true>(sm, blockIdx.y, blockIdx.x, Y, sv.sz, sv.codes, sv.n_cap, sv.ng_cap, g, bits, n, t_lr, Bcur, partial,
                                npart, Atmp);
 }
 
@@ -615,9 +613,7 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(float* __restrict__ gram,
   *g = sum;
 }
 
-// B <- G^rounds B0, then the Q factor of its QR (the orthonormalisation of B that opens the last
-// round of Algorithm 2).  grid (B*H), block 128: thread c owns row c of B.  Dynamic LDS: G as
-// [128][129] floats, B as [128][R] doubles.
+// Dynamic LDS of the solve kernel: G as [128][129] floats, B as [128][R] doubles, and small matrices.
 constexpr int GP = D + 1;
 template <int R>
 struct SolveSmem {
@@ -1108,11 +1104,10 @@ static hipError_t run_pi(bool is_k, const PiTensor& x, const Dims& dm, int n, in
                      0, 0, 0, Bcur, 0, x.sv.Bf, x.sv.Bf);
   const dim3 grid(npart, slabs);
   if (is_k)
-    hipLaunchKernelGGL((pi_sweep_kernel<true, R, true>), grid, dim3(256), 0, st, x.Y, x.sv, g, dm.bits, n, t_lr, (const float*)Bcur, partial, npart, Atmp);
+    hipLaunchKernelGGL((pi_sweep_kernel<true, R>), grid, dim3(256), 0, st, x.Y, x.sv, g, dm.bits, n, t_lr, (const float*)Bcur, partial, npart, Atmp);
   else
-    hipLaunchKernelGGL((pi_sweep_kernel<false, R, true>), grid, dim3(256), 0, st, x.Y, x.sv, g, dm.bits, n, t_lr, (const float*)Bcur, partial, npart, Atmp);
-  hipLaunchKernelGGL(pi_update_kernel<R>, dim3(slabs), dim3(256), 0, st, 0, x.sb, x.sv.rank,
-                     (const float*)partial, npart, 0, 1, Bcur, cmat, x.sv);
+    hipLaunchKernelGGL((pi_sweep_kernel<false, R>), grid, dim3(256), 0, st, x.Y, x.sv, g, dm.bits, n, t_lr, (const float*)Bcur, partial, npart, Atmp);
+  hipLaunchKernelGGL(pi_update_kernel<R>, dim3(slabs), dim3(256), 0, st, (const float*)partial, npart, Bcur, cmat, x.sv);
   hipLaunchKernelGGL(pi_finish_kernel<R>, dim3((n + 255) / 256, slabs), dim3(256), 0, st, (const float*)Atmp,
                      (const float*)cmat, x.sv, n);
   return hipGetLastError();
