@@ -8,8 +8,8 @@
 // packed instructions for the extremes and five for the test, against a histogram add in LDS per entry and two scans of 256
 // counters per end in the two-level radix selection (gear_select.h).  That stays as the way out for vectors whose candidates
 // do not fit the list: many entries equal to a threshold, or a ratio close to one entry in two.  Value rows: 64 x 8192 tokens
-// of 1024 entries 504 -> 280 us, 16 x 4096 of 4096 entries 240 -> 134, 32768 of 4096 entries 134 -> 73 (3.7 to 4.0 TB/s; the
-// floor, one read, is a third below); a flushed buffer of 4 x 20 tokens 17 -> 7.
+// of 1024 entries 504 -> 240 us (vector issue 0.86), 16 x 4096 of 4096 entries 240 -> 130, 32768 of 4096 entries 134 -> 70 (3.9 to
+// 4.5 TB/s; the floor is one read); a flushed buffer of 4 x 20 tokens 17 -> 7.
 #pragma once
 #include "gear_internal.h"
 #include "gear_select.h"
@@ -35,7 +35,7 @@ __device__ __forceinline__ RoughBounds rough_bounds(uint32_t tt, uint32_t tb) {
 __device__ __forceinline__ bool rough_usable(uint32_t tt, uint32_t tb) { return tt > 0x0400u && tb > 0x0400u && tt + tb > 0x10000u; }
 // bit j and bit 16 + j of f: the halves of word j (0..15) of a run of words that the clamp changes
 __device__ __forceinline__ uint32_t outside_bits(uint32_t x, const RoughBounds& b, int j) {
-  return min_u16x2(x ^ pk_max_f16(pk_min_f16(x, b.hi), b.lo), 0x00010001u) << j;
+  return nonzero_u16x2(x ^ pk_max_f16(pk_min_f16(x, b.hi), b.lo)) << j;
 }
 // Largest / smallest of the row pieces `w`, added to a running pair (even and odd entries apart).
 __device__ __forceinline__ void extend_extremes(const uint4& v, uint32_t& mx, uint32_t& mn) {
@@ -70,9 +70,45 @@ __device__ __forceinline__ uint32_t wave_kth_largest(const uint32_t (&c)[R], uin
   }
   return x;
 }
+// The same through a histogram of the distances of the keys from the rough threshold (two keys per counter; hist: 256 words of LDS
+// private to the wave): the counter at which k is reached holds one to three entries as a rule, and those too many are dropped
+// one by one.  A chain of some 700 cycles, where the search above takes 10 to 26 dependent steps of 100 to 200: it is what is
+// left for lists whose threshold lies further off, or on a value that many entries share.
+template <int R>
+__device__ __forceinline__ uint32_t wave_kth_by_bins(const uint32_t (&c)[R], uint32_t k, uint32_t rough, uint32_t* hist) {
+  const int lane = lane_id();
+  wave_lds_sync();
+  *reinterpret_cast<uint4*>(hist + 4 * lane) = make_uint4(0u, 0u, 0u, 0u);
+  wave_lds_sync();
+  uint32_t bin[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    bin[i] = 0xFFFFu;   // below the rough threshold, or nothing there
+    if (c[i] >= rough << 16) {
+      bin[i] = min((c[i] >> 16) - rough >> 1, 255u);
+      atomicAdd(&hist[bin[i]], 1u);
+    }
+  }
+  wave_lds_sync();
+  int at;
+  uint32_t above;
+  scan_from_top(hist, k, at, above);
+  const uint32_t spare = (uint32_t)GEAR_WAVE_UNIFORM((int)hist[at]) - (k - above);   // entries of that counter that are too many
+  if (at == 255 || spare > 6u) return wave_kth_largest<R>(c, k, rough);
+  uint32_t x = 0u;
+#pragma unroll 1
+  for (uint32_t i = 0; i <= spare; ++i) {   // the least of the counter's entries above the last one
+    uint32_t m = 0xFFFFFFFFu;
+#pragma unroll
+    for (int r = 0; r < R; ++r) m = min(m, bin[r] == (uint32_t)at && c[r] > x ? c[r] : 0xFFFFFFFFu);
+    m = row16_min_u(m);
+    x = min(min(lane_bcast_u(m, 0), lane_bcast_u(m, 16)), min(lane_bcast_u(m, 32), lane_bcast_u(m, 48)));
+  }
+  return x;
+}
 // list: `total` words (index | fp16 value << 16).  Leaves the selected entries as bits of smask (which may overlap the list).
 template <int R>
-__device__ __forceinline__ void wave_rank_list(const uint32_t* list, uint32_t total, int k_top, int k_bot, uint32_t tt, uint32_t tb,
+__device__ __forceinline__ void wave_rank_list(uint32_t* list, uint32_t total, int k_top, int k_bot, uint32_t tt, uint32_t tb,
                                                uint32_t* smask, int mask_words) {
   const int lane = lane_id();
   uint32_t ct[R], cb[R];   // composites that grow towards the top / the bottom, ties towards the lower index
@@ -86,10 +122,10 @@ __device__ __forceinline__ void wave_rank_list(const uint32_t* list, uint32_t to
       cb[i] = ~c;
     }
   }
+  const uint32_t xt = k_top > 0 ? wave_kth_by_bins<R>(ct, (uint32_t)k_top, tt, list) : 0xFFFFFFFFu;
+  const uint32_t xb = k_bot > 0 ? wave_kth_by_bins<R>(cb, (uint32_t)k_bot, tb, list) : 0xFFFFFFFFu;
   wave_lds_sync();
   for (int i = lane; i < mask_words; i += 64) smask[i] = 0u;
-  const uint32_t xt = k_top > 0 ? wave_kth_largest<R>(ct, (uint32_t)k_top, tt) : 0xFFFFFFFFu;
-  const uint32_t xb = k_bot > 0 ? wave_kth_largest<R>(cb, (uint32_t)k_bot, tb) : 0xFFFFFFFFu;
   wave_lds_sync();
 #pragma unroll
   for (int i = 0; i < R; ++i)
@@ -262,9 +298,9 @@ __device__ __forceinline__ bool row_ext_select(const uint4 (&x)[8], int H, int k
     const uint32_t q = t2 + (0x00010001u << b) - 0x00010001u;   // an entry counts iff it is > q, half by half
     uint32_t n = 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) n += min_u16x2(sub_sat_u16x2(w[i], q), 0x00010001u);
+    for (int i = 0; i < 4; ++i) n += nonzero_u16x2(sub_sat_u16x2(w[i], q));
     n = row16_sum_u(n);
-    t2 += min_u16x2(sub_sat_u16x2(n, km1), 0x00010001u) << b;
+    t2 += nonzero_u16x2(sub_sat_u16x2(n, km1)) << b;
   }
   const uint32_t tt = k_top > 0 ? t2 & 0xFFFFu : 0x10000u, tb = k_bot > 0 ? t2 >> 16 : 0x10000u;
   const RoughBounds rb = rough_bounds(tt, tb);

@@ -50,6 +50,7 @@ inline hipError_t hipGetSymbolAddress(void** p, const void* sym) { *p = const_ca
 #define GEAR_PIN_VGPR(x) asm volatile("" : "+m"(x))
 #define GEAR_SCHED_FENCE() ((void)0)
 #define GEAR_PIN_SGPR(x) asm volatile("" : "+x"(x))
+#define GEAR_OPAQUE_U32(x) ((void)0)
 #define GEAR_PK_MIN_F16(a, b) simt_pk_f16((a), (b), true)
 #define GEAR_PK_MAX_F16(a, b) simt_pk_f16((a), (b), false)
 #define GEAR_LANE_SWAP32(a, b) simt::lane_swap((a), (b), 32)
@@ -292,6 +293,11 @@ inline float atomicAdd(float* p, float v) {
     memcpy(&nw, &g, 4);
   } while (!__atomic_compare_exchange_n(u, &old, nw, false, __ATOMIC_RELAXED, __ATOMIC_RELAXED));
   return f;
+}
+inline uint32_t atomicMax(uint32_t* p, uint32_t v) {
+  uint32_t o = __atomic_load_n(p, __ATOMIC_RELAXED);
+  while (o < v && !__atomic_compare_exchange_n(p, &o, v, false, __ATOMIC_RELAXED, __ATOMIC_RELAXED)) {}
+  return o;
 }
 inline uint32_t atomicOr(uint32_t* p, uint32_t v) { return __atomic_fetch_or(p, v, __ATOMIC_RELAXED); }
 
