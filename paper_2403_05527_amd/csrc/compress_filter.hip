@@ -2,11 +2,15 @@
 // into S, and the launch of the quantization kernel (compress_quant.h).  The result of the Filter is a bit per entry,
 // 16 bytes per token row.
 //   k_select_tiny_kernel   segments of at most 64 tokens (a flushed buffer): one thread per vector
-//   k_select_reg_kernel    up to 8192 tokens: one wave per vector, the vector in registers
-//   k_select_long_kernel   longer: one wave per vector, from a channel-major copy of the keys
+//   k_select_stream_kernel more than 1024 tokens: candidates collected by blocks of 8 or 16 channels, then ranked (gear_select_stream.h)
+//   k_select_reg_kernel    otherwise up to 8192 tokens: one wave per vector, the vector in registers
+//   k_select_long_kernel   otherwise: one wave per vector, from a channel-major copy of the keys
+#include <math.h>
+#include <atomic>
 #include "gear_internal.h"
 #include "gear_select.h"
 #include "gear_launch.h"
+#include "gear_select_stream.h"
 #include "compress_quant.h"
 
 namespace gear {
@@ -18,24 +22,6 @@ struct RegSource {  // the vector lives in the wave's registers
   const uint4* x;
   __device__ __forceinline__ uint4 operator()(int ch) const { return x[ch]; }
 };
-
-// Decodes a 1-D grid of 16 * nslab blocks, one per slab and block of eight channels.  Consecutive block ids go round-robin to
-// the chip's 8 XCDs (each with its own L2), so the id is decoded with the column block fastest INSIDE one XCD: the blocks
-// that share the 128-byte lines of one slab (of its rows, of its mask) then meet in one L2 instead of eight.  The up to
-// seven slabs past a multiple of eight go to all XCDs.  231 slabs x 3000 tokens, which went to all XCDs as a whole before:
-// 245 -> 106 us.
-__device__ __forceinline__ void slab_and_column_block(int nslab, int& slab, int& cb) {
-  constexpr int ncb = D / 8;
-  const int i = blockIdx.x, even = (nslab & ~7) * ncb;
-  if (i < even) {
-    const int xcd = i & 7, j = i >> 3;
-    cb = j % ncb;
-    slab = (j / ncb) * 8 + xcd;
-  } else {
-    cb = i % ncb;
-    slab = i / ncb;
-  }
-}
 
 // A block's eight channels' outlier bits go through LDS as an 8 x 8 bit matrix per eight consecutive tokens, 8 bytes at
 // 8 (t / 8).  Every wave leaves its channel's byte (bit e: token 8 (t / 8) + e), one byte store per chunk and lane; the block
@@ -190,7 +176,7 @@ __global__ __launch_bounds__(512) void k_select_long_kernel(const uint16_t* __re
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < zero_count; i += gridDim.x * blockDim.x) zero[i] = 0u;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   int slab, cb;
-  slab_and_column_block(nslab, slab, cb);
+  slab_and_column_block(nslab, D / 8, slab, cb);
   const int v = slab * D + cb * 8 + wave;   // vector: slab, channel
   const GlobalKeySource src{GEAR_BUF_MAKE(KT + (size_t)v * stride, stride * 2)};
   const Thresh th = wave_select(src, n, k_top, k_bot, hist_all + wave * SELECT_LDS_WORDS, true);
@@ -244,7 +230,7 @@ __global__ __launch_bounds__(512, (NC <= 8 ? 4 : 2)) void k_select_reg_kernel(co
   __shared__ __align__(16) uint32_t stage[8][512];
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < zero_count; i += gridDim.x * blockDim.x) zero[i] = 0u;
   int slab, cb;
-  slab_and_column_block(nslab, slab, cb);
+  slab_and_column_block(nslab, D / 8, slab, cb);
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   // a view of the column block that ends with its last row: rows past n read as 0
   const GEAR_BUF_T xb = GEAR_BUF_MAKE(K + (size_t)slab * n * D + cb * 8, (n - 1) * (D * 2) + 16);
@@ -315,9 +301,44 @@ static hipError_t launch_k_select_reg(const uint16_t* K, const Dims& dm, int n, 
   return hipGetLastError();
 }
 
+template <int PC, int NB, bool ONCE>
+static hipError_t launch_k_select_stream(const uint16_t* K, const Dims& dm, int n, int k_top, int k_bot, const StreamPlan& p, uint4* mask,
+                                         uint32_t* zero, int zero_count, const SegView& sv, hipStream_t st) {
+  static std::atomic<size_t> lds_allowed{0};  // raised once per process and kernel instance (two threads may both raise it: harmless)
+  if (p.lds > lds_allowed.load(std::memory_order_relaxed)) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_select_stream_kernel<PC, NB, ONCE>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
+    if (e != hipSuccess) return e;
+    lds_allowed.store(p.lds, std::memory_order_relaxed);
+  }
+  hipLaunchKernelGGL((k_select_stream_kernel<PC, NB, ONCE>), dim3((D / (8 * PC)) * dm.B * dm.H), dim3(STREAM_THREADS), p.lds, st, K, n, p.L, dm.B * dm.H,
+                     k_top, k_bot, p.j_top, p.j_bot, p.cap, mask, zero, zero_count, dm.kcvt ? sv.sz : (uint32_t*)nullptr, sv.ng_cap,
+                     dm.qmax);
+  return hipGetLastError();
+}
+
 hipError_t launch_k_select(const uint16_t* K, const Dims& dm, int n, int k_top, int k_bot, uint4* mask,
                            uint32_t* zero, int zero_count, const SegView& sv, uint16_t* kt_scratch, hipStream_t st) {
   if (dm.ppm == 0) mask = nullptr;
+  // Lists of candidates, where they fit (a ratio of a few per cent) and the work fills the chip.  A call at rank 0 and 2 %, before
+  // and after: 512 slabs x 8192 tokens 1382 -> 1239 us, 128 x 20000 1184 -> 855, 32 x 32768 514 -> 421, 512 x 4096 630 -> 596, 1280 x 2048
+  // 763 -> 731; 8 x 8192 64 -> 67 and 32 x 2048 42.5 -> 43, hence the bound on the rows.  Up to 1024 tokens the barriers between the phases
+  // of a short vector cost more than its histograms do (512 x 1024: 164 against 178), and at 5 % the lists are so long that it is even
+  // up to 8192 tokens (512 x 8192: 1947 and 1952; 128 x 12000: 893 against 764).
+  StreamPlan p;
+  if (mask && (n > 8192 || (n > 1024 && (long long)dm.B * dm.H * n > 65536))) {
+    const bool rest = dm.kcvt != 0;
+#define GEAR_STREAM(PC, NB, ONCE, LDS)                                                       \
+  do {                                                                                       \
+    if (stream_plan(PC, NB, ONCE, n, k_top, k_bot, rest, LDS, p))                                  \
+      return launch_k_select_stream<PC, NB, ONCE>(K, dm, n, k_top, k_bot, p, mask, zero, zero_count, sv, st); \
+  } while (0)
+    if (n <= 2048) GEAR_STREAM(2, 8, true, 80 * 1024);
+    else if (n <= 4096) GEAR_STREAM(2, 16, true, 80 * 1024);
+    else GEAR_STREAM(2, 8, false, 80 * 1024);
+    GEAR_STREAM(1, 8, false, 160 * 1024);
+#undef GEAR_STREAM
+  }
   // segments of more than 8192 tokens: through a channel-major copy of the keys
   if (n > 8192) {
     const int stride = (n + 7) & ~7;
