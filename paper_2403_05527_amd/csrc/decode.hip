@@ -10,6 +10,8 @@
 // (decode_mfma.h); the last split index handles the appended chunk segments and
 // the fp16 buffer (decode_tail.h).  Every block writes one partial softmax
 // record (m, l, o) per query head; decode_combine merges the records.
+// A cache of few pieces is read by one block per slab instead, in one launch
+// (decode_single_kernel, chosen by single_read).
 #include <atomic>
 #include "gear_internal.h"
 #include "gear_launch.h"
@@ -62,8 +64,62 @@ __global__ __launch_bounds__(256, (GQ == 8 ? 3 : (BITS == 2 && (GQ <= 2 || (GQ =
     tw0 = WTOK * part;
     nw = n_j - tw0;
   }
-  mfma_block<BITS, GQ, LG>(smem_raw, dm, kw_, vw_, qg, slab, b, tw0, nw, k0.rank, v0.rank, rank_cap, odd_rank != 0, split < nsplit,
-                           rec_base, rec_stride);
+  mfma_block<BITS, GQ, LG, false>(smem_raw, dm, kw_, vw_, qg, slab, b, tw0, nw, k0.rank, v0.rank, rank_cap, odd_rank != 0,
+                                  split < nsplit, rec_base, rec_stride, 0, 0, 0);
+}
+
+// The whole read of a slab in one block, for caches of few pieces (single_read): grid (B*H_kv), a wave per 128 prefill tokens,
+// then one per chunk piece, then one per 32 buffer rows.  The states meet in LDS and the block writes the result itself: no
+// records and no second launch.  Bound by one wave's chain of dependent steps and the launch; each wave adds its own zero-point
+// and low-rank terms, so that the merge behind the barrier is one plane read per wave.
+template <int BITS, int GQ, int LG>
+__global__ __launch_bounds__(64 * SINGLE_WAVES<GQ>) void decode_single_kernel(Dims dm, SegView k0, SegView v0, ChunkSet cs,
+                                                                              const uint16_t* __restrict__ q,
+                                                                              const uint16_t* __restrict__ Kbuf,
+                                                                              const uint16_t* __restrict__ Vbuf, int n_buf,
+                                                                              int n_buf_cap, int npw, int ncw, int pp, int rank_cap,
+                                                                              int odd_rank, int q_len, int causal,
+                                                                              uint16_t* __restrict__ out) {
+  GEAR_DYN_LDS(smem_raw);
+  const int slab = blockIdx.x, b = slab / dm.H, h = slab - b * dm.H;
+  const uint16_t* qg = q + ((size_t)b * dm.Hq + h * GQ) * D;
+  const int wave = GEAR_WAVE_UNIFORM((int)(threadIdx.x >> 6)), nthreads = (int)blockDim.x, nwaves = nthreads >> 6;
+  const MfmaLayout L = mfma_layout<GQ>(BITS, 1 << LG, k0.rank, v0.rank, rank_cap, odd_rank != 0, nwaves, ncw);
+  if (wave >= npw + ncw) {
+    buffer_wave<GQ>(smem_raw, L, qg, Kbuf + (size_t)slab * n_buf_cap * D, Vbuf + (size_t)slab * n_buf_cap * D, n_buf,
+                    (wave - npw - ncw) * BUF_WAVE_ROWS, q_len, causal, wave, nthreads);
+  } else {
+    SegView kw_ = k0, vw_ = v0;
+    int tw0 = WTOK * wave, nw = k0.n - tw0;
+    const int item = wave - npw;
+    if (item >= 0) {
+      const int j = pp == 2 ? item >> 1 : item, part = item - j * pp;   // pp is 1 or 2
+      kw_ = chunk_view(cs.k0, cs.stride, j, cs.n[j], cs.rank[j]);
+      vw_ = chunk_view(cs.v0, cs.stride, j, cs.n[j], cs.rank[j]);
+      tw0 = WTOK * part;
+      nw = cs.n[j] - tw0;
+    }
+    mfma_block<BITS, GQ, LG, true>(smem_raw, dm, kw_, vw_, qg, slab, b, tw0, nw, k0.rank, v0.rank, rank_cap, odd_rank != 0, item < 0,
+                                   nullptr, 0, nwaves, ncw, item);
+  }
+  block_lds_sync();
+  const MfmaMisc<GQ, SINGLE_WAVES<GQ>>& M = *reinterpret_cast<const MfmaMisc<GQ, SINGLE_WAVES<GQ>>*>(smem_raw + L.misc);
+  for (int i = threadIdx.x; i < GQ * D; i += nthreads) {
+    const int c = i / GQ, hq = i % GQ;   // the lanes of a wave read consecutive plane entries
+    float Mx = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < SINGLE_WAVES<GQ>; ++w)
+      if (w < nwaves) Mx = fmaxf(Mx, M.wstat[w][hq][0]);
+    float o = 0.0f, l = 0.0f;
+#pragma unroll 4
+    for (int w = 0; w < nwaves; ++w) {
+      const float2 st = *reinterpret_cast<const float2*>(&M.wstat[w][hq][0]);
+      const float f = st.x == -INFINITY ? 0.0f : __expf(st.x - Mx);   // a wave none of whose rows the column sees
+      o += f * reinterpret_cast<const float*>(smem_raw + L.wave0 + (size_t)w * L.wave_stride + L.osp)[i];
+      l += f * st.y;
+    }
+    out[((size_t)b * dm.Hq + h * GQ + hq) * D + c] = (uint16_t)f2h(o / l);
+  }
 }
 
 // grid (B*H_q), block 128: thread c merges channel c of the row's nrec records, 64 records per round.
@@ -129,6 +185,26 @@ __global__ __launch_bounds__(128) void decode_combine_kernel(const float* __rest
   out[(size_t)row * D + c] = (uint16_t)f2h(o / L);
 }
 
+// Whether a read goes through the single-launch kernel: `slabs` blocks of nwaves waves, against slabs * nblocks blocks of four
+// waves and the merge's launch.  The second launch is 3 to 4 us; what the single block costs is that all its waves share one CU's
+// vector issue, which a small batch spreads over several.  So the line is drawn at the waves the fullest CU gets beyond the other
+// kernel's, times what a wave issues (850 vector instructions at one column, 1750 at four).  Measured, split and merge -> single:
+//   32 slabs, 1 column, 512 tokens + 1 chunk 13.5 -> 10.7 us, 900 + 2 13.7 -> 11.0 (4 bits 13.3 -> 12.2), 1400 + 2 13.2 -> 14.5
+//   16 slabs, 2 columns, 512 + 5 chunks 13.4 -> 12.3 (4 bits 13.9 -> 13.6), 1400 + 2 13.3 -> 15.6
+//   8 slabs, 4 columns, 512 + 1 15.7 -> 14.4, 512 + 5 15.3 -> 16.9; at 256 slabs 30.5 -> 18.3; 8 columns, 512 + 1: equal
+// With more than 12 waves a CU holds one block, and its end is not covered by another: it has to have nearly no more waves than
+// the other kernel's CU, and few rounds of blocks (1024 slabs, 1400 + 2 tokens: 41.6 -> 49.6; 512 slabs 27.4 -> 27.2).
+// Beyond 1024 slabs the split kernel's whole blocks of prefill rows are as good (2048 slabs, 4 bits, 512 + 1: 50.1 -> 52.0), but
+// not its nearly empty ones (100 tokens: 39.9 -> 16.8).
+static bool single_read(int nwaves, int max_waves, int slabs, int nblocks, int columns, size_t lds) {
+  constexpr int CUS = 256, LDS_MAX = 160 * 1024;
+  if (nwaves > max_waves || lds > LDS_MAX) return false;
+  if (slabs > 4 * CUS) return nwaves <= 4;
+  const int here = nwaves * ((slabs + CUS - 1) / CUS), split = 4 * ((slabs * nblocks + CUS - 1) / CUS);
+  if (nwaves > 12 && (slabs > 2 * CUS || here > split + 2)) return false;
+  return here - split <= (columns == 1 ? 7 : columns == 2 ? 5 : columns == 4 ? 3 : 1);
+}
+
 template <int BITS, int GQ, int LG>
 static hipError_t launch_decode_t(const Dims& dm, const SegView& k0, const SegView& v0, const ChunkSet& cs,
                                   const uint16_t* q, const uint16_t* Kbuf, const uint16_t* Vbuf, int n_buf,
@@ -144,7 +220,24 @@ static hipError_t launch_decode_t(const Dims& dm, const SegView& k0, const SegVi
   auto one_read = [](int r) { return r == 0 || r == 2 || r == 4 || r == 8; };
   bool odd_rank = !one_read(k0.rank) || !one_read(v0.rank);
   for (int j = 0; j < cs.n_chunks; ++j) odd_rank = odd_rank || !one_read(cs.rank[j]);
-  size_t lds = (size_t)mfma_layout<GQ>(BITS, dm.g, k0.rank, v0.rank, rc, dm.ppm, odd_rank).total;
+  {
+    const int npw = (k0.n + WTOK - 1) / WTOK, ncw = cs.n_chunks * pp, nbw = (n_buf + BUF_WAVE_ROWS - 1) / BUF_WAVE_ROWS;
+    const int nwaves = npw + ncw + nbw;
+    const size_t lds1 = (size_t)mfma_layout<GQ>(BITS, dm.g, k0.rank, v0.rank, rc, odd_rank, nwaves, ncw).total;
+    if (single_read(nwaves, SINGLE_WAVES<GQ>, dm.B * dm.H, nsplit + ncb + 1, GQ, lds1)) {
+      static std::atomic<size_t> allowed{0};
+      if (lds1 > allowed.load(std::memory_order_relaxed)) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_single_kernel<BITS, GQ, LG>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1);
+        if (e != hipSuccess) return e;
+        allowed.store(lds1, std::memory_order_relaxed);
+      }
+      hipLaunchKernelGGL((decode_single_kernel<BITS, GQ, LG>), dim3(dm.B * dm.H), dim3(64 * nwaves), lds1, st, dm, k0, v0, cs, q,
+                         Kbuf, Vbuf, n_buf, n_buf_cap, npw, ncw, pp, rc, odd_rank ? 1 : 0, q_len, causal, out);
+      return hipGetLastError();
+    }
+  }
+  size_t lds = (size_t)mfma_layout<GQ>(BITS, dm.g, k0.rank, v0.rank, rc, odd_rank).total;
   if (lds < sizeof(TailSmem<GQ>)) lds = sizeof(TailSmem<GQ>);
   static std::atomic<size_t> lds_allowed{0};  // raised once per process and kernel instance (two threads may both raise it: harmless)
   if (lds > lds_allowed.load(std::memory_order_relaxed)) {

@@ -178,18 +178,22 @@ constexpr int KOP = D + 8;      // Key-side operand column (fp16)
 __host__ __device__ constexpr int vop(int tb) { return tb + 8; }   // Value-side operand row of a tb-token code block (fp16)
 struct MfmaLayout {
   int q, misc;                                 // shared by the four waves
-  int bf, bf_v0, bf_cw, bf_vc;                 // B factors: one (K, V) pair for the block, or one per wave (chunks)
+  int bf, bf_v0, bf_c, bf_cw, bf_vc;           // B factors: one (K, V) pair for the block, or one per wave (chunks)
   int wave0, wave_stride;                      // per-wave region
   int sc, szv, ak, av, osp, opnd, qb;          // offsets inside a wave region
   int total;
 };
-template <int GQ>
+template <int GQ, int NWV>
 struct MfmaMisc {
-  float wstat[4][GQ][2];   // per wave: m, l
-  float wv[4][GQ][8];      // per wave: p^T A_V
-  float pm[4][GQ][4];      // per wave: sum_t p_t * zero_V[t][G]
-  int rv[4];               // per wave: rank of its Value factors
+  float wstat[NWV][GQ][2];   // per wave: m, l
+  float wv[NWV][GQ][8];      // per wave: p^T A_V
+  float pm[NWV][GQ][4];      // per wave: sum_t p_t * zero_V[t][G]
+  int rv[NWV];               // per wave: rank of its Value factors
 };
+// The single-launch read (decode_single_kernel): one block holds every wave of a slab, up to this many.  A wave with eight
+// query columns needs more than the 128 registers that sixteen waves leave each.
+template <int GQ>
+constexpr int SINGLE_WAVES = GQ == 8 ? 8 : 16;
 __host__ __device__ inline int up16i(int x) { return (x + 15) & ~15; }
 // rk0, rv0: ranks of the prefill segment; rc: largest rank of an appended chunk (0: no chunk
 // blocks in the launch).  The four waves of a prefill block read one copy of B_K and B_V at
@@ -200,21 +204,24 @@ __host__ __device__ inline int up16i(int x) { return (x + 15) & ~15; }
 // (ranks other than 0, 2, 4, 8).
 template <int GQ>
 __host__ __device__ inline bool mfma_rows_in_lds(bool odd_rank) { return GQ < 4 || odd_rank; }
+// nwaves, ncw (the single-launch read only, 0 otherwise): the block's waves and those among them that hold a chunk piece; the
+// prefill waves share one pair of B factors at bf, and the i-th chunk wave keeps its pair at bf_c + i * bf_cw.
 template <int GQ>
-__host__ __device__ inline MfmaLayout mfma_layout(int bits, int g, int rk0, int rv0, int rc, int ppm, bool odd_rank) {
+__host__ __device__ inline MfmaLayout mfma_layout(int bits, int g, int rk0, int rv0, int rc, bool odd_rank, int nwaves = 0, int ncw = 0) {
   MfmaLayout L;
   const int TB = bits == 2 ? 64 : 32, lg = g >= 128 ? 7 : g >= 64 ? 6 : 5, NG = D >> lg;   // g is 32, 64 or 128
   const int rk = rk0 > rc ? rk0 : rc, rv = rv0 > rc ? rv0 : rc;
   int o = 0;
   L.q = o; o += GQ * D * 4;
-  L.misc = o; o += up16i((int)sizeof(MfmaMisc<GQ>));
+  L.misc = o; o += up16i((int)(nwaves ? sizeof(MfmaMisc<GQ, SINGLE_WAVES<GQ>>) : sizeof(MfmaMisc<GQ, 4>)));
   L.bf = o;
   L.bf_v0 = up16i(D * rk0 * 2);
   L.bf_vc = up16i(D * rc * 2);
   L.bf_cw = 2 * L.bf_vc;
   {
     const int shared = L.bf_v0 + up16i(D * rv0 * 2), per_wave = 4 * L.bf_cw;
-    o += shared > per_wave ? shared : per_wave;
+    L.bf_c = o + shared;
+    o += nwaves ? shared + ncw * L.bf_cw : shared > per_wave ? shared : per_wave;
   }
   L.wave0 = o;
   int w = 0;
@@ -228,7 +235,7 @@ __host__ __device__ inline MfmaLayout mfma_layout(int bits, int g, int rk0, int 
   L.osp = L.opnd;   // the output plane (GQ * 128 floats <= the operand area) is written after the last operand was read
   L.qb = w; w += GQ * 8 * 4;
   L.wave_stride = up16i(w);
-  L.total = L.wave0 + 4 * L.wave_stride;
+  L.total = L.wave0 + (nwaves ? nwaves : 4) * L.wave_stride;
   return L;
 }
 
@@ -365,11 +372,13 @@ __device__ __forceinline__ uint4 load_factor_row(GEAR_BUF_T view, int row, int r
 // the block's merged partial softmax record (m, l, o[128]) of each of the GQ query
 // heads.  rk0 / rv0 / rc size the LDS layout (see mfma_layout); shared_b: the four waves
 // read the same segment (a prefill block), so its B factors are staged once.
-template <int BITS, int GQ, int LG>
+// SINGLE (the single-launch read): the wave leaves its whole state, the low-rank and zero-point terms included, in its output
+// plane and wstat; nothing is merged or written here.  ncw: the block's chunk waves, ci: this wave's number among them.
+template <int BITS, int GQ, int LG, bool SINGLE>
 __device__ void mfma_block(unsigned char* smem, const Dims& dm, const SegView& ks, const SegView& vs,
                            const uint16_t* __restrict__ qg /* q of query head h*GQ of batch b */, int slab, int b,
                            int tw0, int nw, int rk0, int rv0, int rc, bool odd_rank, bool shared_b,
-                           float* __restrict__ rec_base, int rec_stride) {
+                           float* __restrict__ rec_base, int rec_stride, int nwaves, int ncw, int ci) {
   constexpr int TB = (BITS == 2) ? 64 : 32;   // tokens per Value code block
   constexpr int KW = (BITS == 2) ? 2 : 4;     // Key code words per lane per M-tile
   constexpr int VBLK = WTOK / TB;             // Value blocks per wave
@@ -377,17 +386,19 @@ __device__ void mfma_block(unsigned char* smem, const Dims& dm, const SegView& k
   const int n16 = lane & 15, kg = lane >> 4;
   constexpr int g = 1 << LG, lg = LG, NG = D >> LG;   // the group size (32, 64 or 128) is a template parameter: group loops unroll
   const int rk = ks.rank, rv = vs.rank;
-  const MfmaLayout L = mfma_layout<GQ>(BITS, g, rk0, rv0, rc, dm.ppm, odd_rank);
+  const MfmaLayout L = mfma_layout<GQ>(BITS, g, rk0, rv0, rc, odd_rank, SINGLE ? nwaves : 0, SINGLE ? ncw : 0);
+  constexpr int NWV = SINGLE ? SINGLE_WAVES<GQ> : 4;
+  const int nthreads = SINGLE ? 64 * nwaves : 256;
   const bool rows_lds = mfma_rows_in_lds<GQ>(odd_rank);   // compile-time true for fewer than four query heads
   float* Sq = reinterpret_cast<float*>(smem + L.q);                 // [128][GQ]
-  MfmaMisc<GQ>& M = *reinterpret_cast<MfmaMisc<GQ>*>(smem + L.misc);
+  MfmaMisc<GQ, NWV>& M = *reinterpret_cast<MfmaMisc<GQ, NWV>*>(smem + L.misc);
   unsigned char* wbase = smem + L.wave0 + (size_t)wave * L.wave_stride;
   float* Ssc = reinterpret_cast<float*>(wbase + L.sc);              // [128][GQ] raw scores, then p
   uint32_t* Sszv = reinterpret_cast<uint32_t*>(wbase + L.szv);      // [128][NG]
   uint16_t* Sak = reinterpret_cast<uint16_t*>(wbase + L.ak);        // [128][rk]
   uint16_t* Sav = reinterpret_cast<uint16_t*>(wbase + L.av);
-  uint16_t* Sbfk = reinterpret_cast<uint16_t*>(smem + L.bf + (shared_b ? 0 : wave * L.bf_cw));   // [128][rk]
-  uint16_t* Sbfv = reinterpret_cast<uint16_t*>(smem + L.bf + (shared_b ? L.bf_v0 : wave * L.bf_cw + L.bf_vc));
+  uint16_t* Sbfk = reinterpret_cast<uint16_t*>(smem + (SINGLE && !shared_b ? L.bf_c + ci * L.bf_cw : L.bf + (shared_b ? 0 : wave * L.bf_cw)));   // [128][rk]
+  uint16_t* Sbfv = reinterpret_cast<uint16_t*>(smem + (SINGLE && !shared_b ? L.bf_c + ci * L.bf_cw + L.bf_vc : L.bf + (shared_b ? L.bf_v0 : wave * L.bf_cw + L.bf_vc)));
   float* Sosp = reinterpret_cast<float*>(wbase + L.osp);            // [128][GQ] this wave's output plane (shares the operand area)
   _Float16* opnd = reinterpret_cast<_Float16*>(wbase + L.opnd);
   float* SqB = reinterpret_cast<float*>(wbase + L.qb);              // [GQ][8] q^T B_K
@@ -426,10 +437,10 @@ __device__ void mfma_block(unsigned char* smem, const Dims& dm, const SegView& k
   // into registers (16 bytes per lane and request), LDS writes afterwards, so that all
   // of them are in flight together.  The arena keeps these arrays 16-byte aligned per
   // slab and padded, so whole 16-byte pieces may be read past the wave's last row.
-  uint32_t qreg[2];
+  uint32_t qreg[SINGLE ? GQ : 2];
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int i = tid + 256 * k;
+  for (int k = 0; k < (SINGLE ? GQ : 2); ++k) {
+    const int i = tid + nthreads * k;
     qreg[k] = 0u;
     if (i < GQ * D / 2) qreg[k] = reinterpret_cast<const uint32_t*>(qg)[i];
   }
@@ -505,8 +516,8 @@ __device__ void mfma_block(unsigned char* smem, const Dims& dm, const SegView& k
   }
   // everything is requested; now the LDS writes
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int i = tid + 256 * k;
+  for (int k = 0; k < (SINGLE ? GQ : 2); ++k) {
+    const int i = tid + nthreads * k;
     if (i < GQ * D / 2) {   // channels c, c + 1 of query head hq
       const int hq = i / (D / 2), c = 2 * (i % (D / 2));
       Sq[c * GQ + hq] = h2f(qreg[k] & 0xFFFFu);
@@ -997,6 +1008,41 @@ __device__ void mfma_block(unsigned char* smem, const Dims& dm, const SegView& k
     }
     wave_lds_sync();
   }
+  if constexpr (SINGLE) {
+    // the zero-point and low-rank terms of the lane's channels, into the plane
+#pragma unroll
+    for (int rep = 0; rep < 2; ++rep) {
+      const int c = lane + 64 * rep;
+      float oh[GQ], bb[8];
+      lds_load_f<GQ>(Sosp + c * GQ, oh);
+#pragma unroll
+      for (int r = 0; r < 8; ++r) bb[r] = 0.0f;
+      if (nw > 0) {   // (a wave without rows has staged no factors)
+        if (rv == 4) lds_row_f16<4>(Sbfv + c * 4, bb);
+        else if (rv == 2) lds_row_f16<2>(Sbfv + c * 2, bb);
+        else if (rv == 8) lds_row_f16<8>(Sbfv + c * 8, bb);
+        else {
+#pragma unroll
+          for (int r = 0; r < 8; ++r)
+            if (r < rv) bb[r] = h2f(Sbfv[c * rv + r]);
+        }
+      }
+#pragma unroll
+      for (int hq = 0; hq < GQ; ++hq) {
+        const float* wv = &M.wv[wave][hq][0];   // 0 from entry rv on
+        float o = oh[hq] + M.pm[wave][hq][c >> lg];
+        const float4 a = *reinterpret_cast<const float4*>(wv);
+        o += a.x * bb[0] + a.y * bb[1] + a.z * bb[2] + a.w * bb[3];
+        if (rv > 4) {
+          const float4 a1 = *reinterpret_cast<const float4*>(wv + 4);
+          o += a1.x * bb[4] + a1.y * bb[5] + a1.z * bb[6] + a1.w * bb[7];
+        }
+        oh[hq] = o;
+      }
+      lds_store_f<GQ>(Sosp + c * GQ, oh);
+    }
+    return;
+  } else {
   block_lds_sync();
 
   // =================== merge the four waves' states, write the record ===================
@@ -1085,6 +1131,7 @@ __device__ void mfma_block(unsigned char* smem, const Dims& dm, const SegView& k
       rec[0] = Mx;
       rec[1] = l;
     }
+  }
   }
 }
 

@@ -5,6 +5,7 @@
 #pragma once
 #include "gear_internal.h"
 #include "gear_launch.h"
+#include "decode_mfma.h"
 
 namespace gear {
 
@@ -152,6 +153,109 @@ __device__ __forceinline__ void buffer_block(TailSmem<GQ>& S, const uint16_t* __
       rec[1] = S.red[hq][0] + S.red[hq][1] + S.red[hq][2] + S.red[hq][3];
     }
   }
+}
+
+// One wave of the single-launch read: buffer rows [r0, r0 + BUF_WAVE_ROWS), everything it reads requested before it waits.
+// Leaves the state like mfma_block<SINGLE>: the output plane in the wave's LDS region, (m, l) in wstat.  Joins the block's one
+// barrier in front of the merge's (q in LDS), as every other wave does.
+constexpr int BUF_WAVE_ROWS = 32;
+template <int GQ>
+__device__ __forceinline__ void buffer_wave(unsigned char* smem, const MfmaLayout& L, const uint16_t* __restrict__ qg,
+                                            const uint16_t* __restrict__ Kb, const uint16_t* __restrict__ Vb, int n_buf, int r0,
+                                            int q_len, int causal, int wave, int nthreads) {
+  const int tid = threadIdx.x, lane = tid & 63, row4 = lane >> 4, piece = lane & 15;
+  float* Sq = reinterpret_cast<float*>(smem + L.q);                 // [128][GQ]
+  MfmaMisc<GQ, SINGLE_WAVES<GQ>>& M = *reinterpret_cast<MfmaMisc<GQ, SINGLE_WAVES<GQ>>*>(smem + L.misc);
+  unsigned char* wbase = smem + L.wave0 + (size_t)wave * L.wave_stride;
+  float* Ssc = reinterpret_cast<float*>(wbase + L.sc);              // [32][GQ]
+  float* Sosp = reinterpret_cast<float*>(wbase + L.osp);            // [128][GQ]
+  const float scale = 0.08838834764831845f;  // 1/sqrt(128)
+  uint32_t qreg[GQ];
+#pragma unroll
+  for (int k = 0; k < GQ; ++k) {   // the block's waves share the staging of q
+    const int i = tid + nthreads * k;
+    qreg[k] = 0u;
+    if (i < GQ * D / 2) qreg[k] = reinterpret_cast<const uint32_t*>(qg)[i];
+  }
+  // Keys: the 16 lanes of a row take a 16-byte piece each, four rows per request.  Values: the lane takes channels 2 lane and
+  // 2 lane + 1 of every row.  Rows past the buffer's last read as 0.
+  const int rows = n_buf - r0 < BUF_WAVE_ROWS ? n_buf - r0 : BUF_WAVE_ROWS;
+  const GEAR_BUF_T kview = GEAR_BUF_MAKE(Kb + (size_t)r0 * D, rows * D * 2), vview = GEAR_BUF_MAKE(Vb + (size_t)r0 * D, rows * D * 2);
+  uint4 kv[BUF_WAVE_ROWS / 4];
+  uint32_t vv[BUF_WAVE_ROWS];
+#pragma unroll
+  for (int i = 0; i < BUF_WAVE_ROWS / 4; ++i) kv[i] = GEAR_BUF_LOAD16(kview, (4 * i + row4) * (D * 2) + piece * 16);
+#pragma unroll
+  for (int k = 0; k < BUF_WAVE_ROWS; ++k) vv[k] = GEAR_BUF_LOAD4(vview, k * (D * 2) + lane * 4);
+#pragma unroll
+  for (int k = 0; k < GQ; ++k) {
+    const int i = tid + nthreads * k;
+    if (i < GQ * D / 2) {   // channels c, c + 1 of query column hq
+      const int hq = i / (D / 2), c = 2 * (i % (D / 2));
+      Sq[c * GQ + hq] = h2f(qreg[k] & 0xFFFFu);
+      Sq[(c + 1) * GQ + hq] = h2f(qreg[k] >> 16);
+    }
+  }
+  block_lds_sync();
+  float qf[8 * GQ];   // [channel of the piece][column]
+#pragma unroll
+  for (int i = 0; i < 8 * GQ; i += 4) {
+    const float4 t = *reinterpret_cast<const float4*>(Sq + piece * 8 * GQ + i);
+    qf[i] = t.x; qf[i + 1] = t.y; qf[i + 2] = t.z; qf[i + 3] = t.w;
+  }
+#pragma unroll
+  for (int i = 0; i < BUF_WAVE_ROWS / 4; ++i) {
+    const uint32_t w[4] = {kv[i].x, kv[i].y, kv[i].z, kv[i].w};
+    float p[GQ];
+#pragma unroll
+    for (int hq = 0; hq < GQ; ++hq) p[hq] = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float kf = h2f((w[e >> 1] >> ((e & 1) * 16)) & 0xFFFFu);
+#pragma unroll
+      for (int hq = 0; hq < GQ; ++hq) p[hq] += qf[e * GQ + hq] * kf;
+    }
+#pragma unroll
+    for (int hq = 0; hq < GQ; ++hq) p[hq] = row16_sum(p[hq]);
+    if (piece == 0) lds_store_f<GQ>(Ssc + (4 * i + row4) * GQ, p);
+  }
+  wave_lds_sync();
+  // softmax over the wave's rows: lane = row
+  float s[GQ];
+#pragma unroll
+  for (int hq = 0; hq < GQ; ++hq) s[hq] = 0.0f;
+  if (lane < BUF_WAVE_ROWS) lds_load_f<GQ>(Ssc + lane * GQ, s);
+#pragma unroll
+  for (int hq = 0; hq < GQ; ++hq) {
+    const int seen = causal ? n_buf - q_len + 1 + (hq & (q_len - 1)) : n_buf;   // q_len is a power of two
+    const bool live = lane < BUF_WAVE_ROWS && r0 + lane < seen;
+    const float v = live ? s[hq] * scale : -INFINITY;
+    const float m = wave_max(v);
+    s[hq] = live ? __expf(v - m) : 0.0f;
+    const float l = wave_sum(s[hq]);
+    if (lane == 0) {
+      M.wstat[wave][hq][0] = m;   // -inf when the column sees none of the wave's rows
+      M.wstat[wave][hq][1] = l;
+    }
+  }
+  if (lane < BUF_WAVE_ROWS) lds_store_f<GQ>(Ssc + lane * GQ, s);
+  wave_lds_sync();
+  float o0[GQ], o1[GQ];
+#pragma unroll
+  for (int hq = 0; hq < GQ; ++hq) o0[hq] = o1[hq] = 0.0f;
+#pragma unroll
+  for (int k = 0; k < BUF_WAVE_ROWS; ++k) {
+    const float a = h2f(vv[k] & 0xFFFFu), b = h2f(vv[k] >> 16);
+    float p[GQ];
+    lds_load_f<GQ>(Ssc + k * GQ, p);
+#pragma unroll
+    for (int hq = 0; hq < GQ; ++hq) {
+      o0[hq] += p[hq] * a;
+      o1[hq] += p[hq] * b;
+    }
+  }
+  lds_store_f<GQ>(Sosp + 2 * lane * GQ, o0);
+  lds_store_f<GQ>(Sosp + (2 * lane + 1) * GQ, o1);
 }
 
 }  // namespace gear
