@@ -22,7 +22,8 @@ namespace gear {
 
 static_assert(MFMA_TS == DECODE_SPLIT, "split size is part of the workspace layout");
 
-// grid (nsplit + ncb + 1, B*H_kv), block 256.  Blocks [0, nsplit): 512 prefill tokens each;
+// grid (nsplit + ncb + 1, B*H_kv << lparts), block 256: a slab's query columns are shared by 2^lparts blocks, GQ
+// columns each (column_parts).  Blocks [0, nsplit): 512 prefill tokens each;
 // blocks [nsplit, nsplit + ncb): four pieces of appended chunks each (one piece = up to 128
 // rows of one chunk, pp pieces per chunk), through the same code as the prefill; the
 // last block: the fp16 streaming-buffer rows.
@@ -32,19 +33,20 @@ __global__ __launch_bounds__(256, (GQ == 8 ? 3 : (BITS == 2 && (GQ <= 2 || (GQ =
                                                               const uint16_t* __restrict__ Kbuf,
                                                               const uint16_t* __restrict__ Vbuf, int n_buf,
                                                               int n_buf_cap, int nsplit, int pp, int rank_cap,
-                                                              int odd_rank, int q_len, int causal,
+                                                              int odd_rank, int q_len, int causal, int lparts,
                                                               float* __restrict__ partial) {
   GEAR_DYN_LDS(smem_raw);
-  const int slab = blockIdx.y, split = blockIdx.x;
+  const int slab = blockIdx.y >> lparts, split = blockIdx.x;
   const int nrec = (int)gridDim.x;
-  const int b = slab / dm.H, h = slab - b * dm.H;
-  float* rec_base = partial + (((size_t)b * dm.Hq + h * GQ) * nrec + split) * DECODE_REC;
+  const int b = slab / dm.H;
+  const int row0 = (int)blockIdx.y * GQ;   // the block's first query row: the columns of a slab, and the slabs, lie in a row
+  float* rec_base = partial + ((size_t)row0 * nrec + split) * DECODE_REC;
   const int rec_stride = nrec * DECODE_REC;
-  const uint16_t* qg = q + ((size_t)b * dm.Hq + h * GQ) * D;
+  const uint16_t* qg = q + (size_t)row0 * D;
   const int wave = GEAR_WAVE_UNIFORM((int)(threadIdx.x >> 6));
   if (split == nrec - 1) {
     buffer_block<GQ>(*reinterpret_cast<TailSmem<GQ>*>(smem_raw), qg, Kbuf + (size_t)slab * n_buf_cap * D,
-                     Vbuf + (size_t)slab * n_buf_cap * D, n_buf, q_len, causal, rec_base, rec_stride);
+                     Vbuf + (size_t)slab * n_buf_cap * D, n_buf, q_len, causal, row0, rec_base, rec_stride);
     return;
   }
   // one call site: the prefill segment for every wave, or one chunk piece per wave
@@ -68,9 +70,9 @@ __global__ __launch_bounds__(256, (GQ == 8 ? 3 : (BITS == 2 && (GQ <= 2 || (GQ =
                                   split < nsplit, rec_base, rec_stride, 0, 0, 0);
 }
 
-// The whole read of a slab in one block, for caches of few pieces (single_read): grid (B*H_kv), a wave per 128 prefill tokens,
-// then one per chunk piece, then one per 32 buffer rows.  The states meet in LDS and the block writes the result itself: no
-// records and no second launch.  Bound by one wave's chain of dependent steps and the launch; each wave adds its own zero-point
+// The whole read of a slab (or of a part of its query columns) in one block, for caches of few pieces (single_read): grid
+// (B*H_kv << lparts), a wave per 128 prefill tokens, then one per chunk piece, then one per 32 buffer rows.  The states meet in
+// LDS and the block writes the result itself: no records and no second launch.  Bound by one wave's chain of dependent steps and the launch; each wave adds its own zero-point
 // and low-rank terms, so that the merge behind the barrier is one plane read per wave.
 template <int BITS, int GQ, int LG>
 __global__ __launch_bounds__(64 * SINGLE_WAVES<GQ>) void decode_single_kernel(Dims dm, SegView k0, SegView v0, ChunkSet cs,
@@ -78,16 +80,17 @@ __global__ __launch_bounds__(64 * SINGLE_WAVES<GQ>) void decode_single_kernel(Di
                                                                               const uint16_t* __restrict__ Kbuf,
                                                                               const uint16_t* __restrict__ Vbuf, int n_buf,
                                                                               int n_buf_cap, int npw, int ncw, int pp, int rank_cap,
-                                                                              int odd_rank, int q_len, int causal,
+                                                                              int odd_rank, int q_len, int causal, int lparts,
                                                                               uint16_t* __restrict__ out) {
   GEAR_DYN_LDS(smem_raw);
-  const int slab = blockIdx.x, b = slab / dm.H, h = slab - b * dm.H;
-  const uint16_t* qg = q + ((size_t)b * dm.Hq + h * GQ) * D;
+  const int slab = blockIdx.x >> lparts, b = slab / dm.H;
+  const int row0 = (int)blockIdx.x * GQ;   // the block's first query row
+  const uint16_t* qg = q + (size_t)row0 * D;
   const int wave = GEAR_WAVE_UNIFORM((int)(threadIdx.x >> 6)), nthreads = (int)blockDim.x, nwaves = nthreads >> 6;
   const MfmaLayout L = mfma_layout<GQ>(BITS, 1 << LG, k0.rank, v0.rank, rank_cap, odd_rank != 0, nwaves, ncw);
   if (wave >= npw + ncw) {
     buffer_wave<GQ>(smem_raw, L, qg, Kbuf + (size_t)slab * n_buf_cap * D, Vbuf + (size_t)slab * n_buf_cap * D, n_buf,
-                    (wave - npw - ncw) * BUF_WAVE_ROWS, q_len, causal, wave, nthreads);
+                    (wave - npw - ncw) * BUF_WAVE_ROWS, q_len, causal, row0, wave, nthreads);
   } else {
     SegView kw_ = k0, vw_ = v0;
     int tw0 = WTOK * wave, nw = k0.n - tw0;
@@ -118,7 +121,7 @@ __global__ __launch_bounds__(64 * SINGLE_WAVES<GQ>) void decode_single_kernel(Di
       o += f * reinterpret_cast<const float*>(smem_raw + L.wave0 + (size_t)w * L.wave_stride + L.osp)[i];
       l += f * st.y;
     }
-    out[((size_t)b * dm.Hq + h * GQ + hq) * D + c] = (uint16_t)f2h(o / l);
+    out[((size_t)row0 + hq) * D + c] = (uint16_t)f2h(o / l);
   }
 }
 
@@ -185,6 +188,8 @@ __global__ __launch_bounds__(128) void decode_combine_kernel(const float* __rest
   out[(size_t)row * D + c] = (uint16_t)f2h(o / L);
 }
 
+constexpr int CUS = 256;
+
 // Whether a read goes through the single-launch kernel: `slabs` blocks of nwaves waves, against slabs * nblocks blocks of four
 // waves and the merge's launch.  The second launch is 3 to 4 us; what the single block costs is that all its waves share one CU's
 // vector issue, which a small batch spreads over several.  So the line is drawn at the waves the fullest CU gets beyond the other
@@ -197,7 +202,7 @@ __global__ __launch_bounds__(128) void decode_combine_kernel(const float* __rest
 // Beyond 1024 slabs the split kernel's whole blocks of prefill rows are as good (2048 slabs, 4 bits, 512 + 1: 50.1 -> 52.0), but
 // not its nearly empty ones (100 tokens: 39.9 -> 16.8).
 static bool single_read(int nwaves, int max_waves, int slabs, int nblocks, int columns, size_t lds) {
-  constexpr int CUS = 256, LDS_MAX = 160 * 1024;
+  constexpr int LDS_MAX = 160 * 1024;
   if (nwaves > max_waves || lds > LDS_MAX) return false;
   if (slabs > 4 * CUS) return nwaves <= 4;
   const int here = nwaves * ((slabs + CUS - 1) / CUS), split = 4 * ((slabs * nblocks + CUS - 1) / CUS);
@@ -205,11 +210,50 @@ static bool single_read(int nwaves, int max_waves, int slabs, int nblocks, int c
   return here - split <= (columns == 1 ? 7 : columns == 2 ? 5 : columns == 4 ? 3 : 1);
 }
 
+// How many blocks share the query columns of a slab: 2^result of them, with columns >> result each.  Fewer columns per wave make
+// the wave's chain of steps shorter and the codes are unpacked once per part, so a small grid is read faster by more parts and a
+// large one by fewer.  The times are a model of measured ones, in microseconds: a lone block on a CU takes `first`, each further
+// one adds `more` (beyond three blocks of eight columns, which is what a CU holds, a quarter as much again); a single-launch read
+// takes `base` and `wave` for each wave of the fullest CU, `least` at the least.  Over 492 sizes (1 to 64 batch elements, 100 to
+// 20000 tokens, 2 to 8 columns) the choice is within 1 % of the best one on average and 26 % faster than whole slabs.  Whole -> parts:
+// 5 x 8 heads x 3001 tokens, eight columns 29.9 -> 24.1 us (2 parts); 1 x 8 heads x 3001 21.5 -> 12.4 (4); 16 x 8 heads x 8192 97.7
+// -> 90.9 (2); four columns, 1 x 8 heads x 8192 16.2 -> 15.0 (2), 64 x 8 heads x 1700 61.7 against 67.4 (whole).  A part has to
+// promise 4 % a step.
+static int column_parts(int bits, int columns, int slabs, int nblocks, int nwaves) {
+  struct Cost { float first, more, least, base, wave; };
+  static const Cost costs[2][4] = {   // one, two, four, eight columns
+      {{11.8f, 1.9f, 10.0f, 3.0f, 0.75f}, {12.0f, 3.1f, 10.0f, 4.0f, 1.0f}, {15.6f, 4.75f, 12.0f, 3.0f, 1.7f}, {22.0f, 8.3f, 17.0f, 0.0f, 3.6f}},
+      {{12.3f, 2.5f, 10.0f, 2.0f, 1.05f}, {13.6f, 4.3f, 10.5f, 3.0f, 1.4f}, {17.8f, 5.8f, 14.0f, 3.0f, 2.1f}, {25.8f, 10.0f, 21.0f, 0.0f, 4.3f}}};
+  float best = 0.0f;
+  int pick = 0;
+  for (int p = 0; (columns >> p) > 0; ++p) {
+    const int c = columns >> p, lc = c == 8 ? 3 : c >> 1;
+    const long long blocks = (long long)slabs << p;
+    if (blocks > 65535) break;   // a dimension of the grid
+    const Cost& t = costs[bits == 4 ? 1 : 0][lc];
+    float us;
+    if (single_read(nwaves, c == 8 ? SINGLE_WAVES<8> : SINGLE_WAVES<1>, (int)blocks, nblocks, c, 0)) {
+      us = t.base + t.wave * (float)(nwaves * ((blocks + CUS - 1) / CUS));
+      us = us < t.least ? t.least : us;
+    } else {
+      const long long k = (blocks * nblocks + CUS - 1) / CUS;
+      us = t.first + t.more * (float)(k - 1) + (c == 8 && k > 3 ? 0.25f * t.more * (float)(k - 3) : 0.0f);
+    }
+    us *= 1.0f + 0.04f * (float)p;
+    if (p == 0 || us < best) {
+      best = us;
+      pick = p;
+    }
+  }
+  return pick;
+}
+
 template <int BITS, int GQ, int LG>
 static hipError_t launch_decode_t(const Dims& dm, const SegView& k0, const SegView& v0, const ChunkSet& cs,
                                   const uint16_t* q, const uint16_t* Kbuf, const uint16_t* Vbuf, int n_buf,
-                                  int n_buf_cap, int rank_cap, int q_len, int causal, uint16_t* out, float* partial,
+                                  int n_buf_cap, int rank_cap, int q_len, int causal, int lparts, uint16_t* out, float* partial,
                                   hipStream_t st) {
+  const int blocks = (dm.B * dm.H) << lparts;         // per 512 tokens: a block for each slab and part of its columns
   const int nsplit = (k0.n + MFMA_TS - 1) / MFMA_TS;
   const int pp = n_buf_cap > WTOK ? 2 : 1;            // pieces per chunk
   const int ncb = (cs.n_chunks * pp + 3) / 4;
@@ -224,7 +268,7 @@ static hipError_t launch_decode_t(const Dims& dm, const SegView& k0, const SegVi
     const int npw = (k0.n + WTOK - 1) / WTOK, ncw = cs.n_chunks * pp, nbw = (n_buf + BUF_WAVE_ROWS - 1) / BUF_WAVE_ROWS;
     const int nwaves = npw + ncw + nbw;
     const size_t lds1 = (size_t)mfma_layout<GQ>(BITS, dm.g, k0.rank, v0.rank, rc, odd_rank, nwaves, ncw).total;
-    if (single_read(nwaves, SINGLE_WAVES<GQ>, dm.B * dm.H, nsplit + ncb + 1, GQ, lds1)) {
+    if (single_read(nwaves, SINGLE_WAVES<GQ>, blocks, nsplit + ncb + 1, GQ, lds1)) {
       static std::atomic<size_t> allowed{0};
       if (lds1 > allowed.load(std::memory_order_relaxed)) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_single_kernel<BITS, GQ, LG>),
@@ -232,8 +276,8 @@ static hipError_t launch_decode_t(const Dims& dm, const SegView& k0, const SegVi
         if (e != hipSuccess) return e;
         allowed.store(lds1, std::memory_order_relaxed);
       }
-      hipLaunchKernelGGL((decode_single_kernel<BITS, GQ, LG>), dim3(dm.B * dm.H), dim3(64 * nwaves), lds1, st, dm, k0, v0, cs, q,
-                         Kbuf, Vbuf, n_buf, n_buf_cap, npw, ncw, pp, rc, odd_rank ? 1 : 0, q_len, causal, out);
+      hipLaunchKernelGGL((decode_single_kernel<BITS, GQ, LG>), dim3(blocks), dim3(64 * nwaves), lds1, st, dm, k0, v0, cs, q,
+                         Kbuf, Vbuf, n_buf, n_buf_cap, npw, ncw, pp, rc, odd_rank ? 1 : 0, q_len, causal, lparts, out);
       return hipGetLastError();
     }
   }
@@ -246,9 +290,9 @@ static hipError_t launch_decode_t(const Dims& dm, const SegView& k0, const SegVi
     if (e != hipSuccess) return e;
     lds_allowed.store(lds, std::memory_order_relaxed);
   }
-  dim3 grid(nsplit + ncb + 1, dm.B * dm.H);
+  dim3 grid(nsplit + ncb + 1, blocks);
   hipLaunchKernelGGL((decode_split_kernel<BITS, GQ, LG>), grid, dim3(256), lds, st, dm, k0, v0, cs, q, Kbuf, Vbuf,
-                     n_buf, n_buf_cap, nsplit, pp, rc, odd_rank ? 1 : 0, q_len, causal, partial);
+                     n_buf, n_buf_cap, nsplit, pp, rc, odd_rank ? 1 : 0, q_len, causal, lparts, partial);
   if (nsplit + ncb + 1 > 32)
     hipLaunchKernelGGL(decode_combine_kernel<true>, dim3(dm.B * dm.Hq), dim3(128), 0, st, (const float*)partial,
                        nsplit + ncb + 1, out);
@@ -265,10 +309,13 @@ static hipError_t launch_decode_b(const Dims& dm, const SegView& k0, const SegVi
                                   hipStream_t st) {
 #define GEAR_DECODE_CASE(GQV)                                                                                          \
   case GQV:                                                                                                            \
-    if (dm.g == 32) return launch_decode_t<BITS, GQV, 5>(dm, k0, v0, cs, q, Kbuf, Vbuf, n_buf, n_buf_cap, rank_cap, q_len, causal, out, partial, st); \
-    if (dm.g == 64) return launch_decode_t<BITS, GQV, 6>(dm, k0, v0, cs, q, Kbuf, Vbuf, n_buf, n_buf_cap, rank_cap, q_len, causal, out, partial, st); \
-    return launch_decode_t<BITS, GQV, 7>(dm, k0, v0, cs, q, Kbuf, Vbuf, n_buf, n_buf_cap, rank_cap, q_len, causal, out, partial, st);
-  switch (dm.Hq / dm.H) {
+    if (dm.g == 32) return launch_decode_t<BITS, GQV, 5>(dm, k0, v0, cs, q, Kbuf, Vbuf, n_buf, n_buf_cap, rank_cap, q_len, causal, lparts, out, partial, st); \
+    if (dm.g == 64) return launch_decode_t<BITS, GQV, 6>(dm, k0, v0, cs, q, Kbuf, Vbuf, n_buf, n_buf_cap, rank_cap, q_len, causal, lparts, out, partial, st); \
+    return launch_decode_t<BITS, GQV, 7>(dm, k0, v0, cs, q, Kbuf, Vbuf, n_buf, n_buf_cap, rank_cap, q_len, causal, lparts, out, partial, st);
+  const int pp = n_buf_cap > WTOK ? 2 : 1, nblocks = (k0.n + MFMA_TS - 1) / MFMA_TS + (cs.n_chunks * pp + 3) / 4 + 1;
+  const int nwaves = (k0.n + WTOK - 1) / WTOK + cs.n_chunks * pp + (n_buf + BUF_WAVE_ROWS - 1) / BUF_WAVE_ROWS;
+  const int lparts = column_parts(BITS, dm.Hq / dm.H, dm.B * dm.H, nblocks, nwaves);
+  switch ((dm.Hq / dm.H) >> lparts) {
     GEAR_DECODE_CASE(1)
     GEAR_DECODE_CASE(2)
     GEAR_DECODE_CASE(4)

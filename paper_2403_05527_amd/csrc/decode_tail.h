@@ -43,7 +43,7 @@ __device__ __forceinline__ SegView chunk_view(const SegView& base, uint64_t stri
 // last q_len rows); q_len = 1: the single-query read, every column sees all n_buf rows.
 template <int GQ>
 __device__ __forceinline__ void buffer_block(TailSmem<GQ>& S, const uint16_t* __restrict__ qg, const uint16_t* __restrict__ Kb,
-                             const uint16_t* __restrict__ Vb, int n_buf, int q_len, int causal,
+                             const uint16_t* __restrict__ Vb, int n_buf, int q_len, int causal, int row0,
                              float* __restrict__ rec_base, int rec_stride) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const float scale = 0.08838834764831845f;  // 1/sqrt(128)
@@ -95,7 +95,7 @@ __device__ __forceinline__ void buffer_block(TailSmem<GQ>& S, const uint16_t* __
   float p[GQ];
 #pragma unroll
   for (int hq = 0; hq < GQ; ++hq) {
-    const int seen = causal ? n_buf - q_len + 1 + (hq & (q_len - 1)) : n_buf;   // q_len is a power of two
+    const int seen = causal ? n_buf - q_len + 1 + ((row0 + hq) & (q_len - 1)) : n_buf;   // q_len is a power of two
     s[hq] = tid < seen ? s[hq] * scale : -INFINITY;
     const float mx = wave_max(s[hq]);
     if (lane == 0) S.red[hq][wave] = mx;
@@ -162,7 +162,7 @@ constexpr int BUF_WAVE_ROWS = 32;
 template <int GQ>
 __device__ __forceinline__ void buffer_wave(unsigned char* smem, const MfmaLayout& L, const uint16_t* __restrict__ qg,
                                             const uint16_t* __restrict__ Kb, const uint16_t* __restrict__ Vb, int n_buf, int r0,
-                                            int q_len, int causal, int wave, int nthreads) {
+                                            int q_len, int causal, int row0, int wave, int nthreads) {
   const int tid = threadIdx.x, lane = tid & 63, row4 = lane >> 4, piece = lane & 15;
   float* Sq = reinterpret_cast<float*>(smem + L.q);                 // [128][GQ]
   MfmaMisc<GQ, SINGLE_WAVES<GQ>>& M = *reinterpret_cast<MfmaMisc<GQ, SINGLE_WAVES<GQ>>*>(smem + L.misc);
@@ -227,7 +227,7 @@ __device__ __forceinline__ void buffer_wave(unsigned char* smem, const MfmaLayou
   if (lane < BUF_WAVE_ROWS) lds_load_f<GQ>(Ssc + lane * GQ, s);
 #pragma unroll
   for (int hq = 0; hq < GQ; ++hq) {
-    const int seen = causal ? n_buf - q_len + 1 + (hq & (q_len - 1)) : n_buf;   // q_len is a power of two
+    const int seen = causal ? n_buf - q_len + 1 + ((row0 + hq) & (q_len - 1)) : n_buf;   // q_len is a power of two
     const bool live = lane < BUF_WAVE_ROWS && r0 + lane < seen;
     const float v = live ? s[hq] * scale : -INFINITY;
     const float m = wave_max(v);

@@ -1,4 +1,4 @@
-"""The single-launch read at the edges of what it accepts: no buffer rows, buffer rows at the edges of a wave's 32, chunks of two
+"""The single-launch read, and query columns shared by several blocks, at the edges of what they accept: no buffer rows, buffer rows at the edges of a wave's 32, chunks of two
 pieces (one of them empty), as many waves as a block holds and one more (the split kernel), every number of query columns, causal
 rows that see none of a wave's buffer rows, a rank whose rows are not one read."""
 import pytest
@@ -16,8 +16,11 @@ DEV = "cuda:0"
     (2, 1, 4, 32, 3, 129, 20, (20, 1), (0, 20), 1, 1),                # a second prefill wave of one row, rank 3, no buffer wave
     (1, 2, 2, 0, 4, 128, 255, (255, 20), (0, 255), 1, 256),           # 256 slabs: chunks of two pieces, one of them empty; eight buffer waves
     (2, 4, 4, 128, 8, 300, 40, (40,), (33, 4), 1, 1),                 # four columns
-    (2, 2, 2, 64, 2, 200, 64, (7,), (64, 34), 4, 1),                  # eight columns, four causal rows: some see none of the second
+    (2, 2, 2, 64, 2, 200, 64, (7,), (64, 34), 4, 1),                  # four causal rows of two heads: some see none of the second
                                                                       # buffer wave's rows
+    (2, 2, 2, 64, 2, 200, 64, (7,), (64, 34), 4, 128),                # the same, eight columns in one block
+    (2, 2, 4, 32, 2, 1700, 64, (7,), (64, 4), 4, 64),                 # the same in the split kernel
+    (1, 1, 2, 64, 4, 2100, 64, (7,), (64, 8), 8, 2),                  # eight causal rows over blocks of fewer columns
     (8, 1, 2, 64, 4, 1900, 20, (), (20, 0), 1, 32),                   # 256 slabs: sixteen waves in the block
     (8, 1, 2, 64, 4, 1900, 20, (5,), (20, 0), 1, 32),                 # one more: the split kernel; sixteen without a buffer
 ])
