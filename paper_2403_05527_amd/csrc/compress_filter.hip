@@ -304,13 +304,9 @@ static hipError_t launch_k_select_reg(const uint16_t* K, const Dims& dm, int n, 
 template <int PC, int NB, bool ONCE>
 static hipError_t launch_k_select_stream(const uint16_t* K, const Dims& dm, int n, int k_top, int k_bot, const StreamPlan& p, uint4* mask,
                                          uint32_t* zero, int zero_count, const SegView& sv, hipStream_t st) {
-  static std::atomic<size_t> lds_allowed{0};  // raised once per process and kernel instance (two threads may both raise it: harmless)
-  if (p.lds > lds_allowed.load(std::memory_order_relaxed)) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_select_stream_kernel<PC, NB, ONCE>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
-    if (e != hipSuccess) return e;
-    lds_allowed.store(p.lds, std::memory_order_relaxed);
-  }
+  static std::atomic<bool> lds_raised{false};
+  const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(k_select_stream_kernel<PC, NB, ONCE>), lds_raised);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_select_stream_kernel<PC, NB, ONCE>), dim3((D / (8 * PC)) * dm.B * dm.H), dim3(STREAM_THREADS), p.lds, st, K, n, p.L, dm.B * dm.H,
                      k_top, k_bot, p.j_top, p.j_bot, p.cap, mask, zero, zero_count, dm.kcvt ? sv.sz : (uint32_t*)nullptr, sv.ng_cap,
                      dm.qmax);
@@ -336,7 +332,7 @@ hipError_t launch_k_select(const uint16_t* K, const Dims& dm, int n, int k_top, 
     if (n <= 2048) GEAR_STREAM(2, 8, true, 80 * 1024);
     else if (n <= 4096) GEAR_STREAM(2, 16, true, 80 * 1024);
     else GEAR_STREAM(2, 8, false, 80 * 1024);
-    GEAR_STREAM(1, 8, false, 160 * 1024);
+    GEAR_STREAM(1, 8, false, LDS_PER_CU);
 #undef GEAR_STREAM
   }
   // segments of more than 8192 tokens: through a channel-major copy of the keys

@@ -202,8 +202,7 @@ constexpr int CUS = 256;
 // Beyond 1024 slabs the split kernel's whole blocks of prefill rows are as good (2048 slabs, 4 bits, 512 + 1: 50.1 -> 52.0), but
 // not its nearly empty ones (100 tokens: 39.9 -> 16.8).
 static bool single_read(int nwaves, int max_waves, int slabs, int nblocks, int columns, size_t lds) {
-  constexpr int LDS_MAX = 160 * 1024;
-  if (nwaves > max_waves || lds > LDS_MAX) return false;
+  if (nwaves > max_waves || lds > LDS_PER_CU) return false;
   if (slabs > 4 * CUS) return nwaves <= 4;
   const int here = nwaves * ((slabs + CUS - 1) / CUS), split = 4 * ((slabs * nblocks + CUS - 1) / CUS);
   if (nwaves > 12 && (slabs > 2 * CUS || here > split + 2)) return false;
@@ -269,13 +268,9 @@ static hipError_t launch_decode_t(const Dims& dm, const SegView& k0, const SegVi
     const int nwaves = npw + ncw + nbw;
     const size_t lds1 = (size_t)mfma_layout<GQ>(BITS, dm.g, k0.rank, v0.rank, rc, odd_rank, nwaves, ncw).total;
     if (single_read(nwaves, SINGLE_WAVES<GQ>, blocks, nsplit + ncb + 1, GQ, lds1)) {
-      static std::atomic<size_t> allowed{0};
-      if (lds1 > allowed.load(std::memory_order_relaxed)) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_single_kernel<BITS, GQ, LG>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds1);
-        if (e != hipSuccess) return e;
-        allowed.store(lds1, std::memory_order_relaxed);
-      }
+      static std::atomic<bool> lds_raised{false};
+      const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(decode_single_kernel<BITS, GQ, LG>), lds_raised);
+      if (e != hipSuccess) return e;
       hipLaunchKernelGGL((decode_single_kernel<BITS, GQ, LG>), dim3(blocks), dim3(64 * nwaves), lds1, st, dm, k0, v0, cs, q,
                          Kbuf, Vbuf, n_buf, n_buf_cap, npw, ncw, pp, rc, odd_rank ? 1 : 0, q_len, causal, lparts, out);
       return hipGetLastError();
@@ -283,13 +278,9 @@ static hipError_t launch_decode_t(const Dims& dm, const SegView& k0, const SegVi
   }
   size_t lds = (size_t)mfma_layout<GQ>(BITS, dm.g, k0.rank, v0.rank, rc, odd_rank).total;
   if (lds < sizeof(TailSmem<GQ>)) lds = sizeof(TailSmem<GQ>);
-  static std::atomic<size_t> lds_allowed{0};  // raised once per process and kernel instance (two threads may both raise it: harmless)
-  if (lds > lds_allowed.load(std::memory_order_relaxed)) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(decode_split_kernel<BITS, GQ, LG>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    lds_allowed.store(lds, std::memory_order_relaxed);
-  }
+  static std::atomic<bool> lds_raised{false};
+  const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(decode_split_kernel<BITS, GQ, LG>), lds_raised);
+  if (e != hipSuccess) return e;
   dim3 grid(nsplit + ncb + 1, blocks);
   hipLaunchKernelGGL((decode_split_kernel<BITS, GQ, LG>), grid, dim3(256), lds, st, dm, k0, v0, cs, q, Kbuf, Vbuf,
                      n_buf, n_buf_cap, nsplit, pp, rc, odd_rank ? 1 : 0, q_len, causal, lparts, partial);

@@ -1,8 +1,20 @@
 // Host-side launch functions of the kernel translation units.
 #pragma once
+#include <atomic>
 #include "gear_internal.h"
 
 namespace gear {
+
+// Lets a kernel without static LDS be launched with any dynamic size up to what a CU has.  Raised to the full size at once: were it
+// raised to the size of each larger call, of two threads the one with the smaller size could set it last, below what the other
+// is about to launch with.
+constexpr size_t LDS_PER_CU = 160 * 1024;
+inline hipError_t raise_dynamic_lds(const void* kernel, std::atomic<bool>& raised) {   // raised: one per kernel instance
+  if (raised.load(std::memory_order_relaxed)) return hipSuccess;
+  const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_PER_CU);
+  if (e == hipSuccess) raised.store(true, std::memory_order_relaxed);
+  return e;
+}
 
 // Chunk segments live in equally sized regions; view j = view 0 advanced by
 // j * stride bytes on every pointer.
