@@ -322,7 +322,7 @@ hipError_t launch_k_select(const uint16_t* K, const Dims& dm, int n, int k_top, 
   // of a short vector cost more than its histograms do (512 x 1024: 164 against 178), and at 5 % the lists are so long that it is even
   // up to 8192 tokens (512 x 8192: 1947 and 1952; 128 x 12000: 893 against 764).
   StreamPlan p;
-  if (mask && (n > 8192 || (n > 1024 && (long long)dm.B * dm.H * n > 65536))) {
+  if (mask && (n > 8192 || (n > 1024 && (long long)dm.B * dm.H * n > GEAR_STREAM_MIN_ROWS))) {
     const bool rest = dm.kcvt != 0;
 #define GEAR_STREAM(PC, NB, ONCE, LDS)                                                       \
   do {                                                                                       \

@@ -80,6 +80,10 @@
 #ifndef GEAR_ROWS_MIN_TOKENS
 #define GEAR_ROWS_MIN_TOKENS 16384
 #endif
+// Key rows (slabs x tokens) beyond which segments of 1025 to 8192 tokens are selected by lists of candidates
+#ifndef GEAR_STREAM_MIN_ROWS
+#define GEAR_STREAM_MIN_ROWS 65536
+#endif
 // Resident blocks of the quantization kernel with its Gram accumulators on the whole chip: two on each of the 256 CUs.  (The
 // CPU stand-in lowers it so that its small cases walk strips of several tiles.)
 #ifndef GEAR_BLOCK_SLOTS

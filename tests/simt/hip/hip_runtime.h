@@ -245,6 +245,7 @@ inline void launch(dim3 grid, dim3 block, size_t lds, F&& body) {
 #define __builtin_amdgcn_rsqf(x) (1.0f / sqrtf(x))
 #define __builtin_amdgcn_rcpf(x) (1.0f / (x))
 #define GEAR_ROWS_MIN_TOKENS 64   // the small emulated cases take the token-row kernels too
+#define GEAR_STREAM_MIN_ROWS 3000   // the same for the Key selection by lists of candidates
 #ifndef GEAR_BLOCK_SLOTS
 #define GEAR_BLOCK_SLOTS 16       // and strips of two tiles and more
 #endif

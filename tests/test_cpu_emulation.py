@@ -84,6 +84,7 @@ def test_workspace_holds_exactly_the_most_strips(tmp_path, slots):
                                                            # segment of 255 tokens (two 128-row pieces in the decode kernel)
     (1, 2, 8, 1100, 2, 128, 10000, 8, 7, False, 20, 20, -1),   # n > 1024: Key vectors selected in registers; rank 8, four
                                                            # query heads per KV head, groups of 128
+    (1, 3, 3, 1030, 2, 64, 20000, 2, 3, False, 20, 20, -1),    # more Key rows: selected by lists of candidates
     (1, 1, 8, 150, 4, 64, 20000, 3, 4, False, 33, 40, -1),     # eight query heads per KV head, a rank that is not one read
                                                            # (factor rows staged in LDS), a flushed segment of 33 tokens
     (1, 2, 4, 330, 2, 64, 20000, 4, 6, False, 20, 20, 100),  # the low-rank term on the last 100 of 330 tokens only
