@@ -268,8 +268,8 @@ static hipError_t launch_decode_t(const Dims& dm, const SegView& k0, const SegVi
     const int nwaves = npw + ncw + nbw;
     const size_t lds1 = (size_t)mfma_layout<GQ>(BITS, dm.g, k0.rank, v0.rank, rc, odd_rank, nwaves, ncw).total;
     if (single_read(nwaves, SINGLE_WAVES<GQ>, blocks, nsplit + ncb + 1, GQ, lds1)) {
-      static std::atomic<bool> lds_raised{false};
-      const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(decode_single_kernel<BITS, GQ, LG>), lds_raised);
+      static std::atomic<uint64_t> lds_raised{0};
+      const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(decode_single_kernel<BITS, GQ, LG>), lds_raised, LDS_PER_CU);
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL((decode_single_kernel<BITS, GQ, LG>), dim3(blocks), dim3(64 * nwaves), lds1, st, dm, k0, v0, cs, q,
                          Kbuf, Vbuf, n_buf, n_buf_cap, npw, ncw, pp, rc, odd_rank ? 1 : 0, q_len, causal, lparts, out);
@@ -278,8 +278,8 @@ static hipError_t launch_decode_t(const Dims& dm, const SegView& k0, const SegVi
   }
   size_t lds = (size_t)mfma_layout<GQ>(BITS, dm.g, k0.rank, v0.rank, rc, odd_rank).total;
   if (lds < sizeof(TailSmem<GQ>)) lds = sizeof(TailSmem<GQ>);
-  static std::atomic<bool> lds_raised{false};
-  const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(decode_split_kernel<BITS, GQ, LG>), lds_raised);
+  static std::atomic<uint64_t> lds_raised{0};
+  const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(decode_split_kernel<BITS, GQ, LG>), lds_raised, LDS_PER_CU);
   if (e != hipSuccess) return e;
   dim3 grid(nsplit + ncb + 1, blocks);
   hipLaunchKernelGGL((decode_split_kernel<BITS, GQ, LG>), grid, dim3(256), lds, st, dm, k0, v0, cs, q, Kbuf, Vbuf,

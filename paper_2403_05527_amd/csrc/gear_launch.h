@@ -5,16 +5,22 @@
 
 namespace gear {
 
-// Lets a kernel without static LDS be launched with any dynamic size up to what a CU has.  Raised to the full size at once: were it
-// raised to the size of each larger call, of two threads the one with the smaller size could set it last, below what the other
-// is about to launch with.
-constexpr size_t LDS_PER_CU = 160 * 1024;
-inline hipError_t raise_dynamic_lds(const void* kernel, std::atomic<bool>& raised) {   // raised: one per kernel instance
-  if (raised.load(std::memory_order_relaxed)) return hipSuccess;
-  const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_PER_CU);
-  if (e == hipSuccess) raised.store(true, std::memory_order_relaxed);
+// Lets a kernel be launched with up to `bytes` of dynamic LDS on the current device.  The attribute belongs to a device's copy of the
+// kernel, so every device that a process works on gets it.  `raised`: one per kernel instance, a bit per device; two threads may both
+// raise it: harmless.
+inline hipError_t raise_dynamic_lds(const void* kernel, std::atomic<uint64_t>& raised, size_t bytes) {
+  int dev = -1;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = dev >= 0 && dev < 64 ? 1ull << dev : 0ull;   // (further devices: raised on each call)
+  if (raised.load(std::memory_order_relaxed) & bit) return hipSuccess;
+  e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e == hipSuccess) raised.fetch_or(bit, std::memory_order_relaxed);
   return e;
 }
+// A kernel without static LDS is raised to what a CU has, at once: were it raised to the size of each larger call, of two threads the
+// one with the smaller size could set it last, below what the other is about to launch with.
+constexpr size_t LDS_PER_CU = 160 * 1024;
 
 // Chunk segments live in equally sized regions; view j = view 0 advanced by
 // j * stride bytes on every pointer.

@@ -1051,12 +1051,8 @@ __global__ __launch_bounds__(256) void pi_tiny_kernel(const uint16_t* __restrict
 // ------------------------------------------------------------------ host side
 template <int R>
 static hipError_t raise_solve_lds() {
-  static std::atomic<bool> lds_raised{false};   // per kernel instance (R); two threads may both raise it: harmless
-  if (lds_raised.load(std::memory_order_relaxed)) return hipSuccess;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pi_solve_kernel<R>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(SolveSmem<R>));
-  if (e == hipSuccess) lds_raised.store(true, std::memory_order_relaxed);
-  return e;
+  static std::atomic<uint64_t> lds_raised{0};
+  return raise_dynamic_lds(reinterpret_cast<const void*>(pi_solve_kernel<R>), lds_raised, sizeof(SolveSmem<R>));
 }
 
 // Keys' per-vector grouping: one group per segment

@@ -40,10 +40,12 @@ typedef int hipError_t;
 typedef void* hipStream_t;
 enum { hipSuccess = 0, hipErrorInvalidValue = 1 };
 enum { hipFuncAttributeMaxDynamicSharedMemorySize = 8 };
-inline hipError_t hipGetLastError() { return hipSuccess; }
-inline hipError_t hipFuncSetAttribute(const void*, int, int) { return hipSuccess; }
+// a current device, and per device and kernel the dynamic LDS that a launch may ask for (64 KB until it is raised)
+hipError_t hipGetLastError();
+hipError_t hipFuncSetAttribute(const void* kernel, int attribute, int value);
 inline const char* hipGetErrorString(hipError_t) { return "emulated"; }
-inline hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int d);
+hipError_t hipGetDevice(int* d);
 #define HIP_SYMBOL(x) x
 inline hipError_t hipGetSymbolAddress(void** p, const void* sym) { *p = const_cast<void*>(sym); return hipSuccess; }
 #define GEAR_DYN_LDS(name) unsigned char* name = simt::dyn_lds
@@ -230,11 +232,15 @@ inline f4 mfma4x4x1(float a, float b, f4 c) {
   return d;
 }
 extern unsigned char* dyn_lds;
+// Every launch goes to `observer`, if there is one (a text that names the kernel as the launch does); with `dry` it then ends there.
+typedef void (*Observer)(const char* kernel, dim3 grid, dim3 block, size_t lds);
+extern Observer observer;
+extern bool dry;
 // run a whole grid: one OS thread per lane, blocks one after the other
-void launch_grid(dim3 grid, dim3 block, size_t lds, void (*fn)(void*), void* arg);
+void launch_grid(const void* kernel, const char* name, dim3 grid, dim3 block, size_t lds, void (*fn)(void*), void* arg);
 template <class F>
-inline void launch(dim3 grid, dim3 block, size_t lds, F&& body) {
-  launch_grid(grid, block, lds, [](void* p) { (*static_cast<F*>(p))(); }, &body);
+inline void launch(const void* kernel, const char* name, dim3 grid, dim3 block, size_t lds, F&& body) {
+  launch_grid(kernel, name, grid, block, lds, [](void* p) { (*static_cast<F*>(p))(); }, &body);
 }
 }  // namespace simt
 
@@ -302,4 +308,5 @@ inline uint32_t atomicMax(uint32_t* p, uint32_t v) {
 }
 inline uint32_t atomicOr(uint32_t* p, uint32_t v) { return __atomic_fetch_or(p, v, __ATOMIC_RELAXED); }
 
-#define hipLaunchKernelGGL(kernel, grid, block, lds, st, ...) simt::launch((grid), (block), (lds), [&] { kernel(__VA_ARGS__); })
+#define hipLaunchKernelGGL(kernel, grid, block, lds, st, ...) \
+  simt::launch(reinterpret_cast<const void*>(kernel), #kernel, (grid), (block), (lds), [&] { (kernel)(__VA_ARGS__); })

@@ -1,5 +1,7 @@
 // Runtime of the CPU stand-in for the HIP device environment (see hip/hip_runtime.h).
 #include <hip/hip_runtime.h>
+#include <map>
+#include <utility>
 #include <vector>
 #if defined(__has_feature)
 #if __has_feature(memory_sanitizer)
@@ -9,7 +11,20 @@
 #endif
 thread_local dim3 threadIdx, blockIdx;
 dim3 blockDim, gridDim;
+static int device = 0;
+static hipError_t last_error = hipSuccess;
+static std::map<std::pair<const void*, int>, size_t> raised;
+hipError_t hipSetDevice(int d) { device = d; return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = device; return hipSuccess; }
+hipError_t hipGetLastError() { const hipError_t e = last_error; last_error = hipSuccess; return e; }
+hipError_t hipFuncSetAttribute(const void* kernel, int attribute, int value) {
+  if (attribute != hipFuncAttributeMaxDynamicSharedMemorySize || value > 160 * 1024) return hipErrorInvalidValue;
+  raised[{kernel, device}] = (size_t)value;
+  return hipSuccess;
+}
 namespace simt {
+Observer observer = nullptr;
+bool dry = false;
 Wave waves[16];
 pthread_barrier_t block_bar;
 unsigned char* dyn_lds = nullptr;
@@ -49,7 +64,14 @@ static void spawn(int nthreads, void* (*entry)(void*), std::vector<Start>& st) {
   for (int w = 0; w < nw; ++w) pthread_barrier_destroy(&waves[w].bar);
   pthread_barrier_destroy(&block_bar);
 }
-void launch_grid(dim3 grid, dim3 block, size_t lds, void (*fn)(void*), void* arg) {
+void launch_grid(const void* kernel, const char* name, dim3 grid, dim3 block, size_t lds, void (*fn)(void*), void* arg) {
+  const auto allowed = raised.find({kernel, device});
+  if (lds > (allowed == raised.end() ? 64 * 1024 : std::max<size_t>(allowed->second, 64 * 1024))) {
+    last_error = hipErrorInvalidValue;   // nothing runs
+    return;
+  }
+  if (observer) observer(name, grid, block, lds);
+  if (dry) return;
   if (block.y != 1 || block.z != 1) { fprintf(stderr, "only 1-D blocks are modelled\n"); abort(); }
   gridDim = grid; blockDim = block;
   // exact-size heap buffer: the address sanitizer flags any access past the requested LDS size

@@ -30,7 +30,8 @@ def find_clang():
 
 
 @pytest.fixture(scope="module")
-def emulator(tmp_path_factory):
+def build(tmp_path_factory):
+    """build(name): the library and tests/simt/<name>.cpp as one program."""
     cxx = find_clang()
     if cxx is None:
         pytest.skip("no clang++ to build the CPU emulation")
@@ -39,25 +40,36 @@ def emulator(tmp_path_factory):
     # switch contraction off (the quantizer's decision sequence), which the bit-exact code comparison checks
     flags = ["-std=c++17", "-O1", "-g", "-ffp-contract=fast", "-fsanitize=address", "-fno-omit-frame-pointer", "-pthread",
              "-I", SIMT, "-I", os.path.join(ROOT, "include"), "-I", CSRC]
-    procs = []
-    objs = []
-    for s in SOURCES:
-        o = str(out / (s + ".o"))
-        objs.append(o)
-        procs.append(subprocess.Popen([cxx, "-x", "c++", "-c", os.path.join(CSRC, s + ".hip"), "-o", o] + flags,
-                                      stderr=subprocess.PIPE, text=True))
-    for s in ("simt_rt", "run_pipeline"):
-        o = str(out / (s + ".o"))
-        objs.append(o)
-        procs.append(subprocess.Popen([cxx, "-c", os.path.join(SIMT, s + ".cpp"), "-o", o] + flags,
-                                      stderr=subprocess.PIPE, text=True))
-    for p in procs:
-        err = p.communicate()[1]
-        assert p.returncode == 0, err[-3000:]
-    exe = str(out / "run_pipeline")
-    r = subprocess.run([cxx] + objs + ["-o", exe] + flags, capture_output=True, text=True)
-    assert r.returncode == 0, r.stderr[-3000:]
-    return exe
+
+    def objects(names):
+        procs = []
+        for s in names:
+            src = ["-x", "c++", "-c", os.path.join(CSRC, s + ".hip")] if s in SOURCES else ["-c", os.path.join(SIMT, s + ".cpp")]
+            procs.append(subprocess.Popen([cxx] + src + ["-o", str(out / (s + ".o"))] + flags, stderr=subprocess.PIPE, text=True))
+        for p in procs:
+            err = p.communicate()[1]
+            assert p.returncode == 0, err[-3000:]
+        return [str(out / (s + ".o")) for s in names]
+
+    common = objects(SOURCES + ["simt_rt"])
+
+    def program(name):
+        exe = str(out / name)
+        if not os.path.exists(exe):
+            r = subprocess.run([cxx] + common + objects([name]) + ["-o", exe] + flags, capture_output=True, text=True)
+            assert r.returncode == 0, r.stderr[-3000:]
+        return exe
+    return program
+
+
+@pytest.fixture(scope="module")
+def emulator(build):
+    return build("run_pipeline")
+
+
+def test_dynamic_lds_is_raised_on_every_device(build):
+    r = subprocess.run([build("check_devices")], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
 
 
 @pytest.mark.parametrize("slots", [512, 16])
