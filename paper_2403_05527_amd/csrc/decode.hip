@@ -11,7 +11,7 @@
 // the fp16 buffer (decode_tail.h).  Every block writes one partial softmax
 // record (m, l, o) per query head; decode_combine merges the records.
 // A cache of few pieces is read by one block per slab instead, in one launch
-// (decode_single_kernel, chosen by single_read).
+// (decode_single_kernel, chosen by read_plan).
 #include <atomic>
 #include "gear_internal.h"
 #include "gear_launch.h"
@@ -23,7 +23,7 @@ namespace gear {
 static_assert(MFMA_TS == DECODE_SPLIT, "split size is part of the workspace layout");
 
 // grid (nsplit + ncb + 1, B*H_kv << lparts), block 256: a slab's query columns are shared by 2^lparts blocks, GQ
-// columns each (column_parts).  Blocks [0, nsplit): 512 prefill tokens each;
+// columns each (read_plan).  Blocks [0, nsplit): 512 prefill tokens each;
 // blocks [nsplit, nsplit + ncb): four pieces of appended chunks each (one piece = up to 128
 // rows of one chunk, pp pieces per chunk), through the same code as the prefill; the
 // last block: the fp16 streaming-buffer rows.
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(256, (GQ == 8 ? 3 : (BITS == 2 && (GQ <= 2 || (GQ =
                                   split < nsplit, rec_base, rec_stride, 0, 0, 0);
 }
 
-// The whole read of a slab (or of a part of its query columns) in one block, for caches of few pieces (single_read): grid
+// The whole read of a slab (or of a part of its query columns) in one block, for caches of few pieces (read_plan): grid
 // (B*H_kv << lparts), a wave per 128 prefill tokens, then one per chunk piece, then one per 32 buffer rows.  The states meet in
 // LDS and the block writes the result itself: no records and no second launch.  Bound by one wave's chain of dependent steps and the launch; each wave adds its own zero-point
 // and low-rank terms, so that the merge behind the barrier is one plane read per wave.
@@ -209,87 +209,114 @@ static bool single_read(int nwaves, int max_waves, int slabs, int nblocks, int c
   return here - split <= (columns == 1 ? 7 : columns == 2 ? 5 : columns == 4 ? 3 : 1);
 }
 
-// How many blocks share the query columns of a slab: 2^result of them, with columns >> result each.  Fewer columns per wave make
-// the wave's chain of steps shorter and the codes are unpacked once per part, so a small grid is read faster by more parts and a
-// large one by fewer.  The times are a model of measured ones, in microseconds: a lone block on a CU takes `first`, each further
-// one adds `more` (beyond three blocks of eight columns, which is what a CU holds, a quarter as much again); a single-launch read
-// takes `base` and `wave` for each wave of the fullest CU, `least` at the least.  Over 492 sizes (1 to 64 batch elements, 100 to
-// 20000 tokens, 2 to 8 columns) the choice is within 1 % of the best one on average and 26 % faster than whole slabs.  Whole -> parts:
+// What a read consists of, as the choice of its launch sees it.
+struct ReadShape {
+  int bits, g, columns, slabs;     // columns: query columns of a slab
+  int npw, ncw, nbw, nblocks;      // waves of the single-launch read (prefill rows, chunk pieces, buffer rows); blocks of four of the other
+  int pp, rk0, rv0, rc, odd_rank;  // pieces per chunk; ranks of the prefill segment, largest rank of a chunk; a rank whose rows are not one read
+  int waves() const { return npw + ncw + nbw; }
+};
+static ReadShape read_shape(const Dims& dm, const SegView& k0, const SegView& v0, const ChunkSet& cs, int n_buf, int n_buf_cap) {
+  ReadShape s;
+  s.bits = dm.bits;
+  s.g = dm.g;
+  s.columns = dm.Hq / dm.H;
+  s.slabs = dm.B * dm.H;
+  s.pp = n_buf_cap > WTOK ? 2 : 1;
+  s.npw = (k0.n + WTOK - 1) / WTOK;
+  s.ncw = cs.n_chunks * s.pp;
+  s.nbw = (n_buf + BUF_WAVE_ROWS - 1) / BUF_WAVE_ROWS;
+  s.nblocks = (k0.n + MFMA_TS - 1) / MFMA_TS + (s.ncw + 3) / 4 + 1;
+  s.rk0 = k0.rank;
+  s.rv0 = v0.rank;
+  s.rc = 0;
+  // a rank whose rows are not one 4-, 8- or 16-byte read anywhere in the launch
+  auto one_read = [](int r) { return r == 0 || r == 2 || r == 4 || r == 8; };
+  s.odd_rank = !one_read(k0.rank) || !one_read(v0.rank);
+  for (int j = 0; j < cs.n_chunks; ++j) {
+    s.rc = cs.rank[j] > s.rc ? cs.rank[j] : s.rc;
+    s.odd_rank = s.odd_rank || !one_read(cs.rank[j]);
+  }
+  return s;
+}
+template <int GQ>
+static size_t single_lds(const ReadShape& s) {
+  return (size_t)mfma_layout<GQ>(s.bits, s.g, s.rk0, s.rv0, s.rc, s.odd_rank != 0, s.waves(), s.ncw).total;
+}
+
+// How a read is launched: 2^lparts blocks share a slab's query columns, in one launch (single) or by the split kernel and the merge.
+struct ReadPlan {
+  int lparts;
+  bool single;
+};
+// Fewer columns per wave make the wave's chain of steps shorter and the codes are unpacked once per part, so a small grid is read
+// faster by more parts and a large one by fewer.  The times are a model of measured ones, in microseconds: a lone block on a CU
+// takes `first`, each further one adds `more` (beyond three blocks of eight columns, which is what a CU holds, a quarter as much
+// again); a single-launch read takes `base` and `wave` for each wave of the fullest CU, `least` at the least.  Whole -> parts:
 // 5 x 8 heads x 3001 tokens, eight columns 29.9 -> 24.1 us (2 parts); 1 x 8 heads x 3001 21.5 -> 12.4 (4); 16 x 8 heads x 8192 97.7
 // -> 90.9 (2); four columns, 1 x 8 heads x 8192 16.2 -> 15.0 (2), 64 x 8 heads x 1700 61.7 against 67.4 (whole).  A part has to
-// promise 4 % a step.
-static int column_parts(int bits, int columns, int slabs, int nblocks, int nwaves) {
+// promise 4 % a step.  The constants are those of rank 4 and 2 % outliers: a read without them is up to a third shorter, one with
+// 5 % twice as long, for all choices nearly alike.  Over 1237 sizes drawn at random (1 to 64 batch elements, 60 to 20000 tokens, up to
+// 20 chunks, one to eight columns, ranks 0 to 8, at most 5 % outliers; profiles/decode_routes.csv) the choice takes 0.72 of the time of
+// whole slabs by the split kernel, geometric mean, and the best one of each size would take 0.67.  26 of them are more than 3 % slower
+// than that kernel, at worst 1.24 (44 slabs x 1606 tokens, eight columns, rank 8, 155 buffer rows: 27.5 -> 34.1, the parts' buffer
+// blocks one after another); a larger margin loses more on the other sizes than it wins on these.
+static ReadPlan read_plan(const ReadShape& s) {
   struct Cost { float first, more, least, base, wave; };
   static const Cost costs[2][4] = {   // one, two, four, eight columns
       {{11.8f, 1.9f, 10.0f, 3.0f, 0.75f}, {12.0f, 3.1f, 10.0f, 4.0f, 1.0f}, {15.6f, 4.75f, 12.0f, 3.0f, 1.7f}, {22.0f, 8.3f, 17.0f, 0.0f, 3.6f}},
       {{12.3f, 2.5f, 10.0f, 2.0f, 1.05f}, {13.6f, 4.3f, 10.5f, 3.0f, 1.4f}, {17.8f, 5.8f, 14.0f, 3.0f, 2.1f}, {25.8f, 10.0f, 21.0f, 0.0f, 4.3f}}};
   float best = 0.0f;
-  int pick = 0;
-  for (int p = 0; (columns >> p) > 0; ++p) {
-    const int c = columns >> p, lc = c == 8 ? 3 : c >> 1;
-    const long long blocks = (long long)slabs << p;
-    if (blocks > 65535) break;   // a dimension of the grid
-    const Cost& t = costs[bits == 4 ? 1 : 0][lc];
+  ReadPlan plan{0, false};
+  for (int p = 0; (s.columns >> p) > 0; ++p) {
+    const int c = s.columns >> p, lc = c == 8 ? 3 : c >> 1;
+    const long long blocks = (long long)s.slabs << p;
+    if (p > 0 && blocks > 65535) break;   // a dimension of the grid
+    const Cost& t = costs[s.bits == 4 ? 1 : 0][lc];
+    const size_t lds = c == 8 ? single_lds<8>(s) : c == 4 ? single_lds<4>(s) : c == 2 ? single_lds<2>(s) : single_lds<1>(s);
+    const bool single = single_read(s.waves(), c == 8 ? SINGLE_WAVES<8> : SINGLE_WAVES<1>, (int)blocks, s.nblocks, c, lds);
     float us;
-    if (single_read(nwaves, c == 8 ? SINGLE_WAVES<8> : SINGLE_WAVES<1>, (int)blocks, nblocks, c, 0)) {
-      us = t.base + t.wave * (float)(nwaves * ((blocks + CUS - 1) / CUS));
+    if (single) {
+      us = t.base + t.wave * (float)(s.waves() * ((blocks + CUS - 1) / CUS));
       us = us < t.least ? t.least : us;
     } else {
-      const long long k = (blocks * nblocks + CUS - 1) / CUS;
+      const long long k = (blocks * s.nblocks + CUS - 1) / CUS;
       us = t.first + t.more * (float)(k - 1) + (c == 8 && k > 3 ? 0.25f * t.more * (float)(k - 3) : 0.0f);
+      if (c == 8 && (s.odd_rank || (s.g == 32 && s.rk0 > 4))) us *= 1.1f;   // (factor rows through LDS; four groups of factors)
     }
     us *= 1.0f + 0.04f * (float)p;
     if (p == 0 || us < best) {
       best = us;
-      pick = p;
+      plan = ReadPlan{p, single};
     }
   }
-  return pick;
+  return plan;
 }
 
 template <int BITS, int GQ, int LG>
-static hipError_t launch_decode_t(const Dims& dm, const SegView& k0, const SegView& v0, const ChunkSet& cs,
-                                  const uint16_t* q, const uint16_t* Kbuf, const uint16_t* Vbuf, int n_buf,
-                                  int n_buf_cap, int rank_cap, int q_len, int causal, int lparts, uint16_t* out, float* partial,
-                                  hipStream_t st) {
-  const int blocks = (dm.B * dm.H) << lparts;         // per 512 tokens: a block for each slab and part of its columns
-  const int nsplit = (k0.n + MFMA_TS - 1) / MFMA_TS;
-  const int pp = n_buf_cap > WTOK ? 2 : 1;            // pieces per chunk
-  const int ncb = (cs.n_chunks * pp + 3) / 4;
-  int rc = 0;                                         // largest rank of an appended chunk
-  for (int j = 0; j < cs.n_chunks; ++j) rc = cs.rank[j] > rc ? cs.rank[j] : rc;
-  if (rc > rank_cap) return hipErrorInvalidValue;     // the cache never stores more than its configured rank
-  // a rank whose rows are not one 4-, 8- or 16-byte read anywhere in the launch
-  auto one_read = [](int r) { return r == 0 || r == 2 || r == 4 || r == 8; };
-  bool odd_rank = !one_read(k0.rank) || !one_read(v0.rank);
-  for (int j = 0; j < cs.n_chunks; ++j) odd_rank = odd_rank || !one_read(cs.rank[j]);
-  {
-    const int npw = (k0.n + WTOK - 1) / WTOK, ncw = cs.n_chunks * pp, nbw = (n_buf + BUF_WAVE_ROWS - 1) / BUF_WAVE_ROWS;
-    const int nwaves = npw + ncw + nbw;
-    const size_t lds1 = (size_t)mfma_layout<GQ>(BITS, dm.g, k0.rank, v0.rank, rc, odd_rank, nwaves, ncw).total;
-    if (single_read(nwaves, SINGLE_WAVES<GQ>, blocks, nsplit + ncb + 1, GQ, lds1)) {
-      static std::atomic<uint64_t> lds_raised{0};
-      const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(decode_single_kernel<BITS, GQ, LG>), lds_raised, LDS_PER_CU);
-      if (e != hipSuccess) return e;
-      hipLaunchKernelGGL((decode_single_kernel<BITS, GQ, LG>), dim3(blocks), dim3(64 * nwaves), lds1, st, dm, k0, v0, cs, q,
-                         Kbuf, Vbuf, n_buf, n_buf_cap, npw, ncw, pp, rc, odd_rank ? 1 : 0, q_len, causal, lparts, out);
-      return hipGetLastError();
-    }
+static hipError_t launch_decode_t(const Dims& dm, const SegView& k0, const SegView& v0, const ChunkSet& cs, const ReadShape& s,
+                                  const ReadPlan& plan, const uint16_t* q, const uint16_t* Kbuf, const uint16_t* Vbuf, int n_buf,
+                                  int n_buf_cap, int q_len, int causal, uint16_t* out, float* partial, hipStream_t st) {
+  const int blocks = s.slabs << plan.lparts;          // per 512 tokens: a block for each slab and part of its columns
+  if (plan.single) {
+    static std::atomic<uint64_t> lds_raised{0};
+    const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(decode_single_kernel<BITS, GQ, LG>), lds_raised, LDS_PER_CU);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((decode_single_kernel<BITS, GQ, LG>), dim3(blocks), dim3(64 * s.waves()), single_lds<GQ>(s), st, dm, k0, v0, cs, q,
+                       Kbuf, Vbuf, n_buf, n_buf_cap, s.npw, s.ncw, s.pp, s.rc, s.odd_rank, q_len, causal, plan.lparts, out);
+    return hipGetLastError();
   }
-  size_t lds = (size_t)mfma_layout<GQ>(BITS, dm.g, k0.rank, v0.rank, rc, odd_rank).total;
+  size_t lds = (size_t)mfma_layout<GQ>(BITS, dm.g, k0.rank, v0.rank, s.rc, s.odd_rank != 0).total;
   if (lds < sizeof(TailSmem<GQ>)) lds = sizeof(TailSmem<GQ>);
   static std::atomic<uint64_t> lds_raised{0};
   const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(decode_split_kernel<BITS, GQ, LG>), lds_raised, LDS_PER_CU);
   if (e != hipSuccess) return e;
-  dim3 grid(nsplit + ncb + 1, blocks);
-  hipLaunchKernelGGL((decode_split_kernel<BITS, GQ, LG>), grid, dim3(256), lds, st, dm, k0, v0, cs, q, Kbuf, Vbuf,
-                     n_buf, n_buf_cap, nsplit, pp, rc, odd_rank ? 1 : 0, q_len, causal, lparts, partial);
-  if (nsplit + ncb + 1 > 32)
-    hipLaunchKernelGGL(decode_combine_kernel<true>, dim3(dm.B * dm.Hq), dim3(128), 0, st, (const float*)partial,
-                       nsplit + ncb + 1, out);
+  hipLaunchKernelGGL((decode_split_kernel<BITS, GQ, LG>), dim3(s.nblocks, blocks), dim3(256), lds, st, dm, k0, v0, cs, q, Kbuf, Vbuf,
+                     n_buf, n_buf_cap, (k0.n + MFMA_TS - 1) / MFMA_TS, s.pp, s.rc, s.odd_rank, q_len, causal, plan.lparts, partial);
+  if (s.nblocks > 32)
+    hipLaunchKernelGGL(decode_combine_kernel<true>, dim3(dm.B * dm.Hq), dim3(128), 0, st, (const float*)partial, s.nblocks, out);
   else
-    hipLaunchKernelGGL(decode_combine_kernel<false>, dim3(dm.B * dm.Hq), dim3(128), 0, st, (const float*)partial,
-                       nsplit + ncb + 1, out);
+    hipLaunchKernelGGL(decode_combine_kernel<false>, dim3(dm.B * dm.Hq), dim3(128), 0, st, (const float*)partial, s.nblocks, out);
   return hipGetLastError();
 }
 
@@ -298,15 +325,15 @@ static hipError_t launch_decode_b(const Dims& dm, const SegView& k0, const SegVi
                                   const uint16_t* q, const uint16_t* Kbuf, const uint16_t* Vbuf, int n_buf,
                                   int n_buf_cap, int rank_cap, int q_len, int causal, uint16_t* out, float* partial,
                                   hipStream_t st) {
+  const ReadShape s = read_shape(dm, k0, v0, cs, n_buf, n_buf_cap);
+  if (s.rc > rank_cap) return hipErrorInvalidValue;   // the cache never stores more than its configured rank
+  const ReadPlan plan = read_plan(s);
 #define GEAR_DECODE_CASE(GQV)                                                                                          \
   case GQV:                                                                                                            \
-    if (dm.g == 32) return launch_decode_t<BITS, GQV, 5>(dm, k0, v0, cs, q, Kbuf, Vbuf, n_buf, n_buf_cap, rank_cap, q_len, causal, lparts, out, partial, st); \
-    if (dm.g == 64) return launch_decode_t<BITS, GQV, 6>(dm, k0, v0, cs, q, Kbuf, Vbuf, n_buf, n_buf_cap, rank_cap, q_len, causal, lparts, out, partial, st); \
-    return launch_decode_t<BITS, GQV, 7>(dm, k0, v0, cs, q, Kbuf, Vbuf, n_buf, n_buf_cap, rank_cap, q_len, causal, lparts, out, partial, st);
-  const int pp = n_buf_cap > WTOK ? 2 : 1, nblocks = (k0.n + MFMA_TS - 1) / MFMA_TS + (cs.n_chunks * pp + 3) / 4 + 1;
-  const int nwaves = (k0.n + WTOK - 1) / WTOK + cs.n_chunks * pp + (n_buf + BUF_WAVE_ROWS - 1) / BUF_WAVE_ROWS;
-  const int lparts = column_parts(BITS, dm.Hq / dm.H, dm.B * dm.H, nblocks, nwaves);
-  switch ((dm.Hq / dm.H) >> lparts) {
+    if (dm.g == 32) return launch_decode_t<BITS, GQV, 5>(dm, k0, v0, cs, s, plan, q, Kbuf, Vbuf, n_buf, n_buf_cap, q_len, causal, out, partial, st); \
+    if (dm.g == 64) return launch_decode_t<BITS, GQV, 6>(dm, k0, v0, cs, s, plan, q, Kbuf, Vbuf, n_buf, n_buf_cap, q_len, causal, out, partial, st); \
+    return launch_decode_t<BITS, GQV, 7>(dm, k0, v0, cs, s, plan, q, Kbuf, Vbuf, n_buf, n_buf_cap, q_len, causal, out, partial, st);
+  switch (s.columns >> plan.lparts) {
     GEAR_DECODE_CASE(1)
     GEAR_DECODE_CASE(2)
     GEAR_DECODE_CASE(4)

@@ -72,6 +72,26 @@ def test_dynamic_lds_is_raised_on_every_device(build):
     assert r.returncode == 0, r.stderr
 
 
+@pytest.mark.parametrize("size,launch", [
+    # bits, group, B, H_kv, H_q, n, rank, n_buf, n_buf_cap, chunks: the kernel, the blocks that share a slab's columns.  The single
+    # launch of four columns would need more LDS than there is (factor rows staged, groups of 32): two columns per block fit.
+    ("2 32 32 8 32 877 7 12 20 4", "single 2"),
+    ("2 32 32 8 32 1765 7 0 20 1", "single 2"),
+    ("2 32 64 4 16 1049 7 11 20 5", "single 2"),
+    ("2 32 64 2 16 789 7 3 20 6", "single 4"),         # eight columns: neither fits as a whole nor in two parts
+    ("4 32 16 8 64 1091 7 16 20 5", "single 4"),
+    ("4 64 1 32 32 512 4 7 20 0", "single 1"),
+    ("2 64 5 8 64 3001 4 13 20 2", "split 2"),
+])
+def test_read_is_launched_as_planned(build, size, launch):
+    """The choice of the kernel and that of the parts rest on the same LDS size: where one block's LDS does not hold the single
+    launch, the parts are those that are best without it."""
+    r = subprocess.run([build("list_reads")], input=size + "\n", capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
+    kernel, parts, lds = r.stdout.split()
+    assert kernel + " " + parts == launch and int(lds) <= 160 * 1024
+
+
 @pytest.mark.parametrize("slots", [512, 16])
 def test_workspace_holds_exactly_the_most_strips(tmp_path, slots):
     """The bound by which the workspace of the Gram matrices is sized is reached and never passed, at the device's number of
