@@ -228,10 +228,9 @@ __device__ __forceinline__ void buffer_wave(unsigned char* smem, const MfmaLayou
 #pragma unroll
   for (int hq = 0; hq < GQ; ++hq) {
     const int seen = causal ? n_buf - q_len + 1 + ((row0 + hq) & (q_len - 1)) : n_buf;   // q_len is a power of two
-    const bool live = lane < BUF_WAVE_ROWS && r0 + lane < seen;
-    const float v = live ? s[hq] * scale : -INFINITY;
+    const float v = lane < BUF_WAVE_ROWS && r0 + lane < seen ? s[hq] * scale : -INFINITY;
     const float m = wave_max(v);
-    s[hq] = live ? __expf(v - m) : 0.0f;
+    s[hq] = v == -INFINITY ? 0.0f : __expf(v - m);   // (a score of -inf may be all that the wave has)
     const float l = wave_sum(s[hq]);
     if (lane == 0) {
       M.wstat[wave][hq][0] = m;   // -inf when the column sees none of the wave's rows

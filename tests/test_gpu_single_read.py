@@ -50,3 +50,19 @@ def test_single_read(H, gq, bits, g, rank, n, n_b, chunks, n_bufs, q_len, slab_c
             want = pu.go.decode_attn_multi(oc, pu.np16(q), pu.np16(Kb), pu.np16(Vb), n_buf, True)
         assert torch.equal(got, got[:1].expand_as(got)), "equal batch elements, equal results"
         print("  n_buf", n_buf, pu.check_attention(pu.np16(got[:1]), want), flush=True)
+
+
+@pytest.mark.parametrize("H,gq,n_buf,low", [(2, 1, 33, 32), (2, 4, 70, 64), (32, 1, 96, 64)])
+def test_buffer_rows_of_minus_infinity_weigh_nothing(H, gq, n_buf, low):
+    """Rows from `low` on score -inf: they are all that the last wave has, and the read is the one without them."""
+    print("case", H, gq, n_buf, low, flush=True)
+    gen = torch.Generator(device=DEV).manual_seed(n_buf)
+    t = lambda *shape: torch.randn(*shape, generator=gen, device=DEV).half()
+    gc, _ = pu.make_pair(1, H, H * gq, 2, 64, 20000, 128, 300, 1, 4)
+    gc.compress(t(1, H, 300, 128), t(1, H, 300, 128), 4, 3, None)
+    K, V, q = t(1, H, 128, 128), t(1, H, 128, 128), t(1, H * gq, 1, 128)
+    q[..., 0] = -1.0
+    want = gc.decode_attn(q, K, V, low)
+    K[:, :, low:, 0] = float("inf")
+    got = gc.decode_attn(q, K, V, n_buf)
+    assert torch.equal(got, want)
