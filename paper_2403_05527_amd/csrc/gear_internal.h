@@ -308,6 +308,13 @@ __device__ __forceinline__ uint32_t sub_sat_u16x2(uint32_t a, uint32_t b) {
 __device__ __forceinline__ uint32_t min_u16x2(uint32_t a, uint32_t b) {
   return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b)));
 }
+__device__ __forceinline__ uint32_t max_u16x2(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, a), __builtin_bit_cast(u16x2_t, b)));
+}
+// 0xFFFF in each half that is 1, 0 in one that is 0
+__device__ __forceinline__ uint32_t neg_u16x2(uint32_t z) {
+  return __builtin_bit_cast(uint32_t, u16x2_t{0, 0} - __builtin_bit_cast(u16x2_t, z));
+}
 // 1 in each half that is not 0.  (With the 1 in sight the compiler takes the minimum apart into two comparisons, two selects and a
 // permutation: 64 x 8192 Value rows of 1024 entries took 161 million vector instructions and 280 us, now 127 million and 240.)
 __device__ __forceinline__ uint32_t nonzero_u16x2(uint32_t z) {

@@ -45,11 +45,8 @@ __device__ __forceinline__ uint32_t slot16(const uint4& v, int e) {
 // h: 256 counters in LDS (all lanes of the wave see the final values).
 // Finds the bin where the count taken from the top reaches k (k >= 1):
 // bin, and `above` = entries in bins strictly above it.
-__device__ __forceinline__ void scan_from_top(const uint32_t* h, uint32_t k, int& bin, uint32_t& above) {
+__device__ __forceinline__ void scan_bins_from_top(const uint32_t (&hh)[4] /* counters 4 lane .. */, uint32_t k, int& bin, uint32_t& above) {
   const int lane = lane_id();
-  uint32_t hh[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) hh[i] = h[4 * lane + i];
   const uint32_t s = hh[0] + hh[1] + hh[2] + hh[3];
   const uint32_t suf = wave_incl_suffix(s);
   const unsigned long long m = __ballot(suf >= k);  // lanes 0..L
@@ -72,6 +69,11 @@ __device__ __forceinline__ void scan_from_top(const uint32_t* h, uint32_t k, int
   }
   bin = (int)lane_bcast_u((uint32_t)bsel, GEAR_WAVE_UNIFORM(L));
   above = lane_bcast_u(ab, GEAR_WAVE_UNIFORM(L));
+}
+__device__ __forceinline__ void scan_from_top(const uint32_t* h, uint32_t k, int& bin, uint32_t& above) {
+  const int lane = lane_id();
+  const uint32_t hh[4] = {h[4 * lane], h[4 * lane + 1], h[4 * lane + 2], h[4 * lane + 3]};
+  scan_bins_from_top(hh, k, bin, above);
 }
 __device__ __forceinline__ void scan_from_bottom(const uint32_t* h, uint32_t k, int& bin, uint32_t& below) {
   const int lane = lane_id();

@@ -72,10 +72,12 @@ __device__ __forceinline__ uint32_t wave_kth_largest(const uint32_t (&c)[R], uin
 }
 // The same through a histogram of the distances of the keys from the rough threshold (two keys per counter; hist: 256 words of LDS
 // private to the wave): the counter at which k is reached holds one to three entries as a rule, and those too many are dropped
-// one by one.  A chain of some 700 cycles, where the search above takes 10 to 26 dependent steps of 100 to 200: it is what is
-// left for lists whose threshold lies further off, or on a value that many entries share.
+// one by one.  Where many entries share the threshold, a second histogram finds the index among them (the lower halves are complements of
+// indices below `rows`).  A chain of some 700 cycles each, where the search above takes 10 to 26 dependent steps of 100 to 200: it is
+// what is left for lists whose threshold lies further off.  key_only: the lower half of the result does not matter.
 template <int R>
-__device__ __forceinline__ uint32_t wave_kth_by_bins(const uint32_t (&c)[R], uint32_t k, uint32_t rough, uint32_t* hist) {
+__device__ __forceinline__ uint32_t wave_kth_by_bins(const uint32_t (&c)[R], uint32_t k, uint32_t rough, uint32_t* hist, int rows,
+                                                     bool key_only = false) {
   const int lane = lane_id();
   wave_lds_sync();
   *reinterpret_cast<uint4*>(hist + 4 * lane) = make_uint4(0u, 0u, 0u, 0u);
@@ -85,7 +87,7 @@ __device__ __forceinline__ uint32_t wave_kth_by_bins(const uint32_t (&c)[R], uin
   for (int i = 0; i < R; ++i) {
     bin[i] = 0xFFFFu;   // below the rough threshold, or nothing there
     if (c[i] >= rough << 16) {
-      bin[i] = min((c[i] >> 16) - rough >> 1, 255u);
+      bin[i] = min(((c[i] >> 16) - rough) >> 1, 255u);
       atomicAdd(&hist[bin[i]], 1u);
     }
   }
@@ -94,16 +96,48 @@ __device__ __forceinline__ uint32_t wave_kth_by_bins(const uint32_t (&c)[R], uin
   uint32_t above;
   scan_from_top(hist, k, at, above);
   const uint32_t spare = (uint32_t)GEAR_WAVE_UNIFORM((int)hist[at]) - (k - above);   // entries of that counter that are too many
-  if (at == 255 || spare > 6u) return wave_kth_largest<R>(c, k, rough);
+  if (__builtin_expect(at == 255, 0)) return wave_kth_largest<R>(c, k, rough);
   uint32_t x = 0u;
+  if (__builtin_expect(spare <= 6u, 1)) {
 #pragma unroll 1
-  for (uint32_t i = 0; i <= spare; ++i) {   // the least of the counter's entries above the last one
-    uint32_t m = 0xFFFFFFFFu;
+    for (uint32_t i = 0; i <= spare; ++i) {   // the least of the counter's entries above the last one
+      uint32_t m = 0xFFFFFFFFu;
 #pragma unroll
-    for (int r = 0; r < R; ++r) m = min(m, bin[r] == (uint32_t)at && c[r] > x ? c[r] : 0xFFFFFFFFu);
-    m = row16_min_u(m);
-    x = min(min(lane_bcast_u(m, 0), lane_bcast_u(m, 16)), min(lane_bcast_u(m, 32), lane_bcast_u(m, 48)));
+      for (int r = 0; r < R; ++r) m = min(m, bin[r] == (uint32_t)at && c[r] > x ? c[r] : 0xFFFFFFFFu);
+      m = row16_min_u(m);
+      x = min(min(lane_bcast_u(m, 0), lane_bcast_u(m, 16)), min(lane_bcast_u(m, 32), lane_bcast_u(m, 48)));
+    }
+    return x;
   }
+  auto count = [&](uint32_t y) {
+    uint32_t n = 0;
+#pragma unroll
+    for (int i = 0; i < R; ++i) n += (uint32_t)__popcll(__ballot(c[i] >= y));
+    return n;
+  };
+  uint32_t key = rough + 2u * (uint32_t)at + 1u;   // which of the counter's two keys
+  const uint32_t upper = count(key << 16);
+  if (upper < k) --key;
+  if (key_only) return key << 16;
+  const uint32_t need = k - (upper < k ? upper : above);
+  const int shift = rows > 256 ? 24 - __clz(rows - 1) : 0;   // 256 counters for the indices
+  wave_lds_sync();
+  *reinterpret_cast<uint4*>(hist + 4 * lane) = make_uint4(0u, 0u, 0u, 0u);
+  wave_lds_sync();
+  uint32_t low = (256u << shift) - 0x10000u, from = key << 16;   // (lower halves lie in the last 256 << shift of theirs)
+  GEAR_PIN_VGPR(low);
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    const uint32_t off = c[i] - from;
+    if (off <= 0xFFFFu) atomicAdd(&hist[(off + low) >> shift], 1u);
+    GEAR_SCHED_FENCE();
+  }
+  wave_lds_sync();
+  scan_from_top(hist, need, at, above);
+  x = key << 16 | (0xFFFFu - ((256u - (uint32_t)at) << shift) + 1u);   // the last index of the counter
+#pragma unroll 1
+  for (int b = shift - 1; b >= 0; --b)
+    if (count(x + (1u << b)) >= k) x += 1u << b;
   return x;
 }
 // list: `total` words (index | fp16 value << 16).  Leaves the selected entries as bits of smask (which may overlap the list).
@@ -122,8 +156,8 @@ __device__ __forceinline__ void wave_rank_list(uint32_t* list, uint32_t total, i
       cb[i] = ~c;
     }
   }
-  const uint32_t xt = k_top > 0 ? wave_kth_by_bins<R>(ct, (uint32_t)k_top, tt, list) : 0xFFFFFFFFu;
-  const uint32_t xb = k_bot > 0 ? wave_kth_by_bins<R>(cb, (uint32_t)k_bot, tb, list) : 0xFFFFFFFFu;
+  const uint32_t xt = k_top > 0 ? wave_kth_by_bins<R>(ct, (uint32_t)k_top, tt, list, 32 * mask_words) : 0xFFFFFFFFu;
+  const uint32_t xb = k_bot > 0 ? wave_kth_by_bins<R>(cb, (uint32_t)k_bot, tb, list, 32 * mask_words) : 0xFFFFFFFFu;
   wave_lds_sync();
   for (int i = lane; i < mask_words; i += 64) smask[i] = 0u;
   wave_lds_sync();

@@ -1,6 +1,7 @@
 """Filter_s where it works on lists of candidates: the Value rows, whose rough threshold comes from the extremes of groups of entries,
-and the Key channels, whose rough threshold comes from a sample of the rows (of all of them up to 2048 or 4096).  The sizes are those at which the number of candidates reaches the ends of the lists and of their register counts, and the
-values those for which it does not fit (the selection then takes its other way): the set is the oracle's, entry by entry."""
+and the Key channels, whose rough threshold comes from a sample of the rows (of all of them up to 2048 or 4096).  The sizes are those at
+which the number of candidates reaches the ends of the lists and of their register counts, and the values those for which it does not
+fit (the selection then takes its other way): the set is the oracle's, entry by entry."""
 import numpy as np
 import pytest
 import torch
@@ -31,6 +32,21 @@ def _values(kind, shape, seed):
         x = x.sort(dim=2).values
     elif kind == "periodic":
         x = x + 4 * torch.sin(torch.arange(shape[2]) * (3.14159265 / 4))[:, None]
+    elif kind == "falling":
+        x = x.sort(dim=2, descending=True).values
+    elif kind == "coarse grid":  # a dozen values: ties of a tenth of a vector
+        x = torch.round(x * 2) / 2
+    elif kind == "constant":     # channels of one value, of either sign, among others
+        c = torch.arange(shape[3]) % 4
+        x = torch.where(c == 0, 1.5, torch.where(c == 1, -1.5, torch.where(c == 2, 0.0, x)))
+    elif kind == "two values":
+        x = torch.where(torch.rand(shape, generator=gen) < 0.3, 1.0, -2.0)
+    elif kind == "one end":      # ties at the top only, and in some channels at the bottom only
+        x = torch.where(torch.arange(shape[3]) % 2 == 0, x.clamp_max(1.0), x.clamp_min(-1.0))
+    elif kind == "half":         # more than half of the entries at the bottom's threshold, the top's far above all others
+        x = torch.where(torch.rand(shape, generator=gen) < 0.97, x.clamp_min(0.5), x.abs() * 3000)
+    elif kind == "steps":        # the value a function of the row: equal entries lie together
+        x = ((torch.arange(shape[2]) * 37 // shape[2]) % 8 - 3.5)[:, None].expand(shape)
     elif kind == "few vectors":  # ties in some token rows and channels only: waves that go both ways
         t = (torch.arange(shape[2]) % 37 == 0)[:, None]
         x = torch.where(t, torch.sign(x), x)
@@ -46,11 +62,6 @@ def _values(kind, shape, seed):
     ("normal", 1, 32, 513, 20000), ("normal", 1, 32, 300, 50000), ("normal", 1, 32, 257, 110000), ("grid", 1, 32, 301, 20000),
     ("cliff", 1, 32, 66, 20000), ("zeros", 1, 32, 67, 20000), ("one sign", 1, 32, 68, 20000), ("extremes", 1, 40, 65, 10000),
     ("few vectors", 1, 33, 257, 20000), ("normal", 1, 40, 130, 50000), ("normal", 1, 64, 65, 20000), ("normal", 1, 64, 65, 1), ("normal", 1, 41, 65, 500000),
-    # Key channels: the sample holds every row / one row less than there are, a ragged last round of rows, long lists, no room for a list
-    ("normal", 1, 2, 2047, 20000), ("normal", 1, 2, 2048, 20000), ("normal", 1, 2, 2049, 20000), ("normal", 1, 9, 2303, 10000), ("normal", 1, 2, 4096, 90000),
-    ("normal", 1, 2, 4097, 90000), ("grid", 1, 3, 4099, 20000), ("cliff", 1, 2, 2100, 20000), ("zeros", 1, 2, 2600, 20000), ("one sign", 1, 2, 1500, 30000),
-    ("extremes", 1, 2, 3000, 10000), ("few vectors", 1, 3, 5000, 20000), ("sorted", 1, 2, 6001, 20000), ("periodic", 1, 2, 8192, 20000),
-    ("normal", 1, 1, 32768, 1), ("normal", 1, 1, 32768, 10000), ("normal", 1, 2, 32767, 50000), ("grid", 1, 1, 20001, 20000), ("sorted", 1, 1, 32768, 30000),
 ])
 def test_sets_equal_the_oracle(kind, B, H, n, ppm):
     shape = (B, H, n, 128)
@@ -58,11 +69,46 @@ def test_sets_equal_the_oracle(kind, B, H, n, ppm):
     gc = gb.GearCache(gb.make_config(B, H, H, 2, 64, ppm, 20, n, 0, 2), "cuda:0")
     gc.compress(K, V, 0, 1, None)
     for which, x, want in ((0, K, go.filter_keys), (1, V, go.filter_values)):
-        mask, vals = (t.cpu().numpy() for t in gc.export_sparse(which))
-        x16 = x.cpu().numpy()
-        m = want(x16, ppm)
-        assert np.array_equal(mask.astype(bool), m), which
-        assert np.array_equal(vals.view(np.uint16)[m], x16.view(np.uint16)[m]), which
+        _check_sparse(gc, which, x, want, ppm)
+
+
+def _check_sparse(gc, which, x, want, ppm):
+    """The exported sparse matrix against the oracle's, the batch elements behind the first against that one where they are its copies."""
+    mask, vals = gc.export_sparse(which)
+    if x.stride(0) == 0:
+        assert torch.equal(mask, mask[:1].expand_as(mask)) and torch.equal(vals, vals[:1].expand_as(vals)), which
+        mask, vals, x = mask[:1], vals[:1], x[:1]
+    mask, vals, x16 = mask.cpu().numpy(), vals.cpu().numpy(), x.cpu().numpy()
+    m = want(x16, ppm)
+    assert np.array_equal(mask.astype(bool), m), which
+    assert np.array_equal(vals.view(np.uint16)[m], x16.view(np.uint16)[m]), which
+
+
+def _copies(x, rows=65536):
+    """x [1, H, n, 128] as a view of as many batch elements as it takes for more than `rows` Key rows."""
+    return x.expand(rows // (x.shape[1] * x.shape[2]) + 1, -1, -1, -1)
+
+
+# (the segments of 1025 to 8192 tokens are one batch element over and over: that many Key rows go by lists of candidates)
+@pytest.mark.parametrize("kind,H,n,ppm,group", [
+    # the sample holds every row (up to 2048, up to 4096 rows), one row of each stretch (up to 8192), eight channels per block (beyond)
+    ("normal", 2, 1025, 20000, 64), ("normal", 1, 2047, 20000, 64), ("normal", 2, 2048, 50000, 64), ("normal", 2, 2049, 20000, 64),
+    ("normal", 3, 2303, 10000, 64), ("normal", 1, 4096, 20000, 64), ("normal", 2, 4097, 20000, 64), ("normal", 1, 8192, 30000, 64),
+    ("normal", 1, 5000, 1000, 64), ("normal", 1, 32768, 1, 64), ("normal", 1, 32768, 10000, 64), ("normal", 2, 32767, 50000, 64),
+    # thresholds that many entries share: lists too long, at one end or at both; the channel a single value, or two
+] + [(kind, 1, n, 20000, group) for kind in ("grid", "coarse grid", "cliff", "zeros", "one sign", "extremes", "few vectors", "sorted", "falling", "periodic",
+                                             "constant", "two values", "one end", "half", "steps") for n, group in (
+    (1501, 64), (2048, 0), (4095, 0), (4096, 64), (6001, 0), (8192, 64), (9001, 0), (20001, 64), (32768, 0))])
+def test_key_sets_equal_the_oracle(kind, H, n, ppm, group):
+    K = _values(kind, (1, H, n, 128), n + H + ppm)
+    x = K if n > 8192 else _copies(K)
+    B = x.shape[0]
+    print("case", kind, B, H, n, ppm, group, flush=True)
+    gc = gb.GearCache(gb.make_config(B, H, H, 2, group, ppm, 20, n, 0, 2), "cuda:0")
+    gc.compress(x.contiguous(), torch.zeros_like(x).contiguous(), 0, 1, None)
+    _check_sparse(gc, 0, x, go.filter_keys, ppm)
+    if group == 0:
+        _check_one_group(gc, 0, K, go.filter_keys, ppm, 2)
 
 
 @pytest.mark.parametrize("kind,H,n,ppm", [("normal", 2, 300, 20000), ("normal", 2, 5000, 20000), ("grid", 2, 5000, 20000), ("normal", 1, 9001, 10000),
@@ -74,11 +120,16 @@ def test_one_group_per_vector(kind, H, n, ppm):
     gc = gb.GearCache(gb.make_config(1, H, H, 4, 0, ppm, 20, n, 0, 2), "cuda:0")
     gc.compress(K, V, 0, 1, None)
     for which, x, filt in ((0, K, go.filter_keys), (1, V, go.filter_values)):
-        x16 = x.cpu().numpy()
-        y = np.where(filt(x16, ppm), np.float16(0), x16).astype(np.float32)
-        axes = 2 if which == 0 else (1, 3)
-        lo, hi = y.min(axis=axes, keepdims=True), y.max(axis=axes, keepdims=True)
-        scale = ((hi - lo) / np.float32(15)).astype(np.float16)
-        _, got_scale, got_zero = (t.cpu().numpy().astype(np.float32) for t in gc.export_codes(which))
-        assert np.array_equal(got_scale, np.broadcast_to(scale, got_scale.shape).astype(np.float32)), which
-        assert np.array_equal(got_zero, np.broadcast_to(lo, got_zero.shape).astype(np.float32)), which
+        _check_one_group(gc, which, x, filt, ppm, 4)
+
+
+def _check_one_group(gc, which, x, filt, ppm, bits):
+    """The (scale, zero) of the first batch element's vectors, outliers counted as 0."""
+    x16 = x.cpu().numpy()
+    y = np.where(filt(x16, ppm), np.float16(0), x16).astype(np.float32)
+    axes = 2 if which == 0 else (1, 3)
+    lo, hi = y.min(axis=axes, keepdims=True), y.max(axis=axes, keepdims=True)
+    scale = ((hi - lo) / np.float32(2 ** bits - 1)).astype(np.float16)
+    _, got_scale, got_zero = (t[:1].cpu().numpy().astype(np.float32) for t in gc.export_codes(which))
+    assert np.array_equal(got_scale, np.broadcast_to(scale, got_scale.shape).astype(np.float32)), which
+    assert np.array_equal(got_zero, np.broadcast_to(lo, got_zero.shape).astype(np.float32)), which
