@@ -319,11 +319,15 @@ hipError_t launch_k_select(const uint16_t* K, const Dims& dm, int n, int k_top, 
   // Lists of candidates, where they fit (a ratio of a few per cent) and the work fills the chip.  A call at rank 0 and 2 %, before
   // and after: 512 slabs x 8192 tokens 1382 -> 1239 us, 128 x 20000 1184 -> 855, 32 x 32768 514 -> 421, 512 x 4096 630 -> 596, 1280 x 2048
   // 763 -> 731; 8 x 8192 64 -> 67 and 32 x 2048 42.5 -> 43, hence the bound on the rows.  Up to 1024 tokens the barriers between the phases
-  // of a short vector cost more than its histograms do (512 x 1024: 164 against 178), and at 5 % the lists are so long that it is even
-  // up to 8192 tokens (512 x 8192: 1947 and 1952; 128 x 12000: 893 against 764).
+  // of a short vector cost more than its histograms do (512 x 1024: 164 against 178).  Up to 8192 tokens, where the other way reads the
+  // column once too, the line lies between 5 % (512 x 8192: 1947 and 1952, 256 x 6000 898 -> 844) and 10 % (256 x 6000 928 against 954,
+  // 1024 x 3000 1496 against 1588); beyond, 5 % is 893 -> 764 for 128 x 12000.
   StreamPlan p;
-  if (mask && (n > 8192 || (n > 1024 && (long long)dm.B * dm.H * n > GEAR_STREAM_MIN_ROWS))) {
+  const int slabs = dm.B * dm.H;
+  if (mask && (n > 8192 || (n > 1024 && (long long)slabs * n > GEAR_STREAM_MIN_ROWS && 100LL * (k_top + k_bot) <= 6LL * n))) {
     const bool rest = dm.kcvt != 0;
+    // (blocks of 8 channels where those of 16 are too few to go round: 3 x 9000 tokens 64.4 -> 53.6, 61.0 from a channel-major copy)
+    const bool wide = n <= 8192 || 8 * slabs >= 128;
 #define GEAR_STREAM(PC, NB, ONCE, LDS)                                                       \
   do {                                                                                       \
     if (stream_plan(PC, NB, ONCE, n, k_top, k_bot, rest, LDS, p))                                  \
@@ -331,7 +335,7 @@ hipError_t launch_k_select(const uint16_t* K, const Dims& dm, int n, int k_top, 
   } while (0)
     if (n <= 2048) GEAR_STREAM(2, 8, true, 80 * 1024);
     else if (n <= 4096) GEAR_STREAM(2, 16, true, 80 * 1024);
-    else GEAR_STREAM(2, 8, false, 80 * 1024);
+    else if (wide) GEAR_STREAM(2, 8, false, 80 * 1024);
     GEAR_STREAM(1, 8, false, LDS_PER_CU);
 #undef GEAR_STREAM
   }

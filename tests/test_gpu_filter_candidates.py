@@ -95,6 +95,10 @@ def _copies(x, rows=65536):
     ("normal", 2, 1025, 20000, 64), ("normal", 1, 2047, 20000, 64), ("normal", 2, 2048, 50000, 64), ("normal", 2, 2049, 20000, 64),
     ("normal", 3, 2303, 10000, 64), ("normal", 1, 4096, 20000, 64), ("normal", 2, 4097, 20000, 64), ("normal", 1, 8192, 30000, 64),
     ("normal", 1, 5000, 1000, 64), ("normal", 1, 32768, 1, 64), ("normal", 1, 32768, 10000, 64), ("normal", 2, 32767, 50000, 64),
+    # sixteen channels per block beyond 8192 tokens; a ratio for which the vectors stay in registers
+    ("normal", 16, 8195, 20000, 64), ("cliff", 17, 8193, 20000, 0), ("normal", 1, 4096, 60000, 64), ("normal", 1, 4096, 61000, 64),
+    # beyond 8192 tokens ties at a ratio for which the lists have no room: from a channel-major copy
+    ("grid", 1, 9001, 150000, 64), ("cliff", 2, 16385, 200000, 0), ("constant", 1, 8193, 300000, 64),
     # thresholds that many entries share: lists too long, at one end or at both; the channel a single value, or two
 ] + [(kind, 1, n, 20000, group) for kind in ("grid", "coarse grid", "cliff", "zeros", "one sign", "extremes", "few vectors", "sorted", "falling", "periodic",
                                              "constant", "two values", "one end", "half", "steps") for n, group in (
