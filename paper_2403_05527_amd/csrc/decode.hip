@@ -188,7 +188,7 @@ __global__ __launch_bounds__(128) void decode_combine_kernel(const float* __rest
   out[(size_t)row * D + c] = (uint16_t)f2h(o / L);
 }
 
-constexpr int CUS = 256;
+constexpr int CUS = GEAR_CUS;
 
 // Whether a read goes through the single-launch kernel: `slabs` blocks of nwaves waves, against slabs * nblocks blocks of four
 // waves and the merge's launch.  The second launch is 3 to 4 us; what the single block costs is that all its waves share one CU's
@@ -202,7 +202,7 @@ constexpr int CUS = 256;
 // Beyond 1024 slabs the split kernel's whole blocks of prefill rows are as good (2048 slabs, 4 bits, 512 + 1: 50.1 -> 52.0), but
 // not its nearly empty ones (100 tokens: 39.9 -> 16.8).
 static bool single_read(int nwaves, int max_waves, int slabs, int nblocks, int columns, size_t lds) {
-  if (nwaves > max_waves || lds > LDS_PER_CU) return false;
+  if (nwaves > max_waves || nwaves > GEAR_SINGLE_WAVES || lds > LDS_PER_CU) return false;
   if (slabs > 4 * CUS) return nwaves <= 4;
   const int here = nwaves * ((slabs + CUS - 1) / CUS), split = 4 * ((slabs * nblocks + CUS - 1) / CUS);
   if (nwaves > 12 && (slabs > 2 * CUS || here > split + 2)) return false;
@@ -313,7 +313,7 @@ static hipError_t launch_decode_t(const Dims& dm, const SegView& k0, const SegVi
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((decode_split_kernel<BITS, GQ, LG>), dim3(s.nblocks, blocks), dim3(256), lds, st, dm, k0, v0, cs, q, Kbuf, Vbuf,
                      n_buf, n_buf_cap, (k0.n + MFMA_TS - 1) / MFMA_TS, s.pp, s.rc, s.odd_rank, q_len, causal, plan.lparts, partial);
-  if (s.nblocks > 32)
+  if (s.nblocks > GEAR_MERGE_AT_ONCE)
     hipLaunchKernelGGL(decode_combine_kernel<true>, dim3(dm.B * dm.Hq), dim3(128), 0, st, (const float*)partial, s.nblocks, out);
   else
     hipLaunchKernelGGL(decode_combine_kernel<false>, dim3(dm.B * dm.Hq), dim3(128), 0, st, (const float*)partial, s.nblocks, out);

@@ -84,6 +84,13 @@
 #ifndef GEAR_STREAM_MIN_ROWS
 #define GEAR_STREAM_MIN_ROWS 65536
 #endif
+// Compute units; waves of a block that reads a slab in one launch, at most; records of a query row beyond which the merge requests them
+// all at once.  (The CPU stand-in lowers them so that its small cases are read by every kernel.)
+#ifndef GEAR_CUS
+#define GEAR_CUS 256
+#define GEAR_SINGLE_WAVES 16
+#define GEAR_MERGE_AT_ONCE 32
+#endif
 // Resident blocks of the quantization kernel with its Gram accumulators on the whole chip: two on each of the 256 CUs.  (The
 // CPU stand-in lowers it so that its small cases walk strips of several tiles.)
 #ifndef GEAR_BLOCK_SLOTS

@@ -252,6 +252,11 @@ inline void launch(const void* kernel, const char* name, dim3 grid, dim3 block, 
 #define __builtin_amdgcn_rcpf(x) (1.0f / (x))
 #define GEAR_ROWS_MIN_TOKENS 64   // the small emulated cases take the token-row kernels too
 #define GEAR_STREAM_MIN_ROWS 3000   // the same for the Key selection by lists of candidates
+#ifndef GEAR_CUS
+#define GEAR_CUS 1                // reads in one launch (at most four waves) and split ones, of all numbers of columns; both merges
+#define GEAR_SINGLE_WAVES 4
+#define GEAR_MERGE_AT_ONCE 3
+#endif
 #ifndef GEAR_BLOCK_SLOTS
 #define GEAR_BLOCK_SLOTS 16       // and strips of two tiles and more
 #endif

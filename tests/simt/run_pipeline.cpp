@@ -5,6 +5,7 @@
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
+#include <hip/hip_runtime.h>
 #include "gear.h"
 static void* rd(const char* dir, const char* name, int idx) {
   char p[512];
@@ -22,6 +23,9 @@ static void wr(const char* dir, const char* name, const void* v, size_t bytes) {
 #define CK(x) do { int s_ = (x); if (s_ != GEAR_OK) { fprintf(stderr, "%s -> %s\n", #x, gear_strerror(s_)); return 3; } } while (0)
 int main(int argc, char** argv) {
   const char* dir = argv[1];
+  simt::observer = [](const char* kernel, dim3 grid, dim3 block, size_t) {
+    fprintf(stderr, "launch %s grid %u x %u block %u\n", kernel + (kernel[0] == '('), grid.x, grid.y, block.x);
+  };
   int B, H, Hq, bits, g, ppm, n, rank, nchunks, chunk_n, rank_chunk, n_buf, n_buf_cap, iters, flags = 0, n_lowrank = -1;
   char p[512]; snprintf(p, sizeof p, "%s/meta.txt", dir);
   FILE* f = fopen(p, "r");

@@ -1,13 +1,15 @@
 """The library's kernels and launchers, compiled as plain C++ against the CPU stand-in
 for the HIP device environment in tests/simt/ and run under the address sanitizer:
-one small end-to-end case (prefill compress, one chunk, decode attention over cache +
-buffer, decompress) through the C ABI, compared with the oracle.  This checks the host
+small end-to-end cases (prefill compress, one chunk, decode attention over cache +
+buffer, decompress) through the C ABI and the Key selection by itself, compared with the oracle.  This checks the host
 logic (grids, LDS sizes, arena and workspace layout) and that no kernel reads or
 writes outside its buffers or its LDS; it does not replace the GPU parity tests (the
 emulation knows nothing of the real compiler's code or the hardware's timing)."""
 import os
+import re
 import shutil
 import subprocess
+from concurrent.futures import ThreadPoolExecutor
 
 import numpy as np
 import pytest
@@ -38,25 +40,32 @@ def build(tmp_path_factory):
     out = tmp_path_factory.mktemp("simt")
     # -ffp-contract=fast: the host compiler may fuse every multiply-add it finds, except where the sources
     # switch contraction off (the quantizer's decision sequence), which the bit-exact code comparison checks
-    flags = ["-std=c++17", "-O1", "-g", "-ffp-contract=fast", "-fsanitize=address", "-fno-omit-frame-pointer", "-pthread",
+    flags = ["-std=c++17", "-O1", "-gline-tables-only", "-ffp-contract=fast", "-fsanitize=address", "-fno-omit-frame-pointer", "-pthread",
              "-I", SIMT, "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
-    def objects(names):
+    def objects(names, extra=()):
         procs = []
+        suffix = ".d.o" if extra else ".o"
         for s in names:
             src = ["-x", "c++", "-c", os.path.join(CSRC, s + ".hip")] if s in SOURCES else ["-c", os.path.join(SIMT, s + ".cpp")]
-            procs.append(subprocess.Popen([cxx] + src + ["-o", str(out / (s + ".o"))] + flags, stderr=subprocess.PIPE, text=True))
+            procs.append(subprocess.Popen([cxx] + src + ["-o", str(out / (s + suffix))] + flags + list(extra), stderr=subprocess.PIPE,
+                                          text=True))
         for p in procs:
             err = p.communicate()[1]
             assert p.returncode == 0, err[-3000:]
-        return [str(out / (s + ".o")) for s in names]
+        return [str(out / (s + suffix)) for s in names]
 
     common = objects(SOURCES + ["simt_rt"])
 
-    def program(name):
+    def program(name, device=False):
+        """device: the choice of a read's launch as on the device (the stand-in lowers its limits for the small cases)."""
         exe = str(out / name)
         if not os.path.exists(exe):
-            r = subprocess.run([cxx] + common + objects([name]) + ["-o", exe] + flags, capture_output=True, text=True)
+            parts = list(common)
+            if device:
+                parts[SOURCES.index("decode")] = objects(["decode"], ["-O0", "-fno-sanitize=address", "-DGEAR_CUS=256", "-DGEAR_SINGLE_WAVES=16",
+                                                                      "-DGEAR_MERGE_AT_ONCE=32"])[0]
+            r = subprocess.run([cxx] + parts + objects([name]) + ["-o", exe] + flags, capture_output=True, text=True)
             assert r.returncode == 0, r.stderr[-3000:]
         return exe
     return program
@@ -68,7 +77,7 @@ def emulator(build):
 
 
 def test_dynamic_lds_is_raised_on_every_device(build):
-    r = subprocess.run([build("check_devices")], capture_output=True, text=True, timeout=120)
+    r = subprocess.run([build("check_devices", device=True)], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stderr
 
 
@@ -86,7 +95,7 @@ def test_dynamic_lds_is_raised_on_every_device(build):
 def test_read_is_launched_as_planned(build, size, launch):
     """The choice of the kernel and that of the parts rest on the same LDS size: where one block's LDS does not hold the single
     launch, the parts are those that are best without it."""
-    r = subprocess.run([build("list_reads")], input=size + "\n", capture_output=True, text=True, timeout=120)
+    r = subprocess.run([build("list_reads", device=True)], input=size + "\n", capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stderr
     kernel, parts, lds = r.stdout.split()
     assert kernel + " " + parts == launch and int(lds) <= 160 * 1024
@@ -107,7 +116,8 @@ def test_workspace_holds_exactly_the_most_strips(tmp_path, slots):
     assert r.returncode == 0, r.stderr
 
 
-@pytest.mark.parametrize("B,H,Hq,n,bits,g,ppm,rank,n_buf,per_head,chunk_n,n_b,n_lowrank", [
+# B, H, Hq, n, bits, g, ppm, rank, n_buf, per_head, chunk_n, n_b, n_lowrank
+CASES = [
     (1, 4, 8, 290, 2, 64, 20000, 4, 5, False, 20, 20, -1),     # the method as stated; n > 256: Gram-matrix power iteration
     (1, 2, 2, 140, 4, 0, 30000, 2, 3, True, 20, 20, -1),       # per-vector groups and the per-head Value Filter
     (1, 8, 8, 70, 2, 64, 20000, 2, 3, False, 20, 20, -1),      # eight KV heads: Value token rows of 1024 entries, four per wave
@@ -124,12 +134,13 @@ def test_workspace_holds_exactly_the_most_strips(tmp_path, slots):
     # low-rank term begins inside a strip's second tile):
     (1, 1, 1, 390, 4, 32, 50000, 2, 3, False, 20, 20, -1),     # groups of 32, long overflow lists
     (1, 1, 1, 390, 2, 0, 20000, 4, 3, True, 20, 20, 250),      # per-vector groups, the per-head Value Filter, a late low-rank term
-])
-def test_pipeline_under_address_sanitizer(emulator, tmp_path, B, H, Hq, n, bits, g, ppm, rank, n_buf, per_head, chunk_n, n_b,
-                                          n_lowrank):
+]
+
+
+def _run_case(exe, d, B, H, Hq, n, bits, g, ppm, rank, n_buf, per_head, chunk_n, n_b, n_lowrank):
+    """Writes a case's inputs to d and runs it: (the process's result, the oracle's cache, the inputs of its reads)."""
     w = gw.Workload("emu", B=B, H_kv=H, H_q=Hq, n=n, bits=bits, group=g, outlier_ppm=ppm, rank=rank,
                     rank_chunk=2, n_b=n_b, steps=1, seed=5)
-    d = str(tmp_path)
     a = lambda t: t.numpy()
     oc = go.OracleCache(B, H, Hq, 128, bits, g, ppm, per_head)
     K, V, ib = a(gw.make_keys(w, n, 0)), a(gw.make_values(w, n, 0)), a(gw.make_init_B(w, rank, 0))
@@ -150,8 +161,30 @@ def test_pipeline_under_address_sanitizer(emulator, tmp_path, B, H, Hq, n, bits,
     q2.tofile(os.path.join(d, "q2.bin"))
     with open(os.path.join(d, "meta.txt"), "w") as f:
         f.write(" ".join(str(x) for x in [B, H, Hq, bits, g, ppm, n, rank, 1, chunk_n, 2, n_buf, n_b, 3, 1 if per_head else 0, n_lowrank]) + "\n")
-    r = subprocess.run([emulator, d], capture_output=True, text=True, timeout=900,
+    r = subprocess.run([exe, d], capture_output=True, text=True, timeout=900,
                        env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0"))
+    return r, oc, q, q2, Kb, Vb
+
+
+LAUNCHED = set()   # the kernels that this module's runs have launched
+
+
+@pytest.fixture(scope="module")
+def pipeline_runs(request, emulator, tmp_path_factory):
+    def one(case):
+        d = str(tmp_path_factory.mktemp("case"))
+        return (d,) + _run_case(emulator, d, *case)
+    selected = {tuple(i.callspec.params["case"]) for i in request.session.items
+                if getattr(i, "originalname", "") == "test_pipeline_under_address_sanitizer"}
+    pool = ThreadPoolExecutor(3)   # (an emulated run is bound by its barriers: a few at a time)
+    return {c: pool.submit(one, c) for c in CASES if c in selected}
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
+def test_pipeline_under_address_sanitizer(pipeline_runs, case):
+    B, H, Hq, n, bits, g, ppm, rank, n_buf, per_head, chunk_n, n_b, n_lowrank = case
+    d, r, oc, q, q2, Kb, Vb = pipeline_runs[case].result()
+    LAUNCHED.update(re.findall(r"^launch (\w+)", r.stderr, re.M))
     assert r.returncode == 0, r.stderr[-4000:]
     assert "AddressSanitizer" not in r.stderr
     out = np.fromfile(os.path.join(d, "out.bin"), np.float16).reshape(B, Hq, 1, 128)
@@ -195,3 +228,61 @@ def test_pipeline_under_address_sanitizer(emulator, tmp_path, B, H, Hq, n, bits,
     if 2 * (Hq // H) <= 8 and n_buf >= 2:
         out2 = np.fromfile(os.path.join(d, "out2.bin"), np.float16).reshape(B, Hq, 2, 128)
         pu.check_attention(out2, go.decode_attn_multi(oc, q2, Kb, Vb, n_buf, True), "two query rows")
+
+
+SELECTIONS = [   # kind of values, slabs, tokens, outliers in ppm, per-vector groups
+    ("normal", 1, 3003, 20000, 1),          # the sample is the whole segment
+    ("normal", 1, 5003, 20000, 0),          # ... is one row of each stretch, 16 channels per block
+    ("normal", 1, 9001, 10000, 1),          # ... 8 channels per block
+    ("cliff", 1, 3003, 20000, 1), ("two channels", 1, 4100, 20000, 0), ("coarse grid", 1, 5003, 20000, 1), ("one sign", 1, 3003, 20000, 0),
+    ("constant", 1, 9001, 20000, 0), ("falling", 1, 4100, 20000, 1), ("grid", 1, 9001, 150000, 0),   # the last: from a channel-major copy
+]
+
+
+@pytest.fixture(scope="module")
+def selection_runs(request, build, tmp_path_factory):
+    exe = build("select_keys")
+
+    def one(case):
+        kind, slabs, n, ppm, per_vector = case
+        K = pu.values_of_kind(kind, (1, slabs, n, 128), n + ppm).numpy()
+        f = str(tmp_path_factory.mktemp("keys") / "k")
+        K.tofile(f)
+        return K, f, subprocess.run([exe], input="%s %d %d %d %d\n" % (f, slabs, n, ppm, per_vector), capture_output=True, text=True,
+                                    timeout=900, env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0"))
+    selected = {tuple(i.callspec.params["case"]) for i in request.session.items if getattr(i, "originalname", "") == "test_key_selection_under_address_sanitizer"}
+    pool = ThreadPoolExecutor(3)
+    return {c: pool.submit(one, c) for c in SELECTIONS if c in selected}
+
+
+@pytest.mark.parametrize("case", SELECTIONS, ids=lambda c: "-".join(map(str, c)))
+def test_key_selection_under_address_sanitizer(selection_runs, case):
+    kind, slabs, n, ppm, per_vector = case
+    K, f, r = selection_runs[case].result()
+    assert r.returncode == 0 and "AddressSanitizer" not in r.stderr, r.stderr[-4000:]
+    LAUNCHED.update(re.findall(r"^launch (\w+)", r.stdout, re.M))
+    got = np.unpackbits(np.fromfile(f + ".mask", np.uint8).reshape(1, slabs, n, 16), axis=-1, bitorder="little").astype(bool)
+    want = go.filter_keys(K, ppm)
+    assert np.array_equal(got, want)
+    if per_vector:
+        y = np.where(want, np.float16(0), K).astype(np.float32)
+        lo, hi = y.min(axis=2), y.max(axis=2)
+        sz = np.fromfile(f + ".sz", np.float16).reshape(1, slabs, 128, 2).astype(np.float32)
+        assert np.array_equal(sz[..., 0], ((hi - lo) / np.float32(3)).astype(np.float16).astype(np.float32))
+        assert np.array_equal(sz[..., 1], lo)
+
+
+NOT_EMULATED = {"gram_sum_kernel",                                            # eight partial Gram matrices and more per slab
+                "pi_sweep_kernel", "pi_update_kernel", "pi_finish_kernel"}    # a single round
+
+
+def test_every_kernel_ran(request):
+    """The cases above run each kernel of the library, those of both ways to read among them."""
+    if sum(getattr(i, "originalname", "").endswith("under_address_sanitizer") for i in request.session.items) < len(CASES) + len(SELECTIONS):
+        pytest.skip("not all cases were selected")
+    kernels = set()
+    for f in sorted(os.listdir(CSRC)):
+        with open(os.path.join(CSRC, f)) as src:
+            kernels |= set(re.findall(r"__global__(?:\s+__launch_bounds__\((?:[^()]|\([^()]*\))*\))?\s+void\s+(\w+)\(", src.read()))
+    assert len(kernels) > 15
+    assert kernels - LAUNCHED == NOT_EMULATED

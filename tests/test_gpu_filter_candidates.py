@@ -8,49 +8,13 @@ import torch
 
 from oracle import gear_oracle as go
 from paper_2403_05527_amd import binding as gb
+from tests import parity_util as pu
 
 pytestmark = pytest.mark.gpu
 
 
 def _values(kind, shape, seed):
-    gen = torch.Generator().manual_seed(seed)
-    x = torch.randn(shape, generator=gen)
-    if kind == "grid":           # about fifty values: a threshold is shared by up to a few per cent of a vector
-        x = torch.round(x * 8) / 8
-    elif kind == "cliff":        # the wanted entries and many more share one value at either end
-        u = torch.rand(shape, generator=gen)
-        x = torch.where(u < 0.1, 3.0, torch.where(u > 0.9, -3.0, x.clamp(-2, 2)))
-    elif kind == "zeros":        # most entries are zeros of both signs, the wanted ones few
-        u = torch.rand(shape, generator=gen)
-        x = torch.where(u < 0.99, torch.sign(torch.randn(shape, generator=gen)) * 0.0, x * 10)
-    elif kind == "one sign":     # a bottom threshold at +0
-        x = x.clamp_min(0.0) * torch.where(torch.rand(shape, generator=gen) < 0.5, 1.0, -0.0)
-    elif kind == "extremes":     # the largest finite values and denormals
-        u = torch.rand(shape, generator=gen)
-        x = torch.where(u < 0.02, 65504.0, torch.where(u > 0.98, -65504.0, x * 1e-7))
-    elif kind == "sorted":       # a channel's largest entries all lie together, none in most stretches of the sample
-        x = x.sort(dim=2).values
-    elif kind == "periodic":
-        x = x + 4 * torch.sin(torch.arange(shape[2]) * (3.14159265 / 4))[:, None]
-    elif kind == "falling":
-        x = x.sort(dim=2, descending=True).values
-    elif kind == "coarse grid":  # a dozen values: ties of a tenth of a vector
-        x = torch.round(x * 2) / 2
-    elif kind == "constant":     # channels of one value, of either sign, among others
-        c = torch.arange(shape[3]) % 4
-        x = torch.where(c == 0, 1.5, torch.where(c == 1, -1.5, torch.where(c == 2, 0.0, x)))
-    elif kind == "two values":
-        x = torch.where(torch.rand(shape, generator=gen) < 0.3, 1.0, -2.0)
-    elif kind == "one end":      # ties at the top only, and in some channels at the bottom only
-        x = torch.where(torch.arange(shape[3]) % 2 == 0, x.clamp_max(1.0), x.clamp_min(-1.0))
-    elif kind == "half":         # more than half of the entries at the bottom's threshold, the top's far above all others
-        x = torch.where(torch.rand(shape, generator=gen) < 0.97, x.clamp_min(0.5), x.abs() * 3000)
-    elif kind == "steps":        # the value a function of the row: equal entries lie together
-        x = ((torch.arange(shape[2]) * 37 // shape[2]) % 8 - 3.5)[:, None].expand(shape)
-    elif kind == "few vectors":  # ties in some token rows and channels only: waves that go both ways
-        t = (torch.arange(shape[2]) % 37 == 0)[:, None]
-        x = torch.where(t, torch.sign(x), x)
-    return x.to(torch.float16).to("cuda:0")
+    return pu.values_of_kind(kind, shape, seed).to("cuda:0")
 
 
 @pytest.mark.parametrize("kind,B,H,n,ppm", [
@@ -101,7 +65,7 @@ def _copies(x, rows=65536):
     ("grid", 1, 9001, 150000, 64), ("cliff", 2, 16385, 200000, 0), ("constant", 1, 8193, 300000, 64),
     # thresholds that many entries share: lists too long, at one end or at both; the channel a single value, or two
 ] + [(kind, 1, n, 20000, group) for kind in ("grid", "coarse grid", "cliff", "zeros", "one sign", "extremes", "few vectors", "sorted", "falling", "periodic",
-                                             "constant", "two values", "one end", "half", "steps") for n, group in (
+                                             "constant", "two values", "one end", "half", "steps", "two channels") for n, group in (
     (1501, 64), (2048, 0), (4095, 0), (4096, 64), (6001, 0), (8192, 64), (9001, 0), (20001, 64), (32768, 0))])
 def test_key_sets_equal_the_oracle(kind, H, n, ppm, group):
     K = _values(kind, (1, H, n, 128), n + H + ppm)

@@ -146,10 +146,10 @@ def test_heavy_ties_and_constant_vectors(n):
 @pytest.mark.parametrize("n,g,ties", [(1100, 64, False), (2500, 64, True), (4101, 128, False), (8192, 64, True),
                                       (8461, 64, False), (8461, 0, True), (12000, 128, True)])
 def test_key_selection_paths_by_segment_length(n, g, ties):
-    """The Key Filter (Eq. 4 along the token axis) takes a different kernel by segment length: channel vectors
-    in registers (1025 .. 8192 tokens, three sizes) and, beyond, a channel-major copy of the keys read from
-    global memory.  Element-wise against the oracle at ragged lengths; `ties`: values on a coarse grid, so
-    that the threshold value is shared by many entries and the lowest-index rule decides, with one constant head."""
+    """The Key Filter (Eq. 4 along the token axis) takes a different kernel by segment length: few channel vectors of 1025 .. 8192 tokens
+    stay in registers (three sizes), beyond that lists of candidates are ranked (many vectors of up to 8192 tokens, and what has no room
+    for lists: test_gpu_filter_candidates.py).  Element-wise against the oracle at ragged lengths; `ties`: values on a coarse grid, so
+    that the threshold value is shared by many entries and the lowest-index rule decides, with a few constant channels."""
     bits = 4 if g == 0 else 2
     w = small_workload(B=1, H_kv=2, H_q=2, n=n, bits=bits, g=g, ppm=20000, rank=2, seed=n + g)
     say("case key selection", w, "ties", ties)

@@ -46,7 +46,7 @@ def test_random_valid_configuration(seed):
 def test_random_long_segment(seed):
     """Prefill segments of 2049..9000 tokens (one batch element, one or two KV heads, so that the oracle
     stays fast): the register-resident Key selection with 5..16 chunks and, past 8192 tokens, the
-    selection from the channel-major copy; several strips per slab in the Gram pass."""
+    selection by lists of candidates; several strips per slab in the Gram pass."""
     r = random.Random(2000 + seed)
     w, kw = draw(100 + seed)
     w = dataclasses.replace(w, B=1, H_kv=r.choice([1, 2]), n=r.choice([r.randint(2049, 9000), 8192 + r.randint(-1, 700)]))

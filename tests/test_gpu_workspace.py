@@ -55,7 +55,8 @@ def outputs(cfg, segs, rank, iters, n_lowrank, fill):
     (1, 3, 1, 2, 64, 20000, 255, [65, 255, 100], 2, 8, 3, None, False),        # 65..256 tokens: tensor by tensor
     (1, 2, 4, 4, 0, 20000, 20, [700, 20], 1, 2, 1, None, True),                # a single round
     (1, 2, 1, 2, 64, 20000, 20, [500, 20], 1, 0, 1, None, False),              # no low-rank term
-    (1, 2, 1, 2, 128, 10000, 20, [8200, 20], 1, 4, 3, None, False),            # a channel-major copy of the keys
+    (1, 2, 1, 2, 128, 10000, 20, [8200, 20], 1, 4, 3, None, False),            # more than 8192 tokens
+    (1, 2, 1, 2, 128, 150000, 20, [8200, 20], 1, 4, 3, None, False),           # with a channel-major copy of the keys
     (1, 1, 1, 2, 0, 0, 20, [8200, 20], 1, 2, 1, None, False),                  # the same without outliers, and a single round
     (1, 2, 1, 2, 64, 20000, 20, [9001], 0, 0, 3, None, True),
     (1, 3, 1, 2, 32, 20000, 20, [1100, 20], 1, 4, 3, 333, True),               # the low-rank term on the last rows
