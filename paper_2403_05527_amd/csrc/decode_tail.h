@@ -230,7 +230,7 @@ __device__ __forceinline__ void buffer_wave(unsigned char* smem, const MfmaLayou
     const int seen = causal ? n_buf - q_len + 1 + ((row0 + hq) & (q_len - 1)) : n_buf;   // q_len is a power of two
     const float v = lane < BUF_WAVE_ROWS && r0 + lane < seen ? s[hq] * scale : -INFINITY;
     const float m = wave_max(v);
-    s[hq] = v == -INFINITY ? 0.0f : __expf(v - m);   // (a score of -inf may be all that the wave has)
+    s[hq] = __expf(v - (m == -INFINITY ? 0.0f : m));   // (a score of -inf, like a row that is not seen, weighs nothing)
     const float l = wave_sum(s[hq]);
     if (lane == 0) {
       M.wstat[wave][hq][0] = m;   // -inf when the column sees none of the wave's rows
