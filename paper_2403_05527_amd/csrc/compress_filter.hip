@@ -305,7 +305,7 @@ template <int PC, int NB, bool ONCE>
 static hipError_t launch_k_select_stream(const uint16_t* K, const Dims& dm, int n, int k_top, int k_bot, const StreamPlan& p, uint4* mask,
                                          uint32_t* zero, int zero_count, const SegView& sv, hipStream_t st) {
   static std::atomic<uint64_t> lds_raised{0};
-  const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(k_select_stream_kernel<PC, NB, ONCE>), lds_raised, LDS_PER_CU);
+  const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(k_select_stream_kernel<PC, NB, ONCE>), lds_raised, p.lds, LDS_PER_CU);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_select_stream_kernel<PC, NB, ONCE>), dim3((D / (8 * PC)) * dm.B * dm.H), dim3(STREAM_THREADS), p.lds, st, K, n, p.L, dm.B * dm.H,
                      k_top, k_bot, p.j_top, p.j_bot, p.cap, mask, zero, zero_count, dm.kcvt ? sv.sz : (uint32_t*)nullptr, sv.ng_cap,

@@ -190,7 +190,7 @@ __global__ __launch_bounds__(128) void decode_combine_kernel(const float* __rest
 
 constexpr int CUS = GEAR_CUS;
 
-// Whether a read goes through the single-launch kernel: `slabs` blocks of nwaves waves, against slabs * nblocks blocks of four
+// Whether a read goes through the single-launch kernel, if its LDS fits: `slabs` blocks of nwaves waves, against slabs * nblocks blocks of four
 // waves and the merge's launch.  The second launch is 3 to 4 us; what the single block costs is that all its waves share one CU's
 // vector issue, which a small batch spreads over several.  So the line is drawn at the waves the fullest CU gets beyond the other
 // kernel's, times what a wave issues (850 vector instructions at one column, 1750 at four).  Measured, split and merge -> single:
@@ -201,8 +201,8 @@ constexpr int CUS = GEAR_CUS;
 // the other kernel's CU, and few rounds of blocks (1024 slabs, 1400 + 2 tokens: 41.6 -> 49.6; 512 slabs 27.4 -> 27.2).
 // Beyond 1024 slabs the split kernel's whole blocks of prefill rows are as good (2048 slabs, 4 bits, 512 + 1: 50.1 -> 52.0), but
 // not its nearly empty ones (100 tokens: 39.9 -> 16.8).
-static bool single_read(int nwaves, int max_waves, int slabs, int nblocks, int columns, size_t lds) {
-  if (nwaves > max_waves || nwaves > GEAR_SINGLE_WAVES || lds > LDS_PER_CU) return false;
+static bool single_read(int nwaves, int max_waves, int slabs, int nblocks, int columns) {
+  if (nwaves > max_waves || nwaves > GEAR_SINGLE_WAVES) return false;
   if (slabs > 4 * CUS) return nwaves <= 4;
   const int here = nwaves * ((slabs + CUS - 1) / CUS), split = 4 * ((slabs * nblocks + CUS - 1) / CUS);
   if (nwaves > 12 && (slabs > 2 * CUS || here > split + 2)) return false;
@@ -248,6 +248,7 @@ static size_t single_lds(const ReadShape& s) {
 struct ReadPlan {
   int lparts;
   bool single;
+  size_t lds;   // of the single launch
 };
 // Fewer columns per wave make the wave's chain of steps shorter and the codes are unpacked once per part, so a small grid is read
 // faster by more parts and a large one by fewer.  The times are a model of measured ones, in microseconds: a lone block on a CU
@@ -267,14 +268,18 @@ static ReadPlan read_plan(const ReadShape& s) {
       {{11.8f, 1.9f, 10.0f, 3.0f, 0.75f}, {12.0f, 3.1f, 10.0f, 4.0f, 1.0f}, {15.6f, 4.75f, 12.0f, 3.0f, 1.7f}, {22.0f, 8.3f, 17.0f, 0.0f, 3.6f}},
       {{12.3f, 2.5f, 10.0f, 2.0f, 1.05f}, {13.6f, 4.3f, 10.5f, 3.0f, 1.4f}, {17.8f, 5.8f, 14.0f, 3.0f, 2.1f}, {25.8f, 10.0f, 21.0f, 0.0f, 4.3f}}};
   float best = 0.0f;
-  ReadPlan plan{0, false};
+  ReadPlan plan{0, false, 0};
   for (int p = 0; (s.columns >> p) > 0; ++p) {
     const int c = s.columns >> p, lc = c == 8 ? 3 : c >> 1;
     const long long blocks = (long long)s.slabs << p;
     if (p > 0 && blocks > 65535) break;   // a dimension of the grid
     const Cost& t = costs[s.bits == 4 ? 1 : 0][lc];
-    const size_t lds = c == 8 ? single_lds<8>(s) : c == 4 ? single_lds<4>(s) : c == 2 ? single_lds<2>(s) : single_lds<1>(s);
-    const bool single = single_read(s.waves(), c == 8 ? SINGLE_WAVES<8> : SINGLE_WAVES<1>, (int)blocks, s.nblocks, c, lds);
+    bool single = single_read(s.waves(), c == 8 ? SINGLE_WAVES<8> : SINGLE_WAVES<1>, (int)blocks, s.nblocks, c);
+    size_t lds = 0;
+    if (single) {
+      lds = c == 8 ? single_lds<8>(s) : c == 4 ? single_lds<4>(s) : c == 2 ? single_lds<2>(s) : single_lds<1>(s);
+      single = lds <= LDS_PER_CU;
+    }
     float us;
     if (single) {
       us = t.base + t.wave * (float)(s.waves() * ((blocks + CUS - 1) / CUS));
@@ -287,7 +292,7 @@ static ReadPlan read_plan(const ReadShape& s) {
     us *= 1.0f + 0.04f * (float)p;
     if (p == 0 || us < best) {
       best = us;
-      plan = ReadPlan{p, single};
+      plan = ReadPlan{p, single, lds};
     }
   }
   return plan;
@@ -300,16 +305,16 @@ static hipError_t launch_decode_t(const Dims& dm, const SegView& k0, const SegVi
   const int blocks = s.slabs << plan.lparts;          // per 512 tokens: a block for each slab and part of its columns
   if (plan.single) {
     static std::atomic<uint64_t> lds_raised{0};
-    const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(decode_single_kernel<BITS, GQ, LG>), lds_raised, LDS_PER_CU);
+    const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(decode_single_kernel<BITS, GQ, LG>), lds_raised, plan.lds, LDS_PER_CU);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((decode_single_kernel<BITS, GQ, LG>), dim3(blocks), dim3(64 * s.waves()), single_lds<GQ>(s), st, dm, k0, v0, cs, q,
+    hipLaunchKernelGGL((decode_single_kernel<BITS, GQ, LG>), dim3(blocks), dim3(64 * s.waves()), plan.lds, st, dm, k0, v0, cs, q,
                        Kbuf, Vbuf, n_buf, n_buf_cap, s.npw, s.ncw, s.pp, s.rc, s.odd_rank, q_len, causal, plan.lparts, out);
     return hipGetLastError();
   }
   size_t lds = (size_t)mfma_layout<GQ>(BITS, dm.g, k0.rank, v0.rank, s.rc, s.odd_rank != 0).total;
   if (lds < sizeof(TailSmem<GQ>)) lds = sizeof(TailSmem<GQ>);
   static std::atomic<uint64_t> lds_raised{0};
-  const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(decode_split_kernel<BITS, GQ, LG>), lds_raised, LDS_PER_CU);
+  const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(decode_split_kernel<BITS, GQ, LG>), lds_raised, lds, LDS_PER_CU);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((decode_split_kernel<BITS, GQ, LG>), dim3(s.nblocks, blocks), dim3(256), lds, st, dm, k0, v0, cs, q, Kbuf, Vbuf,
                      n_buf, n_buf_cap, (k0.n + MFMA_TS - 1) / MFMA_TS, s.pp, s.rc, s.odd_rank, q_len, causal, plan.lparts, partial);

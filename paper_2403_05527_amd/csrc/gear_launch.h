@@ -5,10 +5,11 @@
 
 namespace gear {
 
-// Lets a kernel be launched with up to `bytes` of dynamic LDS on the current device.  The attribute belongs to a device's copy of the
-// kernel, so every device that a process works on gets it.  `raised`: one per kernel instance, a bit per device; two threads may both
-// raise it: harmless.
-inline hipError_t raise_dynamic_lds(const void* kernel, std::atomic<uint64_t>& raised, size_t bytes) {
+// Lets a kernel be launched with up to `bytes` of dynamic LDS on the current device, where the launch asks for more (`need`) than any
+// kernel may have without it.  The attribute belongs to a device's copy of the kernel, so every device that a process works on gets it.
+// `raised`: one per kernel instance, a bit per device; two threads may both raise it: harmless.
+inline hipError_t raise_dynamic_lds(const void* kernel, std::atomic<uint64_t>& raised, size_t need, size_t bytes) {
+  if (need <= 64 * 1024) return hipSuccess;
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;

@@ -1052,7 +1052,7 @@ __global__ __launch_bounds__(256) void pi_tiny_kernel(const uint16_t* __restrict
 template <int R>
 static hipError_t raise_solve_lds() {
   static std::atomic<uint64_t> lds_raised{0};
-  return raise_dynamic_lds(reinterpret_cast<const void*>(pi_solve_kernel<R>), lds_raised, sizeof(SolveSmem<R>));
+  return raise_dynamic_lds(reinterpret_cast<const void*>(pi_solve_kernel<R>), lds_raised, sizeof(SolveSmem<R>), sizeof(SolveSmem<R>));
 }
 
 // Keys' per-vector grouping: one group per segment
