@@ -19,6 +19,14 @@
 // The tile passes through LDS once, where the few outliers are looked up by row (Keys) or by channel (Values), put into
 // their slots and lists, and zeroed: the arithmetic per entry then needs no mask.
 //
+// What bounds it: vector issue (0.55 of the time; 13 to 14 instructions per entry) next to the matrix cores (0.26), with two waves per
+// SIMD, which is what the accumulators leave room for; some 170 of 800 us (64 x 8 heads x 8192 tokens, 2 % outliers) go to the loops over
+// the outliers' bits.  So little may wait: a wave's 32 rows are copied straight into LDS while it works on the tile before (a copy
+// needs no registers, of which there are none left), and nearly all of a tile's work is a wave's own: the four waves meet once per Key
+// tile (the extremes of groups of 64 and 128 tokens) and twice per Value tile (the bits by channel, the list).  With the rows in
+// registers and four or five barriers per tile 872 -> 800 us, 16 x 32 heads x 4096 tokens 449 -> 408, 7 x 40 x 1777 at 4 bits 160 -> 138.
+// (Slower: two outliers of a lane per step instead of one, 806 with a loop per lane, 835 with one for the wave: more branches.)
+//
 // A residual entry enters the contraction as two fp16 numbers, its leading part and what that leaves (22 bits
 // together), and a product as three MFMA terms (the lo lo' term is below fp32 resolution); accumulation is fp32.  The
 // leading parts alone are not enough: without orthonormalisation between the rounds the weaker directions of
@@ -94,38 +102,27 @@ template <bool IS_K, int BITS, int LG>
 struct QuantSmem;
 template <int BITS, int LG>
 struct QuantSmem<true, BITS, LG> {
-  static constexpr int NG = LG >= 7 ? 1 : QT >> LG;   // groups per tile
-  uint4 tile[QT][D / 8];
-  uint4 rowmask[QT];
+  static constexpr int WPG = LG >= 7 ? 4 : LG == 6 ? 2 : 1;   // waves (of 32 rows) that share a group
   uint4 slots[QT];
-  uint32_t red_mn[4][D / 2], red_mx[4][D / 2];        // a wave's min / max of its 32 rows, two channels per word
-  __attribute__((aligned(16))) uint2 par[NG][D];      // (scale, zero) as fp16, 1/scale
-  uint32_t ovf_cnt[32], ovf_off[32];                  // overflow lists of the strip's 64-token tiles
+  uint2 red[2 * 4 * D / 2];                           // a wave's (min, max) of its 32 rows, two channels per word; of this tile, of the last
+  __attribute__((aligned(16))) uint2 par[4][D];       // per wave: (scale, zero) as fp16, 1/scale
+  uint32_t ovf_cnt[64], ovf_off[64];                  // overflow entries of the strip's stretches of 32 rows
 };
 template <int BITS, int LG>
 struct QuantSmem<false, BITS, LG> {
   static constexpr int NG = D >> LG;                  // groups per row
-  uint4 tile[QT][D / 8];
-  uint4 rowmask[QT];
-  uint4 colmask[D];                                   // bit t of channel c's 128 bits
-  uint2 par[QT][NG];                                  // (scale, zero) as fp16, 1/scale
-  uint4 codes[QT * D * BITS / 128];                   // code words in operand order
+  uint2 rowmask[2 * QT];                              // the Filter per head
+  uint32_t colmask[4][D];                             // per wave: bit t of channel c's word = its row t
+  __attribute__((aligned(16))) uint2 par[NG * QT];    // [group][row]: (scale, zero) as fp16, 1/scale
+  uint4 codes[4][QT * D * BITS / 512];                // per wave: code words in operand order
   uint32_t list_off[2];
 };
 
+// One block's strip of slab blockIdx.y, 256 threads.  tile: LDS of its own (not part of s), which the next tile is copied into
+// while this one is worked on: with the two in one variable the compiler would wait for the copy at every access to s.
 template <bool IS_K, int BITS, int LG, bool GRAM>
-union QuantLds {
-  QuantSmem<IS_K, BITS, LG> s;
-  float red[GRAM ? GRAM_FLOATS : 4];
-};
-
-// One block's strip of slab blockIdx.y, 256 threads.
-template <bool IS_K, int BITS, int LG, bool GRAM>
-__device__ __forceinline__ void quant_body(QuantLds<IS_K, BITS, LG, GRAM>& sm, const QuantArgs& a) {
-  typedef QuantSmem<IS_K, BITS, LG> Smem;
-  constexpr int NG = Smem::NG;
+__device__ __forceinline__ void quant_body(uint4 (&tile)[QT][D / 8], QuantSmem<IS_K, BITS, LG>& s, const QuantArgs& a) {
   constexpr float QMAX = (float)((1 << BITS) - 1);
-  Smem& s = sm.s;
   const int slab = blockIdx.y, n = a.n;
   int tid = threadIdx.x;
   const int wave = GEAR_WAVE_UNIFORM(tid >> 6);
@@ -137,71 +134,60 @@ __device__ __forceinline__ void quant_body(QuantLds<IS_K, BITS, LG, GRAM>& sm, c
   const int b = slab / a.dm.H, h = slab - b * a.dm.H;
   const GEAR_BUF_T xb = GEAR_BUF_MAKE(a.X + (size_t)slab * n * D, (uint32_t)n * (D * 2));
   const GEAR_BUF_T mb = GEAR_BUF_MAKE(a.mask + (size_t)slab * n, filt && !vhead ? n * 16 : 0);   // (no bits yet: reads as 0)
-  uint16_t* tile16 = reinterpret_cast<uint16_t*>(&s.tile[0][0]);
+  uint16_t* tile16 = reinterpret_cast<uint16_t*>(&tile[0][0]);
   float one = 1.0f;
   GEAR_PIN_SGPR(one);   // fma(fp16 value, one, float) is one mixed-precision instruction: conversion and addition together
 
+  // A wave fetches its own 32 rows, straight into LDS, and each thread the bits of half a row (row tid / 2); no other wave touches
+  // them.  (Rows past the end: the last row once more; they are zeroed when they are read.)
+  uint2 mk;
+  auto fetch = [&](int base) {
+    mk = GEAR_BUF_LOAD8(mb, base * 16 + tid * 8);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int t = base + 32 * wave + 4 * i + (lane >> 4);
+      GEAR_DMA16(xb, (uint32_t)(t < n ? t : n - 1) * (D * 2) + oc * 16, &tile[32 * wave + 4 * i][0]);
+    }
+  };
+  fetch(t_begin);
+
   if constexpr (IS_K) {
     if (filt) {
-      // where the overflow lists of the strip's 64-token tiles go: one allocation per strip
+      // where the overflow entries of the strip's stretches of 32 rows go: one allocation per strip, a list per 64 rows
       const int ntile = (t_end - t_begin + TILE - 1) / TILE;
       for (int i = wave; i < ntile; i += 4) {
         const uint4 m = GEAR_BUF_LOAD16(mb, (t_begin + TILE * i + lane) * 16);
         const uint32_t tot = __popc(m.x) + __popc(m.y) + __popc(m.z) + __popc(m.w);
-        const uint32_t sum = lane_bcast_u(wave_incl_scan(tot > ELL_K ? tot - ELL_K : 0u), 63);
-        if (lane == 0) s.ovf_cnt[i] = sum;
+        const uint32_t inc = wave_incl_scan(tot > ELL_K ? tot - ELL_K : 0u);
+        const uint32_t first = lane_bcast_u(inc, 31), both = lane_bcast_u(inc, 63);
+        if (lane < 2) s.ovf_cnt[2 * i + lane] = lane == 0 ? first : both - first;
       }
       block_lds_sync();
       if (wave == 0) {
-        const uint32_t v = lane < ntile ? s.ovf_cnt[lane] : 0u;
-        const uint32_t inc = wave_incl_scan(v);
+        const uint32_t v = lane < 2 * ntile ? s.ovf_cnt[lane] : 0u;
+        const uint32_t inc = wave_incl_scan(v), pair = v + dpp_u<DPP_XOR1>(v);
         uint32_t off = 0;
         if (lane == 63) off = atomicAdd(&a.pool_ctr[slab], inc);
         off = lane_bcast_u(off, 63) + inc - v;
-        if (lane < ntile) {
+        if (lane < 2 * ntile) {
           s.ovf_off[lane] = off;
-          a.sv.sp_table[(size_t)slab * a.sv.ntile_cap + t_begin / TILE + lane] = make_uint2(off, v);
+          if ((lane & 1) == 0) a.sv.sp_table[(size_t)slab * a.sv.ntile_cap + t_begin / TILE + (lane >> 1)] = make_uint2(off, pair);
         }
       }
+      block_lds_sync();
     }
     if (LG == KLG_VEC) {   // per-vector grouping: the channel's one pair of this segment was found with its thresholds
-      if (tid < D) {
-        const GroupQ q = load_group(a.sv.sz[(size_t)slab * a.sv.ng_cap * D + tid]);
-        s.par[0][tid] = make_uint2(group_bits(q), __float_as_uint(q.inv));
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const GroupQ q = load_group(a.sv.sz[(size_t)slab * a.sv.ng_cap * D + lane + 64 * i]);
+        s.par[wave][lane + 64 * i] = make_uint2(group_bits(q), __float_as_uint(q.inv));
       }
-      block_lds_sync();
     }
   }
 
   floatx4 acc[GRAM ? GRAM_TILES : 1];
 #pragma unroll
   for (int i = 0; i < (GRAM ? GRAM_TILES : 1); ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-  // the eight row pieces of a thread and half a row's mask; rows past the end read as 0
-  uint32_t x[8][4];
-  uint2 mk;
-  auto load_row = [&](int base, int k) {
-    const uint4 v = GEAR_BUF_LOAD16(xb, (base + 8 * r0 + k) * (D * 2) + oc * 16);
-    x[k][0] = v.x; x[k][1] = v.y; x[k][2] = v.z; x[k][3] = v.w;
-  };
-  auto load_mask = [&](int base) { mk = GEAR_BUF_LOAD8(mb, base * 16 + tid * 8); };
-#pragma unroll
-  for (int k = 0; k < 8; ++k) load_row(t_begin, k);
-  load_mask(t_begin);
-
-  // Values: code words of the tile that starts at `base` from LDS to the arena (blocks of TB tokens, operand order);
-  // every word of a block that holds at least one token is written (rows past n carry code 0)
-  constexpr int TB = 128 / BITS;   // 64 (2 bits) or 32 (4 bits) tokens per block
-  auto copy_codes = [&](int base) {
-    if constexpr (!IS_K) {
-      uint4* dst = reinterpret_cast<uint4*>(a.sv.codes + ((size_t)slab * a.sv.nblk_cap + base / TB) * 512);
-#pragma unroll
-      for (int i = 0; i < QT * D * BITS / 128 / 256; ++i) {
-        const int p = tid + 256 * i;
-        if (base + (p >> 7) * TB < n) dst[p] = s.codes[p];
-      }
-    }
-  };
 
 #pragma unroll 1
   for (int base = t_begin; base < t_end; base += QT) {
@@ -211,41 +197,7 @@ __device__ __forceinline__ void quant_body(QuantLds<IS_K, BITS, LG, GRAM>& sm, c
     lane = tid & 63;
     r0 = tid >> 4;
     oc = tid & 15;
-    if constexpr (!IS_K) {
-      if (vhead && filt) {   // the Filter per head: the row's 16 lanes hold the whole vector
-#pragma unroll 1
-        for (int k = 0; k < 8; ++k) {
-          // (the row pieces are read again: a loop over registers could not stay rolled)
-          const uint4 v = GEAR_BUF_LOAD16(xb, (base + 8 * r0 + k) * (D * 2) + oc * 16);
-          const uint32_t kw[4] = {key16x2(v.x), key16x2(v.y), key16x2(v.z), key16x2(v.w)};
-          const ThreshPair tp = row16_thresholds(kw, oc, a.k_top, a.k_bot);
-          uint32_t f = 0;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) f |= (outlier(slot_key(kw, e), (uint32_t)(8 * oc + e), tp) ? 1u : 0u) << e;
-          const int t = base + 8 * r0 + k;
-          if (t >= n) f = 0u;
-          else reinterpret_cast<uint8_t*>(a.mask + (size_t)slab * n + t)[oc] = (uint8_t)f;
-          reinterpret_cast<uint8_t*>(&s.rowmask[8 * r0 + k])[oc] = (uint8_t)f;
-        }
-      }
-    }
-    if (!IS_K || filt) {
-      if (filt) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) s.tile[8 * r0 + k][oc] = make_uint4(x[k][0], x[k][1], x[k][2], x[k][3]);
-        if (!vhead) reinterpret_cast<uint2*>(s.rowmask)[tid] = mk;
-        if (tid < QT) {
-          uint32_t z = 0;
-          GEAR_PIN_VGPR(z);   // (not a register quadruple of zeros over the whole loop)
-          if constexpr (IS_K) s.slots[tid] = make_uint4(z, z, z, z);   // empty slots
-          else s.colmask[tid] = make_uint4(z, z, z, z);
-        }
-      }
-      block_lds_sync();
-    }
-    if constexpr (!IS_K) {
-      if (base > t_begin) copy_codes(base - QT);
-    }
+    GEAR_DMA_WAIT();
 
     // ---- the tile's outliers: into slots and lists, and out of the tile
     if constexpr (IS_K) {
@@ -254,20 +206,16 @@ __device__ __forceinline__ void quant_body(QuantLds<IS_K, BITS, LG, GRAM>& sm, c
       if (filt) {
         static_assert(ELL_K == 4, "the row's slots are stored as one 16-byte word");
         const int row = tid >> 1, half = tid & 1;
-        const uint4 m = s.rowmask[row];
-        const uint32_t lo = __popc(m.x) + __popc(m.y), hi = __popc(m.z) + __popc(m.w);
-        const uint32_t pre = half ? lo : 0u, cnt = half ? hi : lo;
+        reinterpret_cast<uint2*>(s.slots)[tid] = make_uint2(0, 0);   // empty slots
+        const uint32_t cnt = __popc(mk.x) + __popc(mk.y), other = dpp_u<DPP_XOR1>(cnt);
+        const uint32_t pre = half ? other : 0u;
         const uint32_t over = (pre + cnt > ELL_K ? pre + cnt - ELL_K : 0u) - (pre > ELL_K ? pre - ELL_K : 0u);
-        uint32_t off = s.ovf_off[(base - t_begin) / TILE + (tid >> 7)] + wave_incl_scan(over) - over;
-        if (wave & 1) {   // behind the entries of the tile's first 32 rows
-          const uint4 p = s.rowmask[row - 32];
-          const uint32_t tot = half ? 0u : __popc(p.x) + __popc(p.y) + __popc(p.z) + __popc(p.w);
-          off += lane_bcast_u(wave_incl_scan(tot > ELL_K ? tot - ELL_K : 0u), 63);
-        }
+        uint32_t off = s.ovf_off[(base - t_begin) / 32 + wave] + wave_incl_scan(over) - over;
         uint32_t* pool = a.sv.sp_pool + (size_t)slab * a.sv.pool_cap;
         uint32_t* slots = reinterpret_cast<uint32_t*>(&s.slots[row]);
         uint32_t s_i = pre;
-        uint64_t mm = half ? ((uint64_t)m.w << 32 | m.z) : ((uint64_t)m.y << 32 | m.x);
+        uint64_t mm = (uint64_t)mk.y << 32 | mk.x;
+        wave_lds_sync();
         while (mm != 0ull) {
           const int c = 64 * half + __ffsll((long long)mm) - 1;
           mm &= mm - 1ull;
@@ -280,71 +228,127 @@ __device__ __forceinline__ void quant_body(QuantLds<IS_K, BITS, LG, GRAM>& sm, c
           }
           ++s_i;
         }
-        block_lds_sync();
-        if (tid < QT && base + tid < n)
-          *reinterpret_cast<uint4*>(a.sv.ell + ((size_t)slab * a.sv.n_cap + base + tid) * ELL_K) = s.slots[tid];
+        wave_lds_sync();
+        const int t = 32 * wave + lane;
+        if (lane < 32 && base + t < n) *reinterpret_cast<uint4*>(a.sv.ell + ((size_t)slab * a.sv.n_cap + base + t) * ELL_K) = s.slots[t];
       }
     } else {
       // A channel of a 64-token tile: the first ELL_V in token order take its fixed slots, the rest go to the tile's
-      // overflow list, ordered (c, t).  The rows' bits are first sorted by channel.
+      // overflow list, ordered (c, t).  Two waves share the tile; each sorts the bits of its 32 rows by channel, and takes the
+      // entries of its rows.
+      if (vhead && filt) {   // the Filter per head: the row's 16 lanes hold the whole vector
+#pragma unroll 1
+        for (int k = 0; k < 8; ++k) {
+          const uint4 v = tile[8 * r0 + k][oc];
+          const uint32_t kw[4] = {key16x2(v.x), key16x2(v.y), key16x2(v.z), key16x2(v.w)};
+          const ThreshPair tp = row16_thresholds(kw, oc, a.k_top, a.k_bot);
+          uint32_t f = 0;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) f |= (outlier(slot_key(kw, e), (uint32_t)(8 * oc + e), tp) ? 1u : 0u) << e;
+          const int t = base + 8 * r0 + k;
+          if (t >= n) f = 0u;
+          else reinterpret_cast<uint8_t*>(a.mask + (size_t)slab * n + t)[oc] = (uint8_t)f;
+          reinterpret_cast<uint8_t*>(&s.rowmask[2 * (8 * r0 + k)])[oc] = (uint8_t)f;
+        }
+        wave_lds_sync();
+        mk = s.rowmask[tid];
+      }
       if (filt) {
-        static_assert(ELL_V == 2, "the channel's slots are stored as one 8-byte word");
+        static_assert(ELL_V == 2, "the channel's slots are one or the other of two words");
+        s.colmask[wave][lane] = s.colmask[wave][lane + 64] = 0u;
+        wave_lds_sync();
         {
-          const int row = tid >> 1, half = tid & 1;
-          const uint2 m = reinterpret_cast<const uint2*>(&s.rowmask[row])[half];
-          uint64_t mm = (uint64_t)m.y << 32 | m.x;
+          uint64_t mm = (uint64_t)mk.y << 32 | mk.x;
           while (mm != 0ull) {
-            const int c = 64 * half + __ffsll((long long)mm) - 1;
+            const int c = 64 * (lane & 1) + __ffsll((long long)mm) - 1;
             mm &= mm - 1ull;
-            atomicOr(&reinterpret_cast<uint32_t*>(&s.colmask[c])[row >> 5], 1u << (row & 31));
+            atomicOr(&s.colmask[wave][c], 1u << (lane >> 1));
           }
         }
-        block_lds_sync();
-        const int c = tid & (D - 1), th = tid >> 7;
-        const uint2 m = reinterpret_cast<const uint2*>(&s.colmask[c])[th];
-        const uint2 mo = reinterpret_cast<const uint2*>(&s.colmask[c ^ 64])[th];   // what the other wave of the tile sees
-        const uint32_t cnt = __popc(m.x) + __popc(m.y), cnto = __popc(mo.x) + __popc(mo.y);
-        const uint32_t over = cnt > ELL_V ? cnt - ELL_V : 0u, overo = cnto > ELL_V ? cnto - ELL_V : 0u;
-        const uint32_t inc = wave_incl_scan(over);
-        const uint32_t other = lane_bcast_u(wave_incl_scan(overo), 63), tot = lane_bcast_u(inc, 63) + other;
+        GEAR_DMA_BARRIER();
+        const int th = wave >> 1, odd = wave & 1;
+        const uint32_t lo0 = s.colmask[2 * th][lane], hi0 = s.colmask[2 * th + 1][lane];             // channel lane
+        const uint32_t lo1 = s.colmask[2 * th][lane + 64], hi1 = s.colmask[2 * th + 1][lane + 64];   // channel lane + 64
+        const uint32_t cnt0 = __popc(lo0) + __popc(hi0), cnt1 = __popc(lo1) + __popc(hi1);
+        const uint32_t over0 = cnt0 > ELL_V ? cnt0 - ELL_V : 0u, over1 = cnt1 > ELL_V ? cnt1 - ELL_V : 0u;
+        const uint32_t inc0 = wave_incl_scan(over0), inc1 = lane_bcast_u(inc0, 63) + wave_incl_scan(over1);
         const int tl = base / TILE + th;
-        if ((tid & (D - 1)) == 0) {
+        if (odd == 0 && lane == 63) {
+          const uint32_t tot = inc1;
           // a list that fits takes the tile's reserved region; a longer one is allocated behind the regions
           const uint32_t off = tot <= VPOOL_FIXED ? (uint32_t)(h * a.sv.ntile_cap + tl) * VPOOL_FIXED
                                                   : (uint32_t)(a.dm.H * a.sv.ntile_cap) * VPOOL_FIXED + atomicAdd(&a.pool_ctr[b], tot);
           if (TILE * tl < n) a.sv.sp_table[(size_t)slab * a.sv.ntile_cap + tl] = make_uint2(off, tot);
           s.list_off[th] = off;
         }
-        block_lds_sync();
-        uint32_t off = s.list_off[th] + ((wave & 1) ? other : 0u) + inc - over;
+        // my rows' entries of the two channels, in their order; s_i, off: the next one's place among the channel's, in the list
+        const uint32_t before0 = odd ? __popc(lo0) : 0u, before1 = odd ? __popc(lo1) : 0u;
+        uint64_t mm = odd ? ((uint64_t)hi1 << 32 | hi0) : ((uint64_t)lo1 << 32 | lo0);
+        GEAR_DMA_BARRIER();
+        const uint32_t list = s.list_off[th];
+        uint32_t off = list + inc0 - over0 + (before0 > ELL_V ? before0 - ELL_V : 0u), s_i = before0;
+        const uint32_t off1 = list + inc1 - over1 + (before1 > ELL_V ? before1 - ELL_V : 0u);
         uint32_t* pool = a.sv.sp_pool + (size_t)b * a.sv.pool_cap;
-        uint2 slot = make_uint2(0, 0);   // empty slots
-        uint32_t s_i = 0;
-        uint64_t mm = (uint64_t)m.y << 32 | m.x;
+        uint2 slot[2] = {make_uint2(0, 0), make_uint2(0, 0)};   // empty slots
+        uint32_t second = 0;   // at channel lane + 64
         while (mm != 0ull) {
-          const int t = __ffsll((long long)mm) - 1;
+          const uint32_t bit = (uint32_t)__ffsll((long long)mm) - 1u;
           mm &= mm - 1ull;
-          const int at = (TILE * th + t) * D + c;
+          if (bit >= 32u && second == 0u) {
+            second = 1u;
+            off = off1;
+            s_i = before1;
+          }
+          const int t = 32 * odd + (int)(bit & 31u), c = lane + 64 * (int)second, at = (TILE * th + t) * D + c;
           const uint32_t v = tile16[at];
           tile16[at] = 0;
           const uint32_t en = (uint32_t)t | ELL_VALID | (v << 16);
-          if (s_i == 0u) slot.x = en;
-          else if (s_i == 1u) slot.y = en;
-          else {
+          if (s_i >= ELL_V) {
             if (off < a.sv.pool_cap) pool[off] = (uint32_t)(t * D + c) | (v << 16);
             ++off;
+          } else if (second == 0u) {
+            if (s_i == 0u) slot[0].x = en;
+            else slot[0].y = en;
+          } else {
+            if (s_i == 0u) slot[1].x = en;
+            else slot[1].y = en;
           }
           ++s_i;
         }
-        if (TILE * tl < n) *reinterpret_cast<uint2*>(a.sv.ell + (((size_t)slab * a.sv.ntile_cap + tl) * D + c) * ELL_V) = slot;
+        wave_lds_sync();
+        if (TILE * tl < n) {
+          // of a channel's two slots the wave of the first rows stores those that its entries take, the other wave the rest
+          uint2* ell = reinterpret_cast<uint2*>(a.sv.ell + (((size_t)slab * a.sv.ntile_cap + tl) * D + lane) * ELL_V);
+          auto store = [&](uint2* p, uint32_t first, uint2 both) {   // first: entries of the first 32 rows
+            if (first >= 2u) {
+              if (!odd) *p = both;
+            } else if (first == 1u) {
+              reinterpret_cast<uint32_t*>(p)[odd] = odd ? both.y : both.x;
+            } else if (odd) {
+              *p = both;
+            }
+          };
+          store(ell, __popc(lo0), slot[0]);
+          store(ell + 64, __popc(lo1), slot[1]);
+        }
       }
-      block_lds_sync();
     }
-    if (filt) {
+    uint32_t x[8][4];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const uint4 v = tile[8 * r0 + k][oc];
+      x[k][0] = v.x; x[k][1] = v.y; x[k][2] = v.z; x[k][3] = v.w;
+    }
+    if constexpr (IS_K) {
+      GEAR_LDS_DRAIN();
+      if (base + QT < t_end) fetch(base + QT);   // block-uniform
+    }
+    if (ragged) {
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        const uint4 v = s.tile[8 * r0 + k][oc];
-        x[k][0] = v.x; x[k][1] = v.y; x[k][2] = v.z; x[k][3] = v.w;
+        const uint32_t keep = (uint32_t)((base + 8 * r0 + k - n) >> 31);   // all ones: a row before the end
+#pragma unroll
+        for (int w = 0; w < 4; ++w) x[k][w] &= keep;
       }
     }
     if (a.Yout) {
@@ -391,29 +395,31 @@ __device__ __forceinline__ void quant_body(QuantLds<IS_K, BITS, LG, GRAM>& sm, c
         uint32_t x01 = pk_max_f16(mx[0], mx[1]), x23 = pk_max_f16(mx[2], mx[3]);
         GEAR_LANE_SWAP16(n01, n23);
         GEAR_LANE_SWAP16(x01, x23);
-        const int w = ((lane >> 4) & 1) * 2 + (lane >> 5);
-        s.red_mn[wave][oc * 4 + w] = pk_min_f16(n01, n23);
-        s.red_mx[wave][oc * 4 + w] = pk_max_f16(x01, x23);
-        block_lds_sync();
-        constexpr int WPG = (1 << LG) / 32;   // waves per group
+        const int w = ((lane >> 4) & 1) * 2 + (lane >> 5), wpg = QuantSmem<true, BITS, LG>::WPG;
+        const int buf = (((base - t_begin) / QT) & 1) * (2 * D);
+        int at = buf + wave * (D / 2) + oc * 4 + w;
+        GEAR_PIN_VGPR(at);   // (one step from the array to the element, see quant_body's head)
+        s.red[at] = make_uint2(pk_min_f16(n01, n23), pk_max_f16(x01, x23));
+        // each wave makes the parameters of its own group, two channels per lane: what the next barrier would cost is more than
+        // that they are made by all waves of the group
+        if constexpr (wpg > 1) GEAR_DMA_BARRIER();
+        else wave_lds_sync();
+        const int first = wave & ~(wpg - 1), grp = (base + 32 * first) >> LG;
+        at = buf + first * (D / 2) + lane;
+        GEAR_PIN_VGPR(at);
+        uint2 ext = s.red[at];
 #pragma unroll
-        for (int i0 = 0; i0 < NG * D; i0 += 256) {
-          const int i = i0 + tid, gi = i >> 7, c = i & (D - 1);
-          if (i < NG * D) {
-            float fmn = INFINITY, fmx = -INFINITY;
-#pragma unroll
-            for (int wv = 0; wv < WPG; ++wv) {
-              fmn = fminf(fmn, h2f(reinterpret_cast<const uint16_t*>(s.red_mn[gi * WPG + wv])[c]));
-              fmx = fmaxf(fmx, h2f(reinterpret_cast<const uint16_t*>(s.red_mx[gi * WPG + wv])[c]));
-            }
-            const bool valid = base + (gi << LG) < n;
-            const GroupQ q = make_group_b<BITS>(valid ? fmn : 0.0f, valid ? fmx : 0.0f);
-            const uint32_t bits = group_bits(q);
-            s.par[gi][c] = make_uint2(bits, __float_as_uint(q.inv));
-            if (valid) a.sv.sz[((size_t)slab * a.sv.ng_cap + (base >> LG) + gi) * D + c] = bits;
-          }
+        for (int wv = 1; wv < wpg; ++wv) {
+          const uint2 o = s.red[at + wv * (D / 2)];
+          ext = make_uint2(pk_min_f16(ext.x, o.x), pk_max_f16(ext.y, o.y));
         }
-        block_lds_sync();
+        const bool valid = base + 32 * first < n;
+        if (!valid) ext = make_uint2(0, 0);
+        const GroupQ q0 = make_group_b<BITS>(h2f(ext.x & 0xFFFFu), h2f(ext.y & 0xFFFFu)), q1 = make_group_b<BITS>(h2f(ext.x >> 16), h2f(ext.y >> 16));
+        const uint2 bits = make_uint2(group_bits(q0), group_bits(q1));
+        *reinterpret_cast<uint4*>(&s.par[wave][2 * lane]) = make_uint4(bits.x, __float_as_uint(q0.inv), bits.y, __float_as_uint(q1.inv));
+        if (valid && wave == first) *reinterpret_cast<uint2*>(a.sv.sz + ((size_t)slab * a.sv.ng_cap + grp) * D + 2 * lane) = bits;
+        wave_lds_sync();
       }
     } else {
       // word k: (min, -max) of the thread's piece of row k
@@ -455,8 +461,8 @@ __device__ __forceinline__ void quant_body(QuantLds<IS_K, BITS, LG, GRAM>& sm, c
         if (a.dm.kcvt) q = load_group(t < n ? a.vsz[(size_t)b * n + t] : 0u);
         else q = make_group_b<BITS>(lo, hi);
         if (LG != 7 || (lane & 8) == 0) {
-          s.par[row][G] = make_uint2(group_bits(q), __float_as_uint(q.inv));
-          if (t < n) a.sv.sz[((size_t)slab * a.sv.n_cap + t) * NG + G] = group_bits(q);
+          s.par[G * QT + row] = make_uint2(group_bits(q), __float_as_uint(q.inv));
+          if (t < n) a.sv.sz[((size_t)slab * a.sv.n_cap + t) * (D >> LG) + G] = group_bits(q);
         }
       }
       wave_lds_sync();   // (a wave makes the parameters of its own 32 rows)
@@ -466,15 +472,19 @@ __device__ __forceinline__ void quant_body(QuantLds<IS_K, BITS, LG, GRAM>& sm, c
     uint32_t oph[GRAM ? 8 : 1][4], opl[GRAM ? 8 : 1][4];
     {
 #pragma clang fp contract(off)
-      const int gi = IS_K ? (LG >= 7 ? 0 : (8 * r0) >> (LG < 7 ? LG : 7)) : 0;
       constexpr int CPS = 16 / BITS;     // codes per 16 bits
       float cw[8];                       // Keys: 16 bits of codes of my row pieces
+      // Values: where my code words begin (2 bits: half words)
+      int code_at = BITS == 2 ? wave * 512 + ((((r0 >> 1) & 1) * 16 + 8 * (oc & 1)) * 8 + (oc >> 1)) * 2 + (r0 & 1)
+                              : wave * 512 + ((r0 & 3) * 16 + 8 * (oc & 1)) * 8 + (oc >> 1);
+      const int par_at = IS_K ? 0 : ((oc * 8) >> LG) * QT + 8 * r0;   // Values: my first row's parameters
+      if (!IS_K) GEAR_PIN_VGPR(code_at);
       const GEAR_BUF_T cbuf = GEAR_BUF_MAKE(a.sv.codes + (size_t)slab * a.sv.n_cap * (4 * BITS), IS_K ? (uint32_t)n * (16 * BITS) : 0u);
 #pragma unroll
       for (int w = 0; w < 4; ++w) {      // channels 2 w, 2 w + 1
         uint2 kp[2];                     // Keys: their parameters
         if constexpr (IS_K) {
-          const uint4 p = *reinterpret_cast<const uint4*>(&s.par[gi][oc * 8 + 2 * w]);
+          const uint4 p = *reinterpret_cast<const uint4*>(&s.par[wave][oc * 8 + 2 * w]);
           kp[0] = make_uint2(p.x, p.y);
           kp[1] = make_uint2(p.z, p.w);
         }
@@ -483,8 +493,9 @@ __device__ __forceinline__ void quant_body(QuantLds<IS_K, BITS, LG, GRAM>& sm, c
         for (int j = 0; j < 4; ++j) {    // rows 2 j, 2 j + 1
           uint2 vp[2];                   // Values: parameters of the two rows' channel group
           if constexpr (!IS_K) {
-            vp[0] = s.par[8 * r0 + 2 * j][(oc * 8) >> LG];
-            vp[1] = s.par[8 * r0 + 2 * j + 1][(oc * 8) >> LG];
+            const uint4 p = *reinterpret_cast<const uint4*>(s.par + par_at + 2 * j);
+            vp[0] = make_uint2(p.x, p.y);
+            vp[1] = make_uint2(p.z, p.w);
           }
 #pragma unroll
           for (int e2 = 0; e2 < 2; ++e2) {
@@ -510,6 +521,7 @@ __device__ __forceinline__ void quant_body(QuantLds<IS_K, BITS, LG, GRAM>& sm, c
               const uint32_t hi = pack_h2(res[0], res[1]);
               oph[e][j] = hi;
               opl[e][j] = pack_h2(__builtin_fmaf(h2f(hi & 0xFFFFu), -one, res[0]), __builtin_fmaf(h2f(hi >> 16), -one, res[1]));
+              if (!IS_K) GEAR_PIN_VGPR(opl[e][j]);   // (here, and not behind the code words: the residuals would have to be kept)
             }
           }
           if (GRAM && (IS_K || (j & 1))) GEAR_SCHED_FENCE();   // interleaved, the temporaries would not fit next to the accumulators
@@ -517,21 +529,36 @@ __device__ __forceinline__ void quant_body(QuantLds<IS_K, BITS, LG, GRAM>& sm, c
         if constexpr (!IS_K) {
 #pragma unroll
           for (int e2 = 0; e2 < 2; ++e2) {
-            // word (kg*16 + c%16)*8 + c/16 of a block holds channel c = 8 oc + e for the 32/b tokens of lane group kg
-            const int c16 = 8 * (oc & 1) + 2 * w + e2;
+            // word (kg*16 + c%16)*8 + c/16 of a block holds channel c = 8 oc + e for the 32/b tokens of lane group kg: the wave's
+            // 32 rows are two lane groups of a block of 64 (2 bits), or a block (4 bits)
             if (BITS == 2) {
-              const int word = (((r0 >> 1) & 3) * 16 + c16) * 8 + (oc >> 1);
-              reinterpret_cast<uint16_t*>(s.codes)[((r0 >> 3) * 512 + word) * 2 + (r0 & 1)] = (uint16_t)(uint32_t)cv[e2][0];
+              const int word = (2 * w + e2) * 8;
+              reinterpret_cast<uint16_t*>(s.codes)[code_at + word * 2] = (uint16_t)(uint32_t)cv[e2][0];
             } else {
-              const int word = ((r0 & 3) * 16 + c16) * 8 + (oc >> 1);
-              reinterpret_cast<uint32_t*>(s.codes)[(r0 >> 2) * 512 + word] = (uint32_t)cv[e2][0] | ((uint32_t)cv[e2][1] << 16);
+              const int word = (2 * w + e2) * 8;
+              reinterpret_cast<uint32_t*>(s.codes)[code_at + word] = (uint32_t)cv[e2][0] | ((uint32_t)cv[e2][1] << 16);
             }
           }
         }
       }
     }
+    if constexpr (!IS_K) {
+      // the wave's code words; every word of a block that holds at least one token is written (rows past n carry code 0)
+      wave_lds_sync();
+      constexpr int TB = 128 / BITS, WPB = TB / 32;   // tokens of a block: 64 (2 bits) or 32 (4 bits); waves that share it
+      const int blk = base / TB + wave / WPB;
+      uint4* dst = reinterpret_cast<uint4*>(a.sv.codes + ((size_t)slab * a.sv.nblk_cap + blk) * 512) + (wave % WPB) * (128 / WPB);
+      if (blk * TB < n) {
+#pragma unroll
+        for (int i = 0; i < 2 / WPB; ++i) dst[lane + 64 * i] = s.codes[wave][lane + 64 * i];
+      }
+      // (from here on the tile's work touches no LDS: the compiler, which for the Values does not tell the copy from its reads of the
+      // parameters, would wait for the copy there)
+      GEAR_LDS_DRAIN();
+      if (base + QT < t_end) fetch(base + QT);   // block-uniform
+    }
 
-    // ---- the 36 tiles of G: r r' = hi hi' + hi lo' + lo hi'; the next tile's rows are requested as registers fall free
+    // ---- the 36 tiles of G: r r' = hi hi' + hi lo' + lo hi'
     if constexpr (GRAM) {
       const int t0 = base + 8 * r0;
       if (ragged || base < a.t_lr) {   // block-uniform: rows past the end, rows that take no part in the low-rank term
@@ -543,76 +570,49 @@ __device__ __forceinline__ void quant_body(QuantLds<IS_K, BITS, LG, GRAM>& sm, c
           for (int e = 0; e < 8; ++e) { oph[e][j] &= keep; opl[e][j] &= keep; }
         }
       }
-      const bool more = base + QT < t_end;   // block-uniform
       GEAR_SCHED_FENCE();
-      int ti = 0;
+      // (a tile's three terms are as far apart as the order allows: the next one on the same accumulators would wait for the last)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const quant_h8 ah = __builtin_bit_cast(quant_h8, make_uint4(oph[e][0], oph[e][1], oph[e][2], oph[e][3]));
-        const quant_h8 al = __builtin_bit_cast(quant_h8, make_uint4(opl[e][0], opl[e][1], opl[e][2], opl[e][3]));
+      for (int e0 = 0; e0 < 8; e0 += 4) {   // operands e0 .. e0 + 3 with all from them on: 26 and 10 tiles
 #pragma unroll
-        for (int f = e; f < 8; ++f) {
-          const quant_h8 bh = __builtin_bit_cast(quant_h8, make_uint4(oph[f][0], oph[f][1], oph[f][2], oph[f][3]));
-          const quant_h8 bl = __builtin_bit_cast(quant_h8, make_uint4(opl[f][0], opl[f][1], opl[f][2], opl[f][3]));
-          acc[ti] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bh, acc[ti], 0, 0, 0);
-          acc[ti] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, bl, acc[ti], 0, 0, 0);
-          acc[ti] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, bh, acc[ti], 0, 0, 0);
-          ++ti;
-        }
-        GEAR_SCHED_FENCE();
-        if (more && e >= 4) {   // two, one, one and four rows after e = 4 .. 7 (the operands of e and below are dead by then)
-          const int first = e == 4 ? 0 : e - 3, last = e == 7 ? 8 : e - 2;
+        for (int term = 0; term < 3; ++term) {
 #pragma unroll
-          for (int k = 0; k < 8; ++k)
-            if (k >= first && k < last) load_row(base + QT, k);
+          for (int e = e0; e < e0 + 4; ++e) {
+            const auto& oa = term == 2 ? opl : oph;
+            const quant_h8 va = __builtin_bit_cast(quant_h8, make_uint4(oa[e][0], oa[e][1], oa[e][2], oa[e][3]));
+#pragma unroll
+            for (int f = e; f < 8; ++f) {
+              const auto& ob = term == 1 ? opl : oph;
+              const quant_h8 vb = __builtin_bit_cast(quant_h8, make_uint4(ob[f][0], ob[f][1], ob[f][2], ob[f][3]));
+              const int ti = e * 8 - e * (e - 1) / 2 + f - e;
+              acc[ti] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va, vb, acc[ti], 0, 0, 0);
+            }
+          }
+          GEAR_SCHED_FENCE();
         }
       }
-      if (more) load_mask(base + QT);
     }
-  }
-  if constexpr (!IS_K) {
-    block_lds_sync();
-    copy_codes(((t_end - 1 - t_begin) & ~(QT - 1)) + t_begin);
   }
 
-  // ---- the four waves' tiles, added in wave order (a fixed order: results do not vary from run to run); a few tiles
-  // at a time, so that the LDS reads in flight stay few
+  // ---- the four waves' tiles, added in wave order (a fixed order: results do not vary from run to run): four tiles at a time, those of
+  // the next round into the other half of the LDS
   if constexpr (GRAM) {
-    float* red = sm.red;
+    float* red = reinterpret_cast<float*>(&tile[0][0]);   // [2][4][1024]
     float* out = a.gram + ((size_t)slab * gridDim.x + blockIdx.x) * GRAM_FLOATS;
-    block_lds_sync();
-    if (wave == 0) {
+    static_assert(GRAM_TILES % 4 == 0 && sizeof(tile) == 2 * 4 * 1024 * sizeof(float), "two rounds of four tiles of four waves");
+    GEAR_DMA_BARRIER();
 #pragma unroll
-      for (int ti = 0; ti < GRAM_TILES; ++ti)
+    for (int r = 0; r < GRAM_TILES / 4; ++r) {
+      float* part = red + (r & 1) * 4096;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) red[ti * 256 + i * 64 + lane] = acc[ti][i];
-    }
-    block_lds_sync();
-#pragma unroll 1
-    for (int w = 1; w < 3; ++w) {
-      if (wave == w) {
+      for (int ti = 0; ti < 4; ++ti)
 #pragma unroll
-        for (int ti = 0; ti < GRAM_TILES; ++ti) {
-          float v[4];
+        for (int i = 0; i < 4; ++i) part[wave * 1024 + ti * 256 + i * 64 + lane] = acc[4 * r + ti][i];
+      GEAR_DMA_BARRIER();
+      floatx4 sum = *reinterpret_cast<const floatx4*>(part + 4 * tid);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) v[i] = red[ti * 256 + i * 64 + lane];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) red[ti * 256 + i * 64 + lane] = v[i] + acc[ti][i];
-          GEAR_PIN_VGPR(v[0]);   // keeps the tiles' reads from being hoisted above each other's writes en bloc
-        }
-      }
-      block_lds_sync();
-    }
-    if (wave == 3) {
-#pragma unroll
-      for (int ti = 0; ti < GRAM_TILES; ++ti) {
-        float v[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = red[ti * 256 + i * 64 + lane];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) out[ti * 256 + i * 64 + lane] = v[i] + acc[ti][i];
-        GEAR_PIN_VGPR(v[0]);
-      }
+      for (int w = 1; w < 4; ++w) sum += *reinterpret_cast<const floatx4*>(part + w * 1024 + 4 * tid);
+      *reinterpret_cast<floatx4*>(out + r * 1024 + 4 * tid) = sum;
     }
   }
 }
@@ -620,8 +620,9 @@ __device__ __forceinline__ void quant_body(QuantLds<IS_K, BITS, LG, GRAM>& sm, c
 // One tensor, with Y for the solvers that go one tensor at a time.  grid (ceil(n / 128), B*H), block 256.
 template <bool IS_K, int BITS, int LG>
 __global__ __launch_bounds__(256, 3) void quant_kernel(QuantArgs a) {
-  __shared__ QuantLds<IS_K, BITS, LG, false> sm;
-  quant_body<IS_K, BITS, LG, false>(sm, a);
+  __shared__ uint4 tile[QT][D / 8];
+  __shared__ QuantSmem<IS_K, BITS, LG> s;
+  quant_body<IS_K, BITS, LG, false>(tile, s, a);
 }
 
 // Keys and Values of a call whose low-rank terms are solved together: the blocks of z = 0 take the Keys, those of z = 1 the
@@ -631,12 +632,13 @@ __global__ __launch_bounds__(256, 3) void quant_kernel(QuantArgs a) {
 // 565 -> 520).  With the chip full it makes no difference (64 x 8 heads x 8192 tokens: 2640 and 2635 us).  grid (ceil(n / strip), B*H, 2), block 256.
 template <int BITS, int KLG, int VLG, bool GRAM>
 __global__ __launch_bounds__(256, (GRAM ? 2 : 3)) void quant_pair_kernel(QuantArgs k, QuantArgs v) {
+  __shared__ uint4 tile[QT][D / 8];
   __shared__ union {
-    QuantLds<true, BITS, KLG, GRAM> k;
-    QuantLds<false, BITS, VLG, GRAM> v;
-  } sm;
-  if (blockIdx.z == 0) quant_body<true, BITS, KLG, GRAM>(sm.k, k);
-  else quant_body<false, BITS, VLG, GRAM>(sm.v, v);
+    QuantSmem<true, BITS, KLG> k;
+    QuantSmem<false, BITS, VLG> v;
+  } s;
+  if (blockIdx.z == 0) quant_body<true, BITS, KLG, GRAM>(tile, s.k, k);
+  else quant_body<false, BITS, VLG, GRAM>(tile, s.v, v);
 }
 
 template <bool IS_K, int BITS, int LG>

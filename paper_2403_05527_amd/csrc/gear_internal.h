@@ -54,6 +54,23 @@
   } while (0)
 #endif
 
+// Global memory to LDS without a stop in registers: each lane fetches 16 bytes at `off` of a buffer view, and lane l's piece lands at
+// lds + 16 l (lds: the same in all lanes).  The compiler takes such a copy for a write of 16 bytes at `lds`, so whoever uses it
+// orders it by hand: GEAR_DMA_WAIT before the LDS is read, GEAR_LDS_DRAIN before LDS that was read is copied over, and between waves
+// GEAR_DMA_BARRIER, a block barrier for LDS traffic that lets copies and global loads run on (a fence would wait for the copies).
+#ifndef GEAR_DMA16
+#define GEAR_DMA16(b, off, lds) \
+  __builtin_amdgcn_raw_ptr_buffer_load_lds((b), (__attribute__((address_space(3))) void*)(lds), 16, (int)(off), 0, 0, 0)
+#define GEAR_DMA_WAIT()                              \
+  do {                                               \
+    asm volatile("" ::: "memory");                   \
+    __builtin_amdgcn_s_waitcnt(0x0F70); /* vmcnt(0); the compiler sees it and adds no waits of its own */ \
+    asm volatile("" ::: "memory");                   \
+  } while (0)
+#define GEAR_LDS_DRAIN() asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory")
+#define GEAR_DMA_BARRIER() asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory")
+#endif
+
 // v_perm_b32: byte i of the result is byte sel.byte[i] of the 8 bytes {hi, lo}
 // (0..3 = bytes of lo, 4..7 = bytes of hi, 0x0c = zero).
 #ifndef GEAR_BYTE_PERM

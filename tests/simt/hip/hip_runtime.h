@@ -58,6 +58,11 @@ inline hipError_t hipGetSymbolAddress(void** p, const void* sym) { *p = const_ca
 #define GEAR_LANE_SWAP32(a, b) simt::lane_swap((a), (b), 32)
 #define GEAR_LANE_SWAP16(a, b) simt::lane_swap((a), (b), 16)
 #define GEAR_LDS_BARRIER() pthread_barrier_wait(&simt::block_bar)
+// a copy to LDS: every lane moves its own piece at once; the waits order the lanes of a wave
+#define GEAR_DMA16(b, off, lds) (*(reinterpret_cast<uint4*>(lds) + simt::lane()) = simt_buf_load<uint4>((b), (uint32_t)(off)))
+#define GEAR_DMA_WAIT() simt::wave_barrier()
+#define GEAR_LDS_DRAIN() simt::wave_barrier()
+#define GEAR_DMA_BARRIER() pthread_barrier_wait(&simt::block_bar)
 #define GEAR_WAVE_UNIFORM(x) (x)
 #define GEAR_BYTE_PERM(hi, lo, sel) simt_byte_perm((hi), (lo), (sel))
 #define GEAR_FMED3(x, lo, hi) fminf(fmaxf((x), (lo)), (hi))
