@@ -44,24 +44,6 @@ constexpr int KLG_VEC = 15;    // Keys: "log2 of the group size" of the per-vect
 
 typedef _Float16 quant_h8 __attribute__((ext_vector_type(8)));
 
-// Exchanges between the two halves / the odd and even rows of 16 lanes of two registers: after lane_swap32 a holds
-// (a of lanes 0..31, b of lanes 0..31), b holds (a of lanes 32..63, b of lanes 32..63); lane_swap16 does the same with
-// the rows (0, 1) and (2, 3).
-#ifndef GEAR_LANE_SWAP32
-#define GEAR_LANE_SWAP32(a, b)                                                 \
-  do {                                                                         \
-    const auto r__ = __builtin_amdgcn_permlane32_swap((a), (b), false, false); \
-    (a) = r__[0];                                                              \
-    (b) = r__[1];                                                              \
-  } while (0)
-#define GEAR_LANE_SWAP16(a, b)                                                 \
-  do {                                                                         \
-    const auto r__ = __builtin_amdgcn_permlane16_swap((a), (b), false, false); \
-    (a) = r__[0];                                                              \
-    (b) = r__[1];                                                              \
-  } while (0)
-#endif
-
 // (mx - mn) / (2^b - 1), correctly rounded: for these two divisors the product with the rounded reciprocal and one
 // fused correction give the IEEE quotient for every normal fp32 numerator (checked over all mantissas).
 template <int BITS>
@@ -520,7 +502,7 @@ __device__ __forceinline__ void quant_body(uint4 (&tile)[QT][D / 8], QuantSmem<I
             if constexpr (GRAM) {
               const uint32_t hi = pack_h2(res[0], res[1]);
               oph[e][j] = hi;
-              opl[e][j] = pack_h2(__builtin_fmaf(h2f(hi & 0xFFFFu), -one, res[0]), __builtin_fmaf(h2f(hi >> 16), -one, res[1]));
+              opl[e][j] = GEAR_SPLIT_LO(hi, res[0], res[1]);
               if (!IS_K) GEAR_PIN_VGPR(opl[e][j]);   // (here, and not behind the code words: the residuals would have to be kept)
             }
           }

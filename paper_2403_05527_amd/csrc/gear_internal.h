@@ -91,6 +91,37 @@
 #define GEAR_FMED3(x, lo, hi) __builtin_amdgcn_fmed3f((x), (lo), (hi))
 #endif
 
+// Exchanges between the two halves / the odd and even rows of 16 lanes of two registers: after lane_swap32 a holds
+// (a of lanes 0..31, b of lanes 0..31), b holds (a of lanes 32..63, b of lanes 32..63); lane_swap16 does the same with
+// the rows (0, 1) and (2, 3).
+#ifndef GEAR_LANE_SWAP32
+#define GEAR_LANE_SWAP32(a, b)                                                 \
+  do {                                                                         \
+    const auto r__ = __builtin_amdgcn_permlane32_swap((a), (b), false, false); \
+    (a) = r__[0];                                                              \
+    (b) = r__[1];                                                              \
+  } while (0)
+#define GEAR_LANE_SWAP16(a, b)                                                 \
+  do {                                                                         \
+    const auto r__ = __builtin_amdgcn_permlane16_swap((a), (b), false, false); \
+    (a) = r__[0];                                                              \
+    (b) = r__[1];                                                              \
+  } while (0)
+#endif
+
+// What the two halves of hi leave of two floats: v - hi (exact in fp32), rounded to fp16.  The compiler takes three instructions for it.
+#ifndef GEAR_SPLIT_LO
+namespace gear {
+__device__ __forceinline__ uint32_t split_lo(uint32_t hi, float v0, float v1) {
+  uint32_t lo;
+  asm("v_fma_mixlo_f16 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(lo) : "v"(hi), "v"(v0));
+  asm("v_fma_mixhi_f16 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(lo) : "v"(hi), "v"(v1));
+  return lo;
+}
+}  // namespace gear
+#define GEAR_SPLIT_LO(hi, v0, v1) gear::split_lo((hi), (v0), (v1))
+#endif
+
 // Fewest tokens (B * n) of a call for which the Value selection runs by token rows, four tokens per wave
 // (below that a flushed buffer's few tokens take one wave each).  The CPU stand-in lowers it so that its small
 // cases reach those kernels.

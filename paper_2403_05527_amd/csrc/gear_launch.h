@@ -116,7 +116,8 @@ struct PiTensor {
   StartB sb;
 };
 // t_lr: first token of the segment that takes part in the low-rank term (rows before it get A = 0)
-// Bcur: [2][slab][128][padded rank]; gram: [2][slab][nstrips][GRAM_FLOATS], Keys first
+// Bcur: 2 * slabs * (128 * padded rank + PI_PROJECT_FLOATS) floats (what the solver leaves for its last pass); gram: [2][slab][nstrips][GRAM_FLOATS], Keys first
+constexpr int PI_PROJECT_FLOATS = 12;
 hipError_t launch_power_iteration_pair(const PiTensor& k, const PiTensor& v, const Dims& dm, int n, int t_lr, int iters, float* Bcur,
                                        float* gram, int nstrips, hipStream_t st);
 hipError_t launch_power_iteration(bool is_k, const PiTensor& x, const Dims& dm, int n, int t_lr, int iters, float* Bcur, float* partial,

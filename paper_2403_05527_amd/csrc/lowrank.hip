@@ -271,15 +271,12 @@ struct SweepSmem {
   __attribute__((aligned(16))) float prm[IS_K ? 2 * (PT / 32) * D : PT * 4 * 4];
 };
 // One block's share of a sweep: rows [pt * PT, pt * PT + PT) of slab `slab`, 256 threads.
-// PROJECT: only A = R B is wanted, and it is the final A (B holds the projection matrix of the last round):
-// rows go to the arena as fp16, nothing is accumulated.
-template <bool IS_K, int R, bool LAST, bool PROJECT = false>
+template <bool IS_K, int R, bool LAST>
 __device__ __forceinline__ void pi_sweep_body(SweepSmem<IS_K, R>& sm, int slab, int pt, const uint16_t* __restrict__ Y,
                                               const uint32_t* __restrict__ sv_sz, const uint32_t* __restrict__ sv_codes,
                                               int sv_n_cap, int sv_ng_cap, int g, int bits, int n, int t_lr,
                                               const float* __restrict__ Bcur, float* __restrict__ partial, int npart,
-                                              float* __restrict__ Atmp, uint16_t* __restrict__ A_out = nullptr, int rank = 0,
-                                              const uint4* __restrict__ mask = nullptr) {
+                                              float* __restrict__ Atmp) {
   float (&red)[4][D * R] = sm.red;
   float (&redg)[4][R * R] = sm.redg;
   float* prm = sm.prm;
@@ -296,14 +293,12 @@ __device__ __forceinline__ void pi_sweep_body(SweepSmem<IS_K, R>& sm, int slab, 
   // (buffer views of the slab's rows: a row past the end reads as 0)
   const GEAR_BUF_T xbuf = GEAR_BUF_MAKE(Xs, n * (D * 2));
   const GEAR_BUF_T cbuf = GEAR_BUF_MAKE(crow, IS_K ? n * (16 * bits) : 0);
-  const GEAR_BUF_T mbuf = GEAR_BUF_MAKE(mask + (size_t)slab * n, PROJECT && mask ? n * 16 : 0);   // without a mask: reads as 0
   const int xoff0 = (pt * PT + r0) * (D * 2) + oc * 16;
   const int coff0 = (pt * PT + r0) * (16 * bits) + oc * (bits == 4 ? 4 : 2);
-  auto request = [&](int k0, uint4 (&xv)[UN], uint32_t (&cw)[UN], uint32_t (&mk)[UN]) {
+  auto request = [&](int k0, uint4 (&xv)[UN], uint32_t (&cw)[UN]) {
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
       xv[u] = GEAR_BUF_LOAD16_NT(xbuf, xoff0 + 16 * (k0 + u) * (D * 2));
-      if (PROJECT) mk[u] = GEAR_BUF_LOAD1(mbuf, (pt * PT + r0 + 16 * (k0 + u)) * 16 + oc);
       cw[u] = 0u;
       if (IS_K) {
         const int co = coff0 + 16 * (k0 + u) * (16 * bits);
@@ -313,8 +308,7 @@ __device__ __forceinline__ void pi_sweep_body(SweepSmem<IS_K, R>& sm, int slab, 
   };
   uint4 xv_first[UN];
   uint32_t cw_first[UN];   // Keys: the row piece's 8 codes
-  uint32_t mk_first[UN];   // PROJECT: which of its entries belong to S
-  request(0, xv_first, cw_first, mk_first);   // in flight while the parameters are prepared
+  request(0, xv_first, cw_first);   // in flight while the parameters are prepared
 
   if (IS_K) {
     const int ngb = (PT >> lg) > 0 ? (PT >> lg) : 1, grp0 = (pt * PT) >> lg, ng = (n + g - 1) >> lg;
@@ -359,16 +353,12 @@ __device__ __forceinline__ void pi_sweep_body(SweepSmem<IS_K, R>& sm, int slab, 
   for (int k0 = 0; k0 < PT / 16; k0 += UN) {
     if (pt * PT + 16 * k0 >= n) break;  // block-uniform
     uint4 xv[UN];
-    uint32_t cw[UN], mk[UN];
+    uint32_t cw[UN];
     if (k0 == 0) {
 #pragma unroll
-      for (int u = 0; u < UN; ++u) { xv[u] = xv_first[u]; cw[u] = cw_first[u]; mk[u] = mk_first[u]; }
+      for (int u = 0; u < UN; ++u) { xv[u] = xv_first[u]; cw[u] = cw_first[u]; }
     } else {
-      request(k0, xv, cw, mk);
-    }
-    if (PROJECT) {
-#pragma unroll
-      for (int u = 0; u < UN; ++u) xv[u] = drop_entries(xv[u], mk[u]);
+      request(k0, xv, cw);
     }
     float pmn[8], pdl[8];   // Keys: parameters of my 8 channels in the current group
     int gi_prev = -1;
@@ -428,12 +418,6 @@ __device__ __forceinline__ void pi_sweep_body(SweepSmem<IS_K, R>& sm, int slab, 
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) bsel[nb] = 0.0f;
       }
-      if constexpr (PROJECT) {
-        // lane oc < R holds a_t[oc]
-        const float mine = (NB > 1 && oc >= 4) ? bsel[NB - 1] : bsel[0];
-        if (oc < rank && t < n) A_out[((size_t)slab * sv_n_cap + t) * rank + oc] = (uint16_t)f2h(mine);
-        continue;
-      }
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
 #pragma unroll
@@ -457,7 +441,6 @@ __device__ __forceinline__ void pi_sweep_body(SweepSmem<IS_K, R>& sm, int slab, 
     }
   }
 
-  if constexpr (PROJECT) return;
   // reduce over the 16 row-threads that share a channel octet
 #pragma unroll
   for (int e = 0; e < 8; ++e)
@@ -508,26 +491,206 @@ __global__ __launch_bounds__(256, (R <= 2 ? 4 : R <= 4 ? 3 : 2)) void pi_sweep_k
                                npart, Atmp);
 }
 
-// The pass of the last round when the Gram matrix exists: A = R W with the projection matrices W ([2][slab][128][R], Keys
-// first) that pi_solve_kernel left in Bcur, written to the arena as fp16; from X itself, whose entries in S are masked out.
+// ------------------------------------------------------------------ the pass of the last round when the Gram matrix exists
+// A = R W, with the projection matrix W that pi_solve_kernel leaves, straight into the arena as fp16; from X, whose entries in S are
+// left out.  The contraction runs on the matrix cores, 16 tokens x 32 channels x 16 columns at a time (v_mfma_f32_16x16x32_f16): a
+// residual goes in as two fp16 numbers, its leading part and what that leaves, W the same way (columns 0 .. 7 its leading parts, 8 .. 15
+// the rest), and all four products are formed in fp32.  Both are scaled by powers of two first, R by one per slab that keeps the largest
+// residual there can be (the norm of R is the root of G's trace) in range, W by one per column, so that the two parts carry 22 bits
+// also where fp16 alone would underflow.
+//
+// A wave takes 64 tokens, 16 at a time: rows come in as whole 256-byte lines, are turned in LDS (pieces of row r lie at piece ^ r: no bank
+// conflicts in either direction), where the entries of S are zeroed by set bit of the mask, and are read as operands: lane (kg = lane /
+// 16, m = lane % 16) holds channels 32 kg .. + 31 of row m, eight per instruction.  A Value row's group is then the same for all of a
+// lane's channels; of the Keys a lane keeps the parameters of its 32 channels.  A stored Key code is read as an fp16 denormal (an AND
+// for two codes; the power of two is part of the scale).
+//
+// Bound by the bytes (64 x 8 heads x 8192 tokens of rank 4: 2.5 GB in 465 us, 5.4 TB/s) next to vector issue (9 instructions per entry:
+// the residual 3 to 5, the split 1.5, the zeroing 1).  With multiply-adds (rank times 1 per entry) and sums over the 16 lanes of a row it took
+// 549 us and 15.5 instructions; 32 heads x 32768 tokens of rank 8 182 -> 119, 16 x 32 x 4096 of rank 4 273 -> 232 (all under the profiler).
+// Against the same steps in 64 bits the stored A, B and their product are off by what they were before to five digits: the
+// rounding to fp16 (2.07e-4 of A), at magnitudes of the entries from 1e-4 to 500.
+struct ProjectScale {   // per tensor and slab, left by pi_solve_kernel: the scale of R, its inverse, of each column of W the inverse
+  float r, inv_r;
+  float inv_w[8];
+};
+typedef _Float16 project_h8 __attribute__((ext_vector_type(8)));
+constexpr int PROJECT_ROWS = 16;   // tokens of a step
+constexpr int PROJECT_WAVE = 64;   // tokens of a wave
+
+template <bool IS_K, int BITS, int R>
+__device__ __forceinline__ void project_wave(uint4 (&rows)[PROJECT_ROWS][D / 8], const uint16_t* __restrict__ X, const uint4* __restrict__ mask,
+                                             const SegView& sv, int lg /* log2 of the group size */, int slab, int t0, int n, int t_lr,
+                                             const uint16_t* __restrict__ W, const ProjectScale* __restrict__ scale) {
+  const int lane = lane_id(), m = lane & 15, kg = lane >> 4;
+  const GEAR_BUF_T xbuf = GEAR_BUF_MAKE(X + (size_t)slab * n * D, n * (D * 2));   // rows past the end read as 0
+  const GEAR_BUF_T mbuf = GEAR_BUF_MAKE(mask + (size_t)slab * n, mask ? n * 16 : 0);
+  const GEAR_BUF_T cbuf = GEAR_BUF_MAKE(sv.codes + (size_t)slab * sv.n_cap * (4 * BITS), IS_K ? n * (16 * BITS) : 0);
+  const int ngl = 7 - lg;   // Values: log2 of a row's groups
+  const GEAR_BUF_T pbuf = IS_K ? GEAR_BUF_MAKE(sv.sz + (size_t)slab * sv.ng_cap * D, ((n + (1 << lg) - 1) >> lg) * (D * 4))
+                               : GEAR_BUF_MAKE(sv.sz + (((size_t)slab * sv.n_cap) << ngl), (n << ngl) * 4);
+  constexpr float QMAX = (float)((1 << BITS) - 1);
+  constexpr int CW = BITS;   // Keys: words of a lane's 32 codes
+
+  uint4 xn[4];          // the next step's rows
+  uint32_t mk, cn[CW];  // their mask (row lane / 4, channels 32 (lane % 4) ..), codes (Keys) or parameters (Values)
+  auto request = [&](int t) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) xn[i] = GEAR_BUF_LOAD16_NT(xbuf, (t + 4 * i + kg) * (D * 2) + m * 16);
+    mk = GEAR_BUF_LOAD4(mbuf, t * 16 + lane * 4);
+    if constexpr (!IS_K) {
+      cn[0] = GEAR_BUF_LOAD4(pbuf, (((t + m) << ngl) + ((32 * kg) >> lg)) * 4);
+    } else if constexpr (BITS == 2) {
+      const uint2 c = GEAR_BUF_LOAD8(cbuf, (t + m) * 32 + kg * 8);
+      cn[0] = c.x; cn[1] = c.y;
+    } else {
+      const uint4 c = GEAR_BUF_LOAD16(cbuf, (t + m) * 64 + kg * 16);
+      cn[0] = c.x; cn[1] = c.y; cn[2] = c.z; cn[3] = c.w;
+    }
+  };
+  request(t0);
+  // columns of W: lane's column m (of the leading parts, of the rest), channels 32 kg + 8 kb ..
+  project_h8 wf[4];
+  {
+    const int r = m & 7;
+    const GEAR_BUF_T wbuf = GEAR_BUF_MAKE(W + (size_t)slab * (2 * R * D), 2 * R * D * 2);
+    const int at = r < R ? (((m >> 3) * R + r) * D + 32 * kg) * 2 : 2 * R * D * 2;   // columns past R: past the view, 0
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) wf[kb] = __builtin_bit_cast(project_h8, GEAR_BUF_LOAD16(wbuf, at + 16 * kb));
+  }
+  const float rs = scale[slab].r;
+  float back[4];   // of columns 4 (kg % 2) + i
+#pragma unroll
+  for (int i = 0; i < 4; ++i) back[i] = scale[slab].inv_w[4 * (kg & 1) + i] * scale[slab].inv_r;
+
+  float pmn[IS_K ? 32 : 1], pdl[IS_K ? 32 : 1];   // Keys: -zero and scale of the lane's channels, with the scale of R
+  uint16_t* half = reinterpret_cast<uint16_t*>(&rows[0][0]);
+#pragma unroll   // (rolled, the rows in flight are moved from registers to registers: 64 x 8 heads x 8192 tokens 20 us)
+  for (int step = 0; step < PROJECT_WAVE / PROJECT_ROWS; ++step) {
+    const int t = t0 + PROJECT_ROWS * step;
+    if (t >= n) break;   // wave-uniform
+    if constexpr (IS_K) {
+      if (step == 0 || (t & ((1 << lg) - 1)) == 0) {   // a new group
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const uint4 z = GEAR_BUF_LOAD16(pbuf, ((t >> lg) * D + 32 * kg + 4 * i) * 4);
+          const uint32_t zw[4] = {z.x, z.y, z.z, z.w};
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int e = (4 * i + j) & 7;   // channel within its eight
+            const int bit = BITS == 2 ? (e < 5 ? 2 * e : 2 * (e - 5)) : 4 * (e & 1);   // where its code lies after the AND below
+            pmn[4 * i + j] = -(h2f(zw[j] >> 16) * rs);
+            pdl[4 * i + j] = h2f(zw[j] & 0xFFFFu) * (rs * (float)(1 << (24 - bit)));
+          }
+        }
+      }
+    }
+    // this step's rows, turned; the entries of S become 0
+    wave_lds_sync();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) rows[4 * i + kg][m ^ (4 * i + kg)] = xn[i];
+    wave_lds_sync();
+    uint32_t c[CW];
+#pragma unroll
+    for (int i = 0; i < (IS_K ? CW : 1); ++i) c[i] = cn[i];
+    {
+      const int row = lane >> 2, at = row * D + (((4 * (lane & 3)) ^ row) << 3);
+      uint32_t w = mk;
+      while (w != 0u) {
+        const int b = __ffs((int)w) - 1;
+        w &= w - 1u;
+        half[at ^ b] = 0;   // (piece b / 8 of the four, entry b % 8)
+      }
+    }
+    if (step + 1 < PROJECT_WAVE / PROJECT_ROWS) request(t + PROJECT_ROWS);   // (past n: nothing is fetched)
+    wave_lds_sync();
+    float mn = 0.0f, inv = 0.0f, dl = 0.0f;   // Values: my row's group
+    if constexpr (!IS_K) {
+      const GroupQ q = load_group(c[0]);
+      const float inv_rs = scale[slab].inv_r;
+      mn = -(q.mn * rs);
+      dl = q.delta * rs;
+      inv = q.inv * inv_rs;
+    }
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+      const uint4 xv = rows[m][(4 * kg + kb) ^ m];
+      const uint32_t x[4] = {xv.x, xv.y, xv.z, xv.w};
+      uint32_t cv[8];   // Keys: the code of channel e in half `ch`
+      if constexpr (IS_K && BITS == 2) {
+        const uint32_t w = c[kb >> 1], w2 = w >> 10;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) cv[e] = e < 5 ? w & (0x00030003u << (2 * e)) : w2 & (0x00030003u << (2 * (e - 5)));
+      } else if constexpr (IS_K) {
+        const uint32_t w = c[kb], w2 = w >> 8;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) cv[e] = (e < 2 ? w : w2) & (0x000F000Fu << (4 * (e & 1)));
+      }
+      uint32_t hi[4], lo[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float res[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int e = 2 * j + h;
+          const float y = h2f(h ? x[j] >> 16 : x[j] & 0xFFFFu);
+          if constexpr (IS_K) {
+            const int ch = BITS == 2 ? kb & 1 : e >> 2;
+            const uint32_t cw = cv[BITS == 2 ? e : e & 3];
+            const float code = h2f(ch ? cw >> 16 : cw & 0xFFFFu);   // times 2^(bit - 24)
+            res[h] = __builtin_fmaf(-code, pdl[8 * kb + e], __builtin_fmaf(y, rs, pmn[8 * kb + e]));
+          } else {
+#pragma clang fp contract(off)
+            const float ym = __builtin_fmaf(y, rs, mn);   // (y - zero) rs, rounded as y - zero is
+            const float k = clamp_f32(rintf(__fmul_rn(ym, inv)), 0.0f, QMAX);
+            res[h] = __builtin_fmaf(-k, dl, ym);
+          }
+        }
+        hi[j] = pack_h2(res[0], res[1]);
+        lo[j] = GEAR_SPLIT_LO(hi[j], res[0], res[1]);
+      }
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[kb], __builtin_bit_cast(project_h8, make_uint4(hi[0], hi[1], hi[2], hi[3])), acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[kb], __builtin_bit_cast(project_h8, make_uint4(lo[0], lo[1], lo[2], lo[3])), acc, 0, 0, 0);
+    }
+    // register i of lane (kg, m): column 4 kg + i of token t + m; the rest of W's share lies 32 lanes further
+    float av[4];
+    const bool live = t + m >= t_lr;   // rows before t_lr take no part in the low-rank term
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      uint32_t a = __float_as_uint(acc[i]), b = a;
+      GEAR_LANE_SWAP32(a, b);
+      av[i] = live ? (__uint_as_float(a) + __uint_as_float(b)) * back[i] : 0.0f;
+    }
+    const int rank = sv.rank;
+    if (t + m < n && 4 * kg < R) {
+      uint16_t* out = sv.A + ((size_t)slab * sv.n_cap + t + m) * rank + 4 * kg;
+      if (R >= 4 && rank == R) {
+        *reinterpret_cast<uint2*>(out) = make_uint2(pack_h2(av[0], av[1]), pack_h2(av[2], av[3]));
+      } else if (R == 2 && rank == 2) {
+        *reinterpret_cast<uint32_t*>(out) = pack_h2(av[0], av[1]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (4 * kg + i < rank) out[i] = (uint16_t)f2h(av[i]);
+      }
+    }
+  }
+}
 // Both tensors in one launch (z = 0: Keys, 1: Values): on a short prompt each is a few blocks' latency (512 tokens of 32
-// heads: 9.6 + 9.3 us one after the other).
-// grid (ceil(n / 256), B*H, 2), block 256.
-template <int R>
-__global__ __launch_bounds__(256, (R <= 4 ? 4 : 3)) void pi_project_kernel(const uint16_t* __restrict__ XK, const uint16_t* __restrict__ XV,
-                                                                         const uint4* __restrict__ maskK, const uint4* __restrict__ maskV,
-                                                                         SegView ks, SegView vs, int gk, int gv, int bits,
-                                                                         int n, int t_lr, const float* __restrict__ Bcur) {
-  __shared__ union {
-    SweepSmem<true, R> k;
-    SweepSmem<false, R> v;
-  } sm;
+// heads: 9.6 + 9.3 us one after the other).  grid (ceil(n / 256), B*H, 2), block 256.
+template <int BITS, int R>
+__global__ __launch_bounds__(256, 3) void pi_project_kernel(const uint16_t* __restrict__ XK, const uint16_t* __restrict__ XV,
+                                                         const uint4* __restrict__ maskK, const uint4* __restrict__ maskV, SegView ks, SegView vs,
+                                                         int lgk, int lgv, int n, int t_lr, const uint16_t* __restrict__ W,
+                                                         const ProjectScale* __restrict__ scale) {
+  __shared__ uint4 rows[4][PROJECT_ROWS][D / 8];
+  const int wave = GEAR_WAVE_UNIFORM((int)(threadIdx.x >> 6)), t0 = (int)blockIdx.x * (4 * PROJECT_WAVE) + PROJECT_WAVE * wave;
   if (blockIdx.z == 0)
-    pi_sweep_body<true, R, false, true>(sm.k, blockIdx.y, blockIdx.x, XK, ks.sz, ks.codes, ks.n_cap, ks.ng_cap, gk, bits, n, t_lr, Bcur,
-                                        nullptr, 0, nullptr, ks.A, ks.rank, maskK);
+    project_wave<true, BITS, R>(rows[wave], XK, maskK, ks, lgk, blockIdx.y, t0, n, t_lr, W, scale);
   else
-    pi_sweep_body<false, R, false, true>(sm.v, blockIdx.y, blockIdx.x, XV, vs.sz, vs.codes, vs.n_cap, vs.ng_cap, gv, bits, n, t_lr,
-                                         Bcur + (size_t)gridDim.y * D * R, nullptr, 0, nullptr, vs.A, vs.rank, maskV);
+    project_wave<false, BITS, R>(rows[wave], XV, maskV, vs, lgv, blockIdx.y, t0, n, t_lr, W + (size_t)gridDim.y * (2 * R * D),
+                                 scale + gridDim.y);
 }
 
 // A = a C for tokens [256 * pt, 256 * pt + 256) of one slab, one token per thread.  Cs: LDS, R * R floats.
@@ -652,6 +815,11 @@ __device__ __forceinline__ double rsqrt_d(double x) {
   y = y * (1.5 - 0.5 * m * y * y);
   return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, y) - ((uint64_t)h << 52));   // y * 2^-h
 }
+// floor of half the exponent of x > 0, and 2^e: x = m * 4^h with m in [1, 4), so that sqrt(x) lies in [2^h, 2^(h + 1))
+__device__ __forceinline__ int half_exponent(double x) {
+  return ((int)((__builtin_bit_cast(uint64_t, x) >> 52) & 0x7FF) - 1023) >> 1;
+}
+__device__ __forceinline__ double pow2_d(int e) { return __builtin_bit_cast(double, (uint64_t)(e + 1023) << 52); }
 // QR of B (row c of B in thread c < 128, q; the other threads of the block hold zeros and keep them) by
 // Gram-Schmidt applied twice; dependent columns become 0.  Called by all 256 threads.  The rows go
 // through LDS (Bq) once; then each of the two waves that own rows holds ALL 128 rows, two per lane, and
@@ -705,7 +873,8 @@ __device__ __forceinline__ void qr_columns(double (&q)[R], double (*Bq)[R] /* LD
 template <int R>
 __global__ __launch_bounds__(256) void pi_solve_kernel(StartB sb0, StartB sb1, int rank,
                                                        const float* __restrict__ gram_partial, int nstrips, int stride, int rounds,
-                                                       float* __restrict__ Bcur_all, int last_round, uint16_t* Bf0, uint16_t* Bf1) {
+                                                       float* __restrict__ Bcur_all, int last_round, uint16_t* Bf0, uint16_t* Bf1,
+                                                       ProjectScale* __restrict__ scale) {
   GEAR_DYN_LDS(smem_raw);
   SolveSmem<R>& sm = *reinterpret_cast<SolveSmem<R>*>(smem_raw);
   const int slab = blockIdx.x, c = threadIdx.x & (D - 1), half = threadIdx.x >> 7;
@@ -836,20 +1005,39 @@ __global__ __launch_bounds__(256) void pi_solve_kernel(StartB sb0, StartB sb1, i
     sm.GA[i][j] = 0.5 * (sm.C[i][j] + sm.C[j][i]);
   }
   block_lds_sync();
+  double trace = 0.0;
   if (threadIdx.x < 64) coeff_orth<R>(sm.GA, sm.C, sm.cj, (int)threadIdx.x);
+  else if (threadIdx.x < 128) trace = wave_sum_d((double)sm.G[(c - 64) * (GP + 1)] + (double)sm.G[c * (GP + 1)]);
   block_lds_sync();
+  // W for the pass over R (pi_project_kernel), column by column: scaled to a norm of 256 .. 512, which is the norm of C's column as B is
+  // orthonormal, and split into two fp16 parts
+  uint16_t* W = reinterpret_cast<uint16_t*>(Bcur) + (size_t)slab * (2 * R * D);
+  ProjectScale* sc = scale + (size_t)blockIdx.y * gridDim.x + slab;
   if (owner) {
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-      double w = 0.0, bo = 0.0;
+      double w = 0.0, bo = 0.0, n2 = 0.0;
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         w += q[r] * sm.C[r][j];
         bo += pr[r] * sm.C[r][j];
+        n2 += sm.C[r][j] * sm.C[r][j];
       }
-      Bcur[((size_t)slab * D + c) * R + j] = (float)w;
+      const int ex = n2 > 0.0 ? half_exponent(n2) : 0;   // norm in [2^ex, 2^(ex + 1))
+      const double ws = w * pow2_d(8 - ex);
+      const uint32_t hi = f2h((float)ws);
+      W[j * D + c] = (uint16_t)hi;
+      W[(R + j) * D + c] = (uint16_t)f2h((float)(ws - (double)h2f(hi)));
+      if (c == 0) sc->inv_w[j] = (float)pow2_d(ex - 8);
       if (j < rank) Bf[((size_t)slab * D + c) * rank + j] = (uint16_t)f2h((float)bo);
     }
+  }
+  if (threadIdx.x == 64) {   // no residual of the rows that count is larger than the norm of R, which then is below 2^15
+    const int ex = trace > 0.0 ? half_exponent(trace) : 0;
+    sc->r = (float)pow2_d(14 - ex);
+    sc->inv_r = (float)pow2_d(ex - 14);
+#pragma unroll
+    for (int j = R; j < 8; ++j) sc->inv_w[j] = 0.0f;
   }
 }
 
@@ -1057,6 +1245,7 @@ static hipError_t raise_solve_lds() {
 
 // Keys' per-vector grouping: one group per segment
 static int key_group_size(const Dims& dm) { return dm.kcvt ? 32768 : dm.g; }
+static int log2_group(int g) { return 31 - __builtin_clz((unsigned)g); }
 
 template <int R>
 static hipError_t run_pi_pair(const PiTensor& k, const PiTensor& v, const Dims& dm, int n, int t_lr, int iters, float* Bcur,
@@ -1069,14 +1258,23 @@ static hipError_t run_pi_pair(const PiTensor& k, const PiTensor& v, const Dims& 
   }
   const hipError_t e = raise_solve_lds<R>();
   if (e != hipSuccess) return e;
+  ProjectScale* scale = reinterpret_cast<ProjectScale*>(Bcur + 2 * (size_t)slabs * (D * R));   // (PI_PROJECT_FLOATS per tensor and slab)
+  static_assert(sizeof(ProjectScale) <= PI_PROJECT_FLOATS * sizeof(float), "part of the workspace layout");
   // rounds 1 .. L-1: B <- (R^T R)^(L-1) B0 on the Gram matrix; then QR(B), the last round's B and the factor of orth(A)
   const bool summed = nstrips >= GRAM_SUM_MIN;
   if (summed) hipLaunchKernelGGL(gram_sum_kernel, dim3(GRAM_TILES, 2 * slabs), dim3(256), 0, st, gram, nstrips);
   hipLaunchKernelGGL(pi_solve_kernel<R>, dim3(slabs, 2), dim3(256), sizeof(SolveSmem<R>), st, k.sb, v.sb, rank, (const float*)gram,
-                     summed ? 1 : nstrips, nstrips, iters - 1, Bcur, 1, k.sv.Bf, v.sv.Bf);
+                     summed ? 1 : nstrips, nstrips, iters - 1, Bcur, 1, k.sv.Bf, v.sv.Bf, scale);
   // one light pass writes A
-  hipLaunchKernelGGL(pi_project_kernel<R>, dim3((n + PT - 1) / PT, slabs, 2), dim3(256), 0, st, k.X, v.X, k.mask, v.mask, k.sv, v.sv,
-                     key_group_size(dm), dm.g, dm.bits, n, t_lr, (const float*)Bcur);
+  const dim3 grid((n + 4 * PROJECT_WAVE - 1) / (4 * PROJECT_WAVE), slabs, 2);
+  const uint16_t* W = reinterpret_cast<const uint16_t*>(Bcur);
+  const int lgk = log2_group(key_group_size(dm)), lgv = log2_group(dm.g);
+  if (dm.bits == 2)
+    hipLaunchKernelGGL((pi_project_kernel<2, R>), grid, dim3(256), 0, st, k.X, v.X, k.mask, v.mask, k.sv, v.sv, lgk, lgv, n, t_lr, W,
+                       (const ProjectScale*)scale);
+  else
+    hipLaunchKernelGGL((pi_project_kernel<4, R>), grid, dim3(256), 0, st, k.X, v.X, k.mask, v.mask, k.sv, v.sv, lgk, lgv, n, t_lr, W,
+                       (const ProjectScale*)scale);
   return hipGetLastError();
 }
 
@@ -1097,7 +1295,7 @@ static hipError_t run_pi(bool is_k, const PiTensor& x, const Dims& dm, int n, in
   const hipError_t e = raise_solve_lds<R>();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(pi_solve_kernel<R>, dim3(slabs), dim3(256), sizeof(SolveSmem<R>), st, x.sb, x.sb, x.sv.rank, (const float*)nullptr,
-                     0, 0, 0, Bcur, 0, x.sv.Bf, x.sv.Bf);
+                     0, 0, 0, Bcur, 0, x.sv.Bf, x.sv.Bf, (ProjectScale*)nullptr);
   const dim3 grid(npart, slabs);
   if (is_k)
     hipLaunchKernelGGL((pi_sweep_kernel<true, R>), grid, dim3(256), 0, st, x.Y, x.sv, g, dm.bits, n, t_lr, (const float*)Bcur, partial, npart, Atmp);

@@ -1,0 +1,38 @@
+"""The pass that writes A on the matrix cores: steps of 16 tokens and waves of 64 with a remainder, every rank (whole and single
+stores), groups that change inside a wave's tokens, rows without a low-rank term, and entries far from 1, whose residuals and
+projection matrix reach the matrix cores only through their scales."""
+import pytest
+
+import gear_workloads as gw
+from tests import parity_util as pu
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("n,bits,group,ppm,rank,n_lowrank,size", [
+    (257, 2, 32, 20000, 1, None, 1.0),
+    (272, 4, 64, 20000, 2, None, 1.0),
+    (319, 2, 128, 50000, 3, None, 1.0),
+    (320, 4, 0, 20000, 4, None, 1.0),
+    (321, 2, 64, 0, 5, 33, 1.0),         # no Filter; the low-rank term begins inside a step
+    (527, 4, 32, 20000, 6, None, 1.0),
+    (511, 2, 32, 500000, 7, None, 1.0),  # half of the entries outliers
+    (513, 4, 128, 20000, 8, 1, 1.0),     # one row with a low-rank term
+    (400, 2, 64, 20000, 4, None, 1.0 / 1024),
+    (400, 4, 32, 20000, 8, None, 1.0 / 1024),
+    (400, 2, 128, 20000, 4, None, 256.0),
+    (400, 4, 0, 20000, 2, None, 256.0),
+])
+def test_projection(n, bits, group, ppm, rank, n_lowrank, size):
+    B, H = 2, 3
+    w = gw.Workload("projection", B=B, H_kv=H, H_q=H, n=n, bits=bits, group=group, outlier_ppm=ppm, rank=rank, rank_chunk=2, n_b=20,
+                    steps=1, seed=n + rank)
+    gc, oc = pu.make_pair(B, H, H, bits, group, ppm, 20, n, 0, rank)
+    K, V = gw.make_keys(w, n, 0, DEV) * size, gw.make_values(w, n, 0, DEV) * size   # (a power of two)
+    ib = gw.make_init_B(w, rank, 0, DEV)
+    gc.compress(K, V, rank, 3, ib, n_lowrank=n_lowrank)
+    kw = {} if n_lowrank is None else {"n_lowrank": n_lowrank}
+    oc.compress(pu.np16(K), pu.np16(V), rank, 3, pu.np16(ib), **kw)
+    pu.compare_components(gc, oc)
+    pu.compare_lowrank_product(gc, oc, 0)
