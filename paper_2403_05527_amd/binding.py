@@ -90,11 +90,23 @@ def _check(status, what):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+# The handle of the current device's current stream.  torch.cuda.current_stream() builds a Stream object for it, 2.7 us of the 10 that a
+# read's call took on the host (the kernel of a small read takes 8); torch's own generated code asks for the handle alone.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None or _device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
+
+
+def _bytes(t):
+    return t.numel() * t.element_size()
 
 
 GEAR_FLAG_V_FILTER_PER_HEAD = 1
@@ -115,7 +127,7 @@ def gear_cache_bytes(cfg):
 
 def gear_cache_init(cfg, arena):
     cache = gear_cache()
-    _check(load_library().gear_cache_init(ctypes.byref(cfg), _ptr(arena), arena.numel() * arena.element_size(),
+    _check(load_library().gear_cache_init(ctypes.byref(cfg), _ptr(arena), _bytes(arena),
                                           ctypes.byref(cache)), "gear_cache_init")
     return cache
 
@@ -127,15 +139,15 @@ def gear_cache_reset(cache):
 def gear_compress(cache, K, V, rank, iters, init_B, workspace, seed=0):
     n = K.shape[2]
     _check(load_library().gear_compress(ctypes.byref(cache), _ptr(K), _ptr(V), n, rank, iters, _ptr(init_B),
-                                        ctypes.c_uint64(seed), _ptr(workspace), workspace.numel() * workspace.element_size(), _stream()),
+                                        seed, _ptr(workspace), _bytes(workspace), _stream()),
            "gear_compress")
 
 
 def gear_compress_recent(cache, K, V, rank, iters, init_B, n_lowrank, workspace, seed=0):
     n = K.shape[2]
     _check(load_library().gear_compress_recent(ctypes.byref(cache), _ptr(K), _ptr(V), n, rank, iters, _ptr(init_B),
-                                               ctypes.c_uint64(seed), n_lowrank, _ptr(workspace),
-                                               workspace.numel() * workspace.element_size(), _stream()),
+                                               seed, n_lowrank, _ptr(workspace),
+                                               _bytes(workspace), _stream()),
            "gear_compress_recent")
 
 
@@ -146,14 +158,14 @@ def gear_decompress(cache, K_out, V_out):
 
 def gear_decode_attn(cache, q, K_buf, V_buf, n_buf, out, workspace):
     _check(load_library().gear_decode_attn(ctypes.byref(cache), _ptr(q), _ptr(K_buf), _ptr(V_buf), n_buf, _ptr(out),
-                                           _ptr(workspace), workspace.numel() * workspace.element_size(), _stream()),
+                                           _ptr(workspace), _bytes(workspace), _stream()),
            "gear_decode_attn")
 
 
 def gear_decode_attn_mq(cache, q, causal, K_buf, V_buf, n_buf, out, workspace):
     _check(load_library().gear_decode_attn_mq(ctypes.byref(cache), _ptr(q), q.shape[2], 1 if causal else 0, _ptr(K_buf),
                                               _ptr(V_buf), n_buf, _ptr(out), _ptr(workspace),
-                                              workspace.numel() * workspace.element_size(), _stream()),
+                                              _bytes(workspace), _stream()),
            "gear_decode_attn_mq")
 
 
@@ -175,7 +187,7 @@ def gear_export_sparse(cache, which, mask, values):
 def gear_export_sparse_coo(cache, which, lin_index, values, workspace):
     """Returns nnz; with lin_index = values = None only the count is computed (nothing is launched)."""
     nnz = ctypes.c_int64(0)
-    wb = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    wb = 0 if workspace is None else _bytes(workspace)
     _check(load_library().gear_export_sparse_coo(ctypes.byref(cache), which, ctypes.byref(nnz), _ptr(lin_index),
                                                  _ptr(values), _ptr(workspace), wb, _stream()), "gear_export_sparse_coo")
     return nnz.value
