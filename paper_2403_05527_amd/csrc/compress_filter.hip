@@ -301,13 +301,13 @@ static hipError_t launch_k_select_reg(const uint16_t* K, const Dims& dm, int n, 
   return hipGetLastError();
 }
 
-template <int PC, int NB, bool ONCE>
+template <int PC, int NB, bool ONCE, int T>
 static hipError_t launch_k_select_stream(const uint16_t* K, const Dims& dm, int n, int k_top, int k_bot, const StreamPlan& p, uint4* mask,
                                          uint32_t* zero, int zero_count, const SegView& sv, hipStream_t st) {
   static std::atomic<uint64_t> lds_raised{0};
-  const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(k_select_stream_kernel<PC, NB, ONCE>), lds_raised, p.lds, LDS_PER_CU);
+  const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(k_select_stream_kernel<PC, NB, ONCE, T>), lds_raised, p.lds, LDS_PER_CU);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_select_stream_kernel<PC, NB, ONCE>), dim3((D / (8 * PC)) * dm.B * dm.H), dim3(STREAM_THREADS), p.lds, st, K, n, p.L, dm.B * dm.H,
+  hipLaunchKernelGGL((k_select_stream_kernel<PC, NB, ONCE, T>), dim3((D / (8 * PC)) * dm.B * dm.H), dim3(T), p.lds, st, K, n, p.L, dm.B * dm.H,
                      k_top, k_bot, p.j_top, p.j_bot, p.cap, mask, zero, zero_count, dm.kcvt ? sv.sz : (uint32_t*)nullptr, sv.ng_cap,
                      dm.qmax);
   return hipGetLastError();
@@ -328,15 +328,27 @@ hipError_t launch_k_select(const uint16_t* K, const Dims& dm, int n, int k_top, 
     const bool rest = dm.kcvt != 0;
     // (blocks of 8 channels where those of 16 are too few to go round: 3 x 9000 tokens 64.4 -> 53.6, 61.0 from a channel-major copy)
     const bool wide = n <= 8192 || 8 * slabs >= 128;
-#define GEAR_STREAM(PC, NB, ONCE, LDS)                                                       \
+#define GEAR_STREAM(PC, NB, ONCE, T, LDS)                                                       \
   do {                                                                                       \
-    if (stream_plan(PC, NB, ONCE, n, k_top, k_bot, rest, LDS, p))                                  \
-      return launch_k_select_stream<PC, NB, ONCE>(K, dm, n, k_top, k_bot, p, mask, zero, zero_count, sv, st); \
+    if (stream_plan(PC, NB, ONCE, T, n, k_top, k_bot, rest, LDS, p))                                  \
+      return launch_k_select_stream<PC, NB, ONCE, T>(K, dm, n, k_top, k_bot, p, mask, zero, zero_count, sv, st); \
   } while (0)
-    if (n <= 2048) GEAR_STREAM(2, 8, true, 80 * 1024);
-    else if (n <= 4096) GEAR_STREAM(2, 16, true, 80 * 1024);
-    else if (wide) GEAR_STREAM(2, 8, false, 80 * 1024);
-    GEAR_STREAM(1, 8, false, LDS_PER_CU);
+    // One block of 1024 threads and 16 channels per CU, whose lists may take all of its LDS, where these blocks come out nearly even: a
+    // lone round of them beats half as many threads (32 slabs x 9000 at 2 % 116 -> 110 us, x 5000 at 5 % 116 -> 105, 10 x 8192 75 -> 72, but
+    // 40 x 8192 135 -> 152), and blocks of 8 channels, which fetch each line twice as often, wherever the lists of two blocks per CU do not
+    // fit (32 x 32768 at 1 % 381 -> 345, 24 x 20000 at 2 % 201 -> 184, 52 x 16000 376 -> 360, 128 x 20000 847 -> 816).  In a last
+    // round that is a quarter empty the smaller blocks are level or ahead (48 slabs of 16000 to 32768 tokens 0.99 to 1.03, 40 1.01 to 1.04),
+    // and so they are where the larger ones are at most half a round (16 slabs x 32768 207 against 223, 8 x 9001 60 against 68).
+    if (n <= 2048) GEAR_STREAM(2, 8, true, 512, 80 * 1024);
+    else if (n <= 4096) GEAR_STREAM(2, 16, true, 512, 80 * 1024);
+    else {
+      const int blocks = 8 * slabs, rounds = (blocks + GEAR_STREAM_CUS - 1) / GEAR_STREAM_CUS;
+      const bool pairs = wide && stream_plan(2, 8, false, 512, n, k_top, k_bot, rest, 80 * 1024, p);
+      const bool lone = rounds == 1 && (n <= 8192 || pairs || blocks > GEAR_STREAM_CUS / 2);
+      if (lone || (rounds > 1 && !pairs && 32 * blocks >= 25 * rounds * GEAR_STREAM_CUS)) GEAR_STREAM(2, 8, false, 1024, LDS_PER_CU);
+      if (pairs) GEAR_STREAM(2, 8, false, 512, 80 * 1024);
+    }
+    GEAR_STREAM(1, 8, false, 512, LDS_PER_CU);
 #undef GEAR_STREAM
   }
   // segments of more than 8192 tokens: through a channel-major copy of the keys

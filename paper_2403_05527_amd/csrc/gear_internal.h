@@ -139,6 +139,9 @@ __device__ __forceinline__ uint32_t split_lo(uint32_t hi, float v0, float v1) {
 #define GEAR_SINGLE_WAVES 16
 #define GEAR_MERGE_AT_ONCE 32
 #endif
+#ifndef GEAR_STREAM_CUS
+#define GEAR_STREAM_CUS GEAR_CUS   // as the Key selection by lists of candidates counts them
+#endif
 // Resident blocks of the quantization kernel with its Gram accumulators on the whole chip: two on each of the 256 CUs.  (The
 // CPU stand-in lowers it so that its small cases walk strips of several tiles.)
 #ifndef GEAR_BLOCK_SLOTS

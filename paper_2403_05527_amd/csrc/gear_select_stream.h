@@ -15,7 +15,9 @@
 //
 // 64 x 8 slabs x 8192 tokens at 2 %, one wave per vector in registers before: 609 -> 440 us.  Of those the sample and the thresholds
 // take 80, the rest of the read 230 (four 32-byte pieces per line: the first-level cache takes in 32 bytes per cycle and CU, which is
-// 220 us), the appending 60, the ranking 60, the mask 20.  32 slabs x 32768 (8 channels per block) 268 -> 146, 280 x 1777 92 -> 62,
+// 220 us), the appending 60, the ranking 60, the mask 20.  32 slabs x 32768 (8 channels per block) 268 -> 146, in blocks of 16
+// channels and 1024 threads, one per CU, 35 less (32 channels in such a block, half the bytes through the first-level cache again: 512 slabs x
+// 8192 25 us more, 512 x 4096 67 more, one block's phases lie bare), 280 x 1777 92 -> 62,
 // 512 x 4096 261 -> 203.  As three kernels (sample; candidates from whole rows into the workspace; ranking) 72 + 255 + 108: no gain.
 #pragma once
 #include "gear_internal.h"
@@ -25,8 +27,9 @@
 namespace gear {
 
 constexpr int STREAM_BITS = 11;                      // resolution of the rough thresholds (1/32 of an octave)
-constexpr int STREAM_THREADS = 512;
-__host__ __device__ constexpr int stream_rows(int pc) { return STREAM_THREADS / pc; }   // rows a block reads side by side
+// T: threads of a block, 512 or 1024; PC: 16-byte pieces of a row it takes
+__host__ __device__ constexpr int stream_rows(int pc, int t) { return t / pc; }   // rows a block reads side by side
+__host__ __device__ constexpr int stream_wave_channels(int pc, int t) { return 8 * pc / (t / 64); }   // channels that a wave ranks
 constexpr int STREAM_BATCH = 4;                      // rows of a thread in flight, in the passes of the way out
 constexpr int STREAM_WALK = 16;                      // its ordered walk takes 64 times as many rows at a time
 struct StreamState {   // per channel, in LDS; [2]: of the top, of the bottom
@@ -68,9 +71,9 @@ struct StreamColumn {
   __device__ __forceinline__ uint4 load(int row) const { return GEAR_BUF_LOAD16(buf, row * (D * 2) + pc * 16); }
 };
 // f(pieces, row of the first, rows from one to the next) for the rows of the thread, a batch at a time (rows past n are 0)
-template <int PC, class F>
+template <int PC, int T, class F>
 __device__ __forceinline__ void for_each_batch(const StreamColumn& col, F&& f) {
-  constexpr int RS = stream_rows(PC);
+  constexpr int RS = stream_rows(PC, T);
 #pragma unroll 1
   for (int base = col.slot; base < col.n; base += RS * STREAM_BATCH) {
     uint4 v[STREAM_BATCH];
@@ -157,9 +160,10 @@ constexpr uint32_t STREAM_FEW = 64;
 constexpr int STREAM_PROBES = 3;
 constexpr uint32_t STREAM_ALONE = 2;   // so many channels of a block go by histograms at once
 enum : uint32_t { EQUAL_NONE = 0, EQUAL_ALL, EQUAL_LISTED, EQUAL_WALK };   // which of the entries at a threshold are taken
-template <int PC>
+template <int PC, int T>
 __device__ __forceinline__ void stream_way_out(const StreamColumn& usual, StreamState* st, uint32_t* hist /* [8 PC][256] */, uint32_t* bits,
                                                int k_top, int k_bot, bool rest) {
+  constexpr int CW = stream_wave_channels(PC, T);
   int tid = threadIdx.x;
   GEAR_PIN_VGPR(tid);   // (nothing made from it is kept over the usual way)
   const int wave = GEAR_WAVE_UNIFORM(tid >> 6), lane = tid & 63, ch0 = tid % PC * 8;
@@ -192,7 +196,7 @@ __device__ __forceinline__ void stream_way_out(const StreamColumn& usual, Stream
     block_lds_sync();
     uint32_t probed = 0u;
     for (int i = 0; i < 8 * PC; ++i) probed |= st[i].cnt;
-    for (int i = tid; i < 32 * PC; i += STREAM_THREADS) hist[i] = 0u;
+    for (int i = tid; i < 32 * PC; i += T) hist[i] = 0u;
     uint32_t at[2][4], above[2][4], below[2][4], next[2][4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -204,7 +208,7 @@ __device__ __forceinline__ void stream_way_out(const StreamColumn& usual, Stream
     }
     block_lds_sync();
     if (GEAR_WAVE_UNIFORM((int)probed) == 0) break;   // the same in every thread of the block
-    for_each_batch<PC>(col, [&](const uint4 (&v)[STREAM_BATCH], int row, int step) {
+    for_each_batch<PC, T>(col, [&](const uint4 (&v)[STREAM_BATCH], int row, int step) {
 #pragma unroll
       for (int i = 0; i < STREAM_BATCH; ++i) {
         if (row + i * step >= col.n) continue;
@@ -278,10 +282,10 @@ __device__ __forceinline__ void stream_way_out(const StreamColumn& usual, Stream
     block_lds_sync();
     uint32_t searched = 0u;
     for (int i = 0; i < 8 * PC; ++i) searched |= st[i].range.y | st[i].range.w;
-    for (int i = tid; i < 8 * PC * 256; i += STREAM_THREADS) hist[i] = 0u;
+    for (int i = tid; i < 8 * PC * 256; i += T) hist[i] = 0u;
     block_lds_sync();
     if (GEAR_WAVE_UNIFORM((int)searched) == 0) break;   // the same in every thread of the block
-    for_each_batch<PC>(col, [&](const uint4 (&v)[STREAM_BATCH], int row, int step) {
+    for_each_batch<PC, T>(col, [&](const uint4 (&v)[STREAM_BATCH], int row, int step) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const uint4 rg = st[ch0 + e].range;
@@ -314,8 +318,8 @@ __device__ __forceinline__ void stream_way_out(const StreamColumn& usual, Stream
     });
     block_lds_sync();
 #pragma unroll 1
-    for (int i = 0; i < 2 * PC; ++i) {
-      const int ch = wave * PC + (i >> 1), d = i & 1;
+    for (int i = 0; i < 2 * CW; ++i) {
+      const int ch = wave * CW + (i >> 1), d = i & 1;
       StreamState& s = st[ch];
       uint32_t* range = reinterpret_cast<uint32_t*>(&s.range) + 2 * d;
       const uint32_t from = (uint32_t)GEAR_WAVE_UNIFORM((int)range[0]), base = from & 0xFFFFu, shift = from >> 16,
@@ -380,7 +384,7 @@ __device__ __forceinline__ void stream_way_out(const StreamColumn& usual, Stream
     }
     for (int i = 0; i < 8 * PC; ++i) listed |= st[i].equal[0] >> 16 == EQUAL_LISTED || st[i].equal[1] >> 16 == EQUAL_LISTED ? 1u : 0u;
     listed = (uint32_t)GEAR_WAVE_UNIFORM((int)listed);
-    for_each_batch<PC>(col, [&](const uint4 (&v)[STREAM_BATCH], int row0, int step) {
+    for_each_batch<PC, T>(col, [&](const uint4 (&v)[STREAM_BATCH], int row0, int step) {
 #pragma unroll
       for (int i = 0; i < STREAM_BATCH; ++i) {
         const int row = row0 + i * step;
@@ -428,8 +432,8 @@ __device__ __forceinline__ void stream_way_out(const StreamColumn& usual, Stream
   }
   block_lds_sync();
 #pragma unroll 1
-  for (int cc = 0; cc < PC; ++cc) {
-    const int ch = wave * PC + cc;
+  for (int cc = 0; cc < CW; ++cc) {
+    const int ch = wave * CW + cc;
     StreamState& s = st[ch];
     uint32_t left[2], key[2];   // of a walk
 #pragma unroll
@@ -469,17 +473,18 @@ __device__ __forceinline__ void stream_way_out(const StreamColumn& usual, Stream
   block_lds_sync();
 }
 
-// grid: slab_and_column_block over 128 / (8 PC) blocks per slab; block 512; dynamic LDS: StreamPlan.  Thread (slot = tid / PC,
-// pc = tid % PC) takes channels 8 pc .. 8 pc + 7 of the stretches slot + i 512 / PC, i < NB, of L rows each.  ONCE: L is 1.
+// grid: slab_and_column_block over 128 / (8 PC) blocks per slab; block T; dynamic LDS: StreamPlan.  Thread (slot = tid / PC,
+// pc = tid % PC) takes channels 8 pc .. 8 pc + 7 of the stretches slot + i T / PC, i < NB, of L rows each.  ONCE: L is 1.
 // k_top, k_bot: entries wanted per channel; j_top, j_bot: the group extremes that make the rough thresholds; cap: entries of a
 // channel's list.
-template <int PC, int NB, bool ONCE>
-__global__ __launch_bounds__(STREAM_THREADS, ONCE && NB == 8 ? 6 : 4) void k_select_stream_kernel(const uint16_t* __restrict__ K, int n, int L, int nslab, int k_top,
+template <int PC, int NB, bool ONCE, int T>
+__global__ __launch_bounds__(T, ONCE && NB == 8 && T == 512 ? 6 : 4) void k_select_stream_kernel(const uint16_t* __restrict__ K, int n, int L, int nslab, int k_top,
                                                                             int k_bot, int j_top, int j_bot, int cap,
                                                                             uint4* __restrict__ mask, uint32_t* __restrict__ zero,
                                                                             int zero_count, uint32_t* __restrict__ ksz, int ng_cap, float qmax) {
   static_assert(PC == 1 || PC == 2, "the mask is stored a byte or two at a time");
-  constexpr int CB = 8 * PC, RS = stream_rows(PC), NG = RS / 64;
+  static_assert(stream_wave_channels(PC, T) >= 1, "every wave ranks channels");
+  constexpr int CB = 8 * PC, RS = stream_rows(PC, T), NG = RS / 64, CW = stream_wave_channels(PC, T);
   GEAR_DYN_LDS(smem_raw);
   StreamState* st = reinterpret_cast<StreamState*>(smem_raw);
   uint32_t* list = reinterpret_cast<uint32_t*>(smem_raw + CB * sizeof(StreamState));   // also the sample's extremes, and histograms
@@ -521,7 +526,7 @@ __global__ __launch_bounds__(STREAM_THREADS, ONCE && NB == 8 ? 6 : 4) void k_sel
     if (L > 1) request(cur, rows);
   }
   if (tid == 0) st[0].range.w = 0u;
-  for (int i = tid; i < (n * PC + 3) / 4; i += STREAM_THREADS) bits[i] = 0u;
+  for (int i = tid; i < (n * PC + 3) / 4; i += T) bits[i] = 0u;
   {
     uint32_t mx[4], mn[4];
 #pragma unroll
@@ -548,8 +553,8 @@ __global__ __launch_bounds__(STREAM_THREADS, ONCE && NB == 8 ? 6 : 4) void k_sel
   }
   block_lds_sync();
 #pragma unroll 1
-  for (int cc = 0; cc < PC; ++cc) {
-    const int ch = wave * PC + cc;
+  for (int cc = 0; cc < CW; ++cc) {
+    const int ch = wave * CW + cc;
     uint32_t gx[NG], gn[NG];
 #pragma unroll
     for (int i = 0; i < NG; ++i) {
@@ -638,8 +643,8 @@ __global__ __launch_bounds__(STREAM_THREADS, ONCE && NB == 8 ? 6 : 4) void k_sel
 
   // ---- the exact sets
 #pragma unroll 1
-  for (int cc = 0; cc < PC; ++cc) {
-    const int ch = wave * PC + cc;
+  for (int cc = 0; cc < CW; ++cc) {
+    const int ch = wave * CW + cc;
     const uint32_t total = (uint32_t)GEAR_WAVE_UNIFORM((int)st[ch].cnt), tt = (uint32_t)GEAR_WAVE_UNIFORM((int)st[ch].rough[0]), tb = (uint32_t)GEAR_WAVE_UNIFORM((int)st[ch].rough[1]);
     bool ok = GEAR_WAVE_UNIFORM((int)st[ch].fail) == 0;
     uint32_t* l = list + ch * cap;   // (its place serves the ranking once the entries are in registers)
@@ -683,7 +688,7 @@ __global__ __launch_bounds__(STREAM_THREADS, ONCE && NB == 8 ? 6 : 4) void k_sel
   for (int i = 0; i < CB; ++i) failed |= st[i].fail;
   if (__builtin_expect(GEAR_WAVE_UNIFORM((int)failed) != 0, 0)) {   // the same in every thread of the block
     // (a failed channel has no bits yet: stream_rank sets them only where it returns true)
-    stream_way_out<PC>(col, st, list, bits, k_top, k_bot, ksz != nullptr);
+    stream_way_out<PC, T>(col, st, list, bits, k_top, k_bot, ksz != nullptr);
   }
   // per-vector grouping: the channel's (scale, zero), outliers counted as 0
   if (ksz && tid < CB) {
@@ -691,7 +696,7 @@ __global__ __launch_bounds__(STREAM_THREADS, ONCE && NB == 8 ? 6 : 4) void k_sel
     ksz[(size_t)slab * ng_cap * D + cb * CB + tid] = group_bits(make_group(h2f(unkey16(lo)), h2f(unkey16(hi)), qmax));
   }
   uint8_t* mrow = reinterpret_cast<uint8_t*>(mask + (size_t)slab * n) + cb * PC;
-  for (int t = tid; t < n; t += STREAM_THREADS) {
+  for (int t = tid; t < n; t += T) {
     if constexpr (PC == 1) mrow[(size_t)t * 16] = reinterpret_cast<const uint8_t*>(bits)[t];
     else *reinterpret_cast<uint16_t*>(mrow + (size_t)t * 16) = reinterpret_cast<const uint16_t*>(bits)[t];
   }
@@ -707,8 +712,8 @@ struct StreamPlan {
 // room on the list one too long once in some ten thousand (of 43000 normal channels of 24000 tokens at 1 %, one).  That holds for rows in no order:
 // a thread's stretches share one offset, so a channel sorted by position, or periodic in the stretches, may go the long way (not the
 // wrong one).  j of G groups of s sampled entries reach the threshold when a share of 1 - (1 - j / G)^(1/s) of all entries does.
-inline bool stream_plan(int pc, int nb, bool once, int n, int k_top, int k_bot, bool rest, size_t lds_max, StreamPlan& p) {
-  const int slots = stream_rows(pc);
+inline bool stream_plan(int pc, int nb, bool once, int t, int n, int k_top, int k_bot, bool rest, size_t lds_max, StreamPlan& p) {
+  const int slots = stream_rows(pc, t);
   p.L = (n + slots * nb - 1) / (slots * nb);
   const int m = n / p.L, groups = m < slots ? m : slots;   // rows of the sample, groups that hold some
   double expect = 0.0, spread = 0.0;

@@ -258,6 +258,7 @@ inline void launch(const void* kernel, const char* name, dim3 grid, dim3 block, 
 #define __builtin_amdgcn_rcpf(x) (1.0f / (x))
 #define GEAR_ROWS_MIN_TOKENS 64   // the small emulated cases take the token-row kernels too
 #define GEAR_STREAM_MIN_ROWS 3000   // the same for the Key selection by lists of candidates
+#define GEAR_STREAM_CUS 16        // and its blocks of 512 and of 1024 threads
 #ifndef GEAR_CUS
 #define GEAR_CUS 1                // reads in one launch (at most four waves) and split ones, of all numbers of columns; both merges
 #define GEAR_SINGLE_WAVES 4

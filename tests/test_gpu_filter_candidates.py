@@ -79,6 +79,23 @@ def test_key_sets_equal_the_oracle(kind, H, n, ppm, group):
         _check_one_group(gc, 0, K, go.filter_keys, ppm, 2)
 
 
+@pytest.mark.parametrize("kind", ["normal", "cliff", "falling", "two channels"])
+@pytest.mark.parametrize("slabs,n,ppm,group", [
+    (32, 4097, 20000, 64), (33, 4097, 20000, 64), (32, 8192, 50000, 0), (33, 8191, 20000, 0),   # a round of blocks of 1024 threads; more of 512
+    (15, 8193, 20000, 64), (16, 8193, 20000, 0), (32, 8195, 20000, 64), (33, 8195, 20000, 64),   # 8 channels; 1024; 1024; 512
+    (16, 16001, 20000, 64), (17, 16001, 20000, 0), (49, 16001, 20000, 64), (50, 16001, 20000, 64), (32, 32768, 10000, 0),   # 8 channels; 1024; 8; 1024
+])
+def test_key_sets_in_blocks_of_either_size(kind, slabs, n, ppm, group):
+    K = _values(kind, (1, 1, n, 128), n + slabs)
+    x = K.expand(slabs, -1, -1, -1)
+    print("case", kind, slabs, n, ppm, group, flush=True)
+    gc = gb.GearCache(gb.make_config(slabs, 1, 1, 2, group, ppm, 20, n, 0, 2), "cuda:0")
+    gc.compress(x.contiguous(), torch.zeros_like(x).contiguous(), 0, 1, None)
+    _check_sparse(gc, 0, x, go.filter_keys, ppm)
+    if group == 0:
+        _check_one_group(gc, 0, K, go.filter_keys, ppm, 2)
+
+
 @pytest.mark.parametrize("kind,H,n,ppm", [("normal", 2, 300, 20000), ("normal", 2, 5000, 20000), ("grid", 2, 5000, 20000), ("normal", 1, 9001, 10000),
                                           ("cliff", 9, 700, 20000), ("one sign", 2, 3000, 20000), ("normal", 40, 70, 20000)])
 def test_one_group_per_vector(kind, H, n, ppm):
