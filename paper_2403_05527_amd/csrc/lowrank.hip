@@ -66,56 +66,123 @@ __device__ __forceinline__ double wave_sum_d(double v) {
   v += dpp_d<DPP_MIRROR>(v);
   return (lane_bcast_d(v, 0) + lane_bcast_d(v, 16)) + (lane_bcast_d(v, 32) + lane_bcast_d(v, 48));
 }
-// Gram-Schmidt (applied twice) in coefficient space: given the r x r Gram matrix G = A^T A of the columns of some A, finds C
-// with orth(A) = A C (column j of orth(A) is A * C[:, j]; dependent columns get C[:, j] = 0).  Called by the
-// 64 threads c = 0..63 of one wave; lane a * R + b carries the (a, b) term of every quadratic form x^T G y, a
-// sum over the wave finishes it.  G, C, cj: LDS.
-template <int R>
-__device__ __forceinline__ void coeff_orth(double (&G)[R][R], double (&C)[R][R], double* cj, int c) {
-  const int a = c / R, b = c % R;
-  const bool in = c < R * R;
-  const double Gab = in ? G[a][b] : 0.0;
-  uint32_t valid = 0;   // bit j: column j is kept
-  for (int j = 0; j < R; ++j) {
-    if (c < R) cj[c] = (c == j) ? 1.0 : 0.0;
-    wave_lds_sync();
-    const double before2 = G[j][j];
-    bool ok = before2 > 0.0;
-    if (ok) {
-      // two passes; the projections of a pass are taken together from the same vector (their reductions
-      // are independent of each other and overlap), then removed together
-      for (int pass = 0; pass < 2; ++pass) {
-        double dot[R];
+// A double's lanes exchanged as GEAR_LANE_SWAP32 and GEAR_LANE_SWAP16 exchange a word's.
+__device__ __forceinline__ uint64_t bits_of(double v) { return __builtin_bit_cast(uint64_t, v); }
+__device__ __forceinline__ double double_of(uint32_t lo, uint32_t hi) { return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo); }
+__device__ __forceinline__ void lane_swap32_d(double& a, double& b) {
+  uint32_t al = (uint32_t)bits_of(a), ah = (uint32_t)(bits_of(a) >> 32), bl = (uint32_t)bits_of(b), bh = (uint32_t)(bits_of(b) >> 32);
+  GEAR_LANE_SWAP32(al, bl);
+  GEAR_LANE_SWAP32(ah, bh);
+  a = double_of(al, ah);
+  b = double_of(bl, bh);
+}
+__device__ __forceinline__ void lane_swap16_d(double& a, double& b) {
+  uint32_t al = (uint32_t)bits_of(a), ah = (uint32_t)(bits_of(a) >> 32), bl = (uint32_t)bits_of(b), bh = (uint32_t)(bits_of(b) >> 32);
+  GEAR_LANE_SWAP16(al, bl);
+  GEAR_LANE_SWAP16(ah, bh);
+  a = double_of(al, ah);
+  b = double_of(bl, bh);
+}
+__device__ __forceinline__ double row16_sum_d(double v) {
+  v += dpp_d<DPP_XOR1>(v);
+  v += dpp_d<DPP_XOR2>(v);
+  v += dpp_d<DPP_HALF_MIRROR>(v);
+  return v + dpp_d<DPP_MIRROR>(v);
+}
+// The first `count` (a constant once unrolled) of N values, each summed over the 64 lanes, in every lane.  Four sums at a time: the halves and then
+// the rows of the wave take one of them each (row r of lanes: value {0, 2, 1, 3}[r]), so that the four cost little more than one.
+template <int N>
+__device__ __forceinline__ void wave_sums_d(double (&v)[N], int count) {
 #pragma unroll
-        for (int k = 0; k < R; ++k) {
-          dot[k] = 0.0;
-          if (k < j && ((valid >> k) & 1u)) dot[k] = wave_sum_d(in ? C[a][k] * Gab * cj[b] : 0.0);   // q_k^T v = c_k^T G c_j
-        }
-        wave_lds_sync();
-        if (c < R) {
-          double v = cj[c];
-#pragma unroll
-          for (int k = 0; k < R; ++k)
-            if (k < j) v -= dot[k] * C[c][k];
-          cj[c] = v;
-        }
-        wave_lds_sync();
-      }
-      const double after2 = wave_sum_d(in ? cj[a] * Gab * cj[b] : 0.0);
-      wave_lds_sync();
-      // (the Gram matrix is a sum of fp32 products: what is left of a dependent column is
-      // rounding noise of relative size ~1e-7 in after2, so the cut sits above that)
-      if (!(after2 > 1e-6 * before2)) ok = false;
-      else {
-        const double inv = 1.0 / sqrt(after2);
-        if (c < R) cj[c] *= inv;
-        wave_lds_sync();
-      }
+  for (int i = 0; i < N; i += 4) {
+    if (i >= count) continue;
+    if (i + 1 == count) {
+      v[i] = wave_sum_d(v[i]);
+      continue;
     }
-    if (ok) valid |= 1u << j;
-    if (c < R) C[c][j] = ok ? cj[c] : 0.0;
-    wave_lds_sync();
+    double a = v[i], b = v[i + 1], c = i + 2 < count ? v[(i + 2) % N] : 0.0, d = i + 3 < count ? v[(i + 3) % N] : 0.0;
+    lane_swap32_d(a, b);
+    lane_swap32_d(c, d);
+    double e = a + b, f = c + d;
+    lane_swap16_d(e, f);
+    const double t = row16_sum_d(e + f);
+    v[i] = lane_bcast_d(t, 0);
+    v[i + 1] = lane_bcast_d(t, 32);
+    if (i + 2 < count) v[(i + 2) % N] = lane_bcast_d(t, 16);
+    if (i + 3 < count) v[(i + 3) % N] = lane_bcast_d(t, 48);
   }
+}
+// 1 / sqrt(x) for x > 0 in double: the single-precision estimate, refined by two Newton steps
+// (no double-precision square root or division, which are long instruction sequences)
+__device__ __forceinline__ double rsqrt_d(double x) {
+  // scaled into single-precision range by an even power of two taken from the exponent
+  const int ex = (int)((__builtin_bit_cast(uint64_t, x) >> 52) & 0x7FF) - 1023;
+  const int h = ex >> 1;                                   // x = m * 4^h, m in [1, 4)
+  const double m = __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, x) - ((uint64_t)(2 * h) << 52));
+  double y = (double)__builtin_amdgcn_rsqf((float)m);
+  y = y * (1.5 - 0.5 * m * y * y);
+  y = y * (1.5 - 0.5 * m * y * y);
+  return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, y) - ((uint64_t)h << 52));   // y * 2^-h
+}
+// Gram-Schmidt (applied twice) in coefficient space: given the r x r Gram matrix G = A^T A of the columns of some A (G[i][j] for i <= j), finds
+// C (upper triangular) with orth(A) = A C (column j of orth(A) is A * C[:, j]; dependent columns get C[:, j] = 0).  All of it in every lane's
+// registers: some hundred multiply-adds, where a sum over lanes for each quadratic form, and its operands through LDS, took 7200 cycles at
+// r = 4 and 30600 at r = 8.
+// store(a, j, value): C[a][j] from the next column on.  IN_LDS: G and C lie there, and no entry is kept in
+// a register from one pass to the next.
+template <int R, bool IN_LDS, class Store>
+__device__ __forceinline__ void coeff_orth(const double (&G)[R][R], const double (&C)[R][R], Store&& store) {
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    double v[R];   // entries 0 .. j; v[j] stays 1 until the end
+#pragma unroll
+    for (int a = 0; a < j; ++a) v[a] = 0.0;
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+      double h[R], dot[R];   // G v; q_k^T v = c_k^T G v, all projections of a pass from the same v
+#pragma unroll
+      for (int a = 0; a < j; ++a) {
+        h[a] = G[a][j];
+        if (pass > 0) {
+#pragma unroll
+          for (int b = 0; b < j; ++b) h[a] = __builtin_fma(a <= b ? G[a][b] : G[b][a], v[b], h[a]);
+        }
+      }
+      if constexpr (IN_LDS) wave_lds_sync();
+#pragma unroll
+      for (int k = 0; k < j; ++k) {
+        dot[k] = 0.0;
+#pragma unroll
+        for (int a = 0; a <= k; ++a) dot[k] = __builtin_fma(C[a][k], h[a], dot[k]);
+      }
+      if constexpr (IN_LDS) wave_lds_sync();
+#pragma unroll
+      for (int a = 0; a < j; ++a)
+#pragma unroll
+        for (int k = a; k < j; ++k) v[a] = __builtin_fma(-dot[k], C[a][k], v[a]);
+      if constexpr (IN_LDS) wave_lds_sync();
+    }
+    double after2 = G[j][j];   // v^T G v
+#pragma unroll
+    for (int a = 0; a < j; ++a) {
+      double h = 2.0 * G[a][j];
+#pragma unroll
+      for (int b = 0; b < j; ++b) h = __builtin_fma(a <= b ? G[a][b] : G[b][a], v[b], h);
+      after2 = __builtin_fma(v[a], h, after2);
+    }
+    // (the Gram matrix is a sum of fp32 products: what is left of a dependent column is
+    // rounding noise of relative size ~1e-7 in after2, so the cut sits above that)
+    const bool ok = G[j][j] > 0.0 && after2 > 1e-6 * G[j][j];
+    const double inv = ok ? rsqrt_d(after2) : 0.0;
+#pragma unroll
+    for (int a = 0; a < R; ++a) store(a, j, a < j ? (ok ? v[a] * inv : 0.0) : a == j ? inv : 0.0);
+    if constexpr (IN_LDS) wave_lds_sync();
+  }
+}
+// The same with G and C in LDS, by the threads of one wave (c: lane): kernels that hold more next to it.
+template <int R>
+__device__ __forceinline__ void coeff_orth_lds(const double (&G)[R][R], double (&C)[R][R], int c) {
+  coeff_orth<R, true>(G, C, [&](int a, int j, double x) { if (c == 0) C[a][j] = x; });
 }
 
 // grid (B*H), block 256: thread c < 128 owns row c of the [128 x R] matrix.
@@ -130,7 +197,6 @@ struct UpdateSmem {
   double red[4];
   double G[R][R];
   double C[R][R];
-  double cj[R];   // work vector of the one thread that orthonormalises in coefficient space
 };
 // The body runs in a block of 256 threads: threads 128.. sum the Gram partials of the final round
 // and otherwise only take part in the barriers.
@@ -193,7 +259,7 @@ __device__ __forceinline__ void pi_update_body(UpdateSmem<R>& sm, int slab, bool
       G[gi / R][gi % R] = s;
     }
     block_lds_sync();
-    if (c < 64) coeff_orth<R>(G, C, sm.cj, c);
+    if (c < 64) coeff_orth_lds<R>(G, C, c);
     block_lds_sync();
     double o[R];
 #pragma unroll
@@ -776,24 +842,44 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(float* __restrict__ gram,
   *g = sum;
 }
 
-// Dynamic LDS of the solve kernel: G as [128][129] floats, B as [128][R] doubles, and small matrices.
-constexpr int GP = D + 1;
+// Dynamic LDS of the solve kernel: G as [128][128] floats, entry (row, c) at c ^ solve_swizzle(row); B as [128][R] doubles, and the Gram
+// matrix of A = R B.  Two blocks fit a CU.
 template <int R>
 struct SolveSmem {
-  float G[D * GP];
-  double Bs[D][R];
-  float part[D][R];    // the upper half block's share of a product (single precision: with it two blocks fit a CU)
-  double red[4 * (R + 1)];
-  double GA[R][R];     // the last round: Gram matrix of A = R B, the factor C of its orthonormalisation
-  double C[R][R];
-  double cj[R];
+  float G[D * D];      // at the end also P = G B, [128][R] doubles
+  __attribute__((aligned(16))) double Bs[D * R];   // rows as SolveRows lays them out
+  double GA[R][R];
 };
+// 128 rows of R doubles in LDS.  The pairs of a row are exchanged by a pattern that changes every time the rows have gone once
+// through the banks, so that neither neighbouring rows nor every eighth one meet in a bank.
+template <int R>
+struct SolveRows {
+  double* base;
+  static __device__ __forceinline__ int turn(int row) { return (row >> (R == 8 ? 2 : R == 4 ? 3 : 4)) & (R / 2 - 1); }
+  __device__ __forceinline__ double at(int row, int r) const { return base[row * R + 2 * ((r >> 1) ^ turn(row)) + (r & 1)]; }
+  __device__ __forceinline__ void load(int row, double (&v)[R]) const {
+#pragma unroll
+    for (int p = 0; p < R / 2; ++p) {
+      const double2 t = *reinterpret_cast<const double2*>(base + row * R + 2 * (p ^ turn(row)));
+      v[2 * p] = t.x;
+      v[2 * p + 1] = t.y;
+    }
+  }
+  __device__ __forceinline__ void store(int row, const double (&v)[R]) const {
+#pragma unroll
+    for (int p = 0; p < R / 2; ++p) *reinterpret_cast<double2*>(base + row * R + 2 * (p ^ turn(row))) = make_double2(v[2 * p], v[2 * p + 1]);
+  }
+};
+// Columns stay together by fours (one 16-byte read).  The eight rows 8 i .. 8 i + 7 that a product reads four at a time lie in both
+// halves of the banks, and the tiles' scattered entries spread over 16 places.
+__device__ __forceinline__ int solve_swizzle(int row) {
+  return ((row & 1) << 5) | (((row >> 3) & 3) << 3) | (((row >> 5) & 1) << 2);
+}
 // Sums of N per-thread values over the block (256 threads), all in every thread: one pair of
 // barriers for the N sums together.
 template <int N>
 __device__ __forceinline__ void block_sum_vec(double (&v)[N], double* red /* 4 * N */) {
-#pragma unroll
-  for (int i = 0; i < N; ++i) v[i] = wave_sum_d(v[i]);
+  wave_sums_d<N>(v, N);
   block_lds_sync();
   if ((threadIdx.x & 63) == 0) {
 #pragma unroll
@@ -803,29 +889,48 @@ __device__ __forceinline__ void block_sum_vec(double (&v)[N], double* red /* 4 *
 #pragma unroll
   for (int i = 0; i < N; ++i) v[i] = (red[i] + red[N + i]) + (red[2 * N + i] + red[3 * N + i]);
 }
-// 1 / sqrt(x) for x > 0 in double: the single-precision estimate, refined by two Newton steps
-// (no double-precision square root or division, which are long instruction sequences)
-__device__ __forceinline__ double rsqrt_d(double x) {
-  // scaled into single-precision range by an even power of two taken from the exponent
-  const int ex = (int)((__builtin_bit_cast(uint64_t, x) >> 52) & 0x7FF) - 1023;
-  const int h = ex >> 1;                                   // x = m * 4^h, m in [1, 4)
-  const double m = __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, x) - ((uint64_t)(2 * h) << 52));
-  double y = (double)__builtin_amdgcn_rsqf((float)m);
-  y = y * (1.5 - 0.5 * m * y * y);
-  y = y * (1.5 - 0.5 * m * y * y);
-  return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, y) - ((uint64_t)h << 52));   // y * 2^-h
-}
 // floor of half the exponent of x > 0, and 2^e: x = m * 4^h with m in [1, 4), so that sqrt(x) lies in [2^h, 2^(h + 1))
 __device__ __forceinline__ int half_exponent(double x) {
   return ((int)((__builtin_bit_cast(uint64_t, x) >> 52) & 0x7FF) - 1023) >> 1;
 }
 __device__ __forceinline__ double pow2_d(int e) { return __builtin_bit_cast(double, (uint64_t)(e + 1023) << 52); }
-// QR of B (row c of B in thread c < 128, q; the other threads of the block hold zeros and keep them) by
-// Gram-Schmidt applied twice; dependent columns become 0.  Called by all 256 threads.  The rows go
-// through LDS (Bq) once; then each of the two waves that own rows holds ALL 128 rows, two per lane, and
-// orthonormalises them by itself: every inner product is one reduction over the lanes of a wave, with no
-// barrier and no LDS traffic (the two waves compute the same numbers in the same order and each keeps
-// its own rows).
+// QR of the 128 rows of B that a wave holds (a: rows lane, b: rows lane + 64) by Gram-Schmidt applied twice; dependent columns become 0.
+// Every inner product is a sum over the lanes, those of a pass together, with no barrier and no LDS traffic.
+template <int R>
+__device__ __forceinline__ void qr_rows(double (&a)[R], double (&b)[R]) {
+  double before2[R];
+#pragma unroll
+  for (int j = 0; j < R; ++j) before2[j] = a[j] * a[j] + b[j] * b[j];
+  wave_sums_d<R>(before2, R);
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    double after2 = before2[j];
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+      if (j == 0) break;
+      double d[R];   // the projections of a pass are taken together (classical Gram-Schmidt, applied twice); the second time the norm as well
+#pragma unroll
+      for (int i = 0; i < j; ++i) d[i] = a[i] * a[j] + b[i] * b[j];
+      d[j] = a[j] * a[j] + b[j] * b[j];
+      wave_sums_d<R>(d, pass == 0 ? j : j + 1);
+      if (pass == 1) after2 = d[j];
+#pragma unroll
+      for (int i = 0; i < j; ++i) {
+        a[j] -= d[i] * a[i];
+        b[j] -= d[i] * b[i];
+        // (what the second pass takes away is the rounding of the first: 1e-16 of the column, far below the cut)
+        if (pass == 1) after2 -= d[i] * d[i];
+      }
+    }
+    const bool ok = before2[j] > 0.0 && after2 > 1e-24 * before2[j];   // norm after > 1e-12 * norm before
+    const double inv = ok ? rsqrt_d(after2) : 0.0;
+    a[j] = ok ? a[j] * inv : 0.0;
+    b[j] = ok ? b[j] * inv : 0.0;
+  }
+}
+// The same for row c of B in thread c < 128 (q; the other threads of the block hold zeros and keep them).  Called by all 256 threads.
+// The rows go through LDS (Bq) once; then each of the two waves that own rows orthonormalises all of them by itself (the same
+// numbers in the same order) and keeps its own.
 template <int R>
 __device__ __forceinline__ void qr_columns(double (&q)[R], double (*Bq)[R] /* LDS [128][R] */) {
   const int c = threadIdx.x & (D - 1);
@@ -838,121 +943,152 @@ __device__ __forceinline__ void qr_columns(double (&q)[R], double (*Bq)[R] /* LD
   block_lds_sync();
   if (!owner) return;   // (whole waves)
   const int lane = c & 63;
-  double a[R], b[R];    // rows lane and lane + 64
+  double a[R], b[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) { a[r] = Bq[lane][r]; b[r] = Bq[lane + 64][r]; }
-#pragma unroll
-  for (int j = 0; j < R; ++j) {
-    const double before2 = wave_sum_d(a[j] * a[j] + b[j] * b[j]);
-    if (before2 == 0.0) { a[j] = 0.0; b[j] = 0.0; continue; }   // wave-uniform
-#pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-      double d[R];   // the projections of a pass are taken together (classical Gram-Schmidt, applied twice)
-#pragma unroll
-      for (int i = 0; i < R; ++i) d[i] = i < j ? wave_sum_d(a[i] * a[j] + b[i] * b[j]) : 0.0;
-#pragma unroll
-      for (int i = 0; i < R; ++i)
-        if (i < j) { a[j] -= d[i] * a[i]; b[j] -= d[i] * b[i]; }
-    }
-    const double after2 = wave_sum_d(a[j] * a[j] + b[j] * b[j]);
-    if (!(after2 > 1e-24 * before2)) { a[j] = 0.0; b[j] = 0.0; }   // norm after <= 1e-12 * norm before
-    else {
-      const double inv = rsqrt_d(after2);
-      a[j] *= inv;
-      b[j] *= inv;
-    }
-  }
+  qr_rows<R>(a, b);
 #pragma unroll
   for (int r = 0; r < R; ++r) q[r] = c < 64 ? a[r] : b[r];
 }
-// grid (B*H, tensors), block 256: thread (half = tid / 128, c = tid % 128).  Row c of B belongs to thread
-// (0, c); the upper half of the block helps with the loads of G and with half of every product.
-// A block is a chain of dependent fp64 steps that nothing in it hides, and at most two blocks fit a CU: Keys (y = 0) and
-// Values (y = 1) of one call go in one launch, which up to 256 slabs costs the time of one tensor.  32 slabs of rank 8:
-// 45 + 45 -> 47 us for both tensors, 128 slabs of rank 4: 23 + 23 -> 25; 512 slabs take what they took (37 us each).
+// Row 32 wave + 4 (lane % 8) + 2 (lane / 32) + (lane / 16) % 2 of G B, in fp64 (G symmetric, swizzled; the same in lanes 8 apart).  A lane
+// multiplies four rows by every eighth row of B, from one 16-byte read of G and R / 2 of B; the eight lanes of the same rows add up.
 template <int R>
-__global__ __launch_bounds__(256) void pi_solve_kernel(StartB sb0, StartB sb1, int rank,
+__device__ __forceinline__ void gram_product(const float* G, const SolveRows<R>& Bs, int wave, int lane, double (&out)[R]) {
+  const int kg = lane >> 3, rows = 32 * wave + 4 * (lane & 7);
+  double acc[4][R];
+#pragma unroll
+  for (int x = 0; x < 4; ++x)
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[x][r] = 0.0;
+#pragma unroll 4
+  for (int i = 0; i < D / 8; ++i) {
+    const int k = 8 * i + kg;
+    const float4 g = *reinterpret_cast<const float4*>(G + k * D + (rows ^ solve_swizzle(k)));
+    const double gd[4] = {(double)g.x, (double)g.y, (double)g.z, (double)g.w};
+    double bk[R];
+    Bs.load(k, bk);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int x = 0; x < 4; ++x) acc[x][r] = __builtin_fma(gd[x], bk[r], acc[x][r]);
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      lane_swap32_d(acc[x][r], acc[x + 2][r]);
+      acc[x][r] += acc[x + 2][r];   // lanes 32 ..: row x + 2
+    }
+    lane_swap16_d(acc[0][r], acc[1][r]);
+    const double t = acc[0][r] + acc[1][r];   // odd rows of 16 lanes: row x + 1
+    out[r] = t + dpp_d<DPP_ROR8>(t);
+  }
+}
+// grid (B*H, tensors), block 256.
+// A block is a chain of dependent fp64 steps that nothing in it hides, and two blocks fit a CU: Keys (y = 0) and Values (y = 1) of one call go in
+// one launch, which up to 256 slabs costs the time of one tensor.  So the chain is kept short: a product G B reads G four rows and B a
+// row at a time and adds up in lanes, every wave orthonormalises all 128 rows of B and finds C by itself, and sums over lanes are
+// taken four at a time.  Cycles of a lone block (rank 4; rank 8), before (two threads per row of B through LDS, one sum at a time,
+// C by one wave from LDS) and now: G 8000 -> 6400, a product 6800 -> 3400 (13000 -> 6800), QR 4600 -> 2600 (17700 -> 8200), B^T P 4000 -> 900
+// (5500 -> 1800), C 7200 -> 1500 (30600 -> 7200), W 4200 -> 2200 (10600 -> 4800).  The kernel: 32 slabs of rank 4 22 -> 13 us, of rank 8
+// (32768 tokens) 52 -> 27, 280 slabs of rank 4 49 -> 30, 512 slabs 68 -> 46.
+template <int R>
+__global__ __launch_bounds__(256, 2) void pi_solve_kernel(StartB sb0, StartB sb1, int rank,
                                                        const float* __restrict__ gram_partial, int nstrips, int stride, int rounds,
                                                        float* __restrict__ Bcur_all, int last_round, uint16_t* Bf0, uint16_t* Bf1,
                                                        ProjectScale* __restrict__ scale) {
   GEAR_DYN_LDS(smem_raw);
   SolveSmem<R>& sm = *reinterpret_cast<SolveSmem<R>*>(smem_raw);
-  const int slab = blockIdx.x, c = threadIdx.x & (D - 1), half = threadIdx.x >> 7;
+  const SolveRows<R> Bs{sm.Bs}, Ps{reinterpret_cast<double*>(sm.G)};   // Ps: P = G B, at the end, in the place of G
+  const int slab = blockIdx.x, tid = threadIdx.x, c = tid & (D - 1), half = GEAR_WAVE_UNIFORM(tid >> 7);
+  const int wave = GEAR_WAVE_UNIFORM(tid >> 6), lane = tid & 63;
   const bool second = blockIdx.y != 0;
   const StartB sb = second ? sb1 : sb0;
   uint16_t* Bf = second ? Bf1 : Bf0;
   float* Bcur = Bcur_all + (size_t)blockIdx.y * gridDim.x * (D * R);
-  const bool owner = half == 0;
-  if (rounds > 0) {
+  auto start = [&]() {   // B <- the start matrix
+#pragma unroll
+    for (int i = 0; i < R / 2; ++i) {
+      const int r = 2 * i + half;
+      sm.Bs[c * R + 2 * (i ^ SolveRows<R>::turn(c)) + half] = r < rank ? (double)start_b(sb, slab, c, rank, r) : 0.0;
+    }
+  };
+  if (rounds == 0) start();
+  else {
     // G = sum of the strips' partial tiles (fixed order): element tid + 256 j is register j % 4... of tile j
     // (stride: strips per slab in memory)
-    const float* gp = gram_partial + ((size_t)blockIdx.y * gridDim.x + slab) * stride * GRAM_FLOATS + threadIdx.x;
+    const float* gp = gram_partial + ((size_t)blockIdx.y * gridDim.x + slab) * stride * GRAM_FLOATS + tid;
+    constexpr int AT_ONCE = 3;   // strips in flight
     float s[GRAM_TILES];
 #pragma unroll
     for (int j = 0; j < GRAM_TILES; ++j) s[j] = 0.0f;
-    for (int st = 0; st < nstrips; ++st) {
-      float t[GRAM_TILES];   // a loop of their own for the loads: added into the sums directly, each would be waited for in turn
+    for (int st = 0; st < nstrips; st += AT_ONCE) {
+      float t[AT_ONCE][GRAM_TILES];   // a loop of their own for the loads: added into the sums directly, each would be waited for in turn
 #pragma unroll
-      for (int j = 0; j < GRAM_TILES; ++j) t[j] = __builtin_nontemporal_load(gp + (size_t)st * GRAM_FLOATS + 256 * j);
+      for (int u = 0; u < AT_ONCE; ++u) {
+        if (u > 0 && st + u >= nstrips) break;   // block-uniform
 #pragma unroll
-      for (int j = 0; j < GRAM_TILES; ++j) s[j] += t[j];
+        for (int j = 0; j < GRAM_TILES; ++j) t[u][j] = __builtin_nontemporal_load(gp + (size_t)(st + u) * GRAM_FLOATS + 256 * j);
+      }
+      if (st == 0) start();   // (while the first ones are on their way)
+#pragma unroll
+      for (int u = 0; u < AT_ONCE; ++u) {
+        if (u > 0 && st + u >= nstrips) break;
+#pragma unroll
+        for (int j = 0; j < GRAM_TILES; ++j) s[j] += t[u][j];
+      }
     }
     // element tid of tile (e, f): register i = tid / 64 of lane l = tid % 64, i.e. G[8*(4*(l/16)+i) + e][8*(l%16) + f]
-    const int i = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int row0 = 8 * (4 * (l >> 4) + i), col0 = 8 * (l & 15);
+    const int row0 = 8 * (4 * (lane >> 4) + wave), col0 = 8 * (lane & 15);
     int j = 0;
 #pragma unroll
     for (int e = 0; e < 8; ++e)
 #pragma unroll
       for (int f = e; f < 8; ++f) {
-        sm.G[(row0 + e) * GP + col0 + f] = s[j];
-        if (e != f) sm.G[(col0 + f) * GP + row0 + e] = s[j];   // a diagonal tile holds both (row, col) and (col, row) itself
+        sm.G[(row0 + e) * D + ((col0 + f) ^ solve_swizzle(row0 + e))] = s[j];
+        // (a diagonal tile holds both (row, col) and (col, row) itself)
+        if (e != f) sm.G[(col0 + f) * D + ((row0 + e) ^ solve_swizzle(col0 + f))] = s[j];
         ++j;
       }
   }
-  double q[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) q[r] = (owner && r < rank) ? (double)start_b(sb, slab, c, rank, r) : 0.0;
+  block_lds_sync();
+  const int row = 32 * wave + 4 * (lane & 7) + 2 * (lane >> 5) + ((lane >> 4) & 1);   // of a product (gram_product)
+  const bool writes = (lane & 8) == 0;
   for (int l = 0; l < rounds; ++l) {
-    block_lds_sync();
-    if (owner) {
+    double y[R], n2[R];
+    gram_product<R>(sm.G, Bs, wave, lane, y);
+    // keep magnitudes in range between rounds: the columns of B are scaled to norm 1 before the product, which is to say its result is
+    // (after the last product the QR below rescales anyway)
+    if (l > 0) {   // block-uniform
+      double a[R], b[R];
+      Bs.load(lane, a);
+      Bs.load(lane + 64, b);
 #pragma unroll
-      for (int r = 0; r < R; ++r) sm.Bs[c][r] = q[r];
+      for (int r = 0; r < R; ++r) n2[r] = a[r] * a[r] + b[r] * b[r];
+      wave_sums_d<R>(n2, R);
+#pragma unroll
+      for (int r = 0; r < R; ++r) y[r] = n2[r] > 0.0 ? y[r] * rsqrt_d(n2[r]) : 0.0;
     }
     block_lds_sync();
-    double qn[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) qn[r] = 0.0;
-#pragma unroll 8
-    for (int k = 64 * half; k < 64 * half + 64; ++k) {
-      const double gk = (double)sm.G[k * GP + c];   // G is symmetric: column c read as row-major neighbours
-#pragma unroll
-      for (int r = 0; r < R; ++r) qn[r] += gk * sm.Bs[k][r];
-    }
-    if (!owner) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) sm.part[c][r] = (float)qn[r];
-    }
+    if (writes) Bs.store(row, y);
     block_lds_sync();
-#pragma unroll
-    for (int r = 0; r < R; ++r) q[r] = owner ? qn[r] + sm.part[c][r] : 0.0;
-    // keep magnitudes in range between rounds (unit columns: the next product stays far inside single
-    // precision, which the upper half block's share passes through); after the last product the QR
-    // below rescales anyway
-    if (l + 1 < rounds) {   // block-uniform
-      double n2[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) n2[r] = q[r] * q[r];
-      block_sum_vec<R>(n2, sm.red);
-#pragma unroll
-      for (int r = 0; r < R; ++r) q[r] = n2[r] > 0.0 ? q[r] * rsqrt_d(n2[r]) : 0.0;
-    }
   }
-  qr_columns<R>(q, sm.Bs);
+  {
+    double qa[R], qb[R];   // rows lane, lane + 64 of B
+    Bs.load(lane, qa);
+    Bs.load(lane + 64, qb);
+    qr_rows<R>(qa, qb);
+    block_lds_sync();
+    if (wave == 0) {
+      Bs.store(lane, qa);
+      Bs.store(lane + 64, qb);
+    }
+    block_lds_sync();
+  }
   if (!last_round) {
-    if (owner) {
+    if (tid < D) {
 #pragma unroll
-      for (int r = 0; r < R; ++r) Bcur[((size_t)slab * D + c) * R + r] = (float)q[r];
+      for (int r = 0; r < R; ++r) Bcur[((size_t)slab * D + c) * R + r] = (float)Bs.at(c, r);
     }
     return;
   }
@@ -960,79 +1096,61 @@ __global__ __launch_bounds__(256) void pi_solve_kernel(StartB sb0, StartB sb1, i
   // orth(A) = A C and the round's result B' = R^T orth(A) = (R^T R) B C = G B C, while the r x r Gram matrix
   // that gives C is A^T A = B^T G B.  What is left for the pass over R is A itself: orth(A) = R (B C), so
   // the projection matrix W = B C goes to Bcur and B' to the arena.
-  block_lds_sync();
-  if (owner) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) sm.Bs[c][r] = q[r];
-  }
-  block_lds_sync();
-  double pr[R];   // row c of P = G B
-#pragma unroll
-  for (int r = 0; r < R; ++r) pr[r] = 0.0;
-#pragma unroll 8
-  for (int k = 64 * half; k < 64 * half + 64; ++k) {
-    const double gk = (double)sm.G[k * GP + c];
-#pragma unroll
-    for (int r = 0; r < R; ++r) pr[r] += gk * sm.Bs[k][r];
-  }
-  if (!owner) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) sm.part[c][r] = (float)pr[r];
-  }
-  block_lds_sync();
-#pragma unroll
-  for (int r = 0; r < R; ++r) pr[r] = owner ? pr[r] + sm.part[c][r] : 0.0;
-  block_lds_sync();
-  if (owner) {   // the whole rows of P, next to those of B in LDS
-#pragma unroll
-    for (int r = 0; r < R; ++r) sm.part[c][r] = (float)pr[r];
-  }
-  block_lds_sync();
-  if (threadIdx.x < R * R) {   // entry (i, j) of B^T P: one thread each (four running sums)
-    const int i = threadIdx.x / R, j = threadIdx.x % R;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    for (int k = 0; k < D; k += 4) {
-      s0 += sm.Bs[k][i] * sm.part[k][j];
-      s1 += sm.Bs[k + 1][i] * sm.part[k + 1][j];
-      s2 += sm.Bs[k + 2][i] * sm.part[k + 2][j];
-      s3 += sm.Bs[k + 3][i] * sm.part[k + 3][j];
-    }
-    sm.C[i][j] = (s0 + s1) + (s2 + s3);
-  }
-  block_lds_sync();
-  if (threadIdx.x < R * R) {   // symmetric up to rounding
-    const int i = threadIdx.x / R, j = threadIdx.x % R;
-    sm.GA[i][j] = 0.5 * (sm.C[i][j] + sm.C[j][i]);
-  }
-  block_lds_sync();
   double trace = 0.0;
-  if (threadIdx.x < 64) coeff_orth<R>(sm.GA, sm.C, sm.cj, (int)threadIdx.x);
-  else if (threadIdx.x < 128) trace = wave_sum_d((double)sm.G[(c - 64) * (GP + 1)] + (double)sm.G[c * (GP + 1)]);
+  {
+    double y[R];
+    gram_product<R>(sm.G, Bs, wave, lane, y);
+    if (wave == 3) trace = wave_sum_d((double)sm.G[lane * D + (lane ^ solve_swizzle(lane))] +
+                                      (double)sm.G[(lane + 64) * D + ((lane + 64) ^ solve_swizzle(lane + 64))]);
+    block_lds_sync();
+    if (writes) Ps.store(row, y);
+    block_lds_sync();
+  }
+#pragma unroll
+  for (int p0 = 0; p0 < R * R; p0 += 16) {   // entry (i, j) of B^T P: 16 lanes each
+    const int p = p0 + (tid >> 4), i = (p / R) % R, j = p % R, k0 = tid & 15;
+    double s = 0.0;
+#pragma unroll
+    for (int u = 0; u < D / 16; ++u) s = __builtin_fma(Bs.at(k0 + 16 * u, i), Ps.at(k0 + 16 * u, j), s);
+    s = row16_sum_d(s);
+    if (k0 == 0 && p < R * R) sm.GA[i][j] = s;
+  }
   block_lds_sync();
+  double C[R][R];
+  {
+    double ga[R][R];   // symmetric up to rounding
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int j = i; j < R; ++j) ga[i][j] = 0.5 * (sm.GA[i][j] + sm.GA[j][i]);
+    coeff_orth<R, false>(ga, C, [&](int a, int j, double x) { C[a][j] = x; });
+  }
   // W for the pass over R (pi_project_kernel), column by column: scaled to a norm of 256 .. 512, which is the norm of C's column as B is
-  // orthonormal, and split into two fp16 parts
+  // orthonormal, and split into two fp16 parts.  The halves of the block take half of the columns each.
   uint16_t* W = reinterpret_cast<uint16_t*>(Bcur) + (size_t)slab * (2 * R * D);
   ProjectScale* sc = scale + (size_t)blockIdx.y * gridDim.x + slab;
-  if (owner) {
+  double q[R], pr[R];
+  Bs.load(c, q);
+  Ps.load(c, pr);
 #pragma unroll
-    for (int j = 0; j < R; ++j) {
-      double w = 0.0, bo = 0.0, n2 = 0.0;
+  for (int j = 0; j < R; ++j) {
+    if ((j < R / 2) != (half == 0)) continue;   // wave-uniform
+    double w = 0.0, bo = 0.0, n2 = 0.0;
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        w += q[r] * sm.C[r][j];
-        bo += pr[r] * sm.C[r][j];
-        n2 += sm.C[r][j] * sm.C[r][j];
-      }
-      const int ex = n2 > 0.0 ? half_exponent(n2) : 0;   // norm in [2^ex, 2^(ex + 1))
-      const double ws = w * pow2_d(8 - ex);
-      const uint32_t hi = f2h((float)ws);
-      W[j * D + c] = (uint16_t)hi;
-      W[(R + j) * D + c] = (uint16_t)f2h((float)(ws - (double)h2f(hi)));
-      if (c == 0) sc->inv_w[j] = (float)pow2_d(ex - 8);
-      if (j < rank) Bf[((size_t)slab * D + c) * rank + j] = (uint16_t)f2h((float)bo);
+    for (int r = 0; r <= j; ++r) {
+      w += q[r] * C[r][j];
+      bo += pr[r] * C[r][j];
+      n2 += C[r][j] * C[r][j];
     }
+    const int ex = n2 > 0.0 ? half_exponent(n2) : 0;   // norm in [2^ex, 2^(ex + 1))
+    const double ws = w * pow2_d(8 - ex);
+    const uint32_t hi = f2h((float)ws);
+    W[j * D + c] = (uint16_t)hi;
+    W[(R + j) * D + c] = (uint16_t)f2h((float)(ws - (double)h2f(hi)));
+    if (c == 0) sc->inv_w[j] = (float)pow2_d(ex - 8);
+    if (j < rank) Bf[((size_t)slab * D + c) * rank + j] = (uint16_t)f2h((float)bo);
   }
-  if (threadIdx.x == 64) {   // no residual of the rows that count is larger than the norm of R, which then is below 2^15
+  if (tid == 192) {   // no residual of the rows that count is larger than the norm of R, which then is below 2^15
     const int ex = trace > 0.0 ? half_exponent(trace) : 0;
     sc->r = (float)pow2_d(14 - ex);
     sc->inv_r = (float)pow2_d(ex - 14);
@@ -1064,10 +1182,9 @@ struct TinySmem {
   double red[4 * (R + 1)];
   double GA[R][R];
   double C[R][R];
-  double cj[R];
 };
 template <int R>
-__global__ __launch_bounds__(256) void pi_tiny_kernel(const uint16_t* __restrict__ YK, const uint16_t* __restrict__ YV, SegView ks,
+__global__ __launch_bounds__(256, 3) void pi_tiny_kernel(const uint16_t* __restrict__ YK, const uint16_t* __restrict__ YV, SegView ks,
                                                       SegView vs, int gk, int gv, int bits, int n, int t_lr, int iters, StartB sbk,
                                                       StartB sbv) {
   __shared__ TinySmem<R> sm;
@@ -1216,7 +1333,7 @@ __global__ __launch_bounds__(256) void pi_tiny_kernel(const uint16_t* __restrict
       sm.GA[i][j] = s;
     }
     block_lds_sync();
-    if (tid < 64) coeff_orth<R>(sm.GA, sm.C, sm.cj, tid);
+    if (tid < 64) coeff_orth_lds<R>(sm.GA, sm.C, tid);
     block_lds_sync();
     if (owner) {
       for (int j = 0; j < rank; ++j) {

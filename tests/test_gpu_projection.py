@@ -36,3 +36,18 @@ def test_projection(n, bits, group, ppm, rank, n_lowrank, size):
     oc.compress(pu.np16(K), pu.np16(V), rank, 3, pu.np16(ib), **kw)
     pu.compare_components(gc, oc)
     pu.compare_lowrank_product(gc, oc, 0)
+
+
+@pytest.mark.parametrize("n,rank,iters", [
+    (270, 8, 3), (300, 4, 2), (384, 2, 5), (512, 5, 3), (513, 8, 2), (768, 1, 3), (896, 8, 5), (897, 4, 3),   # 3 to 8 partial Gram matrices
+])
+def test_solver(n, rank, iters):
+    """Products on the Gram matrix, for every rank the kernel is built for (2, 4, 8) and ranks between, with one, two and four of them."""
+    B, H = 1, 3
+    w = gw.Workload("solver", B=B, H_kv=H, H_q=H, n=n, bits=2, group=64, outlier_ppm=20000, rank=rank, rank_chunk=2, n_b=20, steps=1,
+                    seed=n + rank)
+    gc, oc = pu.make_pair(B, H, H, 2, 64, 20000, 20, n, 0, rank)
+    K, V = gw.make_keys(w, n, 0, DEV), gw.make_values(w, n, 0, DEV)
+    ib = gw.make_init_B(w, rank, 0, DEV)
+    pu.compress_both(gc, oc, K, V, rank, iters, ib)
+    pu.compare_lowrank_product(gc, oc, 0)
