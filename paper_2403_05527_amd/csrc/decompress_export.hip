@@ -58,17 +58,18 @@ __device__ __forceinline__ void for_each_ell(const SegView& sv, int is_k, int sl
 
 // ---- decompress: X-hat = D + A B^T + S of one 64-token tile ----
 // The floor is HBM (2 bytes written per entry, about 0.45 read).  A thread owns eight neighbouring channels, i.e. one
-// 16-byte piece of each of its four rows; the 16 lanes of a row write its 256 bytes together.  Which rows it takes
-// follows the code layout:
-//   Keys    rows r0 + 16 k of the tile (token-major code rows: 2 or 4 bytes hold the thread's eight codes)
-//   Values  four consecutive tokens of one code word per channel: eight words give four row pieces (and serve the
-//           other threads of the same tokens from the cache), and no exchange between lanes is needed
+// 16-byte piece of each of eight neighbouring rows; the 16 lanes of a row write its 256 bytes together.  A Value's eight tokens lie in
+// one code word per channel (all of it at 4 bits, half of it at 2): eight words give eight row pieces, with no exchange between lanes.
 // S goes through an fp16 tile in LDS (entries off its support are 0) because its slots and lists belong to rows (Keys)
 // or channels (Values) and not to the piece's owner.  To keep the arithmetic under the write stream, codes become
 // floats a byte at a time (no bit-field extract per entry) and the rank sum runs on the fp16 factors as they are
 // stored, two ranks per instruction.  Every load that does not depend on the list table is requested before the first
-// wait.  LLaMA-2-7B layer, batch 16, 4096 tokens, 2 bits (0.66 GB moved per tensor): 1296 us with one entry per thread
-// and step and a fp32 S tile, 284 us in this layout with the loads after the S tile and unpacked factors, 190 us now.
+// wait.
+// What bounded it was the number of load instructions (26 for the four row pieces a thread had): so factors and Value parameters come in
+// whole 16-byte pieces, and a thread's channels' words and factors serve eight rows.  Keys and Values together, four rows -> four rows
+// with whole pieces -> eight rows: 16 x 32 heads x 4096 tokens of rank 4 (1.34 GB moved) at 2 bits 363 -> 321 -> 285 us (4.7 TB/s), at 4 bits 358 ->
+// 300 -> 261, 7 x 40 x 1777 at 4 bits 66 -> 56 -> 57, 32 x 32768 of rank 8 189 -> 179 -> 120, 64 x 8192 in groups of 32 88 -> 55 -> 57; stored
+// without the non-temporal hint 289, 272, 75, 175, 80.
 // R: the rank rounded up to 0, 2, 4 or 8; NW = R / 2 words of two factors.
 template <int R>
 struct FactorRow {
@@ -99,6 +100,28 @@ __device__ __forceinline__ FactorRow<R> load_factor(GEAR_BUF_T view, int row, in
   }
   return f;
 }
+// N rows from `row` on (a multiple of N, N R / 8 a whole number or 1): in 16-byte reads where they are stored in a piece.  The view ends with a
+// whole piece.
+template <int R, int N>
+__device__ __forceinline__ void load_factors(GEAR_BUF_T view, int row, int rank, FactorRow<R> (&f)[N]) {
+  if constexpr (R == 2 || R == 4) {
+    if (rank == R) {   // (the same in every thread of the launch)
+      uint32_t w[N * R / 2];
+#pragma unroll
+      for (int i = 0; i < N * R / 8; ++i) {
+        const uint4 t = GEAR_BUF_LOAD16(view, row * (2 * R) + 16 * i);
+        w[4 * i] = t.x; w[4 * i + 1] = t.y; w[4 * i + 2] = t.z; w[4 * i + 3] = t.w;
+      }
+#pragma unroll
+      for (int e = 0; e < N; ++e)
+#pragma unroll
+        for (int i = 0; i < R / 2; ++i) f[e].w[i] = w[e * (R / 2) + i];
+      return;
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < N; ++e) f[e] = load_factor<R>(view, row + e, rank);
+}
 // Eight entries of one row: code * scale + zero, + A B^T, + S, in fp32 in this order, then fp16.
 // c0, c1: the codes of entries 0..3 and 4..7, one per byte.
 template <int R>
@@ -125,107 +148,125 @@ __device__ __forceinline__ uint4 decompress_piece(uint32_t c0, uint32_t c1, cons
   return make_uint4(o[0], o[1], o[2], o[3]);
 }
 constexpr int SP_PITCH = D + 8;   // fp16 entries per row of the S tile (16-byte pieces of neighbouring rows in different banks)
+constexpr int DEC_ROWS = 8;       // rows of a thread
+constexpr int DEC_THREADS = TILE * (D / 8) / DEC_ROWS;
 
-// grid (ceil(n/64), B*H), block 256.
+// grid (ceil(n/64), B*H), block DEC_THREADS.
 template <bool IS_K, int BITS, int R>
-__global__ __launch_bounds__(256) void decompress_kernel(Dims dm, SegView sv, uint16_t* __restrict__ out, int n_total) {
+__global__ __launch_bounds__(DEC_THREADS) void decompress_kernel(Dims dm, SegView sv, uint16_t* __restrict__ out, int n_total) {
   constexpr int TPW = 32 / BITS;
   constexpr int NWG = TILE / TPW;   // Values: code words of a channel in the tile
   constexpr uint32_t CMASK = BITS == 2 ? 0x03030303u : 0x0F0F0F0Fu;
   __shared__ __align__(16) uint16_t sp[TILE * SP_PITCH];
   const int slab = blockIdx.y, tile = blockIdx.x, t0 = tile * TILE;
-  const int tid = threadIdx.x, oc = tid & 15, q16 = tid >> 4;
+  const int tid = threadIdx.x, oc = tid & 15, q8 = tid >> 4;
   const int lg = 31 - __clz(dm.g), lng = 7 - lg;   // log2 of the group size, of a Value row's groups
   const bool sparse = dm.ppm > 0;
-  // the thread's rows of the tile: row0 + step * k
-  const int wg = q16 & (NWG - 1), part = q16 / NWG;   // Values
-  const int row0 = IS_K ? q16 : wg * TPW + 4 * part;
-  constexpr int step = IS_K ? 16 : 1;
-  // views of the slab's rows: what lies past the last row reads as 0 and is not written
+  // the thread's rows of the tile: row0 .. row0 + 7 (a Value's lie in one code word per channel: all of it, or half)
+  const int wg = q8 & (NWG - 1), part = q8 / NWG;   // Values
+  const int row0 = IS_K ? DEC_ROWS * q8 : wg * TPW + DEC_ROWS * part;
+  // views of the slab's rows: what lies past the last row is not written (up to a whole piece of the rows' parameters is read)
   const GEAR_BUF_T ob = GEAR_BUF_MAKE(out + ((size_t)slab * n_total + sv.t0) * D, (uint32_t)sv.n * (D * 2));
-  const GEAR_BUF_T ab = GEAR_BUF_MAKE(sv.A + (size_t)slab * sv.n_cap * sv.rank, (uint32_t)sv.n * sv.rank * 2);
+  const GEAR_BUF_T ab = GEAR_BUF_MAKE(sv.A + (size_t)slab * sv.n_cap * sv.rank, ((uint32_t)sv.n * sv.rank * 2 + 15u) & ~15u);
   const GEAR_BUF_T bb = GEAR_BUF_MAKE(sv.Bf + (size_t)slab * D * sv.rank, (uint32_t)(D * 2) * sv.rank);
   uint2 tab = make_uint2(0u, 0u);
-  uint32_t slot = 0u;   // the thread's one fixed slot of the tile (256 of them)
+  uint2 slot = make_uint2(0u, 0u);   // the thread's two fixed slots of the tile (256 of them)
+  static_assert(TILE * ELL_K == 2 * DEC_THREADS && D * ELL_V == 2 * DEC_THREADS, "two slots per thread");
   if (sparse) {
     tab = sv.sp_table[(size_t)slab * sv.ntile_cap + tile];
     if constexpr (IS_K)
-      slot = GEAR_BUF_LOAD4(GEAR_BUF_MAKE(sv.ell + (size_t)slab * sv.n_cap * ELL_K, (uint32_t)sv.n * (ELL_K * 4)), (t0 * ELL_K + tid) * 4);
+      slot = GEAR_BUF_LOAD8(GEAR_BUF_MAKE(sv.ell + (size_t)slab * sv.n_cap * ELL_K, (uint32_t)sv.n * (ELL_K * 4)), (t0 * ELL_K + 2 * tid) * 4);
     else
-      slot = sv.ell[((size_t)slab * sv.ntile_cap + tile) * (D * ELL_V) + tid];
+      slot = *reinterpret_cast<const uint2*>(sv.ell + ((size_t)slab * sv.ntile_cap + tile) * (D * ELL_V) + 2 * tid);
   }
-  uint32_t cw[8];       // Keys: cw[k] the 8 codes of row k; Values: cw[e] the word of channel 8 oc + e
-  uint32_t zv[4];       // Values: (scale, zero) of the rows
-  uint4 zk[2][2];       // Keys: (scale, zero) of the channels in the tile's groups (two when g = 32)
-  FactorRow<R> a[4], bf[8];
-  const bool two = IS_K && !dm.kcvt && lg == 5;
+  uint32_t cw[8];          // Keys: cw[k] the 8 codes of row k; Values: cw[e] the word of channel 8 oc + e
+  uint32_t zv[DEC_ROWS];   // Values: (scale, zero) of the rows
+  uint4 zk[2];             // Keys: (scale, zero) of the channels in the rows' group
+  FactorRow<R> a[DEC_ROWS], bf[8];
   if constexpr (IS_K) {
     const GEAR_BUF_T cb = GEAR_BUF_MAKE(sv.codes + (size_t)slab * sv.n_cap * (4 * BITS), (uint32_t)sv.n * (16 * BITS));
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int t = t0 + row0 + 16 * k;
+    for (int k = 0; k < DEC_ROWS; ++k) {
+      const int t = t0 + row0 + k;
       cw[k] = BITS == 4 ? GEAR_BUF_LOAD4(cb, t * 64 + oc * 4) : GEAR_BUF_LOAD2(cb, t * 32 + oc * 2);
     }
-    const int g0 = dm.kcvt ? 0 : t0 >> lg;
+    const int g0 = dm.kcvt ? 0 : (t0 + row0) >> lg;
     const GEAR_BUF_T zb = GEAR_BUF_MAKE(sv.sz + (size_t)slab * sv.ng_cap * D, (uint32_t)sv.ng_cap * (D * 4));
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      zk[0][h] = GEAR_BUF_LOAD16(zb, (g0 * D + oc * 8) * 4 + 16 * h);
-      zk[1][h] = zk[0][h];
-    }
-    if (two) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) zk[1][h] = GEAR_BUF_LOAD16(zb, ((g0 + 1) * D + oc * 8) * 4 + 16 * h);
-    }
+    for (int h = 0; h < 2; ++h) zk[h] = GEAR_BUF_LOAD16(zb, (g0 * D + oc * 8) * 4 + 16 * h);
   } else {
     // (a tile's last code block may lie past the segment: nothing of it is used then)
     const int blk = (t0 / TPW + wg) >> 2;
     const GEAR_BUF_T cb = GEAR_BUF_MAKE(sv.codes + (size_t)slab * sv.nblk_cap * 512, (uint32_t)sv.nblk_cap * 2048);
 #pragma unroll
     for (int e = 0; e < 8; ++e) cw[e] = GEAR_BUF_LOAD4(cb, (blk * 512 + (wg & 3) * 128 + ((oc & 1) * 8 + e) * 8 + (oc >> 1)) * 4);
-    const GEAR_BUF_T zb = GEAR_BUF_MAKE(sv.sz + (((size_t)slab * sv.n_cap) << lng), ((uint32_t)sv.n << lng) * 4);
+    const GEAR_BUF_T zb = GEAR_BUF_MAKE(sv.sz + (((size_t)slab * sv.n_cap) << lng), (((uint32_t)sv.n << lng) * 4 + 15u) & ~15u);
+    const int G = (oc * 8) >> lg;
+    if (lng == 0) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) zv[k] = GEAR_BUF_LOAD4(zb, (((t0 + row0 + k) << lng) + ((oc * 8) >> lg)) * 4);
+      for (int k = 0; k < DEC_ROWS; k += 4) {
+        const uint4 z = GEAR_BUF_LOAD16(zb, (t0 + row0 + k) * 4);
+        zv[k] = z.x; zv[k + 1] = z.y; zv[k + 2] = z.z; zv[k + 3] = z.w;
+      }
+    } else if (lng == 1) {
+#pragma unroll
+      for (int k = 0; k < DEC_ROWS; k += 2) {
+        const uint4 z = GEAR_BUF_LOAD16(zb, (t0 + row0 + k) * 8);
+        zv[k] = G ? z.y : z.x;
+        zv[k + 1] = G ? z.w : z.z;
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < DEC_ROWS; ++k) zv[k] = GEAR_BUF_LOAD4(zb, (((t0 + row0 + k) << lng) + G) * 4);
+    }
   }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) a[k] = load_factor<R>(ab, t0 + row0 + step * k, sv.rank);
-#pragma unroll
-  for (int e = 0; e < 8; ++e) bf[e] = load_factor<R>(bb, oc * 8 + e, sv.rank);
+  load_factors<R, DEC_ROWS>(ab, t0 + row0, sv.rank, a);
+  load_factors<R, 8>(bb, oc * 8, sv.rank, bf);
 
   if (sparse) {
-    for (int i = tid; i < TILE * SP_PITCH / 8; i += 256) reinterpret_cast<uint4*>(sp)[i] = make_uint4(0, 0, 0, 0);
+    for (int i = tid; i < TILE * SP_PITCH / 8; i += DEC_THREADS) reinterpret_cast<uint4*>(sp)[i] = make_uint4(0, 0, 0, 0);
     block_lds_sync();
     const uint32_t* lst = sv.sp_pool + (size_t)(IS_K ? slab : slab / dm.H) * sv.pool_cap + tab.x;
-    for (uint32_t e = tid; e < tab.y; e += 256) {
+    for (uint32_t e = tid; e < tab.y; e += DEC_THREADS) {
       const uint32_t en = lst[e];
       sp[((en & 0xFFFFu) >> 7) * SP_PITCH + (en & 127u)] = (uint16_t)(en >> 16);
     }
-    if (slot & ELL_VALID) {
-      const int tl = IS_K ? tid / ELL_K : (int)(slot & 63u), c = IS_K ? (int)(slot & 127u) : tid / ELL_V;
-      sp[tl * SP_PITCH + c] = (uint16_t)(slot >> 16);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t en = h ? slot.y : slot.x;
+      if (en & ELL_VALID) {
+        const int i = 2 * tid + h, tl = IS_K ? i / ELL_K : (int)(en & 63u), c = IS_K ? (int)(en & 127u) : i / ELL_V;
+        sp[tl * SP_PITCH + c] = (uint16_t)(en >> 16);
+      }
     }
     block_lds_sync();
   }
+  // Values: the codes of channels 4 h .. 4 h + 3 a byte position at a time: bytes of tokens row0 + 4 p .. (2 bits), row0 + 2 p .. (4 bits)
+  constexpr int NB = IS_K ? 1 : 8 * BITS / 8;
+  uint32_t cb4[NB][2];
+  if constexpr (!IS_K) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int p = 0; p < NB; p += 2) {   // bytes p, p + 1 of my part of the words
+        const uint32_t s2 = 0x05010400u + 0x01010101u * (uint32_t)((BITS == 2 ? 2 * part : 0) + p);   // (lo[p], hi[p], lo[p + 1], hi[p + 1])
+        const uint32_t x = GEAR_BYTE_PERM(cw[4 * h + 1], cw[4 * h], s2), y = GEAR_BYTE_PERM(cw[4 * h + 3], cw[4 * h + 2], s2);
+        cb4[p][h] = GEAR_BYTE_PERM(y, x, 0x05040100u);
+        cb4[p + 1][h] = GEAR_BYTE_PERM(y, x, 0x07060302u);
+      }
+    }
+  }
   float dl[8], mn[8];
-  if constexpr (!IS_K && BITS == 2) {
-    // byte `part` of a word holds the codes of the thread's four tokens: four channels' bytes in one word
-    const uint32_t s2 = 0x0c0c0400u + 0x0101u * part;   // bytes (lo[part], hi[part])
-    const uint32_t x0 = GEAR_BYTE_PERM(GEAR_BYTE_PERM(cw[3], cw[2], s2), GEAR_BYTE_PERM(cw[1], cw[0], s2), 0x05040100u);
-    const uint32_t x1 = GEAR_BYTE_PERM(GEAR_BYTE_PERM(cw[7], cw[6], s2), GEAR_BYTE_PERM(cw[5], cw[4], s2), 0x05040100u);
-    cw[0] = x0;
-    cw[1] = x1;
+  if constexpr (IS_K) {
+    const uint32_t w[8] = {zk[0].x, zk[0].y, zk[0].z, zk[0].w, zk[1].x, zk[1].y, zk[1].z, zk[1].w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { dl[e] = h2f(w[e] & 0xFFFFu); mn[e] = h2f(w[e] >> 16); }
   }
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int tl = row0 + step * k;
+  for (int k = 0; k < DEC_ROWS; ++k) {
+    const int tl = row0 + k;
     uint32_t c0, c1;
     if constexpr (IS_K) {
-      if (k == 0 || (k == 2 && two)) {
-        const uint4 z0 = zk[k >> 1][0], z1 = zk[k >> 1][1];
-        const uint32_t w[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) { dl[e] = h2f(w[e] & 0xFFFFu); mn[e] = h2f(w[e] >> 16); }
-      }
       if constexpr (BITS == 2) {
         // codes e = 0..3 in byte 0, 4..7 in byte 1: spread two bits per byte
         const uint32_t lo = cw[k] & 0xFFu, hi = cw[k] >> 8;
@@ -240,15 +281,9 @@ __global__ __launch_bounds__(256) void decompress_kernel(Dims dm, SegView sv, ui
       const float d = h2f(zv[k] & 0xFFFFu), m = h2f(zv[k] >> 16);
 #pragma unroll
       for (int e = 0; e < 8; ++e) { dl[e] = d; mn[e] = m; }
-      if constexpr (BITS == 2) {
-        c0 = (cw[0] >> (2 * k)) & CMASK;
-        c1 = (cw[1] >> (2 * k)) & CMASK;
-      } else {
-        // token 4 part + k: nibble k of half word `part`
-        const uint32_t sh = 16 * part + 4 * k;
-        c0 = GEAR_UBFE(cw[0], sh, 4) | (GEAR_UBFE(cw[1], sh, 4) << 8) | (GEAR_UBFE(cw[2], sh, 4) << 16) | (GEAR_UBFE(cw[3], sh, 4) << 24);
-        c1 = GEAR_UBFE(cw[4], sh, 4) | (GEAR_UBFE(cw[5], sh, 4) << 8) | (GEAR_UBFE(cw[6], sh, 4) << 16) | (GEAR_UBFE(cw[7], sh, 4) << 24);
-      }
+      constexpr int PER = 8 / BITS;   // tokens of a byte
+      c0 = (cb4[k / PER][0] >> (BITS * (k % PER))) & CMASK;
+      c1 = (cb4[k / PER][1] >> (BITS * (k % PER))) & CMASK;
     }
     const uint4 s4 = sparse ? *reinterpret_cast<const uint4*>(sp + tl * SP_PITCH + oc * 8) : make_uint4(0, 0, 0, 0);
     GEAR_BUF_STORE16_NT(ob, (uint32_t)(t0 + tl) * (D * 2) + oc * 16, decompress_piece<R>(c0, c1, dl, mn, a[k], bf, s4));
@@ -419,10 +454,10 @@ __global__ void export_lowrank_kernel(SegView sv, uint16_t* __restrict__ A, uint
 template <bool IS_K, int BITS>
 static void launch_decompress_t(const Dims& dm, const SegView& sv, uint16_t* out, int n_total, hipStream_t st) {
   const dim3 grid((sv.n + TILE - 1) / TILE, dm.B * dm.H);
-  if (sv.rank == 0) hipLaunchKernelGGL((decompress_kernel<IS_K, BITS, 0>), grid, dim3(256), 0, st, dm, sv, out, n_total);
-  else if (sv.rank <= 2) hipLaunchKernelGGL((decompress_kernel<IS_K, BITS, 2>), grid, dim3(256), 0, st, dm, sv, out, n_total);
-  else if (sv.rank <= 4) hipLaunchKernelGGL((decompress_kernel<IS_K, BITS, 4>), grid, dim3(256), 0, st, dm, sv, out, n_total);
-  else hipLaunchKernelGGL((decompress_kernel<IS_K, BITS, 8>), grid, dim3(256), 0, st, dm, sv, out, n_total);
+  if (sv.rank == 0) hipLaunchKernelGGL((decompress_kernel<IS_K, BITS, 0>), grid, dim3(DEC_THREADS), 0, st, dm, sv, out, n_total);
+  else if (sv.rank <= 2) hipLaunchKernelGGL((decompress_kernel<IS_K, BITS, 2>), grid, dim3(DEC_THREADS), 0, st, dm, sv, out, n_total);
+  else if (sv.rank <= 4) hipLaunchKernelGGL((decompress_kernel<IS_K, BITS, 4>), grid, dim3(DEC_THREADS), 0, st, dm, sv, out, n_total);
+  else hipLaunchKernelGGL((decompress_kernel<IS_K, BITS, 8>), grid, dim3(DEC_THREADS), 0, st, dm, sv, out, n_total);
 }
 
 hipError_t launch_decompress(const Dims& dm, const SegView& ks, const SegView& vs, uint16_t* Kout,

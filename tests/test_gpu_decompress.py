@@ -11,6 +11,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("bits,group,n,rank,ppm", [
     (2, 64, 1, 4, 20000), (4, 64, 63, 3, 20000), (2, 32, 64, 8, 20000), (4, 32, 97, 1, 50000),
+    (2, 64, 131, 2, 20000), (4, 64, 250, 4, 20000), (2, 128, 133, 4, 20000), (4, 128, 126, 2, 20000),   # a last piece with rows past the end
     (2, 128, 129, 2, 20000), (4, 0, 191, 5, 20000), (2, 0, 65, 4, 20000), (2, 32, 223, 0, 20000), (4, 128, 40, 8, 0),
 ])
 def test_decompress_is_the_sum_of_its_components(bits, group, n, rank, ppm):
