@@ -3,100 +3,58 @@
 // and the launch of the quantization kernel (compress_quant.h).  The result of the Filter is a bit per entry, 16 bytes per
 // token row of a head.  (With the Filter per head the quantization kernel finds the entries by itself: a row's 16 lanes
 // hold the whole vector there.)
+#include <type_traits>
 #include "gear_internal.h"
 #include "gear_select.h"
 #include "gear_select_rows.h"
 #include "gear_select_ext.h"
+#include "compress_select.h"
 #include "gear_launch.h"
 #include "compress_quant.h"
 
 namespace gear {
 
-template <int NC>
-struct RegSource {  // the vector lives in the wave's registers
-  static constexpr int kMaxChunks = NC;
-  const uint4* x;
-  __device__ __forceinline__ uint4 operator()(int ch) const { return x[ch]; }
-};
-
-// The mask of a token from the bits of its vector, which the selection leaves in LDS: lane h stores head h's 16 bytes.
-__device__ __forceinline__ void store_token_mask(const uint32_t* smask, uint4* mask, int b, int H, int n, int t) {
-  const int h = lane_id();
-  if (h < H) mask[((size_t)b * H + h) * n + t] = *reinterpret_cast<const uint4*>(smask + 4 * h);
-}
+// Tokens of a Value block of select_pair_kernel: as many waves as have room next to the Keys' LDS.
+constexpr int pair_tokens(bool tiny, int nc) { return tiny ? 2 : nc <= 4 ? 8 : 4; }
 
 // grid (ceil(n / 4), B); block 256, one token per wave.
-// lane l, chunk ch  <->  head 4*ch + l/16, channels 8*(l%16)..+7, i.e. in-vector index
-// ch*512 + l*8 + e.
-// Under the per-vector grouping (vsz != nullptr) the kernel also leaves the token's (scale, zero):
-// its one Value group spans the whole vector, outliers counted as 0.  per_head: the Filter ranks
-// each head's 128 channels (the 16 lanes of a row) on their own; the mask is then not stored (the quantization kernel
-// finds the entries again, they cost less than their round trip).
 template <int NC>
 __global__ __launch_bounds__(256, (NC <= 8 ? 4 : NC <= 10 ? 3 : 2)) void v_select_kernel(const uint16_t* __restrict__ V, int H, int n, int k_top,
                                                        int k_bot, uint4* __restrict__ mask, uint32_t* __restrict__ vsz,
                                                        float qmax, int per_head) {
   __shared__ __align__(16) uint4 raw_all[4 * NC * 64];
   __shared__ __align__(16) uint32_t list_all[4 * EXT_LIST];
-  static_assert(EXT_LIST >= SELECT_LDS_WORDS, "the histograms of the way out take the list's place");
-  const int b = blockIdx.y;
-  const int tid = threadIdx.x, wave = tid >> 6;
-  const int N = H * D;
-  uint4* raw = raw_all + wave * (NC * 64);
-  uint32_t* list = list_all + wave * EXT_LIST;
-  // (a view of the batch element's H * n rows: heads past H read as 0)
-  const GEAR_BUF_T vb = GEAR_BUF_MAKE(V + (size_t)b * H * n * D, (uint32_t)H * n * (D * 2));
-  const int lane = tid & 63, hsub = lane >> 4, oc = lane & 15;
-  const int t = blockIdx.x * 4 + wave;
+  const int wave = GEAR_WAVE_UNIFORM((int)(threadIdx.x >> 6)), t = blockIdx.x * 4 + wave;
   if (t >= n) return;   // (waves are independent)
-  const uint32_t off0 = ((uint32_t)hsub * n + t) * (D * 2) + oc * 16;
-  uint4 x[NC];
-  auto load_row = [&]() {
-#pragma unroll
-    for (int ch = 0; ch < NC; ++ch) x[ch] = GEAR_BUF_LOAD16(vb, off0 + (uint32_t)ch * 4u * n * (D * 2));
-  };
-  load_row();
-  const bool filt = !per_head && (k_top > 0 || k_bot > 0);
-  if (filt && !wave_ext_select<NC>(x, H, k_top, k_bot, raw, list)) {
-#pragma unroll
-    for (int ch = 0; ch < NC; ++ch) x[ch] = make_uint4(key16x2(x[ch].x), key16x2(x[ch].y), key16x2(x[ch].z), key16x2(x[ch].w));
-    RegSource<NC> src{x};
-    const ThreshPair tp = pack_thresh(wave_select(src, N, k_top, k_bot, list, true));
-    const ThreshKeys tk = key_thresh(tp);
-    const bool cut = __ballot(tk.cut) != 0ull;   // wave-uniform
-#pragma unroll
-    for (int ch = 0; ch < NC; ++ch) {
-      reinterpret_cast<uint8_t*>(list)[(ch * 4 + hsub) * 16 + oc] =
-          (uint8_t)(cut ? piece_bits(x[ch], (uint32_t)(ch * 512 + lane * 8), tp) : key_bits(x[ch], tk));
-      GEAR_SCHED_FENCE();
-    }
-    wave_lds_sync();
-    if (vsz) load_row();
+  v_select_token<NC>(raw_all + wave * (NC * 64), list_all + wave * EXT_LIST, V, blockIdx.y, t, H, n, k_top, k_bot, mask, vsz, qmax, per_head);
+}
+
+// Both selections of a call with few blocks, in one launch: the first kblocks blocks take the Keys, the others WAVES tokens each.  Of a
+// flushed buffer (TINY) or of a segment of up to 1024 tokens, each is a launch's latency and a short chain.
+template <bool TINY, int NC>
+__global__ __launch_bounds__(TINY ? 128 : 512, 4) void select_pair_kernel(const uint16_t* __restrict__ K, const uint16_t* __restrict__ V, int H, int n,
+                                                                      int nslab, int k_top, int k_bot, int v_top, int v_bot,
+                                                                      uint4* __restrict__ maskK, uint4* __restrict__ maskV,
+                                                                      uint32_t* __restrict__ zero, int zero_count, uint32_t* __restrict__ ksz,
+                                                                      int ng_cap, uint32_t* __restrict__ vsz, float qmax, int per_head) {
+  constexpr int WAVES = pair_tokens(TINY, NC);
+  __shared__ __align__(16) union {
+    std::conditional_t<TINY, KTinySmem, KRegSmem<2>> k;
+    struct {
+      uint4 raw[WAVES][NC * 64];
+      uint32_t list[WAVES][EXT_LIST];
+    } v;
+  } sm;
+  const int kblocks = TINY ? nslab : (D / 8) * nslab;
+  const int block = (int)blockIdx.x - kblocks;
+  if (block < 0) {
+    if constexpr (TINY) k_select_tiny_block(sm.k, K, blockIdx.x, nslab, n, k_top, k_bot, maskK, zero, zero_count, ksz, ng_cap, qmax);
+    else k_select_reg_block<2>(sm.k, K, blockIdx.x, n, nslab, k_top, k_bot, maskK, zero, zero_count, ksz, ng_cap, qmax);
+    return;
   }
-  if (filt && mask) store_token_mask(list, mask, b, H, n, t);
-  if (vsz) {
-    uint32_t mn = 0x7C007C00u, mx = 0xFC00FC00u;
-#pragma unroll
-    for (int ch = 0; ch < NC; ++ch) {
-      uint32_t f = 0u;
-      if (filt) f = reinterpret_cast<const uint8_t*>(list)[(ch * 4 + hsub) * 16 + oc];
-      if (per_head) {
-        const uint32_t kw[4] = {key16x2(x[ch].x), key16x2(x[ch].y), key16x2(x[ch].z), key16x2(x[ch].w)};
-        const ThreshPair tp = row16_thresholds(kw, oc, k_top, k_bot);   // this head's own thresholds
-        f = piece_bits(make_uint4(kw[0], kw[1], kw[2], kw[3]), (uint32_t)(oc * 8), tp);
-      }
-      if (ch * 4 + hsub < H) extend_extremes(drop_entries(x[ch], f), mx, mn);
-    }
-    mn = key16x2(mn);
-    mx = key16x2(mx);
-    uint32_t kmn = min(mn & 0xFFFFu, mn >> 16), kmx = max(mx & 0xFFFFu, mx >> 16);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      kmn = min(kmn, (uint32_t)__shfl_xor(kmn, o, 64));
-      kmx = max(kmx, (uint32_t)__shfl_xor(kmx, o, 64));
-    }
-    if (lane == 0) vsz[(size_t)b * n + t] = group_bits(make_group(h2f(unkey16(kmn)), h2f(unkey16(kmx)), qmax));
-  }
+  const int wave = GEAR_WAVE_UNIFORM((int)(threadIdx.x >> 6)), per = (n + WAVES - 1) / WAVES, b = block / per, t = (block - b * per) * WAVES + wave;
+  if (wave >= WAVES || t >= n) return;   // (waves are independent)
+  v_select_token<NC>(sm.v.raw[wave], sm.v.list[wave], V, b, t, H, n, v_top, v_bot, maskV, vsz, qmax, per_head);
 }
 
 // The same for token rows of at most 1024 entries (up to eight KV heads), four tokens per
@@ -194,6 +152,45 @@ hipError_t launch_v_select(const uint16_t* V, const Dims& dm, int n, int k_top, 
   if (nc <= 8) return launch_vsel<8>(V, dm, n, kt, kb, mask, vsz, st);
   if (nc <= 10) return launch_vsel<10>(V, dm, n, kt, kb, mask, vsz, st);
   return launch_vsel<16>(V, dm, n, kt, kb, mask, vsz, st);
+}
+
+template <bool TINY, int NC>
+static hipError_t launch_pair(const uint16_t* K, const uint16_t* V, const Dims& dm, int n, int k_top, int k_bot, int v_top, int v_bot,
+                              uint4* maskK, uint4* maskV, uint32_t* zero, int zero_count, const SegView& ks, uint32_t* vsz, hipStream_t st) {
+  constexpr int W = pair_tokens(TINY, NC);
+  const int slabs = dm.B * dm.H;
+  hipLaunchKernelGGL((select_pair_kernel<TINY, NC>), dim3((TINY ? 1 : D / 8) * slabs + dm.B * ((n + W - 1) / W)), dim3(TINY ? 128 : 512), 0, st, K, V,
+                     dm.H, n, slabs, k_top, k_bot, v_top, v_bot, maskK, maskV, zero, zero_count, dm.kcvt ? ks.sz : (uint32_t*)nullptr,
+                     ks.ng_cap, dm.kcvt ? vsz : (uint32_t*)nullptr, dm.qmax, dm.vhead);
+  return hipGetLastError();
+}
+// A flushed buffer's selections go together at every number of slabs (a call of rank 2, launch after launch -> together: 32 slabs x 20 tokens
+// 25.2 -> 21.1 us, 512 x 20 36.2 -> 32.0, 2048 x 20 90.9 -> 88.1, 256 x 64 46.1 -> 39.0), those of up to 1024 tokens while they leave the
+// chip half empty (a call of rank 4, 32 x 512 48.8 -> 45.5, 64 x 1000 71.9 -> 68.3, but 128 x 512 72.5 -> 74.6, 256 x 800 level: the Value
+// blocks hold the Keys' LDS and half of the waves).
+constexpr int PAIR_SLABS = 64;
+bool selects_in_pairs(const Dims& dm, int n) {
+  if (!((dm.ppm > 0 && !dm.vhead) || dm.kcvt)) return false;   // no pass over the Values
+  if (dm.H > 32 || (dm.H <= 8 && !dm.vhead && (long long)dm.B * n >= GEAR_ROWS_MIN_TOKENS)) return false;   // (other Value kernels)
+  return n <= KSEL_TINY_ROWS || (n <= 1024 && dm.B * dm.H <= PAIR_SLABS);
+}
+hipError_t launch_select_pair(const uint16_t* K, const uint16_t* V, const Dims& dm, int n, int k_top, int k_bot, int v_top, int v_bot,
+                              uint4* maskK, uint4* maskV, uint32_t* zero, int zero_count, const SegView& ks, uint32_t* vsz, hipStream_t st) {
+  if (dm.ppm == 0) {
+    k_top = k_bot = v_top = v_bot = 0;
+    maskK = maskV = nullptr;
+  }
+  if (dm.vhead) maskV = nullptr;
+  const int nc = (dm.H + 3) / 4;
+#define GEAR_PAIR(TINY)                                                                                                                      \
+  do {                                                                                                                                       \
+    if (nc <= 2) return launch_pair<TINY, 2>(K, V, dm, n, k_top, k_bot, v_top, v_bot, maskK, maskV, zero, zero_count, ks, vsz, st);            \
+    if (nc <= 4) return launch_pair<TINY, 4>(K, V, dm, n, k_top, k_bot, v_top, v_bot, maskK, maskV, zero, zero_count, ks, vsz, st);            \
+    return launch_pair<TINY, 8>(K, V, dm, n, k_top, k_bot, v_top, v_bot, maskK, maskV, zero, zero_count, ks, vsz, st);                         \
+  } while (0)
+  if (n <= KSEL_TINY_ROWS) GEAR_PAIR(true);
+  GEAR_PAIR(false);
+#undef GEAR_PAIR
 }
 
 template <int BITS>

@@ -405,7 +405,8 @@ int gear_compress_recent(gear_cache* cache, const void* K, const void* V, int32_
   const uint64_t tensor_entries = (uint64_t)slabs * D * rank;
   const StartB sbk{init_B, seed, 0}, sbv{init_B ? init_B + tensor_entries : nullptr, seed, tensor_entries};
   // the Key selection kernel also finds a channel's (scale, zero) under the per-vector grouping
-  if (c.outlier_ppm > 0 || dm.kcvt) {
+  const bool select_pair = paired && selects_in_pairs(dm, n);
+  if (!select_pair && (c.outlier_ppm > 0 || dm.kcvt)) {
     GEAR_HIP(launch_k_select(Kp, dm, n, (kv_k + 1) / 2, kv_k / 2, maskK, pool_ctr, c.B * c.H_kv + c.B, ks,
                              n > 8192 ? reinterpret_cast<uint16_t*>(ws + w.kt) : nullptr, st));
   }
@@ -419,7 +420,10 @@ int gear_compress_recent(gear_cache* cache, const void* K, const void* V, int32_
     uint16_t* YV = on_gram ? nullptr : YK + slabs * n * D;
     const PiTensor pk{Kp, c.outlier_ppm > 0 ? maskK : nullptr, YK, ks, sbk};
     const PiTensor pv{Vp, c.outlier_ppm > 0 ? maskV : nullptr, YV, vs, sbv};
-    GEAR_HIP(launch_v_select(Vp, dm, n, v_top, v_bot, maskV, vsz, st));
+    if (select_pair)
+      GEAR_HIP(launch_select_pair(Kp, Vp, dm, n, (kv_k + 1) / 2, kv_k / 2, v_top, v_bot, maskK, maskV, pool_ctr, c.B * c.H_kv + c.B, ks, vsz, st));
+    else
+      GEAR_HIP(launch_v_select(Vp, dm, n, v_top, v_bot, maskV, vsz, st));
     GEAR_HIP(launch_quant_pair({Kp, ks, maskK, pool_ctr, YK, gram}, {Vp, vs, maskV, pool_ctr + slabs, YV, gramV}, dm, n, t_lr, v_top,
                                v_bot, vsz, strip, st));
     GEAR_HIP(launch_power_iteration_pair(pk, pv, dm, n, t_lr, iters, Bcur, gram, nstrips, st));

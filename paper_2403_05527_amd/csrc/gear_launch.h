@@ -42,6 +42,10 @@ hipError_t launch_k_select(const uint16_t* K, const Dims& dm, int n, int k_top, 
                            uint32_t* zero, int zero_count, const SegView& sv, uint16_t* kt_scratch, hipStream_t st);
 // k_top / k_bot: per Value vector (the token's row over all heads); vsz: [B][n] words, a token's (scale, zero) under the
 // per-vector grouping
+// Both selections in one launch, where selects_in_pairs says so (the arguments of launch_k_select and launch_v_select).
+bool selects_in_pairs(const Dims& dm, int n);
+hipError_t launch_select_pair(const uint16_t* K, const uint16_t* V, const Dims& dm, int n, int k_top, int k_bot, int v_top, int v_bot,
+                              uint4* maskK, uint4* maskV, uint32_t* zero, int zero_count, const SegView& ks, uint32_t* vsz, hipStream_t st);
 hipError_t launch_v_select(const uint16_t* V, const Dims& dm, int n, int k_top, int k_bot, uint4* mask, uint32_t* vsz,
                            hipStream_t st);
 // Quantization of one tensor given its mask (compress_quant.h).  Yout (nullable): [slab][n][128] fp16, Y = X - S, from which

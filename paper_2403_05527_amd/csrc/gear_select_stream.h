@@ -52,8 +52,8 @@ static_assert(sizeof(StreamState) == 48, "part of the LDS that stream_plan count
 // that share the 128-byte lines of one slab (of its rows, of its mask) then meet in one L2 instead of eight.  The up to
 // seven slabs past a multiple of eight go to all XCDs.  231 slabs x 3000 tokens, which went to all XCDs as a whole before:
 // 245 -> 106 us.
-__device__ __forceinline__ void slab_and_column_block(int nslab, int ncb, int& slab, int& cb) {
-  const int i = blockIdx.x, even = (nslab & ~7) * ncb;
+__device__ __forceinline__ void slab_and_column_block(int i, int nslab, int ncb, int& slab, int& cb) {
+  const int even = (nslab & ~7) * ncb;
   if (i < even) {
     const int xcd = i & 7, j = i >> 3;
     cb = j % ncb;
@@ -491,7 +491,7 @@ __global__ __launch_bounds__(T, ONCE && NB == 8 && T == 512 ? 6 : 4) void k_sele
   uint32_t* bits = list + (size_t)CB * cap;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < zero_count; i += gridDim.x * blockDim.x) zero[i] = 0u;
   int slab, cb;
-  slab_and_column_block(nslab, D / CB, slab, cb);
+  slab_and_column_block(blockIdx.x, nslab, D / CB, slab, cb);
   const int tid = threadIdx.x, wave = GEAR_WAVE_UNIFORM(tid >> 6), lane = tid & 63;
   const int pc = tid % PC, slot = tid / PC;
   const StreamColumn col{GEAR_BUF_MAKE(K + (size_t)slab * n * D + cb * CB, (n - 1) * (D * 2) + CB * 2), n, pc, slot};

@@ -235,6 +235,7 @@ SELECTIONS = [   # kind of values, slabs, tokens, outliers in ppm, per-vector gr
     ("normal", 1, 5003, 20000, 0),          # ... is one row of each stretch, 16 channels per block
     ("normal", 1, 9001, 10000, 1),          # ... 8 channels per block
     ("normal", 3, 4100, 20000, 0),          # more than one round of blocks of 1024 threads: blocks of 512
+    ("normal", 1, 40, 50000, 1),            # a flushed buffer, without its Values
     ("cliff", 1, 3003, 20000, 1), ("two channels", 1, 4100, 20000, 0), ("coarse grid", 1, 5003, 20000, 1), ("one sign", 1, 3003, 20000, 0),
     ("constant", 1, 9001, 20000, 0), ("falling", 1, 4100, 20000, 1), ("grid", 1, 9001, 150000, 0),   # the last: from a channel-major copy
 ]

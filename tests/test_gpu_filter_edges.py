@@ -38,3 +38,19 @@ def test_filter_and_codes_equal_the_oracle(kind, B, H, n, bits, group, ppm):
         pu.compress_both(gc, oc, _values(kind, (B, H, ns, 128), n + seg), _values(kind, (B, H, ns, 128), n + seg + 7), 2, w.iters,
                          gw.make_init_B(w, 2, seg, "cuda:0"))
     pu.compare_components(gc, oc)
+
+
+@pytest.mark.parametrize("B,H,n,group,ppm,rank,per_head", [
+    (1, 1, 1, 64, 20000, 2, False), (3, 7, 64, 64, 50000, 2, False), (2, 8, 33, 0, 20000, 1, False), (5, 32, 63, 32, 20000, 4, False),
+    (1, 33, 20, 64, 20000, 2, False),                                      # too many heads
+    (2, 12, 21, 0, 20000, 2, True), (2, 5, 40, 0, 0, 2, False),            # (scale, zero) of the Values without their Filter
+    (1, 32, 257, 64, 20000, 4, False), (2, 32, 1024, 0, 20000, 2, False), (3, 32, 513, 64, 20000, 2, False),   # 32, 64 and 96 slabs
+    (64, 1, 301, 64, 20000, 2, False), (4, 9, 515, 128, 20000, 8, False), (1, 16, 1023, 64, 50000, 3, False),
+])
+def test_selections_of_a_short_segment(B, H, n, group, ppm, rank, per_head):
+    """Keys and Values selected in one launch, or in two: the edges of the rule, and blocks whose last tokens do not exist."""
+    dev = "cuda:0"
+    w = gw.Workload("s", B=B, H_kv=H, H_q=H, n=n, bits=2, group=group, outlier_ppm=ppm, rank=rank, rank_chunk=2, n_b=20, steps=1, seed=n + H)
+    gc, oc = pu.make_pair(B, H, H, 2, group, ppm, 20, n, 0, rank, v_per_head=per_head)
+    pu.compress_both(gc, oc, gw.make_keys(w, n, 0, dev), gw.make_values(w, n, 0, dev), rank, 3, gw.make_init_B(w, rank, 0, dev))
+    pu.compare_components(gc, oc)
