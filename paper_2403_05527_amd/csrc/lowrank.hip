@@ -1166,10 +1166,11 @@ __global__ __launch_bounds__(256, 2) void pi_solve_kernel(StartB sb0, StartB sb1
 // Same steps and the same precision choices as the kernels above: A = R B and B' = R^T A accumulate in
 // fp32, column scaling, the QR of B and the coefficient-space orth(A) in fp64.
 // grid (B*H, 2): Keys (y = 0) and Values (y = 1) in one launch, block 256 (a block is one long chain of steps: a
-// flushed buffer of 128 slabs takes 12 us, the two launches one after the other took 13 + 11).
+// flushed buffer of 128 slabs took 12 us, the two launches one after the other 13 + 11).  Sums over rows keep eight reads or 16 lanes at
+// work: one row after the other, a call on 32 slabs x 20 tokens took 21.1 us and not 19.2, on 2048 x 33 of rank 4 157 and not 139.
 // Thread (r0 = tid/16, oc = tid%16) derives channels 8*oc..+7 of rows
 // r0 + 16 k and later forms their share of A; thread (half = tid/128, c = tid%128) sums rows
-// [32 half, 32 half + 32) of B'[c][:], thread (0, c) owns row c of B.
+// 8 half .. + 7 of every 16 of B'[c][:], thread (0, c) owns row c of B.
 constexpr int TINY_ROWS = PI_TINY_ROWS;
 constexpr int TINY_PITCH = D + 4;   // floats per residual row in LDS (16-byte aligned pieces)
 template <int R>
@@ -1298,12 +1299,12 @@ __global__ __launch_bounds__(256, 3) void pi_tiny_kernel(const uint16_t* __restr
     float p[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) p[r] = 0.0f;
-    {
-      const int t_hi = n < 32 * half + 32 ? n : 32 * half + 32;
-      for (int t = 32 * half; t < t_hi; ++t) {
-        const float rv = sm.Rs[t][c];
+    for (int t0 = 8 * half; t0 < n; t0 += 16) {   // (rows n .. of the last 16 are 0; eight reads in flight: one by one, each costs its latency)
 #pragma unroll
-        for (int r = 0; r < R; ++r) p[r] += rv * sm.As[t][r];
+      for (int u = 0; u < 8; ++u) {
+        const float rv = sm.Rs[t0 + u][c];
+#pragma unroll
+        for (int r = 0; r < R; ++r) p[r] += rv * sm.As[t0 + u][r];
       }
     }
     if (!owner) {
@@ -1326,11 +1327,15 @@ __global__ __launch_bounds__(256, 3) void pi_tiny_kernel(const uint16_t* __restr
       continue;
     }
     // last round: orth(A) = A C from the r x r Gram matrix of A; B = R^T orth(A) = B' C
-    if (tid < R * R) {
-      const int i = tid / R, j = tid % R;
+#pragma unroll
+    for (int p0 = 0; p0 < R * R; p0 += 16) {   // an entry by 16 lanes
+      const int e = p0 + (tid >> 4), i = (e / R) % R, j = e % R;
       double s = 0.0;
-      for (int t = 0; t < n; ++t) s += (double)sm.As[t][i] * (double)sm.As[t][j];
-      sm.GA[i][j] = s;
+#pragma unroll
+      for (int t = 0; t < TINY_ROWS; t += 16)
+        if (t + oc < n) s += (double)sm.As[t + oc][i] * (double)sm.As[t + oc][j];
+      s = row16_sum_d(s);
+      if (oc == 0 && e < R * R) sm.GA[i][j] = s;
     }
     block_lds_sync();
     if (tid < 64) coeff_orth_lds<R>(sm.GA, sm.C, tid);
