@@ -125,63 +125,46 @@ __global__ __launch_bounds__(64 * SINGLE_WAVES<GQ>) void decode_single_kernel(Di
   }
 }
 
-// grid (B*H_q), block 128: thread c merges channel c of the row's nrec records, 64 records per round.
-// Lane s of every wave fetches (m, l) of record s, so the weights of up to 64 records come from one
-// round of loads.  WIDE (rows with many records: long contexts at a small batch, where the kernel is a
-// few blocks' latency): a thread requests its channel of all the round's records before anything is
-// used, one load latency per round; otherwise eight at a time (fewer registers: more rows in flight).
+// grid (B*H_q), block 128: thread c merges channel c of the row's nrec records, AT_ONCE (16, 32 or 64) records per round.
+// Lane s of every wave fetches (m, l) of record s, so the weights of a round's records come from one
+// round of loads, and the thread's channel of all of them is requested along with it: the kernel is one load latency and a short
+// chain, which registers alone exchange lanes in.  Eight records at a time behind the weights, with shuffles through LDS, a read took a
+// microsecond more (16 x 32 heads x 4096 tokens, 11 records, 58.2 -> 57.2 us, 32 x 32768, 66 records, 33.9 -> 33.0, 40 slabs x 3001 23.9 -> 23.5).
 // Records past the last read as 0 through the buffer view.
-template <bool WIDE>
+template <int AT_ONCE>
 __global__ __launch_bounds__(128) void decode_combine_kernel(const float* __restrict__ partial, int nrec,
                                                              uint16_t* __restrict__ out) {
   const int row = blockIdx.x, c = threadIdx.x, lane = threadIdx.x & 63;
   const GEAR_BUF_T rb = GEAR_BUF_MAKE(partial + (size_t)row * nrec * DECODE_REC, nrec * (DECODE_REC * 4));
   float M = -INFINITY, L = 0.0f, o = 0.0f;
-  for (int s0 = 0; s0 < nrec; s0 += 64) {
-    const int cnt = nrec - s0 < 64 ? nrec - s0 : 64;
+  for (int s0 = 0; s0 < nrec; s0 += AT_ONCE) {
+    const int cnt = nrec - s0 < AT_ONCE ? nrec - s0 : AT_ONCE;
     const uint2 ml = GEAR_BUF_LOAD8(rb, (s0 + lane) * (DECODE_REC * 4));
-    float v[WIDE ? 64 : 1];
-    if constexpr (WIDE) {
+    float v[AT_ONCE];
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        if (16 * b < cnt) {   // block-uniform
+    for (int b = 0; b < AT_ONCE; b += 8) {
+      if (b < cnt) {   // block-uniform
 #pragma unroll
-          for (int u = 0; u < 16; ++u)
-            v[16 * b + u] = __uint_as_float(GEAR_BUF_LOAD4(rb, ((s0 + 16 * b + u) * DECODE_REC + 2 + c) * 4));
-        } else {
+        for (int u = 0; u < 8; ++u) v[b + u] = __uint_as_float(GEAR_BUF_LOAD4(rb, ((s0 + b + u) * DECODE_REC + 2 + c) * 4));
+      } else {
 #pragma unroll
-          for (int u = 0; u < 16; ++u) v[16 * b + u] = 0.0f;
-        }
+        for (int u = 0; u < 8; ++u) v[b + u] = 0.0f;
       }
     }
     const float m = lane < cnt ? __uint_as_float(ml.x) : -INFINITY;
     const float l = lane < cnt ? __uint_as_float(ml.y) : 0.0f;
-    float Mn = m;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) Mn = fmaxf(Mn, __shfl_xor(Mn, d, 64));
-    Mn = fmaxf(Mn, M);
+    const float Mn = fmaxf(wave_max(m), M);
     if (Mn == -INFINITY) continue;                      // nothing but empty records so far
     const float f = (m == -INFINITY) ? 0.0f : __expf(m - Mn);
     const float keep = (M == -INFINITY) ? 0.0f : __expf(M - Mn);
-    L = L * keep + wave_sum_shfl(l * f);
+    L = L * keep + wave_sum(l * f);
     o *= keep;
     M = Mn;
-    if constexpr (WIDE) {
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        if (16 * b < cnt) {
+    for (int b = 0; b < AT_ONCE; b += 8) {
+      if (b < cnt) {
 #pragma unroll
-          for (int u = 0; u < 16; ++u) o += v[16 * b + u] * __shfl(f, 16 * b + u, 64);
-        }
-      }
-    } else {
-      constexpr int UN = 8;
-      for (int j0 = 0; j0 < cnt; j0 += UN) {
-        float w[UN];
-#pragma unroll
-        for (int u = 0; u < UN; ++u) w[u] = __uint_as_float(GEAR_BUF_LOAD4(rb, ((s0 + j0 + u) * DECODE_REC + 2 + c) * 4));
-#pragma unroll
-        for (int u = 0; u < UN; ++u) o += w[u] * __shfl(f, (j0 + u) & 63, 64);
+        for (int u = 0; u < 8; ++u) o += v[b + u] * lane_bcast(f, b + u);
       }
     }
   }
@@ -318,10 +301,10 @@ static hipError_t launch_decode_t(const Dims& dm, const SegView& k0, const SegVi
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((decode_split_kernel<BITS, GQ, LG>), dim3(s.nblocks, blocks), dim3(256), lds, st, dm, k0, v0, cs, q, Kbuf, Vbuf,
                      n_buf, n_buf_cap, (k0.n + MFMA_TS - 1) / MFMA_TS, s.pp, s.rc, s.odd_rank, q_len, causal, plan.lparts, partial);
-  if (s.nblocks > GEAR_MERGE_AT_ONCE)
-    hipLaunchKernelGGL(decode_combine_kernel<true>, dim3(dm.B * dm.Hq), dim3(128), 0, st, (const float*)partial, s.nblocks, out);
-  else
-    hipLaunchKernelGGL(decode_combine_kernel<false>, dim3(dm.B * dm.Hq), dim3(128), 0, st, (const float*)partial, s.nblocks, out);
+  const dim3 rows(dm.B * dm.Hq);
+  if (s.nblocks > GEAR_MERGE_AT_ONCE) hipLaunchKernelGGL(decode_combine_kernel<64>, rows, dim3(128), 0, st, (const float*)partial, s.nblocks, out);
+  else if (s.nblocks > GEAR_MERGE_AT_ONCE / 2) hipLaunchKernelGGL(decode_combine_kernel<32>, rows, dim3(128), 0, st, (const float*)partial, s.nblocks, out);
+  else hipLaunchKernelGGL(decode_combine_kernel<16>, rows, dim3(128), 0, st, (const float*)partial, s.nblocks, out);
   return hipGetLastError();
 }
 
