@@ -2,7 +2,9 @@
 // into S, and the launch of the quantization kernel (compress_quant.h).  The result of the Filter is a bit per entry,
 // 16 bytes per token row.
 //   k_select_tiny_kernel   segments of at most 64 tokens (a flushed buffer): one thread per vector
-//   k_select_stream_kernel more than 1024 tokens: candidates collected by blocks of 8 or 16 channels, then ranked (gear_select_stream.h)
+//   (it and k_select_reg_kernel's shortest segments mostly go together with the Values: select_pair_kernel)
+//   k_select_stream_kernel more than 1024 tokens: candidates collected by blocks of 8 or 16 channels and 512 or 1024 threads, then ranked
+//                          (gear_select_stream.h)
 //   k_select_reg_kernel    otherwise up to 8192 tokens: one wave per vector, the vector in registers
 //   k_select_long_kernel   otherwise: one wave per vector, from a channel-major copy of the keys
 #include <math.h>
