@@ -502,7 +502,7 @@ __device__ __forceinline__ void quant_body(uint4 (&tile)[QT][D / 8], QuantSmem<I
             if constexpr (GRAM) {
               const uint32_t hi = pack_h2(res[0], res[1]);
               oph[e][j] = hi;
-              opl[e][j] = GEAR_SPLIT_LO(hi, res[0], res[1]);
+              opl[e][j] = pack_h2(__builtin_fmaf(h2f(hi & 0xFFFFu), -one, res[0]), __builtin_fmaf(h2f(hi >> 16), -one, res[1]));
               if (!IS_K) GEAR_PIN_VGPR(opl[e][j]);   // (here, and not behind the code words: the residuals would have to be kept)
             }
           }

@@ -34,6 +34,10 @@
 #ifndef GEAR_OPAQUE_U32
 #define GEAR_OPAQUE_U32(x) asm("" : "+s"(x))
 #endif
+// Four values that the compiler does not see through (in vector registers; not volatile).
+#ifndef GEAR_OPAQUE_VGPR4
+#define GEAR_OPAQUE_VGPR4(x) asm("" : "+v"((x)[0]), "+v"((x)[1]), "+v"((x)[2]), "+v"((x)[3]))
+#endif
 
 // The scheduler moves no instruction across this point.
 #ifndef GEAR_SCHED_FENCE
@@ -107,19 +111,6 @@
     (a) = r__[0];                                                              \
     (b) = r__[1];                                                              \
   } while (0)
-#endif
-
-// What the two halves of hi leave of two floats: v - hi (exact in fp32), rounded to fp16.  The compiler takes three instructions for it.
-#ifndef GEAR_SPLIT_LO
-namespace gear {
-__device__ __forceinline__ uint32_t split_lo(uint32_t hi, float v0, float v1) {
-  uint32_t lo;
-  asm("v_fma_mixlo_f16 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(lo) : "v"(hi), "v"(v0));
-  asm("v_fma_mixhi_f16 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(lo) : "v"(hi), "v"(v1));
-  return lo;
-}
-}  // namespace gear
-#define GEAR_SPLIT_LO(hi, v0, v1) gear::split_lo((hi), (v0), (v1))
 #endif
 
 // Fewest tokens (B * n) of a call for which the Value selection runs by token rows, four tokens per wave

@@ -584,6 +584,28 @@ typedef _Float16 project_h8 __attribute__((ext_vector_type(8)));
 constexpr int PROJECT_ROWS = 16;   // tokens of a step
 constexpr int PROJECT_WAVE = 64;   // tokens of a wave
 
+// Eight floats as the two fp16 parts of a matrix operand: hi, and what it leaves, v - hi (exact in fp32), rounded.  `one` is 1 in a scalar register
+// that the compiler does not see through, so that the difference and its rounding are one mixed-precision instruction per entry.  It has to find
+// them by itself: of instructions in inline asm it does not know that they write vector registers, and it leaves out wait states before
+// a matrix instruction that reads those (it put one of two) and after one whose operands they overwrite.  (hi opaque: otherwise its
+// halves are made twice; l0 opaque: otherwise the two halves of lo are rounded together, three instructions instead of two; by
+// fours: behind such an asm the compiler leaves a wait state.  2493 vector instructions in the kernel of rank 4 and 2 bits, as with asm; 2635
+// with neither, 2981 with a subtraction.)
+__device__ __forceinline__ void split8(const float (&v)[8], float one, uint32_t (&hi)[4], uint32_t (&lo)[4]) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) hi[j] = pack_h2(v[2 * j], v[2 * j + 1]);
+  GEAR_OPAQUE_VGPR4(hi);
+  _Float16 l0[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) l0[j] = (_Float16)__builtin_fmaf((float)__builtin_bit_cast(h2_t, hi[j])[0], -one, v[2 * j]);
+  GEAR_OPAQUE_VGPR4(l0);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const h2_t l = {l0[j], (_Float16)__builtin_fmaf((float)__builtin_bit_cast(h2_t, hi[j])[1], -one, v[2 * j + 1])};
+    lo[j] = __builtin_bit_cast(uint32_t, l);
+  }
+}
+
 template <bool IS_K, int BITS, int R>
 __device__ __forceinline__ void project_wave(uint4 (&rows)[PROJECT_ROWS][D / 8], const uint16_t* __restrict__ X, const uint4* __restrict__ mask,
                                              const SegView& sv, int lg /* log2 of the group size */, int slab, int t0, int n, int t_lr,
@@ -624,6 +646,8 @@ __device__ __forceinline__ void project_wave(uint4 (&rows)[PROJECT_ROWS][D / 8],
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) wf[kb] = __builtin_bit_cast(project_h8, GEAR_BUF_LOAD16(wbuf, at + 16 * kb));
   }
+  float one = 1.0f;
+  GEAR_PIN_SGPR(one);
   const float rs = scale[slab].r;
   float back[4];   // of columns 4 (kg % 2) + i
 #pragma unroll
@@ -693,10 +717,9 @@ __device__ __forceinline__ void project_wave(uint4 (&rows)[PROJECT_ROWS][D / 8],
 #pragma unroll
         for (int e = 0; e < 4; ++e) cv[e] = (e < 2 ? w : w2) & (0x000F000Fu << (4 * (e & 1)));
       }
-      uint32_t hi[4], lo[4];
+      float res[8];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        float res[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           const int e = 2 * j + h;
@@ -705,17 +728,17 @@ __device__ __forceinline__ void project_wave(uint4 (&rows)[PROJECT_ROWS][D / 8],
             const int ch = BITS == 2 ? kb & 1 : e >> 2;
             const uint32_t cw = cv[BITS == 2 ? e : e & 3];
             const float code = h2f(ch ? cw >> 16 : cw & 0xFFFFu);   // times 2^(bit - 24)
-            res[h] = __builtin_fmaf(-code, pdl[8 * kb + e], __builtin_fmaf(y, rs, pmn[8 * kb + e]));
+            res[e] = __builtin_fmaf(-code, pdl[8 * kb + e], __builtin_fmaf(y, rs, pmn[8 * kb + e]));
           } else {
 #pragma clang fp contract(off)
             const float ym = __builtin_fmaf(y, rs, mn);   // (y - zero) rs, rounded as y - zero is
             const float k = clamp_f32(rintf(__fmul_rn(ym, inv)), 0.0f, QMAX);
-            res[h] = __builtin_fmaf(-k, dl, ym);
+            res[e] = __builtin_fmaf(-k, dl, ym);
           }
         }
-        hi[j] = pack_h2(res[0], res[1]);
-        lo[j] = GEAR_SPLIT_LO(hi[j], res[0], res[1]);
       }
+      uint32_t hi[4], lo[4];
+      split8(res, one, hi, lo);
       acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[kb], __builtin_bit_cast(project_h8, make_uint4(hi[0], hi[1], hi[2], hi[3])), acc, 0, 0, 0);
       acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[kb], __builtin_bit_cast(project_h8, make_uint4(lo[0], lo[1], lo[2], lo[3])), acc, 0, 0, 0);
     }

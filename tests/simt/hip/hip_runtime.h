@@ -55,6 +55,7 @@ inline hipError_t hipGetSymbolAddress(void** p, const void* sym) { *p = const_ca
 #define GEAR_SCHED_FENCE() ((void)0)
 #define GEAR_PIN_SGPR(x) asm volatile("" : "+x"(x))
 #define GEAR_OPAQUE_U32(x) ((void)0)
+#define GEAR_OPAQUE_VGPR4(x) ((void)0)
 #define GEAR_PK_MIN_F16(a, b) simt_pk_f16((a), (b), true)
 #define GEAR_PK_MAX_F16(a, b) simt_pk_f16((a), (b), false)
 #define GEAR_LANE_SWAP32(a, b) simt::lane_swap((a), (b), 32)
@@ -69,7 +70,6 @@ inline hipError_t hipGetSymbolAddress(void** p, const void* sym) { *p = const_ca
 #define GEAR_BYTE_PERM(hi, lo, sel) simt_byte_perm((hi), (lo), (sel))
 #define GEAR_FMED3(x, lo, hi) fminf(fmaxf((x), (lo)), (hi))
 #define GEAR_FDOT2(a, b, c) simt_fdot2((a), (b), (c))
-#define GEAR_SPLIT_LO(hi, v0, v1) gear::pack_h2((v0) - gear::h2f((hi) & 0xFFFFu), (v1) - gear::h2f((hi) >> 16))
 #define GEAR_UBFE(x, off, width) (((uint32_t)(x) >> (off)) & ((1u << (width)) - 1u))
 struct simt_buf { const unsigned char* p; uint32_t n; };
 #define GEAR_BUF_T simt_buf
