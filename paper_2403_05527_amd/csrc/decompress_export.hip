@@ -58,18 +58,19 @@ __device__ __forceinline__ void for_each_ell(const SegView& sv, int is_k, int sl
 
 // ---- decompress: X-hat = D + A B^T + S of one 64-token tile ----
 // The floor is HBM (2 bytes written per entry, about 0.45 read).  A thread owns eight neighbouring channels, i.e. one
-// 16-byte piece of each of eight neighbouring rows; the 16 lanes of a row write its 256 bytes together.  A Value's eight tokens lie in
-// one code word per channel (all of it at 4 bits, half of it at 2): eight words give eight row pieces, with no exchange between lanes.
+// 16-byte piece of each of four or eight neighbouring rows; the 16 lanes of a row write its 256 bytes together.  A Value's tokens lie in
+// one code word per channel: eight words give the row pieces, with no exchange between lanes.
 // S goes through an fp16 tile in LDS (entries off its support are 0) because its slots and lists belong to rows (Keys)
 // or channels (Values) and not to the piece's owner.  To keep the arithmetic under the write stream, codes become
 // floats a byte at a time (no bit-field extract per entry) and the rank sum runs on the fp16 factors as they are
 // stored, two ranks per instruction.  Every load that does not depend on the list table is requested before the first
 // wait.
 // What bounded it was the number of load instructions (26 for the four row pieces a thread had): so factors and Value parameters come in
-// whole 16-byte pieces, and a thread's channels' words and factors serve eight rows.  Keys and Values together, four rows -> four rows
-// with whole pieces -> eight rows: 16 x 32 heads x 4096 tokens of rank 4 (1.34 GB moved) at 2 bits 363 -> 321 -> 285 us (4.7 TB/s), at 4 bits 358 ->
-// 300 -> 261, 7 x 40 x 1777 at 4 bits 66 -> 56 -> 57, 32 x 32768 of rank 8 189 -> 179 -> 120, 64 x 8192 in groups of 32 88 -> 55 -> 57; stored
-// without the non-temporal hint 289, 272, 75, 175, 80.
+// whole 16-byte pieces, and on a full chip a thread's channels' words and factors serve eight rows (decompress_rows).  Keys and Values together, four
+// rows -> four rows with whole pieces -> eight rows: 16 x 32 heads x 4096 tokens of rank 4 (1.34 GB moved) at 2 bits 363 -> 321 -> 285 us (4.7 TB/s), at 4
+// bits 358 -> 300 -> 261, 7 x 40 x 1777 at 4 bits 66 -> 56 -> 57, 32 x 32768 of rank 8 189 -> 179 -> 120, 64 x 8192 in groups of 32 88 -> 55 -> 57; stored
+// without the non-temporal hint 289, 272, 75, 175, 80. A thread has two entries
+// of the list in flight: large grids at 15 % outliers take 0.87 of the time that they took with one, those of up to 5 % 0.98 to 1.0 (four: 0.88, and 1.00 to 1.01).
 // R: the rank rounded up to 0, 2, 4 or 8; NW = R / 2 words of two factors.
 template <int R>
 struct FactorRow {
@@ -148,45 +149,54 @@ __device__ __forceinline__ uint4 decompress_piece(uint32_t c0, uint32_t c1, cons
   return make_uint4(o[0], o[1], o[2], o[3]);
 }
 constexpr int SP_PITCH = D + 8;   // fp16 entries per row of the S tile (16-byte pieces of neighbouring rows in different banks)
-constexpr int DEC_ROWS = 8;       // rows of a thread
-constexpr int DEC_THREADS = TILE * (D / 8) / DEC_ROWS;
+constexpr int dec_threads(int rows) { return TILE * (D / 8) / rows; }   // rows: of a thread
 
-// grid (ceil(n/64), B*H), block DEC_THREADS.
-template <bool IS_K, int BITS, int R>
-__global__ __launch_bounds__(DEC_THREADS) void decompress_kernel(Dims dm, SegView sv, uint16_t* __restrict__ out, int n_total) {
-  constexpr int TPW = 32 / BITS;
+// grid (ceil(n/64), B*H), block dec_threads(ROWS).
+template <bool IS_K, int BITS, int R, int ROWS>
+__global__ __launch_bounds__(dec_threads(ROWS)) void decompress_kernel(Dims dm, SegView sv, uint16_t* __restrict__ out, int n_total) {
+  constexpr int THREADS = dec_threads(ROWS), TPW = 32 / BITS;
   constexpr int NWG = TILE / TPW;   // Values: code words of a channel in the tile
   constexpr uint32_t CMASK = BITS == 2 ? 0x03030303u : 0x0F0F0F0Fu;
   __shared__ __align__(16) uint16_t sp[TILE * SP_PITCH];
   const int slab = blockIdx.y, tile = blockIdx.x, t0 = tile * TILE;
-  const int tid = threadIdx.x, oc = tid & 15, q8 = tid >> 4;
+  const int tid = threadIdx.x, oc = tid & 15, q = tid >> 4;
   const int lg = 31 - __clz(dm.g), lng = 7 - lg;   // log2 of the group size, of a Value row's groups
   const bool sparse = dm.ppm > 0;
-  // the thread's rows of the tile: row0 .. row0 + 7 (a Value's lie in one code word per channel: all of it, or half)
-  const int wg = q8 & (NWG - 1), part = q8 / NWG;   // Values
-  const int row0 = IS_K ? DEC_ROWS * q8 : wg * TPW + DEC_ROWS * part;
+  // the thread's rows of the tile: row0 .. row0 + ROWS - 1 (a Value's lie in one code word per channel: all of it, or a part)
+  const int wg = q & (NWG - 1), part = q / NWG;   // Values
+  const int row0 = IS_K ? ROWS * q : wg * TPW + ROWS * part;
   // views of the slab's rows: what lies past the last row is not written (up to a whole piece of the rows' parameters is read)
   const GEAR_BUF_T ob = GEAR_BUF_MAKE(out + ((size_t)slab * n_total + sv.t0) * D, (uint32_t)sv.n * (D * 2));
   const GEAR_BUF_T ab = GEAR_BUF_MAKE(sv.A + (size_t)slab * sv.n_cap * sv.rank, ((uint32_t)sv.n * sv.rank * 2 + 15u) & ~15u);
   const GEAR_BUF_T bb = GEAR_BUF_MAKE(sv.Bf + (size_t)slab * D * sv.rank, (uint32_t)(D * 2) * sv.rank);
   uint2 tab = make_uint2(0u, 0u);
-  uint2 slot = make_uint2(0u, 0u);   // the thread's two fixed slots of the tile (256 of them)
-  static_assert(TILE * ELL_K == 2 * DEC_THREADS && D * ELL_V == 2 * DEC_THREADS, "two slots per thread");
+  constexpr int SLOTS = TILE * ELL_K / THREADS;   // the thread's fixed slots of the tile
+  static_assert(TILE * ELL_K == D * ELL_V && (SLOTS == 1 || SLOTS == 2), "one or two slots per thread");
+  uint32_t slot[2] = {0u, 0u};
   if (sparse) {
     tab = sv.sp_table[(size_t)slab * sv.ntile_cap + tile];
-    if constexpr (IS_K)
-      slot = GEAR_BUF_LOAD8(GEAR_BUF_MAKE(sv.ell + (size_t)slab * sv.n_cap * ELL_K, (uint32_t)sv.n * (ELL_K * 4)), (t0 * ELL_K + 2 * tid) * 4);
-    else
-      slot = *reinterpret_cast<const uint2*>(sv.ell + ((size_t)slab * sv.ntile_cap + tile) * (D * ELL_V) + 2 * tid);
+    // (a Key segment's last rows may not all exist)
+    const uint32_t* ell = sv.ell + ((size_t)slab * sv.ntile_cap + tile) * (D * ELL_V) + SLOTS * tid;   // Values
+    const GEAR_BUF_T eb = GEAR_BUF_MAKE(sv.ell + (size_t)slab * sv.n_cap * ELL_K, (uint32_t)sv.n * (ELL_K * 4));
+    if constexpr (SLOTS == 2) {
+      uint2 t;
+      if constexpr (IS_K) t = GEAR_BUF_LOAD8(eb, (t0 * ELL_K + 2 * tid) * 4);
+      else t = *reinterpret_cast<const uint2*>(ell);
+      slot[0] = t.x;
+      slot[1] = t.y;
+    } else {
+      if constexpr (IS_K) slot[0] = GEAR_BUF_LOAD4(eb, (t0 * ELL_K + tid) * 4);
+      else slot[0] = *ell;
+    }
   }
   uint32_t cw[8];          // Keys: cw[k] the 8 codes of row k; Values: cw[e] the word of channel 8 oc + e
-  uint32_t zv[DEC_ROWS];   // Values: (scale, zero) of the rows
+  uint32_t zv[ROWS];   // Values: (scale, zero) of the rows
   uint4 zk[2];             // Keys: (scale, zero) of the channels in the rows' group
-  FactorRow<R> a[DEC_ROWS], bf[8];
+  FactorRow<R> a[ROWS], bf[8];
   if constexpr (IS_K) {
     const GEAR_BUF_T cb = GEAR_BUF_MAKE(sv.codes + (size_t)slab * sv.n_cap * (4 * BITS), (uint32_t)sv.n * (16 * BITS));
 #pragma unroll
-    for (int k = 0; k < DEC_ROWS; ++k) {
+    for (int k = 0; k < ROWS; ++k) {
       const int t = t0 + row0 + k;
       cw[k] = BITS == 4 ? GEAR_BUF_LOAD4(cb, t * 64 + oc * 4) : GEAR_BUF_LOAD2(cb, t * 32 + oc * 2);
     }
@@ -204,55 +214,57 @@ __global__ __launch_bounds__(DEC_THREADS) void decompress_kernel(Dims dm, SegVie
     const int G = (oc * 8) >> lg;
     if (lng == 0) {
 #pragma unroll
-      for (int k = 0; k < DEC_ROWS; k += 4) {
+      for (int k = 0; k < ROWS; k += 4) {
         const uint4 z = GEAR_BUF_LOAD16(zb, (t0 + row0 + k) * 4);
         zv[k] = z.x; zv[k + 1] = z.y; zv[k + 2] = z.z; zv[k + 3] = z.w;
       }
     } else if (lng == 1) {
 #pragma unroll
-      for (int k = 0; k < DEC_ROWS; k += 2) {
+      for (int k = 0; k < ROWS; k += 2) {
         const uint4 z = GEAR_BUF_LOAD16(zb, (t0 + row0 + k) * 8);
         zv[k] = G ? z.y : z.x;
         zv[k + 1] = G ? z.w : z.z;
       }
     } else {
 #pragma unroll
-      for (int k = 0; k < DEC_ROWS; ++k) zv[k] = GEAR_BUF_LOAD4(zb, (((t0 + row0 + k) << lng) + G) * 4);
+      for (int k = 0; k < ROWS; ++k) zv[k] = GEAR_BUF_LOAD4(zb, (((t0 + row0 + k) << lng) + G) * 4);
     }
   }
-  load_factors<R, DEC_ROWS>(ab, t0 + row0, sv.rank, a);
+  load_factors<R, ROWS>(ab, t0 + row0, sv.rank, a);
   load_factors<R, 8>(bb, oc * 8, sv.rank, bf);
 
   if (sparse) {
-    for (int i = tid; i < TILE * SP_PITCH / 8; i += DEC_THREADS) reinterpret_cast<uint4*>(sp)[i] = make_uint4(0, 0, 0, 0);
+    for (int i = tid; i < TILE * SP_PITCH / 8; i += THREADS) reinterpret_cast<uint4*>(sp)[i] = make_uint4(0, 0, 0, 0);
     block_lds_sync();
     const uint32_t* lst = sv.sp_pool + (size_t)(IS_K ? slab : slab / dm.H) * sv.pool_cap + tab.x;
-    for (uint32_t e = tid; e < tab.y; e += DEC_THREADS) {
-      const uint32_t en = lst[e];
-      sp[((en & 0xFFFFu) >> 7) * SP_PITCH + (en & 127u)] = (uint16_t)(en >> 16);
+    auto place = [&](uint32_t en) { sp[((en & 0xFFFFu) >> 7) * SP_PITCH + (en & 127u)] = (uint16_t)(en >> 16); };
+    for (uint32_t e = tid; e < tab.y; e += 2 * THREADS) {   // (two of a thread's entries in flight)
+      const bool more = e + THREADS < tab.y;
+      const uint32_t en = lst[e], en2 = more ? lst[e + THREADS] : 0u;
+      place(en);
+      if (more) place(en2);
     }
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const uint32_t en = h ? slot.y : slot.x;
-      if (en & ELL_VALID) {
-        const int i = 2 * tid + h, tl = IS_K ? i / ELL_K : (int)(en & 63u), c = IS_K ? (int)(en & 127u) : i / ELL_V;
-        sp[tl * SP_PITCH + c] = (uint16_t)(en >> 16);
+    for (int h = 0; h < SLOTS; ++h) {
+      if (slot[h] & ELL_VALID) {
+        const int i = SLOTS * tid + h, tl = IS_K ? i / ELL_K : (int)(slot[h] & 63u), c = IS_K ? (int)(slot[h] & 127u) : i / ELL_V;
+        sp[tl * SP_PITCH + c] = (uint16_t)(slot[h] >> 16);
       }
     }
     block_lds_sync();
   }
   // Values: the codes of channels 4 h .. 4 h + 3 a byte position at a time: bytes of tokens row0 + 4 p .. (2 bits), row0 + 2 p .. (4 bits)
-  constexpr int NB = IS_K ? 1 : 8 * BITS / 8;
+  constexpr int NB = IS_K ? 1 : ROWS * BITS / 8;
   uint32_t cb4[NB][2];
   if constexpr (!IS_K) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
 #pragma unroll
       for (int p = 0; p < NB; p += 2) {   // bytes p, p + 1 of my part of the words
-        const uint32_t s2 = 0x05010400u + 0x01010101u * (uint32_t)((BITS == 2 ? 2 * part : 0) + p);   // (lo[p], hi[p], lo[p + 1], hi[p + 1])
+        const uint32_t s2 = 0x05010400u + 0x01010101u * (uint32_t)(NB * part + p);   // (lo[p], hi[p], lo[p + 1], hi[p + 1])
         const uint32_t x = GEAR_BYTE_PERM(cw[4 * h + 1], cw[4 * h], s2), y = GEAR_BYTE_PERM(cw[4 * h + 3], cw[4 * h + 2], s2);
         cb4[p][h] = GEAR_BYTE_PERM(y, x, 0x05040100u);
-        cb4[p + 1][h] = GEAR_BYTE_PERM(y, x, 0x07060302u);
+        if (p + 1 < NB) cb4[p + 1][h] = GEAR_BYTE_PERM(y, x, 0x07060302u);
       }
     }
   }
@@ -263,7 +275,7 @@ __global__ __launch_bounds__(DEC_THREADS) void decompress_kernel(Dims dm, SegVie
     for (int e = 0; e < 8; ++e) { dl[e] = h2f(w[e] & 0xFFFFu); mn[e] = h2f(w[e] >> 16); }
   }
 #pragma unroll
-  for (int k = 0; k < DEC_ROWS; ++k) {
+  for (int k = 0; k < ROWS; ++k) {
     const int tl = row0 + k;
     uint32_t c0, c1;
     if constexpr (IS_K) {
@@ -451,23 +463,48 @@ __global__ void export_lowrank_kernel(SegView sv, uint16_t* __restrict__ A, uint
   }
 }
 
-template <bool IS_K, int BITS>
+template <bool IS_K, int BITS, int ROWS>
 static void launch_decompress_t(const Dims& dm, const SegView& sv, uint16_t* out, int n_total, hipStream_t st) {
-  const dim3 grid((sv.n + TILE - 1) / TILE, dm.B * dm.H);
-  if (sv.rank == 0) hipLaunchKernelGGL((decompress_kernel<IS_K, BITS, 0>), grid, dim3(DEC_THREADS), 0, st, dm, sv, out, n_total);
-  else if (sv.rank <= 2) hipLaunchKernelGGL((decompress_kernel<IS_K, BITS, 2>), grid, dim3(DEC_THREADS), 0, st, dm, sv, out, n_total);
-  else if (sv.rank <= 4) hipLaunchKernelGGL((decompress_kernel<IS_K, BITS, 4>), grid, dim3(DEC_THREADS), 0, st, dm, sv, out, n_total);
-  else hipLaunchKernelGGL((decompress_kernel<IS_K, BITS, 8>), grid, dim3(DEC_THREADS), 0, st, dm, sv, out, n_total);
+  const dim3 grid((sv.n + TILE - 1) / TILE, dm.B * dm.H), block(dec_threads(ROWS));
+  if (sv.rank == 0) hipLaunchKernelGGL((decompress_kernel<IS_K, BITS, 0, ROWS>), grid, block, 0, st, dm, sv, out, n_total);
+  else if (sv.rank <= 2) hipLaunchKernelGGL((decompress_kernel<IS_K, BITS, 2, ROWS>), grid, block, 0, st, dm, sv, out, n_total);
+  else if (sv.rank <= 4) hipLaunchKernelGGL((decompress_kernel<IS_K, BITS, 4, ROWS>), grid, block, 0, st, dm, sv, out, n_total);
+  else hipLaunchKernelGGL((decompress_kernel<IS_K, BITS, 8, ROWS>), grid, block, 0, st, dm, sv, out, n_total);
+}
+// Rows of a thread, 4 or 8.  Eight halve the loads of codes and factors, four have twice the waves and half the chain.  Times of four rows to those of
+// eight, Keys and Values, nothing of the cache in the chip's caches; by tiles (of 64 tokens, all slabs):
+//   tiles         up to 512      to 768      to 1024     to 1536     to 8192       more
+//   rank 0        0.87 to 0.98   0.96        0.98        1.06        0.99 to 1.04  1.01
+//   rank 1        0.87 to 0.98   1.05        1.06        1.09        1.13          1.32
+//   rank 2, 4     0.75 to 0.97   0.88, 0.95  0.94, 0.98  1.02, 1.08  0.96 to 1.10  1.07
+//   rank 8        0.76 to 0.89   0.92        0.99        1.03        0.99 to 1.10  1.22  (where the cache is near, 1.16 at 1024)
+//   others        1.0 to 1.3 up to 256 tiles, 1.2 to 1.85 beyond, where the cache is near (a row's factors are several loads)
+// The more entries in lists, which 128 threads fetch half as fast, the less eight gain where factors come in whole pieces: level at 15 % outliers (rank 0
+// 0.93), and 149 : 178 us at 40 % (12 x 16 x 4052, rank 4).  Tiles of few rows (segments of up to 110 tokens) do not count as whole ones for these
+// ranks: 0.90 to 0.97 up to 7000 of them.
+static int decompress_rows(const Dims& dm, const SegView& sv) {
+  const long long tiles = (long long)((sv.n + TILE - 1) / TILE) * dm.B * dm.H, rows = (long long)sv.n * dm.B * dm.H;
+  switch (sv.rank) {
+    case 0: case 2: case 4: return rows > 1024 * TILE && dm.ppm <= 100000 ? 8 : 4;
+    case 1: return tiles > 512 ? 8 : 4;
+    case 8: return tiles > 768 ? 8 : 4;
+    default: return 8;
+  }
+}
+template <bool IS_K, int BITS>
+static void launch_decompress_r(const Dims& dm, const SegView& sv, uint16_t* out, int n_total, hipStream_t st) {
+  if (decompress_rows(dm, sv) == 4) launch_decompress_t<IS_K, BITS, 4>(dm, sv, out, n_total, st);
+  else launch_decompress_t<IS_K, BITS, 8>(dm, sv, out, n_total, st);
 }
 
 hipError_t launch_decompress(const Dims& dm, const SegView& ks, const SegView& vs, uint16_t* Kout,
                              uint16_t* Vout, int n_total, hipStream_t st) {
   if (dm.bits == 2) {
-    if (Kout) launch_decompress_t<true, 2>(dm, ks, Kout, n_total, st);
-    if (Vout) launch_decompress_t<false, 2>(dm, vs, Vout, n_total, st);
+    if (Kout) launch_decompress_r<true, 2>(dm, ks, Kout, n_total, st);
+    if (Vout) launch_decompress_r<false, 2>(dm, vs, Vout, n_total, st);
   } else {
-    if (Kout) launch_decompress_t<true, 4>(dm, ks, Kout, n_total, st);
-    if (Vout) launch_decompress_t<false, 4>(dm, vs, Vout, n_total, st);
+    if (Kout) launch_decompress_r<true, 4>(dm, ks, Kout, n_total, st);
+    if (Vout) launch_decompress_r<false, 4>(dm, vs, Vout, n_total, st);
   }
   return hipGetLastError();
 }

@@ -1,6 +1,7 @@
 """gear_decompress at the edges of its 64-token tiles, against the reconstruction from the exported components."""
 import numpy as np
 import pytest
+import torch
 
 import gear_workloads as gw
 from paper_2403_05527_amd import binding as gb
@@ -42,3 +43,37 @@ def test_decompress_is_the_sum_of_its_components(bits, group, n, rank, ppm):
             bar = 0.5 * np.spacing(np.abs(got[:, :, t0:t0 + ns]).astype(np.float16)).astype(np.float64) * (1 + 2.0 ** -10) + 22 * 2.0 ** -24 * size
             assert (np.abs(got[:, :, t0:t0 + ns].astype(np.float64) - want) <= bar).all(), (which, seg)
             t0 += ns
+
+
+@pytest.mark.parametrize("B,H,bits,group,n,rank,ppm", [
+    (2, 3, 2, 64, 131, 0, 400000), (2, 3, 4, 32, 97, 4, 400000),    # four rows of a thread, lists of more entries than threads
+    (2, 3, 2, 128, 190, 3, 400000), (2, 3, 4, 64, 65, 7, 150000),   # eight rows
+    (16, 32, 2, 64, 9, 1, 20000), (16, 33, 2, 32, 9, 1, 20000),     # 512 tiles: four rows; 528: eight
+    (24, 16, 4, 64, 70, 8, 20000), (25, 31, 2, 64, 21, 8, 20000),   # 768: four rows; 775: eight
+    (32, 32, 2, 64, 64, 4, 20000), (25, 41, 4, 32, 64, 2, 100000),  # 1024 full tiles: four rows; 1025: eight
+    (25, 41, 2, 32, 67, 4, 20000), (25, 41, 4, 64, 65, 0, 0),       # ... eight
+    (25, 41, 4, 64, 63, 4, 20000),                                  # 1025 that are not all full: four
+    (25, 41, 4, 64, 64, 4, 100001), (25, 41, 2, 64, 64, 0, 400000), # ... four with long lists
+])
+def test_four_and_eight_rows_of_a_thread(B, H, bits, group, n, rank, ppm):
+    dev = "cuda:0"
+    print("case", B, H, bits, group, n, rank, ppm, flush=True)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(n + rank)
+    K, V = [torch.randn(B, H, n, 128, generator=gen, device=dev).to(torch.float16) for _ in range(2)]
+    c = gb.GearCache(gb.make_config(B, H, H, bits, group, ppm, 20, n, 0, max(rank, 1)), dev)
+    c.compress(K, V, rank, 2, None, seed=1)
+    for which, got in enumerate(c.decompress()):
+        codes, scale, zero = [x.double() for x in c.export_codes(which)]
+        S = c.export_sparse(which)[1].double()
+        if which == 0:
+            at = torch.arange(n, device=dev) // group
+            scale, zero = scale[:, :, at], zero[:, :, at]
+        else:
+            scale, zero = [x.repeat_interleave(group, dim=3) for x in (scale, zero)]
+        A, Bf = [x.double() for x in c.export_lowrank(which, 0)] if rank else (None, None)
+        terms = [codes * scale, zero, S] + [A[..., r:r + 1] * Bf[..., r:r + 1].transpose(-1, -2) for r in range(rank)]
+        want, size = sum(terms), sum(x.abs() for x in terms)
+        # the same bar as above
+        half = 0.5 * torch.from_numpy(np.spacing(np.abs(pu.np16(got)).astype(np.float16)).astype(np.float64)).to(dev)
+        assert bool(((got.double() - want).abs() <= half * (1 + 2.0 ** -10) + 22 * 2.0 ** -24 * size).all()), which
