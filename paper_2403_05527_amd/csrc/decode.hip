@@ -302,8 +302,8 @@ static hipError_t launch_decode_t(const Dims& dm, const SegView& k0, const SegVi
   hipLaunchKernelGGL((decode_split_kernel<BITS, GQ, LG>), dim3(s.nblocks, blocks), dim3(256), lds, st, dm, k0, v0, cs, q, Kbuf, Vbuf,
                      n_buf, n_buf_cap, (k0.n + MFMA_TS - 1) / MFMA_TS, s.pp, s.rc, s.odd_rank, q_len, causal, plan.lparts, partial);
   const dim3 rows(dm.B * dm.Hq);
-  if (s.nblocks > GEAR_MERGE_AT_ONCE) hipLaunchKernelGGL(decode_combine_kernel<64>, rows, dim3(128), 0, st, (const float*)partial, s.nblocks, out);
-  else if (s.nblocks > GEAR_MERGE_AT_ONCE / 2) hipLaunchKernelGGL(decode_combine_kernel<32>, rows, dim3(128), 0, st, (const float*)partial, s.nblocks, out);
+  if (s.nblocks > GEAR_MERGE_32) hipLaunchKernelGGL(decode_combine_kernel<64>, rows, dim3(128), 0, st, (const float*)partial, s.nblocks, out);
+  else if (s.nblocks > GEAR_MERGE_16) hipLaunchKernelGGL(decode_combine_kernel<32>, rows, dim3(128), 0, st, (const float*)partial, s.nblocks, out);
   else hipLaunchKernelGGL(decode_combine_kernel<16>, rows, dim3(128), 0, st, (const float*)partial, s.nblocks, out);
   return hipGetLastError();
 }

@@ -123,12 +123,13 @@
 #ifndef GEAR_STREAM_MIN_ROWS
 #define GEAR_STREAM_MIN_ROWS 65536
 #endif
-// Compute units; waves of a block that reads a slab in one launch, at most; records of a query row beyond which the merge requests them
-// all at once.  (The CPU stand-in lowers them so that its small cases are read by every kernel.)
+// Compute units; waves of a block that reads a slab in one launch, at most; records of a query row up to which the merge requests 16 and
+// 32 of them at once (64 beyond).  (The CPU stand-in lowers them so that its small cases are read by every kernel.)
 #ifndef GEAR_CUS
 #define GEAR_CUS 256
 #define GEAR_SINGLE_WAVES 16
-#define GEAR_MERGE_AT_ONCE 32
+#define GEAR_MERGE_16 16
+#define GEAR_MERGE_32 32
 #endif
 #ifndef GEAR_STREAM_CUS
 #define GEAR_STREAM_CUS GEAR_CUS   // as the Key selection by lists of candidates counts them

@@ -262,9 +262,10 @@ inline void launch(const void* kernel, const char* name, dim3 grid, dim3 block, 
 #define GEAR_STREAM_MIN_ROWS 3000   // the same for the Key selection by lists of candidates
 #define GEAR_STREAM_CUS 16        // and its blocks of 512 and of 1024 threads
 #ifndef GEAR_CUS
-#define GEAR_CUS 1                // reads in one launch (at most four waves) and split ones, of all numbers of columns; both merges
+#define GEAR_CUS 1                // reads in one launch (at most four waves) and split ones, of all numbers of columns; merges of up to 3, of 4 and of more records
 #define GEAR_SINGLE_WAVES 4
-#define GEAR_MERGE_AT_ONCE 3
+#define GEAR_MERGE_16 3
+#define GEAR_MERGE_32 4
 #endif
 #ifndef GEAR_BLOCK_SLOTS
 #define GEAR_BLOCK_SLOTS 16       // and strips of two tiles and more

@@ -64,7 +64,7 @@ def build(tmp_path_factory):
             parts = list(common)
             if device:
                 parts[SOURCES.index("decode")] = objects(["decode"], ["-O0", "-fno-sanitize=address", "-DGEAR_CUS=256", "-DGEAR_SINGLE_WAVES=16",
-                                                                      "-DGEAR_MERGE_AT_ONCE=32"])[0]
+                                                                      "-DGEAR_MERGE_16=16", "-DGEAR_MERGE_32=32"])[0]
             r = subprocess.run([cxx] + parts + objects([name]) + ["-o", exe] + flags, capture_output=True, text=True)
             assert r.returncode == 0, r.stderr[-3000:]
         return exe
@@ -134,6 +134,7 @@ CASES = [
     # low-rank term begins inside a strip's second tile):
     (1, 1, 1, 390, 4, 32, 50000, 2, 3, False, 20, 20, -1),     # groups of 32, long overflow lists
     (1, 1, 1, 390, 2, 0, 20000, 4, 3, True, 20, 20, 250),      # per-vector groups, the per-head Value Filter, a late low-rank term
+    (1, 1, 2, 600, 2, 64, 20000, 2, 3, False, 20, 20, -1),     # a merge of four records
 ]
 
 
@@ -272,6 +273,16 @@ def test_key_selection_under_address_sanitizer(selection_runs, case):
         sz = np.fromfile(f + ".sz", np.float16).reshape(1, slabs, 128, 2).astype(np.float32)
         assert np.array_equal(sz[..., 0], ((hi - lo) / np.float32(3)).astype(np.float16).astype(np.float32))
         assert np.array_equal(sz[..., 1], lo)
+
+
+def test_every_form_of_the_merge_ran(pipeline_runs):
+    """The merge is built for 16, 32 and 64 records at once: split reads of the cases above go through each."""
+    if len(pipeline_runs) < len(CASES):
+        pytest.skip("not all cases were selected")
+    forms = set()
+    for run in pipeline_runs.values():
+        forms |= set(re.findall(r"^launch decode_combine_kernel<(\d+)>", run.result()[1].stderr, re.M))
+    assert forms == {"16", "32", "64"}
 
 
 NOT_EMULATED = {"gram_sum_kernel",                                            # eight partial Gram matrices and more per slab
