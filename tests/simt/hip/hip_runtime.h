@@ -61,9 +61,10 @@ inline hipError_t hipGetSymbolAddress(void** p, const void* sym) { *p = const_ca
 #define GEAR_LANE_SWAP32(a, b) simt::lane_swap((a), (b), 32)
 #define GEAR_LANE_SWAP16(a, b) simt::lane_swap((a), (b), 16)
 #define GEAR_LDS_BARRIER() pthread_barrier_wait(&simt::block_bar)
-// a copy to LDS: every lane moves its own piece at once; the waits order the lanes of a wave
-#define GEAR_DMA16(b, off, lds) (*(reinterpret_cast<uint4*>(lds) + simt::lane()) = simt_buf_load<uint4>((b), (uint32_t)(off)))
-#define GEAR_DMA_WAIT() simt::wave_barrier()
+// a copy to LDS: as late as the device may make it.  Its place holds garbage from the request on, the wait brings the data; a block
+// that ends with a copy on its way is an error.  (The waits also order the lanes of a wave.)
+#define GEAR_DMA16(b, off, lds) simt::request_copy((b), (uint32_t)(off), reinterpret_cast<uint4*>(lds) + simt::lane())
+#define GEAR_DMA_WAIT() simt::wait_for_copies()
 #define GEAR_LDS_DRAIN() simt::wave_barrier()
 #define GEAR_DMA_BARRIER() pthread_barrier_wait(&simt::block_bar)
 #define GEAR_WAVE_UNIFORM(x) (x)
@@ -134,6 +135,19 @@ extern pthread_barrier_t block_bar;
 inline int lane() { return threadIdx.x & 63; }
 inline Wave& W() { return waves[threadIdx.x >> 6]; }
 inline void wave_barrier() { pthread_barrier_wait(&W().bar); }
+struct Copy { simt_buf from; uint32_t off; uint4* to; };
+extern thread_local Copy copies[16];   // a lane's copies on their way
+extern thread_local int copies_on_way;
+inline void request_copy(const simt_buf& b, uint32_t off, uint4* to) {
+  if (copies_on_way == 16) { fprintf(stderr, "more copies to LDS on their way than the stand-in holds\n"); abort(); }
+  memset(to, 0xA5, sizeof *to);
+  copies[copies_on_way++] = Copy{b, off, to};
+}
+inline void wait_for_copies() {
+  for (int i = 0; i < copies_on_way; ++i) *copies[i].to = simt_buf_load<uint4>(copies[i].from, copies[i].off);
+  copies_on_way = 0;
+  wave_barrier();
+}
 inline uint64_t xchg(uint64_t v, int src) {
   Wave& w = W();
   w.slot[lane()] = v;

@@ -27,6 +27,8 @@ Observer observer = nullptr;
 bool dry = false;
 Wave waves[16];
 pthread_barrier_t block_bar;
+thread_local Copy copies[16];
+thread_local int copies_on_way = 0;
 unsigned char* dyn_lds = nullptr;
 extern "C" unsigned char __start_simt_lds[], __stop_simt_lds[];
 static unsigned poison_seed = 12345;
@@ -48,6 +50,7 @@ static void* tramp_grid(void* p) {
         if (s->tid == 0) poison_lds();
         pthread_barrier_wait(&block_bar);
         s->fn(s->arg);
+        if (copies_on_way) { fprintf(stderr, "a block ends with copies to LDS on their way\n"); abort(); }
         pthread_barrier_wait(&block_bar);   // the block has finished before the next one starts
       }
   return nullptr;

@@ -81,6 +81,11 @@ def test_dynamic_lds_is_raised_on_every_device(build):
     assert r.returncode == 0, r.stderr
 
 
+def test_copies_to_lds_arrive_at_the_wait(build):
+    r = subprocess.run([build("check_copies")], capture_output=True, text=True, timeout=120, env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0"))
+    assert r.returncode == 0, r.stderr
+
+
 @pytest.mark.parametrize("size,launch", [
     # bits, group, B, H_kv, H_q, n, rank, n_buf, n_buf_cap, chunks: the kernel, the blocks that share a slab's columns.  The single
     # launch of four columns would need more LDS than there is (factor rows staged, groups of 32): two columns per block fit.
