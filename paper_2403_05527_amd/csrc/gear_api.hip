@@ -134,7 +134,7 @@ WorkLayout work_layout(const gear_config& c) {
   // pair
   o = w.mask + mask_bytes(n_max);
   w.pair.mask_v = o; o += mask_bytes(n_max);
-  w.pair.Bcur = o; o += up(2 * slabs * (D * R + PI_PROJECT_FLOATS) * 4);
+  w.pair.Bcur = o; o += up(2 * slabs * D * R * 4);
   w.pair.gram = o;
   w.gram_strips = c.rank_max > 0 && n_max > 256 ? pi_gram_strips_max(n_max, (int)slabs) : 0;
   if (w.gram_strips > 0) reach(o + up(2 * slabs * (size_t)w.gram_strips * GRAM_FLOATS * 4));

@@ -40,12 +40,12 @@ hipError_t launch_fill_u32(uint32_t* p, uint32_t v, size_t count, hipStream_t st
 // writes every channel's (scale, zero) of the segment sv
 hipError_t launch_k_select(const uint16_t* K, const Dims& dm, int n, int k_top, int k_bot, uint4* mask,
                            uint32_t* zero, int zero_count, const SegView& sv, uint16_t* kt_scratch, hipStream_t st);
-// k_top / k_bot: per Value vector (the token's row over all heads); vsz: [B][n] words, a token's (scale, zero) under the
-// per-vector grouping
 // Both selections in one launch, where selects_in_pairs says so (the arguments of launch_k_select and launch_v_select).
 bool selects_in_pairs(const Dims& dm, int n);
 hipError_t launch_select_pair(const uint16_t* K, const uint16_t* V, const Dims& dm, int n, int k_top, int k_bot, int v_top, int v_bot,
                               uint4* maskK, uint4* maskV, uint32_t* zero, int zero_count, const SegView& ks, uint32_t* vsz, hipStream_t st);
+// k_top / k_bot: per Value vector (the token's row over all heads); vsz: [B][n] words, a token's (scale, zero) under the
+// per-vector grouping
 hipError_t launch_v_select(const uint16_t* V, const Dims& dm, int n, int k_top, int k_bot, uint4* mask, uint32_t* vsz,
                            hipStream_t st);
 // Quantization of one tensor given its mask (compress_quant.h).  Yout (nullable): [slab][n][128] fp16, Y = X - S, from which
@@ -120,8 +120,7 @@ struct PiTensor {
   StartB sb;
 };
 // t_lr: first token of the segment that takes part in the low-rank term (rows before it get A = 0)
-// Bcur: 2 * slabs * (128 * padded rank + PI_PROJECT_FLOATS) floats (what the solver leaves for its last pass); gram: [2][slab][nstrips][GRAM_FLOATS], Keys first
-constexpr int PI_PROJECT_FLOATS = 12;
+// Bcur: [2][slab][128][padded rank]; gram: [2][slab][nstrips][GRAM_FLOATS], Keys first; the solver writes to both for its last pass
 hipError_t launch_power_iteration_pair(const PiTensor& k, const PiTensor& v, const Dims& dm, int n, int t_lr, int iters, float* Bcur,
                                        float* gram, int nstrips, hipStream_t st);
 hipError_t launch_power_iteration(bool is_k, const PiTensor& x, const Dims& dm, int n, int t_lr, int iters, float* Bcur, float* partial,

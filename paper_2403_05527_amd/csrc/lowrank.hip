@@ -576,10 +576,14 @@ __global__ __launch_bounds__(256, (R <= 2 ? 4 : R <= 4 ? 3 : 2)) void pi_sweep_k
 // 549 us and 15.5 instructions; 32 heads x 32768 tokens of rank 8 182 -> 119, 16 x 32 x 4096 of rank 4 273 -> 232 (all under the profiler).
 // Against the same steps in 64 bits the stored A, B and their product are off by what they were before to five digits: the
 // rounding to fp16 (2.07e-4 of A), at magnitudes of the entries from 1e-4 to 500.
-struct ProjectScale {   // per tensor and slab, left by pi_solve_kernel: the scale of R, its inverse, of each column of W the inverse
+struct ProjectScale {   // per tensor and slab, left by pi_solve_kernel where its first partial Gram matrix was: the scale of R, its inverse, of each column of W the inverse
   float r, inv_r;
   float inv_w[8];
 };
+// `gram` as pi_solve_kernel takes it: strip matrices of the tensors' slabs, one after the other
+__device__ __forceinline__ const ProjectScale& project_scale(const float* gram, size_t slab, int strips) {
+  return *reinterpret_cast<const ProjectScale*>(gram + slab * strips * GRAM_FLOATS);
+}
 typedef _Float16 project_h8 __attribute__((ext_vector_type(8)));
 constexpr int PROJECT_ROWS = 16;   // tokens of a step
 constexpr int PROJECT_WAVE = 64;   // tokens of a wave
@@ -609,7 +613,7 @@ __device__ __forceinline__ void split8(const float (&v)[8], float one, uint32_t 
 template <bool IS_K, int BITS, int R>
 __device__ __forceinline__ void project_wave(uint4 (&rows)[PROJECT_ROWS][D / 8], const uint16_t* __restrict__ X, const uint4* __restrict__ mask,
                                              const SegView& sv, int lg /* log2 of the group size */, int slab, int t0, int n, int t_lr,
-                                             const uint16_t* __restrict__ W, const ProjectScale* __restrict__ scale) {
+                                             const uint16_t* __restrict__ W, const ProjectScale& scale) {
   const int lane = lane_id(), m = lane & 15, kg = lane >> 4;
   const GEAR_BUF_T xbuf = GEAR_BUF_MAKE(X + (size_t)slab * n * D, n * (D * 2));   // rows past the end read as 0
   const GEAR_BUF_T mbuf = GEAR_BUF_MAKE(mask + (size_t)slab * n, mask ? n * 16 : 0);
@@ -648,10 +652,10 @@ __device__ __forceinline__ void project_wave(uint4 (&rows)[PROJECT_ROWS][D / 8],
   }
   float one = 1.0f;
   GEAR_PIN_SGPR(one);
-  const float rs = scale[slab].r;
+  const float rs = scale.r;
   float back[4];   // of columns 4 (kg % 2) + i
 #pragma unroll
-  for (int i = 0; i < 4; ++i) back[i] = scale[slab].inv_w[4 * (kg & 1) + i] * scale[slab].inv_r;
+  for (int i = 0; i < 4; ++i) back[i] = scale.inv_w[4 * (kg & 1) + i] * scale.inv_r;
 
   float pmn[IS_K ? 32 : 1], pdl[IS_K ? 32 : 1];   // Keys: -zero and scale of the lane's channels, with the scale of R
   uint16_t* half = reinterpret_cast<uint16_t*>(&rows[0][0]);
@@ -697,7 +701,7 @@ __device__ __forceinline__ void project_wave(uint4 (&rows)[PROJECT_ROWS][D / 8],
     float mn = 0.0f, inv = 0.0f, dl = 0.0f;   // Values: my row's group
     if constexpr (!IS_K) {
       const GroupQ q = load_group(c[0]);
-      const float inv_rs = scale[slab].inv_r;
+      const float inv_rs = scale.inv_r;
       mn = -(q.mn * rs);
       dl = q.delta * rs;
       inv = q.inv * inv_rs;
@@ -772,14 +776,14 @@ template <int BITS, int R>
 __global__ __launch_bounds__(256, 3) void pi_project_kernel(const uint16_t* __restrict__ XK, const uint16_t* __restrict__ XV,
                                                          const uint4* __restrict__ maskK, const uint4* __restrict__ maskV, SegView ks, SegView vs,
                                                          int lgk, int lgv, int n, int t_lr, const uint16_t* __restrict__ W,
-                                                         const ProjectScale* __restrict__ scale) {
+                                                         const float* __restrict__ gram, int nstrips) {
   __shared__ uint4 rows[4][PROJECT_ROWS][D / 8];
   const int wave = GEAR_WAVE_UNIFORM((int)(threadIdx.x >> 6)), t0 = (int)blockIdx.x * (4 * PROJECT_WAVE) + PROJECT_WAVE * wave;
   if (blockIdx.z == 0)
-    project_wave<true, BITS, R>(rows[wave], XK, maskK, ks, lgk, blockIdx.y, t0, n, t_lr, W, scale);
+    project_wave<true, BITS, R>(rows[wave], XK, maskK, ks, lgk, blockIdx.y, t0, n, t_lr, W, project_scale(gram, blockIdx.y, nstrips));
   else
     project_wave<false, BITS, R>(rows[wave], XV, maskV, vs, lgv, blockIdx.y, t0, n, t_lr, W + (size_t)gridDim.y * (2 * R * D),
-                                 scale + gridDim.y);
+                                 project_scale(gram, (size_t)gridDim.y + blockIdx.y, nstrips));
 }
 
 // A = a C for tokens [256 * pt, 256 * pt + 256) of one slab, one token per thread.  Cs: LDS, R * R floats.
@@ -1017,9 +1021,8 @@ __device__ __forceinline__ void gram_product(const float* G, const SolveRows<R>&
 // (32768 tokens) 52 -> 27, 280 slabs of rank 4 49 -> 30, 512 slabs 68 -> 46.
 template <int R>
 __global__ __launch_bounds__(256, 2) void pi_solve_kernel(StartB sb0, StartB sb1, int rank,
-                                                       const float* __restrict__ gram_partial, int nstrips, int stride, int rounds,
-                                                       float* __restrict__ Bcur_all, int last_round, uint16_t* Bf0, uint16_t* Bf1,
-                                                       ProjectScale* __restrict__ scale) {
+                                                       float* __restrict__ gram_partial, int nstrips, int stride, int rounds,
+                                                       float* __restrict__ Bcur_all, int last_round, uint16_t* Bf0, uint16_t* Bf1) {
   GEAR_DYN_LDS(smem_raw);
   SolveSmem<R>& sm = *reinterpret_cast<SolveSmem<R>*>(smem_raw);
   const SolveRows<R> Bs{sm.Bs}, Ps{reinterpret_cast<double*>(sm.G)};   // Ps: P = G B, at the end, in the place of G
@@ -1151,7 +1154,8 @@ __global__ __launch_bounds__(256, 2) void pi_solve_kernel(StartB sb0, StartB sb1
   // W for the pass over R (pi_project_kernel), column by column: scaled to a norm of 256 .. 512, which is the norm of C's column as B is
   // orthonormal, and split into two fp16 parts.  The halves of the block take half of the columns each.
   uint16_t* W = reinterpret_cast<uint16_t*>(Bcur) + (size_t)slab * (2 * R * D);
-  ProjectScale* sc = scale + (size_t)blockIdx.y * gridDim.x + slab;
+  // (into the first partial matrix of this slab, which this block alone has read)
+  ProjectScale* sc = reinterpret_cast<ProjectScale*>(gram_partial + ((size_t)blockIdx.y * gridDim.x + slab) * stride * GRAM_FLOATS);
   double q[R], pr[R];
   Bs.load(c, q);
   Ps.load(c, pr);
@@ -1403,23 +1407,21 @@ static hipError_t run_pi_pair(const PiTensor& k, const PiTensor& v, const Dims& 
   }
   const hipError_t e = raise_solve_lds<R>();
   if (e != hipSuccess) return e;
-  ProjectScale* scale = reinterpret_cast<ProjectScale*>(Bcur + 2 * (size_t)slabs * (D * R));   // (PI_PROJECT_FLOATS per tensor and slab)
-  static_assert(sizeof(ProjectScale) <= PI_PROJECT_FLOATS * sizeof(float), "part of the workspace layout");
   // rounds 1 .. L-1: B <- (R^T R)^(L-1) B0 on the Gram matrix; then QR(B), the last round's B and the factor of orth(A)
   const bool summed = nstrips >= GRAM_SUM_MIN;
   if (summed) hipLaunchKernelGGL(gram_sum_kernel, dim3(GRAM_TILES, 2 * slabs), dim3(256), 0, st, gram, nstrips);
-  hipLaunchKernelGGL(pi_solve_kernel<R>, dim3(slabs, 2), dim3(256), sizeof(SolveSmem<R>), st, k.sb, v.sb, rank, (const float*)gram,
-                     summed ? 1 : nstrips, nstrips, iters - 1, Bcur, 1, k.sv.Bf, v.sv.Bf, scale);
+  hipLaunchKernelGGL(pi_solve_kernel<R>, dim3(slabs, 2), dim3(256), sizeof(SolveSmem<R>), st, k.sb, v.sb, rank, gram,
+                     summed ? 1 : nstrips, nstrips, iters - 1, Bcur, 1, k.sv.Bf, v.sv.Bf);
   // one light pass writes A
   const dim3 grid((n + 4 * PROJECT_WAVE - 1) / (4 * PROJECT_WAVE), slabs, 2);
   const uint16_t* W = reinterpret_cast<const uint16_t*>(Bcur);
   const int lgk = log2_group(key_group_size(dm)), lgv = log2_group(dm.g);
   if (dm.bits == 2)
     hipLaunchKernelGGL((pi_project_kernel<2, R>), grid, dim3(256), 0, st, k.X, v.X, k.mask, v.mask, k.sv, v.sv, lgk, lgv, n, t_lr, W,
-                       (const ProjectScale*)scale);
+                       (const float*)gram, nstrips);
   else
     hipLaunchKernelGGL((pi_project_kernel<4, R>), grid, dim3(256), 0, st, k.X, v.X, k.mask, v.mask, k.sv, v.sv, lgk, lgv, n, t_lr, W,
-                       (const ProjectScale*)scale);
+                       (const float*)gram, nstrips);
   return hipGetLastError();
 }
 
@@ -1439,8 +1441,8 @@ static hipError_t run_pi(bool is_k, const PiTensor& x, const Dims& dm, int n, in
   // a single round (no Gram pass): A = R B, orth(A) through its r x r Gram matrix, B = R^T A
   const hipError_t e = raise_solve_lds<R>();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(pi_solve_kernel<R>, dim3(slabs), dim3(256), sizeof(SolveSmem<R>), st, x.sb, x.sb, x.sv.rank, (const float*)nullptr,
-                     0, 0, 0, Bcur, 0, x.sv.Bf, x.sv.Bf, (ProjectScale*)nullptr);
+  hipLaunchKernelGGL(pi_solve_kernel<R>, dim3(slabs), dim3(256), sizeof(SolveSmem<R>), st, x.sb, x.sb, x.sv.rank, (float*)nullptr,
+                     0, 0, 0, Bcur, 0, x.sv.Bf, x.sv.Bf);
   const dim3 grid(npart, slabs);
   if (is_k)
     hipLaunchKernelGGL((pi_sweep_kernel<true, R>), grid, dim3(256), 0, st, x.Y, x.sv, g, dm.bits, n, t_lr, (const float*)Bcur, partial, npart, Atmp);

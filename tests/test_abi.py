@@ -79,6 +79,15 @@ def test_workspace_holds_one_solver_at_a_time(lib, B, H_kv, H_q, n, chunks):
     assert slabs * n * (16 + 256 + 32 + 17) < w <= slabs * (n + 256) * (16 + 256 + 32 + 17) + 8500 * slabs + records + 4096
 
 
+@pytest.mark.parametrize("cfg,most", [
+    ((1, 1, 1, 2, 0, 400000, 5, 487, 2, 2), 323072), ((1, 8, 8, 4, 64, 20000, 20, 300, 1, 4), 1924608),
+    ((39, 8, 8, 2, 64, 50000, 128, 408, 6, 1), 53286144), ((45, 7, 14, 4, 64, 20000, 128, 395, 7, 1), 54322944)])
+def test_workspace_does_not_grow(lib, cfg, most):
+    """A program that keeps its own buffers may have sized them once: what sufficed suffices.  Segments of a few hundred tokens, whose
+    workspace the pairwise solver sets."""
+    assert gb.gear_cache_bytes(gb.make_config(*cfg))[1] <= most
+
+
 def test_workspace_is_enough_for_every_entry_point(lib):
     """Where other calls need more than the solvers: many appended segments behind a short prompt."""
     for B, H_kv, gq, n, n_b, chunks, rank, ppm in ((1, 2, 1, 257, 20, 256, 1, 20000), (2, 4, 4, 300, 255, 256, 4, 1), (1, 1, 2, 512, 1, 256, 8, 0),
