@@ -96,6 +96,29 @@ def test_key_sets_in_blocks_of_either_size(kind, slabs, n, ppm, group):
         _check_one_group(gc, 0, K, go.filter_keys, ppm, 2)
 
 
+@pytest.mark.parametrize("kind", ["normal", "two channels"])
+@pytest.mark.parametrize("slabs,n,ppm,group", [
+    (32, 4097, 20000, 64), (33, 8191, 20000, 0), (15, 8193, 20000, 64), (16, 8193, 20000, 0), (33, 8195, 20000, 64), (17, 16001, 20000, 0),
+    (49, 16001, 20000, 64), (50, 16001, 20000, 64), (32, 32768, 10000, 0), (43, 2047, 20000, 0), (91, 1025, 20000, 64)])
+def test_key_sets_of_slabs_that_differ(kind, slabs, n, ppm, group):
+    """Every slab is the first one with its channels turned by another number, and so are its set, values and parameters."""
+    K = _values(kind, (1, 1, n, 128), n + slabs + 1)
+    turned = lambda t: torch.cat([t.roll(37 * i, dims=-1) for i in range(slabs)])
+    x = turned(K)
+    print("case", kind, slabs, n, ppm, group, flush=True)
+    gc = gb.GearCache(gb.make_config(slabs, 1, 1, 2, group, ppm, 20, n, 0, 2), "cuda:0")
+    gc.compress(x, torch.zeros_like(x), 0, 1, None)
+    mask, vals = gc.export_sparse(0)
+    want = torch.from_numpy(go.filter_keys(K.cpu().numpy(), ppm)).cuda()
+    assert torch.equal(mask.bool(), turned(want))
+    assert torch.equal(torch.where(mask.bool(), vals, 0).view(torch.int16), torch.where(turned(want), x, 0).view(torch.int16))
+    codes, scale, zero = gc.export_codes(0)
+    for t in (codes, scale, zero):
+        assert torch.equal(t, turned(t[:1]))
+    if group == 0:
+        _check_one_group(gc, 0, K, go.filter_keys, ppm, 2)
+
+
 @pytest.mark.parametrize("kind,H,n,ppm", [("normal", 2, 300, 20000), ("normal", 2, 5000, 20000), ("grid", 2, 5000, 20000), ("normal", 1, 9001, 10000),
                                           ("cliff", 9, 700, 20000), ("one sign", 2, 3000, 20000), ("normal", 40, 70, 20000)])
 def test_one_group_per_vector(kind, H, n, ppm):
