@@ -86,10 +86,13 @@ template <int BITS, int LG>
 struct QuantSmem<true, BITS, LG> {
   static constexpr int WPG = LG >= 7 ? 4 : LG == 6 ? 2 : 1;   // waves (of 32 rows) that share a group
   uint4 slots[QT];
-  uint2 red[2 * 4 * D / 2];                           // a wave's (min, max) of its 32 rows, two channels per word; of this tile, of the last
+  // a wave's (min, max) of its 32 rows, two channels per word; of this tile, of the last.  (None with one group per vector: four blocks fit a
+  // CU without them.  1024 slabs x 20 tokens at 40 % outliers, 15.6 us with three blocks and 11.5 with four.)
+  uint2 red[LG == KLG_VEC ? 1 : 2 * 4 * D / 2];
   __attribute__((aligned(16))) uint2 par[4][D];       // per wave: (scale, zero) as fp16, 1/scale
   uint32_t ovf_cnt[64], ovf_off[64];                  // overflow entries of the strip's stretches of 32 rows
 };
+static_assert(4 * (QT * D * 2 + sizeof(QuantSmem<true, 2, KLG_VEC>)) <= 160 * 1024, "four blocks per CU");
 template <int BITS, int LG>
 struct QuantSmem<false, BITS, LG> {
   static constexpr int NG = D >> LG;                  // groups per row
