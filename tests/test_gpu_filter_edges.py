@@ -54,3 +54,16 @@ def test_selections_of_a_short_segment(B, H, n, group, ppm, rank, per_head):
     gc, oc = pu.make_pair(B, H, H, 2, group, ppm, 20, n, 0, rank, v_per_head=per_head)
     pu.compress_both(gc, oc, gw.make_keys(w, n, 0, dev), gw.make_values(w, n, 0, dev), rank, 3, gw.make_init_B(w, rank, 0, dev))
     pu.compare_components(gc, oc)
+
+
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 63, 64, 65, 129, 190])
+@pytest.mark.parametrize("H,bits,group,ppm,rank,per_head", [(3, 2, 64, 400000, 0, False), (4, 4, 0, 150000, 2, False), (2, 2, 32, 300000, 0, True),
+                                                            (9, 2, 128, 20000, 2, False)])
+def test_outliers_of_a_tile_of_few_rows(n, H, bits, group, ppm, rank, per_head):
+    """The lists of a tile's Values, by rows or by channels, and up to its fullest."""
+    B, dev = 2, "cuda:0"
+    w = gw.Workload("f", B=B, H_kv=H, H_q=H, n=n, bits=bits, group=group, outlier_ppm=ppm, rank=rank, rank_chunk=2, n_b=20, steps=1, seed=n + H)
+    gc, oc = pu.make_pair(B, H, H, bits, group, ppm, 20, n, 0, max(rank, 1), v_per_head=per_head)
+    pu.compress_both(gc, oc, gw.make_keys(w, n, 0, dev), gw.make_values(w, n, 0, dev), rank, 3, gw.make_init_B(w, rank, 0, dev))
+    pu.compare_components(gc, oc)
+    pu.compare_decompress(gc, oc)
