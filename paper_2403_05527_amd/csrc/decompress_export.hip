@@ -474,7 +474,8 @@ static void launch_decompress_t(const Dims& dm, const SegView& sv, uint16_t* out
 // Rows of a thread, 4 or 8.  Eight halve the loads of codes and factors, four have twice the waves and half the chain.  Times of four rows to those of
 // eight, Keys and Values, nothing of the cache in the chip's caches; by tiles (of 64 tokens, all slabs):
 //   tiles         up to 512      to 768      to 1024     to 1536     to 8192       more
-//   rank 0        0.87 to 0.98   0.96        0.98        1.06        0.99 to 1.04  1.01
+//   rank 0        0.87 to 0.98   0.96        0.98        1.06        0.99 to 1.04  1.01; where the cache is near 0.91 to 0.99 up to 8192 tiles,
+//                 0.98 to 1.0 at 16384, 1.01 to 1.07 from 30000 (64 x 2048 tokens at 5 % 14.2 : 15.2 us, 512 x 8192 484 : 458): hence its line
 //   rank 1        0.87 to 0.98   1.05        1.06        1.09        1.13          1.32
 //   rank 2, 4     0.75 to 0.97   0.88, 0.95  0.94, 0.98  1.02, 1.08  0.96 to 1.10  1.07
 //   rank 8        0.76 to 0.89   0.92        0.99        1.03        0.99 to 1.10  1.22  (where the cache is near, 1.16 at 1024)
@@ -485,7 +486,8 @@ static void launch_decompress_t(const Dims& dm, const SegView& sv, uint16_t* out
 static int decompress_rows(const Dims& dm, const SegView& sv) {
   const long long tiles = (long long)((sv.n + TILE - 1) / TILE) * dm.B * dm.H, rows = (long long)sv.n * dm.B * dm.H;
   switch (sv.rank) {
-    case 0: case 2: case 4: return rows > 1024 * TILE && dm.ppm <= 100000 ? 8 : 4;
+    case 0: return tiles > 24 * 1024 && dm.ppm <= 100000 ? 8 : 4;
+    case 2: case 4: return rows > 1024 * TILE && dm.ppm <= 100000 ? 8 : 4;
     case 1: return tiles > 512 ? 8 : 4;
     case 8: return tiles > 768 ? 8 : 4;
     default: return 8;

@@ -77,3 +77,8 @@ def test_four_and_eight_rows_of_a_thread(B, H, bits, group, n, rank, ppm):
         # the same bar as above
         half = 0.5 * torch.from_numpy(np.spacing(np.abs(pu.np16(got)).astype(np.float16)).astype(np.float64)).to(dev)
         assert bool(((got.double() - want).abs() <= half * (1 + 2.0 ** -10) + 22 * 2.0 ** -24 * size).all()), which
+
+
+@pytest.mark.parametrize("B,H,bits,n", [(192, 64, 4, 65), (193, 64, 2, 65)])   # 24576 tiles: four rows; 24704: eight
+def test_rows_of_a_thread_without_a_lowrank_term(B, H, bits, n):
+    test_four_and_eight_rows_of_a_thread(B, H, bits, 64, n, 0, 20000)
