@@ -166,14 +166,19 @@ hipError_t launch_k_select(const uint16_t* K, const Dims& dm, int n, int k_top, 
     // 40 x 8192 135 -> 152), and blocks of 8 channels, which fetch each line twice as often, wherever the lists of two blocks per CU do not
     // fit (32 x 32768 at 1 % 381 -> 345, 24 x 20000 at 2 % 201 -> 184, 52 x 16000 376 -> 360, 128 x 20000 847 -> 816).  In a last
     // round that is a quarter empty the smaller blocks are level or ahead (48 slabs of 16000 to 32768 tokens 0.99 to 1.03, 40 1.01 to 1.04),
-    // and so they are where the larger ones are at most half a round (16 slabs x 32768 207 against 223, 8 x 9001 60 against 68).
+    // and so they are where the larger ones are at most half a round (16 slabs x 32768 207 against 223, 8 x 9001 60 against 68, 10 x 8000 at
+    // 4 % 74 against 79).  Long lists keep a lone block at its ranking, which nothing then hides: from 4 % on several rounds of the
+    // smaller blocks win (128 x 8000 at 4 % 450 against 475, 80 x 8504 at 5 % 375 against 403), at 3 % where the last round is an eighth empty
+    // (80 x 11000 369 against 378, but 64 x 16000 448 against 434).
     if (n <= 2048) GEAR_STREAM(2, 8, true, 512, 80 * 1024);
     else if (n <= 4096) GEAR_STREAM(2, 16, true, 512, 80 * 1024);
     else {
       const int blocks = 8 * slabs, rounds = (blocks + GEAR_STREAM_CUS - 1) / GEAR_STREAM_CUS;
       const bool pairs = wide && stream_plan(2, 8, false, 512, n, k_top, k_bot, rest, 80 * 1024, p);
-      const bool lone = rounds == 1 && (n <= 8192 || pairs || blocks > GEAR_STREAM_CUS / 2);
-      if (lone || (rounds > 1 && !pairs && 32 * blocks >= 25 * rounds * GEAR_STREAM_CUS)) GEAR_STREAM(2, 8, false, 1024, LDS_PER_CU);
+      const bool lone = rounds == 1 && (pairs || blocks > GEAR_STREAM_CUS / 2);
+      const bool even = 200LL * (k_top + k_bot) <= 5LL * n ? 32 * blocks >= 25 * rounds * GEAR_STREAM_CUS
+                                                           : 200LL * (k_top + k_bot) <= 7LL * n && 8 * blocks >= 7 * rounds * GEAR_STREAM_CUS;
+      if (lone || (rounds > 1 && !pairs && even)) GEAR_STREAM(2, 8, false, 1024, LDS_PER_CU);
       if (pairs) GEAR_STREAM(2, 8, false, 512, 80 * 1024);
     }
     GEAR_STREAM(1, 8, false, 512, LDS_PER_CU);

@@ -99,7 +99,9 @@ def test_key_sets_in_blocks_of_either_size(kind, slabs, n, ppm, group):
 @pytest.mark.parametrize("kind", ["normal", "two channels"])
 @pytest.mark.parametrize("slabs,n,ppm,group", [
     (32, 4097, 20000, 64), (33, 8191, 20000, 0), (15, 8193, 20000, 64), (16, 8193, 20000, 0), (33, 8195, 20000, 64), (17, 16001, 20000, 0),
-    (49, 16001, 20000, 64), (50, 16001, 20000, 64), (32, 32768, 10000, 0), (43, 2047, 20000, 0), (91, 1025, 20000, 64)])
+    (49, 16001, 20000, 64), (50, 16001, 20000, 64), (32, 32768, 10000, 0), (43, 2047, 20000, 0), (91, 1025, 20000, 64),
+    # 8 channels; 1024 threads up to 3.5 % in nearly full rounds; 8 channels
+    (10, 8000, 40000, 64), (17, 8000, 40000, 64), (64, 9500, 30000, 64), (61, 9500, 34000, 0), (64, 9500, 36000, 64), (80, 8504, 30000, 0), (80, 8504, 50000, 0)])
 def test_key_sets_of_slabs_that_differ(kind, slabs, n, ppm, group):
     """Every slab is the first one with its channels turned by another number, and so are its set, values and parameters."""
     K = _values(kind, (1, 1, n, 128), n + slabs + 1)
