@@ -124,10 +124,11 @@ __device__ __forceinline__ void quant_body(uint4 (&tile)[QT][D / 8], QuantSmem<I
   GEAR_PIN_SGPR(one);   // fma(fp16 value, one, float) is one mixed-precision instruction: conversion and addition together
 
   // A wave fetches its own 32 rows, straight into LDS, and each thread the bits of half a row (row tid / 2); no other wave touches
-  // them.  (Rows past the end: the last row once more; they are zeroed when they are read.)
+  // them.  (Rows past the end: the last row once more, or nothing where a wave has no others; they are zeroed when they are read.)
   uint2 mk;
   auto fetch = [&](int base) {
     mk = GEAR_BUF_LOAD8(mb, base * 16 + tid * 8);
+    if (!GRAM && base + 32 * wave >= n) return;   // wave-uniform (1536 slabs x 64 tokens without outliers or a low-rank term 19.1 -> 17.9 us)
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int t = base + 32 * wave + 4 * i + (lane >> 4);
