@@ -1,9 +1,11 @@
 """The pass that writes A on the matrix cores: steps of 16 tokens and waves of 64 with a remainder, every rank (whole and single
 stores), groups that change inside a wave's tokens, rows without a low-rank term, and entries far from 1, whose residuals and
 projection matrix reach the matrix cores only through their scales."""
+import numpy as np
 import pytest
 
 import gear_workloads as gw
+from oracle import gear_oracle as go
 from tests import parity_util as pu
 
 pytestmark = pytest.mark.gpu
@@ -51,3 +53,23 @@ def test_solver(n, rank, iters):
     ib = gw.make_init_B(w, rank, 0, DEV)
     pu.compress_both(gc, oc, K, V, rank, iters, ib)
     pu.compare_lowrank_product(gc, oc, 0)
+
+
+@pytest.mark.parametrize("n,bits,group,rank,size", [(272, 2, 64, 4, 1.0), (700, 4, 128, 2, 1.0), (1030, 2, 32, 8, 1.0), (601, 2, 64, 4, 1.0 / 1024), (333, 4, 0, 3, 32.0)])
+def test_error_of_the_factors_is_their_rounding(n, bits, group, rank, size):
+    """Against the same steps in 64 bits the stored A is off by its rounding to fp16 (2^-12 of an entry at most, 2.1e-4 of the whole).  The operands' 22 bits
+    and the sums in 32 add some 2^-20 of it, which is nothing next to that in quadrature, so 1 % more is allowed.  With
+    the leading parts alone (11 bits) it would be 1.4 times as much."""
+    H = 2
+    w = gw.Workload("error", B=1, H_kv=H, H_q=H, n=n, bits=bits, group=group, outlier_ppm=20000, rank=rank, rank_chunk=2, n_b=20, steps=1, seed=n)
+    gc, oc = pu.make_pair(1, H, H, bits, group, 20000, 20, n, 0, rank)
+    K, V = gw.make_keys(w, n, 0, DEV) * size, gw.make_values(w, n, 0, DEV) * size
+    ib = gw.make_init_B(w, rank, 0, DEV)
+    pu.compress_both(gc, oc, K, V, rank, 3, ib)
+    for which, (X, seg) in enumerate(((pu.np16(K), oc.K[0]), (pu.np16(V), oc.V[0]))):
+        Dh = go.dequant_keys(seg.codes, seg.scale, seg.zero, group or n) if which == 0 else go.dequant_values(seg.codes, seg.scale, seg.zero, group or 128)
+        R = np.where(seg.mask, np.float16(0), X).astype(np.float64) - Dh
+        A = pu.np16(gc.export_lowrank(which, 0)[0]).astype(np.float64)
+        exact = np.stack([go.svd_solver(R[0, h], pu.np16(ib)[which, 0, h], 3)[0] for h in range(H)])[None]
+        rounding = np.linalg.norm(exact.astype(np.float16).astype(np.float64) - exact)
+        assert np.linalg.norm(A - exact) <= 1.01 * rounding, which
