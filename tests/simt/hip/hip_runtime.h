@@ -80,7 +80,6 @@ struct simt_buf { const unsigned char* p; uint32_t n; };
 #define GEAR_BUF_LOAD16_NT(b, off) simt_buf_load<uint4>((b), (uint32_t)(off))
 #define GEAR_BUF_LOAD4(b, off) simt_buf_load<uint32_t>((b), (uint32_t)(off))
 #define GEAR_BUF_LOAD2(b, off) ((uint32_t)simt_buf_load<uint16_t>((b), (uint32_t)(off)))
-#define GEAR_BUF_LOAD1(b, off) ((uint32_t)simt_buf_load<uint8_t>((b), (uint32_t)(off)))
 #define GEAR_BUF_STORE16_NT(b, off, v) simt_buf_store((b), (uint32_t)(off), (v))
 #define GEAR_BUF_STORE2(b, off, v) simt_buf_store<uint16_t>((b), (uint32_t)(off), (uint16_t)(v))
 // a store that does not lie wholly inside the view is dropped
