@@ -19,7 +19,7 @@
 // The tile passes through LDS once, where the few outliers are looked up by row (Keys) or by channel (Values), put into
 // their slots and lists, and zeroed: the arithmetic per entry then needs no mask.
 //
-// What bounds it: vector issue (0.55 of the time; 13 to 14 instructions per entry) next to the matrix cores (0.26), with two waves per
+// What bounds it: vector issue (0.48 of the time under the profiler; 13 to 14 instructions per entry) next to the matrix cores (0.20), with two waves per
 // SIMD, which is what the accumulators leave room for; some 170 of 800 us (64 x 8 heads x 8192 tokens, 2 % outliers) go to the loops over
 // the outliers' bits.  So little may wait: a wave's 32 rows are copied straight into LDS while it works on the tile before (a copy
 // needs no registers, of which there are none left), and nearly all of a tile's work is a wave's own: the four waves meet once per Key
